@@ -71,7 +71,7 @@ hipError_t launch_threshold(const float* colmax, int C, int g, int s, const int3
                             float* scale_out, hipStream_t stream);
 
 // W2 + W3 in one launch for weights (greedy selection repeated by every workgroup, then Eq. 3 and
-// Eq. 1): serves few splits on lists of at most 1024 expanded channels, see `..._fits`.  Writes
+// Eq. 1): serves short lists, see `..._fits`.  Writes
 // what launch_select and launch_expand_quantize together would.
 bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq);
 hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N, int C, int g, int s,
@@ -281,7 +281,7 @@ struct Tuning {
     int max_grid = -1;  // workgroups of the flat pass
     int max_un = -1;    // 16-byte loads in flight per lane in the flat pass (1, 2 or 4)
     int max_bt = -1;    // threads per workgroup of the flat pass (256 or 1024)
-    int sel_inline = -1; // most splits for which the weight pass runs the selection itself (0: never; default 16)
+    int sel_inline = -1; // most splits for which the weight pass runs the selection itself (0: never; default 64)
 };
 Tuning& tuning();
 

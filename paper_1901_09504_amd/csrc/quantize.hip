@@ -879,14 +879,13 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
 
 // The weight pass with the greedy selection of Sec. 3.4 in its prologue: W2 and W3 as one launch.
 // The selection needs only the column maxima (a few KB, already in memory) and a handful of
-// sequential steps on them, so every workgroup repeats it for itself in LDS, behind its first
-// 16-byte fetch of W, instead of waiting for a selector launch of its own: for few splits the
-// repeated work (0.2 us per step on one wave) costs less than the dependent launch it replaces.
+// rounds on them, so every workgroup repeats it for itself in LDS, behind its first 16-byte fetch
+// of W, instead of waiting for a selector launch of its own: on short lists the repeated work
+// costs less than the dependent launch it replaces.
 // The workgroup then expands and quantizes its share of W from the lists in LDS (Eq. 3: every
 // expanded channel j is scaled by 2^-dep[j]; Eq. 1 on the grid of clip_ratio * max|W'|), with
 // the arithmetic of expand_quantize_kernel.  Workgroup 0 also writes the lists, the maximum
-// and the grid for the caller.  32-bit indices; C + s <= 64 << LOG2_S.
-template <int LOG2_S>
+// and the grid for the caller.  32-bit indices.
 __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     const float* __restrict__ W, int64_t ldw, int64_t N, int C, int g, int s,
     const float* __restrict__ colmax, int32_t* __restrict__ split_src,
@@ -894,12 +893,12 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     float clip_ratio, float qmax, float* __restrict__ scale_out, int8_t* __restrict__ Wq, int D,
     int main_units, unsigned magic) {
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr int S = 1 << LOG2_S, P = 64 * S;
     const int E = C + s, Ke = E * g;
-    float* vals = reinterpret_cast<float*>(smem);
-    unsigned short* src = reinterpret_cast<unsigned short*>(vals + P);
+    unsigned long long* cand = reinterpret_cast<unsigned long long*>(smem);
+    float* vals = reinterpret_cast<float*>(cand + greedy_cand_cap(E));
+    unsigned short* src = reinterpret_cast<unsigned short*>(vals + E);
     unsigned short* dep = src + E;
-    __shared__ unsigned wred[kThreads / 64];
+    __shared__ GreedyScratch sc;
     const int tid = threadIdx.x;
     const bool first = blockIdx.x == 0;
     const unsigned total = (unsigned)(N * D);
@@ -924,9 +923,8 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     int d = 0, nd = 0;
     fetch(o, cur, row, d);
 
-    channel_maxima_to_lds(colmax, C, g, P, vals, src, dep);
-    if (tid < 64) greedy_one_wave<LOG2_S>(vals, src, dep, C, s, tid, first ? split_src : nullptr);
-    __syncthreads();
+    channel_maxima_to_lds<kThreads>(colmax, C, g, vals, src, dep);
+    greedy_rounds<kThreads>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
     unsigned m = 0;   // bit pattern of the largest entry (all entries are non-negative)
     for (int j = tid; j < E; j += kThreads) {
         if (first) {
@@ -936,12 +934,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
         const unsigned u = __float_as_uint(vals[j]);
         m = u > m ? u : m;
     }
-    m = wave_umax32(m);
-    if ((tid & 63) == 0) wred[tid >> 6] = m;
-    __syncthreads();
-    m = wred[0];
-#pragma unroll
-    for (int w = 1; w < kThreads / 64; ++w) m = wred[w] > m ? wred[w] : m;
+    m = group_umax<kThreads>(m, sc.red);
     const float mx = __uint_as_float(m);
     const float T = clip_ratio * mx;
     if (first && tid == 0) {
@@ -989,11 +982,13 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     }
 }
 
-// Whether the one-launch form serves this shape: the one-wave selector's list size, few enough
-// steps for the repeated selection to be cheaper than a launch, 32-bit item indices.
+// Whether the one-launch form serves this shape: a list short enough that 256 lanes are through its rounds
+// about as fast as the selector's wide workgroup is (measured over the whole weight path, one launch against
+// two: 512 channels with 26 or 52 splits 14 against 16 us, 2048 x 512 with 26 17.0 against 17.4, 512 x 512 x 9
+// 15.7 against 16.1; 2048 x 1000 with 10 splits 22 against 19), 32-bit item indices.
 bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq) {
-    const int limit = tuning().sel_inline < 0 ? 16 : tuning().sel_inline;
-    if (C + s > 1024 || s > limit || limit == 0) return false;
+    const int limit = tuning().sel_inline < 0 ? 64 : tuning().sel_inline;
+    if (C + s > 640 || s > limit || limit == 0) return false;
     return N * (ldq / 4) + 2 * 2048 * (int64_t)kThreads < ((int64_t)1 << 32);
 }
 
@@ -1011,19 +1006,9 @@ hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N,
     if (tuning().act_grid > 0) grid = tuning().act_grid;
     if (grid > ceil_div(total, kThreads)) grid = ceil_div(total, kThreads);
     const unsigned magic = (unsigned)((((uint64_t)1) << 32) / (uint64_t)D);  // D >= 16
-    int log2_S = 2;        // 64 lanes x S slots hold the E entries
-    while ((64 << log2_S) < E) ++log2_S;
-    const unsigned lds = (unsigned)((64 << log2_S) * 4 + E * 4);
-#define OCS_LAUNCH_SEQ(L_)                                                                        \
-    launch_kernel(kTimeSplitQuantize, select_expand_quantize_kernel<L_>, dim3((unsigned)grid),   \
-                  dim3(kThreads), lds, stream, W, ldw, N, C, g, s, colmax, split_src, chan_src,   \
-                  chan_depth, max_out, clip_ratio, qmax, scale_out, Wq, D, main_units, magic)
-    switch (log2_S) {
-        case 2: return OCS_LAUNCH_SEQ(2);
-        case 3: return OCS_LAUNCH_SEQ(3);
-        default: return OCS_LAUNCH_SEQ(4);
-    }
-#undef OCS_LAUNCH_SEQ
+    return launch_kernel(kTimeSplitQuantize, select_expand_quantize_kernel, dim3((unsigned)grid), dim3(kThreads),
+                         greedy_list_bytes(E), stream, W, ldw, N, C, g, s, colmax, split_src, chan_src, chan_depth,
+                         max_out, clip_ratio, qmax, scale_out, Wq, D, main_units, magic);
 }
 
 // fp32 expanded tensor (Eq. 3 with halve != 0, the weight side of Eq. 4 with halve == 0).

@@ -1,136 +1,235 @@
 // Device-side pieces of the greedy channel selection of Sec. 3.4, shared by the selector kernel
 // and by the weight pass that runs the selection in its own prologue.
 //
-// The list of channel maxima lives in LDS: `vals` holds P = lanes * S slots (slots that do not
-// exist yet hold -1.0), `src` and `dep` the original channel and the number of halvings of each
-// of the C + s expanded channels.  Every lane owns a block of S consecutive slots and caches the
-// best entry of its block.  Ties go to the lowest expanded index: the key packs the value's bit
-// pattern (non-negative floats order like unsigned integers) above the complemented index.
+// The list of channel maxima lives in LDS: `vals` holds one slot per expanded channel, `src` and
+// `dep` the original channel and the number of halvings of each.  The paper splits one channel at a
+// time, always the one with the largest value, the lowest expanded index among equals.  That
+// sequence does not have to be walked step by step: with M the largest value of the list, every
+// entry above M/2 is split before any half that these splits leave behind (a half is at most M/2),
+// so a whole ROUND of splits is the entries above M/2 in descending order, lowest index first among
+// equals, and the i-th of them appends expanded channel cur + i.  After the round the largest value
+// is exactly M/2 (the halves of M), and the next round holds at least twice as many entries as there
+// were halves of M: s splits take at most log2(s) + 2 rounds, whatever the values.  A round is a
+// handful of passes over the list by the whole workgroup; a split costs no sequential step.
 #pragma once
 #include "ocs_internal.h"
 
 namespace ocs {
 
-__device__ inline unsigned long long key_of_bits(unsigned bits, int j) {
-    return ((unsigned long long)bits << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)j);
-}
-
-// Largest key of the wave: largest value first, then the lowest index among the lanes that hold
-// it.  One reduction, on the values alone: blocks lie in lane order and every lane caches the
-// lowest slot among the equals of its own block, so among the lanes that hold the largest value the
-// lowest lane holds the lowest index (lanes without entries carry key 0 and sit above all lanes
-// of the list that have some).
-__device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {
-    const unsigned hi = (unsigned)(k >> 32);
-    const unsigned mhi = wave_umax32(hi);
-    const int winner = __ffsll((long long)__ballot(hi == mhi)) - 1;
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)k, winner);
-    return ((unsigned long long)mhi << 32) | lo;
-}
-
-// Best entry of a block of S slots held in registers (v[q][e] = slot j0 + 4q + e): the largest
-// value, the lowest slot among equals (slots are visited in ascending order and only a strictly
-// larger value replaces the best so far).  Values are compared as signed integers on their bit
-// patterns: existing entries are non-negative floats, slots that do not exist yet hold -1.0
-// (negative as an integer) and can never win.  0 when the block holds no entry.
-template <int S>
-__device__ __forceinline__ unsigned long long best_of(const f32x4 (&v)[S / 4], int j0) {
-    int bv = -1, bj = 0;
-#pragma unroll
-    for (int q = 0; q < S / 4; ++q) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int u = (int)__float_as_uint(v[q][e]);
-            const bool better = u > bv;
-            bv = better ? u : bv;
-            bj = better ? 4 * q + e : bj;
-        }
-    }
-    return bv < 0 ? 0ull : key_of_bits((unsigned)bv, j0 + bj);
-}
-
-// The block of S slots that starts at slot j0, read from LDS (all reads issued together), and
-// its best entry.
-template <int S>
-__device__ __forceinline__ void block_load(const float* vals, int j0, f32x4 (&v)[S / 4]) {
-    const f32x4* p = reinterpret_cast<const f32x4*>(vals + j0);
-#pragma unroll
-    for (int q = 0; q < S / 4; ++q) v[q] = p[q];
-}
-template <int S>
-__device__ __forceinline__ unsigned long long block_best(const float* vals, int j0) {
-    f32x4 v[S / 4];
-    block_load<S>(vals, j0, v);
-    return best_of<S>(v, j0);
-}
-
-// Channel maxima from the K = C * g column maxima into vals[0 .. C), the other slots marked as
-// not existing, src/dep set to the identity.  One coalesced, independent load per column, folded
-// per channel with LDS atomics on the bit pattern.  Called by all kThreads lanes of the
-// workgroup; contains barriers, and ends with one.
+// Channel maxima from the K = C * g column maxima into vals[0 .. C), src/dep set to the identity.
+// One coalesced, independent load per column, folded per channel with LDS atomics on the bit
+// pattern.  Called by all NT lanes of the workgroup; contains barriers, and ends with one.
+template <int NT>
 __device__ __forceinline__ void channel_maxima_to_lds(const float* __restrict__ colmax, int C, int g,
-                                                      int P, float* vals, unsigned short* src,
-                                                      unsigned short* dep) {
+                                                      float* vals, unsigned short* src, unsigned short* dep) {
     const int tid = threadIdx.x;
-    for (int j = tid; j < P; j += kThreads) vals[j] = j < C ? 0.0f : -1.0f;
-    for (int j = tid; j < C; j += kThreads) {
+    for (int j = tid; j < C; j += NT) {
+        vals[j] = 0.0f;
         src[j] = (unsigned short)j;
         dep[j] = 0;
     }
     __syncthreads();
     const int K = C * g;
     unsigned* vbits = reinterpret_cast<unsigned*>(vals);
-    // Sixteen loads per lane are requested before the first value is used: the column maxima were
-    // written a moment ago by other CUs and every load waits a whole trip through the fabric.  (The
-    // compiler keeps a load behind the LDS atomic that precedes it in program order, so a plain
-    // loop, unrolled or not, made one trip per column of a lane: most of the selector's time.)
-    constexpr int UN = 16;
-    for (int k0 = tid; k0 < K; k0 += UN * kThreads) {
+    // Sixteen loads per lane (four in the wide workgroup) are requested before the first value is
+    // used: the column maxima were written a moment ago by other CUs and every load waits a whole
+    // trip through the fabric.  (The compiler keeps a load behind the LDS atomic that precedes it in
+    // program order, so a plain loop, unrolled or not, makes one trip per column of a lane.)
+    constexpr int UN = NT >= 1024 ? 4 : 16;
+    for (int k0 = tid; k0 < K; k0 += UN * NT) {
         float v[UN];
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            const int k = k0 + u * kThreads;
+            const int k = k0 + u * NT;
             v[u] = colmax[k < K ? k : K - 1];
         }
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
-            const int k = k0 + u * kThreads;
+            const int k = k0 + u * NT;
             if (k < K) atomicMax(&vbits[k / g], __float_as_uint(v[u]));
         }
     }
     __syncthreads();
 }
 
-// The s greedy steps on a list of at most 64 * S entries, run by the 64 lanes of ONE wave (lane
-// = its index in the wave, which owns slots lane*S ...): no barrier and no exchange through LDS
-// in a step.  A wave's LDS accesses execute in program order: a slot written in one step is seen
-// by whichever lane re-scans its block in a later one.  split_src (may be null) receives the
-// expanded index chosen at every step.
-template <int LOG2_S>
-__device__ __forceinline__ void greedy_one_wave(float* vals, unsigned short* src, unsigned short* dep,
-                                                int C, int s, int lane, int32_t* split_src) {
-    constexpr int S = 1 << LOG2_S;
-    unsigned long long local = block_best<S>(vals, lane * S);
-    for (int i = 0; i < s; ++i) {
-        const int cur = C + i;
-        const unsigned long long k = wave_max_key(local);   // lane 0 always has an entry
-        const int jstar = (int)(0xFFFFFFFFu - (unsigned)(k & 0xFFFFFFFFull));
-        const float half = __uint_as_float((unsigned)(k >> 32)) * 0.5f;
-        if ((jstar >> LOG2_S) == lane) {
-            // both look-ups first (one trip to LDS for the two), then the stores, then the re-scan
-            const unsigned short s0 = src[jstar];
-            const unsigned short d = (unsigned short)(dep[jstar] + 1);
-            vals[jstar] = half;
-            vals[cur] = half;
-            dep[jstar] = d;
-            src[cur] = s0;
-            dep[cur] = d;
-            if (split_src) split_src[i] = jstar;
-            local = block_best<S>(vals, lane * S);
-        } else if ((cur >> LOG2_S) == lane) {
-            const unsigned long long kn = key_of_bits(__float_as_uint(half), cur);
-            local = kn > local ? kn : local;
+// Scratch of greedy_rounds in LDS.
+constexpr int kGreedyBins = 256;
+struct GreedyScratch {
+    unsigned hist[kGreedyBins];
+    unsigned red[16];
+    unsigned count, bin, before, size;
+};
+// Most splits of a round: at most the entries the list has and at most the splits that are left, and
+// the two add up to no more than E.
+__host__ __device__ inline int greedy_cand_cap(int E) { return E / 2 + 1; }
+// LDS of the list: the keys of a round's splits, the values, sources and depths (in this order).
+__host__ __device__ inline unsigned greedy_list_bytes(int E) { return (unsigned)greedy_cand_cap(E) * 8u + (unsigned)E * 8u; }
+
+// Largest of `v` over the workgroup (bit patterns of non-negative floats).  Two barriers.
+template <int NT>
+__device__ __forceinline__ unsigned group_umax(unsigned v, unsigned* red) {
+    v = wave_umax32(v);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = red[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) v = red[w] > v ? red[w] : v;
+    __syncthreads();
+    return v;
+}
+
+// The s greedy steps on a list of C entries, by all NT lanes.  split_src (may be null) receives the
+// expanded index chosen at every step.  Contains barriers, and ends with one.
+//   Sort key of an entry of the round: (M - value) in units of the last place (below 2^23: values lie
+//   in (M/2, M]) above the index (13 bits): ascending keys are the order of the splits, and no two are
+//   equal.  When a round holds more entries than splits are left, the largest key that still takes
+//   part is found digit by digit (8 bits at a time, a histogram in LDS per digit).
+template <int NT>
+__device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, unsigned short* dep,
+                                              unsigned long long* cand, GreedyScratch& sc, int C, int s,
+                                              int32_t* split_src) {
+    static_assert(NT % 64 == 0 && NT / 64 <= 16 && NT >= kGreedyBins, "waves of the workgroup");
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const unsigned* vbits = reinterpret_cast<const unsigned*>(vals);
+    if (s <= 0) return;
+    unsigned m = 0;
+    for (int j = tid; j < C; j += NT) m = vbits[j] > m ? vbits[j] : m;
+    unsigned mbits = group_umax<NT>(m, sc.red);
+    const int cap = greedy_cand_cap(C + s);
+    int cur = C, rem = s;
+    while (rem > 0) {
+        const unsigned hbits = __float_as_uint(__uint_as_float(mbits) * 0.5f);
+        if (!(mbits > hbits)) {
+            // nothing but zeros left (or an infinite channel): halving changes no value any more, and
+            // every remaining step takes the lowest index that holds the largest value
+            unsigned low = 0;                                    // complemented index: largest = lowest index
+            for (int j = tid; j < cur; j += NT)
+                if (vbits[j] == mbits) { low = 0xFFFFFFFFu - (unsigned)j; break; }
+            const int js = (int)(0xFFFFFFFFu - group_umax<NT>(low, sc.red));
+            const unsigned short s0 = src[js];
+            const int d0 = dep[js];
+            __syncthreads();                                     // everyone has read entry js
+            for (int i = tid; i < rem; i += NT) {
+                vals[cur + i] = __uint_as_float(hbits);
+                src[cur + i] = s0;
+                dep[cur + i] = (unsigned short)(d0 + i + 1);
+                if (split_src) split_src[cur + i - C] = js;
+            }
+            if (tid == 0) {
+                vals[js] = __uint_as_float(hbits);
+                dep[js] = (unsigned short)(d0 + rem);
+            }
+            __syncthreads();
+            return;
         }
+        auto key_of = [&](int j) {
+            return ((unsigned long long)(mbits - vbits[j]) << 13) | (unsigned long long)j;
+        };
+        // the round's entries, in no order yet (whole waves walk the list: one LDS atomic per wave).
+        // `count` is cleared ahead of the barrier that precedes this pass.
+        auto gather = [&](unsigned long long cut) {
+            for (int j0 = tid - lane; j0 < cur; j0 += NT) {
+                const int j = j0 + lane;
+                const bool in = j < cur && vbits[j] > hbits && key_of(j) <= cut;
+                const unsigned long long mask = __ballot(in);
+                if (mask == 0) continue;
+                unsigned base = 0;
+                if (lane == 0) base = atomicAdd(&sc.count, (unsigned)__popcll(mask));
+                base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+                const int pos = (int)base + __popcll(mask & ((1ull << lane) - 1ull));
+                if (in && pos < cap) cand[pos] = key_of(j);
+            }
+        };
+        if (tid == 0) sc.count = 0;
+        __syncthreads();
+        gather(~0ull);
+        __syncthreads();
+        int take = (int)sc.count;
+        if (take > rem) {
+            // the rem smallest keys: find the largest of them
+            unsigned long long prefix = 0;       // digits fixed so far
+            int need = rem;
+            unsigned long long cut = 0;
+            int shift = 28;                      // 36 key bits: digits at 28, 20, 12, 4 and the last 4 bits
+            for (;;) {
+                const int width = shift == 0 ? 4 : 8;
+                if (tid < kGreedyBins) sc.hist[tid] = 0;
+                __syncthreads();
+                for (int j = tid; j < cur; j += NT) {
+                    if (vbits[j] <= hbits) continue;
+                    const unsigned long long k = key_of(j);
+                    if ((k >> (shift + width)) == prefix) atomicAdd(&sc.hist[(unsigned)(k >> shift) & ((1u << width) - 1u)], 1u);
+                }
+                __syncthreads();
+                if (tid < 64) {                  // first bin at which the running count reaches `need`
+                    unsigned h4[4], sum = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { h4[e] = sc.hist[4 * tid + e]; sum += h4[e]; }
+                    unsigned incl = sum;
+#pragma unroll
+                    for (int o = 1; o < 64; o <<= 1) {
+                        const unsigned up = (unsigned)__shfl_up((int)incl, o);
+                        if (tid >= o) incl += up;
+                    }
+                    unsigned run = incl - sum;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (run < (unsigned)need && run + h4[e] >= (unsigned)need) {
+                            sc.bin = 4 * tid + e;
+                            sc.before = run;
+                            sc.size = h4[e];
+                        }
+                        run += h4[e];
+                    }
+                }
+                __syncthreads();
+                prefix = (prefix << width) | sc.bin;
+                need -= (int)sc.before;
+                if ((int)sc.size == need || shift == 0) {        // the whole bin takes part
+                    cut = ((prefix + 1) << shift) - 1;
+                    break;
+                }
+                shift = shift >= 12 ? shift - 8 : 0;
+            }
+            if (tid == 0) sc.count = 0;
+            __syncthreads();
+            gather(cut);
+            __syncthreads();
+            take = rem;
+        }
+        // rank of every split of the round = how many keys are smaller; G lanes share one split's count
+        int log2_G = 0;
+        while (log2_G < 4 && (take << (log2_G + 1)) <= NT) ++log2_G;
+        const int G = 1 << log2_G;
+        const int per = NT >> log2_G;
+        for (int i0 = 0; i0 < take; i0 += per) {
+            const int i = i0 + (tid >> log2_G);
+            const unsigned long long mine = i < take ? cand[i] : 0ull;
+            int rank = 0;
+            if (i < take) {
+                int k = tid & (G - 1);
+                for (; k + 3 * G < take; k += 4 * G)
+                    rank += (cand[k] < mine) + (cand[k + G] < mine) + (cand[k + 2 * G] < mine) +
+                            (cand[k + 3 * G] < mine);
+                for (; k < take; k += G) rank += cand[k] < mine;
+            }
+            for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o);
+            if (i < take && (tid & (G - 1)) == 0) {
+                const int j = (int)(mine & 0x1FFFull), n = cur + rank;
+                const float half = vals[j] * 0.5f;
+                const unsigned short s0 = src[j], d = (unsigned short)(dep[j] + 1);
+                vals[j] = half;
+                vals[n] = half;
+                dep[j] = d;
+                dep[n] = d;
+                src[n] = s0;
+                if (split_src) split_src[n - C] = j;
+            }
+        }
+        __syncthreads();
+        cur += take;
+        rem -= take;
+        mbits = hbits;          // the halves of M are the largest entries now (a cut round is the last one)
     }
 }
 

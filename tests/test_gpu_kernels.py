@@ -148,6 +148,37 @@ def test_select_at_the_list_layout_boundaries(E, kind):
     assert got["max"] == exp["max"]
 
 
+def _maxima(kind, C, rng):
+    """Channel maxima at which a round of splits can go wrong."""
+    if kind == "equal":                       # one round of equals, cut by index
+        return np.full(C, 0.37, np.float32)
+    if kind == "last_digits":                 # values a few units of the last place apart, many of them equal
+        return (np.float32(1.5).view(np.uint32) - rng.integers(0, 40, C).astype(np.uint32)).view(np.float32)
+    if kind == "octaves":                     # powers of two: halves meet other channels' values
+        return np.exp2(-rng.integers(0, 6, C)).astype(np.float32)
+    if kind == "just_above_half":             # the last entries of a round and the first of the next
+        m = np.where(rng.random(C) < 0.5, np.float32(0.5), np.nextafter(np.float32(0.5), np.float32(1)))
+        m[C // 2] = 1.0
+        return m.astype(np.float32)
+    if kind == "denormal":                    # halving rounds, then reaches zero
+        return (rng.integers(0, 9, C) * 1.4e-45).astype(np.float32)
+    return np.exp(rng.uniform(-12, 12, C)).astype(np.float32)
+
+
+@pytest.mark.parametrize("C,s", [(1, 1), (1, 40), (7, 6), (256, 1), (256, 255), (256, 256), (300, 301), (1100, 37),
+                                 (4000, 4000), (7000, 600), (7999, 1)])
+@pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread"])
+def test_select_rounds(C, s, kind):
+    """Rounds cut at every digit of the sort key, rounds that end in zeros, the largest list."""
+    m = _maxima(kind, C, np.random.default_rng(C + s))
+    T = np.ascontiguousarray(np.stack([m * np.float32(0.25), -m]))
+    exp = ref.split_weights(T, C, 1, s)
+    got = gpu_select(T, C, 1, s)
+    for k in ("split_src", "chan_src", "chan_depth"):
+        assert np.array_equal(got[k], exp[k]), k
+    assert got["max"] == exp["max"]
+
+
 def test_select_resplits_one_dominant_channel():
     rng = np.random.default_rng(2)
     T = rng.standard_normal((10, 12)).astype(np.float32)
