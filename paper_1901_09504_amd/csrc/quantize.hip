@@ -895,7 +895,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     const int E = C + s, Ke = E * g;
     unsigned long long* cand = reinterpret_cast<unsigned long long*>(smem);
-    float* vals = reinterpret_cast<float*>(cand + greedy_cand_cap(E));
+    float* vals = reinterpret_cast<float*>(cand + E);
     unsigned short* src = reinterpret_cast<unsigned short*>(vals + E);
     unsigned short* dep = src + E;
     __shared__ GreedyScratch sc;

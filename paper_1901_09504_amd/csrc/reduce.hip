@@ -29,8 +29,10 @@ ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok) {
     if (rb < 1) rb = 1;
     // A layer's weights (few rows, long rows): narrow strips that each run down ALL rows give
     // enough workgroups by themselves, and with a single row block stage 1 writes the column
-    // maxima directly: one launch instead of two launch-latency-bound ones.
-    if (p.vec == 4 && rows <= 2048 && ceil_div(units, 8) >= 32) {
+    // maxima directly: one launch instead of two launch-latency-bound ones.  With up to 512 rows (16
+    // per lane) that is so for any number of strips: 256 x 256 weights 2.9 + 2.1 us and the gap
+    // between them -> 3.4 us in one launch.
+    if (p.vec == 4 && rows <= 2048 && (ceil_div(units, 8) >= 32 || rows <= 512)) {
         p.tx = 8;                                  // 8 lanes x 16 B = one 128-byte line per row
         p.ty = kThreads / p.tx;
         p.col_strips = (int)ceil_div(units, p.tx);

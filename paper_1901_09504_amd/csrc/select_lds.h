@@ -59,11 +59,8 @@ struct GreedyScratch {
     unsigned red[16];
     unsigned count, bin, before, size;
 };
-// Most splits of a round: at most the entries the list has and at most the splits that are left, and
-// the two add up to no more than E.
-__host__ __device__ inline int greedy_cand_cap(int E) { return E / 2 + 1; }
-// LDS of the list: the keys of a round's splits, the values, sources and depths (in this order).
-__host__ __device__ inline unsigned greedy_list_bytes(int E) { return (unsigned)greedy_cand_cap(E) * 8u + (unsigned)E * 8u; }
+// LDS of the list: the keys of a round's entries, the values, sources and depths (in this order).
+__host__ __device__ inline unsigned greedy_list_bytes(int E) { return (unsigned)E * 16u; }
 
 // Largest of `v` over the workgroup (bit patterns of non-negative floats).  Two barriers.
 template <int NT>
@@ -82,8 +79,10 @@ __device__ __forceinline__ unsigned group_umax(unsigned v, unsigned* red) {
 // expanded index chosen at every step.  Contains barriers, and ends with one.
 //   Sort key of an entry of the round: (M - value) in units of the last place (below 2^23: values lie
 //   in (M/2, M]) above the index (13 bits): ascending keys are the order of the splits, and no two are
-//   equal.  When a round holds more entries than splits are left, the largest key that still takes
-//   part is found digit by digit (8 bits at a time, a histogram in LDS per digit).
+//   equal.  An entry's place is the number of smaller keys of the round, counted by all lanes; when a
+//   round holds more entries than splits are left and too many to count over, a bound on the largest
+//   key that still takes part is found first, digit by digit (8 bits at a time, a histogram in LDS per
+//   digit) until few enough entries lie below it.
 template <int NT>
 __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, unsigned short* dep,
                                               unsigned long long* cand, GreedyScratch& sc, int C, int s,
@@ -95,7 +94,6 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
     unsigned m = 0;
     for (int j = tid; j < C; j += NT) m = vbits[j] > m ? vbits[j] : m;
     unsigned mbits = group_umax<NT>(m, sc.red);
-    const int cap = greedy_cand_cap(C + s);
     int cur = C, rem = s;
     while (rem > 0) {
         const unsigned hbits = __float_as_uint(__uint_as_float(mbits) * 0.5f);
@@ -137,15 +135,18 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 if (lane == 0) base = atomicAdd(&sc.count, (unsigned)__popcll(mask));
                 base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
                 const int pos = (int)base + __popcll(mask & ((1ull << lane) - 1ull));
-                if (in && pos < cap) cand[pos] = key_of(j);
+                if (in) cand[pos] = key_of(j);
             }
         };
         if (tid == 0) sc.count = 0;
         __syncthreads();
         gather(~0ull);
         __syncthreads();
-        int take = (int)sc.count;
-        if (take > rem) {
+        int in_round = (int)sc.count;
+        // (counting costs in_round^2 / NT look-ups per lane, a digit three barriers: level at about 32
+        // look-ups)
+        auto countable = [&](int n) { return n * n <= 32 * NT; };
+        if (in_round > rem && !countable(in_round)) {
             // the rem smallest keys: find the largest of them
             unsigned long long prefix = 0;       // digits fixed so far
             int need = rem;
@@ -185,7 +186,8 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 __syncthreads();
                 prefix = (prefix << width) | sc.bin;
                 need -= (int)sc.before;
-                if ((int)sc.size == need || shift == 0) {        // the whole bin takes part
+                in_round = rem - need + (int)sc.size;            // entries up to and in that bin
+                if (in_round == rem || countable(in_round) || shift == 0) {
                     cut = ((prefix + 1) << shift) - 1;
                     break;
                 }
@@ -195,26 +197,26 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
             __syncthreads();
             gather(cut);
             __syncthreads();
-            take = rem;
         }
-        // rank of every split of the round = how many keys are smaller; G lanes share one split's count
+        const int take = in_round < rem ? in_round : rem;
+        // rank of every entry of the round = how many keys are smaller; G lanes share one entry's count
         int log2_G = 0;
-        while (log2_G < 4 && (take << (log2_G + 1)) <= NT) ++log2_G;
+        while (log2_G < 4 && (in_round << (log2_G + 1)) <= NT) ++log2_G;
         const int G = 1 << log2_G;
         const int per = NT >> log2_G;
-        for (int i0 = 0; i0 < take; i0 += per) {
+        for (int i0 = 0; i0 < in_round; i0 += per) {
             const int i = i0 + (tid >> log2_G);
-            const unsigned long long mine = i < take ? cand[i] : 0ull;
+            const unsigned long long mine = i < in_round ? cand[i] : 0ull;
             int rank = 0;
-            if (i < take) {
+            if (i < in_round) {
                 int k = tid & (G - 1);
-                for (; k + 3 * G < take; k += 4 * G)
+                for (; k + 3 * G < in_round; k += 4 * G)
                     rank += (cand[k] < mine) + (cand[k + G] < mine) + (cand[k + 2 * G] < mine) +
                             (cand[k + 3 * G] < mine);
-                for (; k < take; k += G) rank += cand[k] < mine;
+                for (; k < in_round; k += G) rank += cand[k] < mine;
             }
             for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o);
-            if (i < take && (tid & (G - 1)) == 0) {
+            if (i < in_round && rank < take && (tid & (G - 1)) == 0) {
                 const int j = (int)(mine & 0x1FFFull), n = cur + rank;
                 const float half = vals[j] * 0.5f;
                 const unsigned short s0 = src[j], d = (unsigned short)(dep[j] + 1);
