@@ -704,6 +704,174 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_wholek_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Few tiles: the K extent dealt over the waves of a workgroup.  A layer of a few rows (one time step
+// of a recurrent layer, a small batch) has too few tiles for the chip, and a tile's walk along K with
+// a barrier per step is then one long chain on a handful of compute units.  Here every wave computes
+// the WHOLE tile over its own 64-byte steps of K (step `wave`, `wave` + NW, ...; neighbouring waves
+// share a row's lines): its operands go global -> LDS into a ring of its own (NBUF steps, the layout
+// and swizzle of the whole-K kernel), which only this wave fills and reads, so the loop has no
+// barrier and the waves drift as their requests come back.  The NW partial tiles then meet in LDS:
+// one barrier, every wave sums its rows over the NW copies (integer sums: any order gives the same
+// bits) and stores them.
+// What bounds it: the latency of a wave's few requests, the sum over the partial tiles and the launch
+// itself.  Operands straight into registers instead (no LDS on the way) was slower from a few hundred
+// bytes of K on: a lane's 16 bytes of its own row cost the L1 a look-up per lane, where the LDS form
+// asks for four lanes' worth of a row at once (64 x 256 x 2420: 7.0 against 4.1 us).
+// ---------------------------------------------------------------------------------------------
+template <int TM, int TN, int NW, int NBUF>
+__global__ __launch_bounds__(NW * 64) void qgemm_slice_kernel(
+    const int8_t* __restrict__ Xq, int64_t ldx, const int8_t* __restrict__ Wq, int64_t ldw, int M,
+    int N, int ksteps, const float* __restrict__ scale_x, const float* __restrict__ scale_w,
+    int32_t* __restrict__ acc_out, int64_t ldacc, float* __restrict__ Y, int64_t ldy, int tiles_m, int tiles_n,
+    int rows_first, Requant rq) {
+    constexpr int BM = 32 * TM, BN = 32 * TN;
+    constexpr int LPS = (BM + BN) / 16;                           // 1 KB requests of a step: 16 rows each
+    constexpr int STEP = (BM + BN) * 64;
+    constexpr int RING = NBUF * STEP;                             // LDS of a wave: its ring, then its partial tile
+    constexpr int EW = BM * BN / 256 < NW ? BM * BN / 256 : NW;   // waves that store: at least 64 x 4 outputs each
+    constexpr int ROWS = BM / EW;
+    static_assert(EW * ROWS == BM && ROWS * BN % 256 == 0, "whole waves of 16-byte outputs");
+    static_assert(RING >= BM * BN * 4, "a wave's partial tile replaces its ring");
+    static_assert((NBUF - 1) * LPS < 64, "prefetch ring exceeds the vmcnt range");
+    static_assert(NBUF >= 2 && NBUF <= 4, "waits below");
+    static_assert(BN <= 256, "a dup_list entry holds the column in 8 bits");
+    extern __shared__ __align__(1024) int8_t slds[];
+    int* dup_list = reinterpret_cast<int*>(slds + NW * RING);     // only with copies to write
+    int* dup_count = dup_list + kDupCap;
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(3))) int8_t* lptr_t;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lptr_t)&slds[0];
+#else
+    const unsigned lds0 = 0;
+#endif
+
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);    // uniform: the step counts below are scalar
+    const unsigned tile = xcd_remap(blockIdx.x, (unsigned)tiles_m * (unsigned)tiles_n);
+    // tiles that share the larger operand's panel follow each other on one XCD
+    const int bm = rows_first ? (int)(tile % (unsigned)tiles_m) : (int)(tile / (unsigned)tiles_n);
+    const int bn = rows_first ? (int)(tile / (unsigned)tiles_m) : (int)(tile % (unsigned)tiles_n);
+    const int row0 = bm * BM, col0 = bn * BN;
+
+    // request q of a step: lane l fills row 16q + l/4, chunk slot l%4 of the step's image (A rows, then
+    // B rows); the swizzle depends on the row's low four bits only, so a lane's piece is the same in all
+    const int piece = swz<64>(lane >> 2, lane & 3);
+    const int8_t* src[LPS];
+#pragma unroll
+    for (int q = 0; q < LPS; ++q) {
+        const int r = q * 16 + (lane >> 2);
+        src[q] = q * 16 < BM ? Xq + (int64_t)col_clamp(row0 + r, M) * ldx          // (rows past the edge are never stored)
+                             : Wq + (int64_t)col_clamp(col0 + r - BM, N) * ldw;
+    }
+    // a row's pitch may end inside the last K-step: pieces past it come from zero_chunk
+    const int a_end = (int)(ldx / 16), b_end = (int)(ldw / 16);
+    const unsigned ring0 = lds0 + (unsigned)wave * RING;
+    const int8_t* ring = slds + wave * RING;
+    const int trips = (ksteps - wave + NW - 1) / NW;              // this wave's steps (none: its tile is zero)
+    auto fetch = [&](int it, int buf) {
+        const int p = (it * NW + wave) * 4 + piece;
+#pragma unroll
+        for (int q = 0; q < LPS; ++q)
+            lds_dma16(p < (q * 16 < BM ? a_end : b_end) ? src[q] + (int64_t)p * 16 : zero_chunk,
+                      ring0 + (unsigned)(buf * STEP + q * 1024));
+    };
+
+    i32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+
+#pragma unroll
+    for (int u = 0; u + 1 < NBUF; ++u)
+        if (u < trips) fetch(u, u);
+    if (rq.Yq != nullptr && rq.s_next > 0) build_dup_list<NW * 64>(rq, N, col0, BN, dup_list, dup_count);
+
+    const int frag_row = lane & 31, frag_half = lane >> 5;
+    for (int it0 = 0; it0 < trips; it0 += NBUF) {
+#pragma unroll
+        for (int u = 0; u < NBUF; ++u) {
+            const int it = it0 + u;
+            if (it >= trips) break;
+            const int left = trips - 1 - it;                      // this wave's steps after this one
+            if (left >= NBUF - 1) {
+                // the buffer requested into was read by the step before: its reads have returned
+                __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));   // lgkmcnt(0)
+                fetch(it + NBUF - 1, (u + NBUF - 1) % NBUF);
+                wait_vmcnt<(NBUF - 1) * LPS>();
+            } else if (NBUF > 3 && left == 2) {
+                wait_vmcnt<(NBUF > 3 ? 2 : 0) * LPS>();
+            } else if (NBUF > 2 && left == 1) {
+                wait_vmcnt<(NBUF > 2 ? 1 : 0) * LPS>();
+            } else {
+                wait_vmcnt<0>();
+            }
+            asm volatile("" ::: "memory");                        // no read of the step above its wait
+            const int8_t* base = ring + u * STEP;
+            i32x4 a[2][TM], b[2][TN];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i) {
+                    const int r = i * 32 + frag_row;
+                    a[ks][i] = *reinterpret_cast<const i32x4*>(&base[r * 64 + swz<64>(r, ks * 2 + frag_half) * 16]);
+                }
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    const int r = j * 32 + frag_row;
+                    b[ks][j] = *reinterpret_cast<const i32x4*>(&base[(BM + r) * 64 + swz<64>(r, ks * 2 + frag_half) * 16]);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);                    // all reads on their way before the first product
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks][i], b[ks][j], acc[i][j], 0, 0, 0);
+        }
+    }
+    // every request of this wave has landed and every read has returned (the last step waited for
+    // both): the ring takes the partial tile
+    constexpr int PSTRIDE = RING / 4;
+    int32_t* part = reinterpret_cast<int32_t*>(slds);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                part[wave * PSTRIDE + (i * 32 + (v >> 2) * 8 + frag_half * 4 + (v & 3)) * BN + j * 32 + frag_row] = acc[i][j][v];
+    __syncthreads();
+    if (wave >= EW) return;                       // no barrier follows
+
+    int32_t* stage = part + wave * (ROWS * BN);   // this wave's rows of copy 0: the sum goes there
+#pragma unroll
+    for (int o = 0; o < ROWS * BN / 256; ++o) {
+        i32x4 sum = *reinterpret_cast<const i32x4*>(&stage[(o * 64 + lane) * 4]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const i32x4 v = *reinterpret_cast<const i32x4*>(&stage[w * PSTRIDE + (o * 64 + lane) * 4]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += v[e];
+        }
+        *reinterpret_cast<i32x4*>(&stage[(o * 64 + lane) * 4]) = sum;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const float scale = scale_x[1] * scale_w[1];
+    const float inv = requant_inv(rq, blockIdx.x == 0 && tid == 0);
+    const int dup_n = (rq.Yq != nullptr && rq.s_next > 0) ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
+    const bool vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && (ldy % 4 == 0);
+    const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) && (ldacc % 4 == 0);
+    emit_staged_rows<ROWS, BN>(stage, lane, row0 + wave * ROWS, col0, 0, M, N, scale, Y, ldy, acc_out, ldacc, vec_y,
+                               vec_a, rq, inv, dup_list, dup_n, rq.Yq != nullptr && bn == tiles_n - 1);
+}
+
 constexpr int64_t kWholeKMaxLds = 160 * 1024;  // LDS of one CU
 constexpr int kMaxDevices = 64;
 
@@ -1118,6 +1286,35 @@ static hipError_t run_wholek(const int8_t* Xq, int64_t ldx, const int8_t* Wq, in
                          acc_out, ldacc, Y, ldy, (int)tiles_n, (unsigned)total, dup_off, rq);
 }
 
+// The K extent dealt over the waves.  Any K extent and pitch the GEMM accepts.
+template <int TM, int TN, int NW, int NBUF>
+static hipError_t run_slice(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw, int64_t M, int64_t N,
+                            int64_t Kpad, const float* scale_x, const float* scale_w, int32_t* acc_out,
+                            int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream, const Requant& rq) {
+    constexpr int BM = 32 * TM, BN = 32 * TN;
+    const unsigned lds = (unsigned)(NW * NBUF * (BM + BN) * 64 + (rq.Yq != nullptr && rq.s_next > 0 ? (kDupCap + 1) * 4 : 0));
+    if (Kpad < 64 || Kpad % 64 != 0) return hipErrorInvalidValue;
+    if (lds > 65536) {
+        static std::atomic<bool> opted_in[kMaxDevices];
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+        if (!opted_in[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&qgemm_slice_kernel<TM, TN, NW, NBUF>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
+            if (e != hipSuccess) return e;
+            opted_in[dev].store(true, std::memory_order_release);
+        }
+    }
+    const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
+    const int64_t total = tiles_m * tiles_n;
+    if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
+    return launch_kernel(kTimeGemm, qgemm_slice_kernel<TM, TN, NW, NBUF>, dim3((unsigned)total), dim3(NW * 64), lds,
+                         stream, Xq, ldx, Wq, ldw, (int)M, (int)N, (int)(Kpad / 64), scale_x, scale_w, acc_out,
+                         ldacc, Y, ldy, (int)tiles_m, (int)tiles_n, N > M ? 1 : 0, rq);
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NBUF, bool MASK = false>
 static hipError_t run_dma(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw, int64_t M,
                           int64_t N, int64_t Kpad, const float* scale_x, const float* scale_w,
@@ -1293,8 +1490,23 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
                         int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy,
                         hipStream_t stream, const Requant& rq) {
     int tile = tuning().gemm_tile;
+    if (tile < 0) {
+        // Too few tiles for the chip: the smallest tiles that still give every compute unit at most one
+        // workgroup, with K dealt over its waves; with 64 x 64 tiles and a long K the ring kernel's waves
+        // share their fragments and its four workgroups' worth of look-ahead wins.  Launched one after
+        // the other (a launch that does nothing takes 2.9 us this way), against what the rules below
+        // pick: 20 x 6000 x 3150 10.2 -> 6.3 us, 64 x 256 x 269 4.9 -> 3.1, 700 x 256 x 2420 9.4 -> 4.4,
+        // 1500 x 256 x 2420 10.2 -> 5.5, 64 x 6000 x 3150 11.6 -> 8.1, 1000 x 512 x 4842 18.0 -> 10.4,
+        // 3000 x 256 x 269 5.4 -> 4.7, 3000 x 256 x 2420 11.0 -> 8.3 (ring), 12544 x 64 x 600 5.5 -> 4.3
+        // (ring).  Beyond one workgroup per compute unit the next larger tile is ahead every time.
+        const int64_t cus = compute_units();
+        const int64_t t3264 = ceil_div(M, 32) * ceil_div(N, 64), t6432 = ceil_div(M, 64) * ceil_div(N, 32);
+        if (ceil_div(M, 32) * ceil_div(N, 32) <= cus) tile = 26;
+        else if (t3264 <= cus || t6432 <= cus) tile = t6432 < t3264 ? 28 : 27;
+        else if (ceil_div(M, 64) * ceil_div(N, 64) <= cus) tile = Kpad <= 320 ? 29 : 7;
+    }
     // A pitch that is not a whole number of 64-byte K-steps, or shorter than the K extent rounded
-    // up to one (allowed up to 320 bytes of K), is something only the whole-K kernel walks.
+    // up to one (allowed up to 320 bytes of K), is something only the whole-K kernel and the sliced ones walk.
     const bool ring_ok = ldx % 64 == 0 && ldw % 64 == 0 && ldx >= Kpad && ldw >= Kpad;
     if (!ring_ok) {
         if (Kpad > 320) return hipErrorInvalidValue;
@@ -1302,7 +1514,7 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
         // wide N is better served by the ring kernel's tile order, see below)
         if (tile == 9 || (tile < 0 && N >= 1024))
             return run_dma<128, 128, 4, 2, 64, 4, true>(OCS_GEMM_ARGS);
-        if (tile != 16 && tile != 17 && tile != 18 && tile != 19) tile = N <= 64 ? 17 : (N >= 512 ? (Kpad <= 192 ? 17 : 19) : 16);
+        if (tile != 16 && tile != 17 && tile != 18 && tile != 19 && !(tile >= 26 && tile <= 29)) tile = N <= 64 ? 17 : (N >= 512 ? (Kpad <= 192 ? 17 : 19) : 16);
     }
     if (tile < 0) {
         // Measured on MI355X over the layer shapes of the paper's networks.  What a CU can draw is
@@ -1314,7 +1526,6 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
         // order (one L2 fill of an X row panel for all its N tiles).  With N >= 256 and enough
         // tiles, 256 columns per tile halve the reads of X.
         const int64_t t256 = ceil_div(M, 256) * ceil_div(N, 128);
-        const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128);
         const int64_t t256sq = ceil_div(M, 256) * ceil_div(N, 256);
         if (Kpad <= 320) tile = N <= 64 ? 17 : (N >= 1024 ? 9 : (N >= 512 ? (Kpad <= 192 ? 17 : 19) : 16));   // (512 outputs from
                                         // 128 channels: the 128 x 64 tile, 70 against 83 us at M = 200,704)
@@ -1329,15 +1540,14 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
                                         // 128 x 256 (X rows asked for by two tiles, not four; 43-46 against 45-47 us
                                         // on the 512 -> 512 3x3 layers at M = 12544; behind at half that K)
         else if (t256 >= 128) tile = 11;                 // N = 256 with K below 1024 included (89 against 92 us)
-        else if (t128 >= 48) tile = 23;   // 128-byte K-steps when the operands allow them
-        else tile = 6;
+        else tile = 23;   // 128-byte K-steps when the operands allow them
     }
     // A 128-byte K-step needs a K extent that is a multiple of 128.  The extent is the codes
     // rounded up to 64; when both leading dimensions hold 64 bytes more, those are zero padding
     // on both operands (the producers' contract) and the walk may include them.
     const int64_t K128 = round_up(Kpad, 128);
     const bool k128 = K128 == Kpad || (ldx >= K128 && ldw >= K128);
-    // Tile variants by id (the dispatcher above picks 6, 9, 11, 12, 16, 17, 19, 23, 24 or 25; the others
+    // Tile variants by id (the dispatcher above picks 7, 9, 11, 12, 16, 17, 19 or 23 to 29; the others
     // are kept selectable because the parity tests run every kernel family through them).
     switch (tile) {
         case 6: return run_dma<128, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);
@@ -1364,6 +1574,11 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
                              : run_dma<128, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);
         case 25: return k128 ? run_dma<128, 256, 2, 4, 128, 3>(OCS_GEMM_ARGS128)
                              : run_dma<256, 128, 4, 2, 64, 4>(OCS_GEMM_ARGS);
+        // K dealt over eight waves; any pitch
+        case 26: return run_slice<1, 1, 8, 4>(OCS_GEMM_ARGS);    // 32 x 32
+        case 27: return run_slice<1, 2, 8, 3>(OCS_GEMM_ARGS);    // 32 x 64
+        case 28: return run_slice<2, 1, 8, 3>(OCS_GEMM_ARGS);    // 64 x 32
+        case 29: return run_slice<2, 2, 8, 2>(OCS_GEMM_ARGS);    // 64 x 64
         default: return run_dma<64, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);
     }
 }

@@ -810,6 +810,46 @@ def test_qgemm_requant(tile, M, N, K, s_next, relu):
     assert np.array_equal(host(Yq), q_ref)
 
 
+@pytest.mark.parametrize("tile", [26, 27, 28, 29])
+@pytest.mark.parametrize("steps", [1, 2, 5, 7, 8, 9, 15, 16, 17, 24, 25, 32, 33, 40, 41])
+@pytest.mark.parametrize("M,N", [(1, 1), (31, 65), (33, 32), (64, 64), (65, 63), (97, 130)])
+def test_qgemm_k_over_the_waves(tile, steps, M, N):
+    """The tiles whose K is dealt over eight waves: fewer K-steps than waves, whole and broken rounds of
+    them, the ring's fill and drain, a last step that the pitch cuts; an output pitch that takes no 16-byte
+    stores; and the same outputs as codes with copies."""
+    rng = np.random.default_rng(1000 * steps + M + N)
+    K = 64 * steps - int(rng.integers(0, 60))
+    ld = -(-K // 16) * 16 if 64 * steps <= 320 else 64 * steps
+    Xq = np.zeros((M, ld), dtype=np.int8)
+    Wq = np.zeros((N, ld), dtype=np.int8)
+    Xq[:, :K] = rng.integers(-127, 128, (M, K))
+    Wq[:, :K] = rng.integers(-31, 32, (N, K))
+    sx = np.array([3.0, 3.0 / 127], dtype=np.float32)
+    sw = np.array([0.7, 0.7 / 31], dtype=np.float32)
+    acc_ref, y_ref = ref.qgemm(Xq, Wq, K, sx[1], sw[1])
+    T = float(np.float32(0.5 * np.abs(y_ref).max())) if np.abs(y_ref).max() > 0 else 1.0
+    s_next = 3
+    cs = _next_layer_list(rng, N, s_next)
+    ldy = B.ocs_padded_channels(N + s_next) + 16
+    q_ref, sc_ref = ref.requantize(acc_ref, sx[1], sw[1], T, 5, cs, s_next, relu=True, ldq=ldy)
+    Xd, Wd, sxd, swd = dev(Xq), dev(Wq), dev(sx), dev(sw)
+    acc = torch.full((M, N), -9, dtype=torch.int32, device="cuda")
+    Y = torch.full((M, N + 3), -7.0, dtype=torch.float32, device="cuda")
+    Yq = torch.full((M, ldy), 77, dtype=torch.int8, device="cuda")
+    sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+    thr = torch.tensor([T], dtype=torch.float32, device="cuda")
+    B.ocs_tune("gemm_tile", tile)
+    try:
+        B.ocs_qgemm(Xd, ld, Wd, ld, M, N, K, 8, 6, sxd, swd, acc, N, Y, N + 3)
+        B.ocs_qgemm_requant(Xd, ld, Wd, ld, M, N, K, 8, 6, sxd, swd, True, thr, 5, dev(cs), s_next, Yq, ldy, sc)
+    finally:
+        B.ocs_tune("gemm_tile", -1)
+    assert np.array_equal(host(acc), acc_ref)
+    assert_y_close(host(Y)[:, :N], y_ref)
+    assert np.all(host(Y)[:, N:] == -7.0)
+    assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
+
+
 @pytest.mark.parametrize("tile", [-1, 6, 10])
 def test_conv_chain_with_codes_between_the_layers(tile):
     # 3x3 convolution -> ReLU -> codes -> 1x1 layer (a GEMM on those codes), against the oracle
