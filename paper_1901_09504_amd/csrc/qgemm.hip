@@ -52,12 +52,13 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N_ & 15) | (7 << 4) | (15 << 8) | ((N_ >> 4) << 14));
 }
 
-__device__ __forceinline__ unsigned out_code(int a, float scale, int relu, float inv, float qmax) {
-    float y = (float)a * scale;
-    if (relu) y = y > 0.0f ? y : 0.0f;
+// The next layer's code of an accumulator, in the low byte: dequantized, ReLU, Eq. 1.  lo: -qmax, or 0
+// with a ReLU (inv >= 0, so max(y, 0) inv clamped to +-qmax is y inv clamped to [0, qmax]).
+__device__ __forceinline__ unsigned out_code_bits(int a, float scale, float lo, float inv, float qmax) {
+    const float y = (float)a * scale;
     float p = y * inv;
-    p = __builtin_amdgcn_fmed3f(p, -qmax, qmax);
-    return __float_as_uint(p + 12582912.0f) & 0xFFu;   // round half to even; low byte = code
+    p = __builtin_amdgcn_fmed3f(p, lo, qmax);
+    return __float_as_uint(p + 12582912.0f);           // round half to even; low byte = code
 }
 
 // Copies the next layer wants of this workgroup's output columns: entries (j << 8 | column
@@ -86,8 +87,8 @@ __device__ __forceinline__ void build_dup_list(const Requant& rq, int N, int col
 // rbase / cbase: global row and column of the staged block's corner; wcol: its first column
 // inside the workgroup's tile.  fp32 (and the optional int32 dump): lane = (row, four
 // consecutive columns), 16-byte stores.  Codes: lane = (row, sixteen consecutive columns),
-// again 16-byte stores.
-template <int ROWS, int WN>
+// again 16-byte stores.  STRIDE: accumulators from one staged row to the next.
+template <int ROWS, int WN, int STRIDE = WN>
 __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane, int rbase, int cbase,
                                                  int wcol, int M, int N, float scale,
                                                  float* __restrict__ Y, int64_t ldy,
@@ -102,7 +103,7 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
         for (int it = 0; it < SLOTS / 64; ++it) {
             const int idx = it * 64 + lane;
             const int rr = idx / LPR, cc = (idx % LPR) * 4;
-            const i32x4 a = *reinterpret_cast<const i32x4*>(&stage[rr * WN + cc]);
+            const i32x4 a = *reinterpret_cast<const i32x4*>(&stage[rr * STRIDE + cc]);
             const int r = rbase + rr, c = cbase + cc;
             if (r >= M || c >= N) continue;
             if (rq.Yq == nullptr) {
@@ -132,6 +133,7 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
     }
     if (rq.Yq == nullptr) return;
 
+    const float lo = rq.relu ? 0.0f : -rq.qmax;
     constexpr int LPR16 = WN / 16;         // lanes per row, sixteen columns each (2, 4 or 8)
     constexpr int SLOTS16 = ROWS * LPR16;
 #pragma unroll
@@ -143,11 +145,9 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
         unsigned w[4];
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-            const i32x4 a = *reinterpret_cast<const i32x4*>(&stage[rr * WN + cc + 4 * g4]);
-            w[g4] = out_code(a[0], scale, rq.relu, inv, rq.qmax) |
-                    (out_code(a[1], scale, rq.relu, inv, rq.qmax) << 8) |
-                    (out_code(a[2], scale, rq.relu, inv, rq.qmax) << 16) |
-                    (out_code(a[3], scale, rq.relu, inv, rq.qmax) << 24);
+            const i32x4 a = *reinterpret_cast<const i32x4*>(&stage[rr * STRIDE + cc + 4 * g4]);
+            w[g4] = pack4(out_code_bits(a[0], scale, lo, inv, rq.qmax), out_code_bits(a[1], scale, lo, inv, rq.qmax),
+                          out_code_bits(a[2], scale, lo, inv, rq.qmax), out_code_bits(a[3], scale, lo, inv, rq.qmax));
         }
         if (r >= M || c >= N) continue;
         int8_t* qp = rq.Yq + (int64_t)r * rq.ldyq + c;      // 16-byte aligned: ldyq % 16 == 0, c % 16 == 0
@@ -161,25 +161,104 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
                 if (c + e < N) qp[e] = (int8_t)((w[e >> 2] >> (8 * (e & 3))) & 0xFFu);
         }
     }
-    // copies for the channels the next layer splits: the wave that holds the source column
-    // writes appended column N + j, one lane per staged row
-    if (dup_n > 0 && lane < ROWS) {
-        const int r = rbase + lane;
-        for (int k = 0; k < dup_n; ++k) {
-            const int e = dup_list[k];
-            const int local = (e & 0xFF) - wcol;
-            if (local >= 0 && local < WN && r < M)
-                rq.Yq[(int64_t)r * rq.ldyq + N + (e >> 8)] =
-                    (int8_t)out_code(stage[lane * WN + local], scale, rq.relu, inv, rq.qmax);
-        }
+    // copies for the channels the next layer splits: the wave that holds the source column writes
+    // appended column N + j; (row, copy) pairs over the lanes, rows first
+    for (int idx = lane; idx < ROWS * dup_n; idx += 64) {
+        const int e = dup_list[idx / ROWS], rr = idx % ROWS, r = rbase + rr;
+        const int local = (e & 0xFF) - wcol;
+        if (local >= 0 && local < WN && r < M)
+            rq.Yq[(int64_t)r * rq.ldyq + N + (e >> 8)] = (int8_t)out_code_bits(stage[rr * STRIDE + local], scale, lo, inv, rq.qmax);
     }
     // the pad columns of the code tensor (past the last copy) are zero codes: written by one wave
-    // of the last tile column, one lane per staged row
-    if (pad_writer && lane < ROWS) {
-        const int r = rbase + lane;
-        if (r < M)
-            for (int64_t c = (int64_t)N + rq.s_next; c < rq.ldyq; ++c) rq.Yq[(int64_t)r * rq.ldyq + c] = 0;
+    // of the last tile column, (row, dword) pairs over the lanes; the first dword of a row may begin
+    // with the last copies, and then takes its bytes one by one
+    if (pad_writer) {
+        const int64_t c0 = (int64_t)N + rq.s_next, d0 = c0 & ~(int64_t)3;
+        const int dwords = (int)((rq.ldyq - d0) / 4);
+        for (int idx = lane; idx < ROWS * dwords; idx += 64) {
+            const int r = rbase + idx % ROWS, d = idx / ROWS;
+            if (r >= M) continue;
+            int8_t* qp = rq.Yq + (int64_t)r * rq.ldyq + d0 + 4 * d;      // ldyq % 16 == 0: aligned
+            if (d0 + 4 * d >= c0) {
+                *reinterpret_cast<int*>(qp) = 0;
+            } else {
+                for (int e = (int)(c0 - d0); e < 4; ++e) qp[e] = 0;
+            }
+        }
     }
+}
+
+// One wave's accumulators through its piece of LDS to memory.  As 4-byte stores straight from the
+// registers a CU retires ~16 B/clk (measured: the output-bound shapes then run at half the HBM write
+// rate); turned through LDS a lane stores 16 bytes that follow its neighbours' along a row.  Only this
+// wave touches its piece and a wave's LDS accesses execute in issue order, so no barrier is needed.
+//   fp32 (RQ false): products taken with the activations as the first operand; a lane holds one column
+//   of a 32 x 32 block and 16 of its rows.  SROWS (8 or 32) rows of the wave's whole width are staged at
+//   a time, so that a row's stores follow each other (staged 32 columns at a time 802816 x 256 from 64
+//   channels takes 134 us, not 127, and rows of 100 outputs, which share lines, 27, not 17).
+//   Codes (RQ): products taken with the weights as the first operand; a lane holds ONE row of a block and
+//   four times four consecutive columns, so the stage (32 x 32, rows 36 words apart: different banks)
+//   takes a quarter of the writes, and every lane turns 16 of its values into codes.  With 8 staged rows
+//   of 64 columns half of the lanes had none: 3x3 64 -> 64 at 100352 pixels 33 -> 22 us with the tile
+//   that passes the same 8 MB on.
+constexpr int kCodeStride = 36;
+template <bool RQ, int WN, int SROWS>
+constexpr int stage_bytes() { return RQ ? 32 * kCodeStride * 4 : SROWS * WN * 4; }   // per wave
+template <bool RQ, int TM, int TN, int SROWS>
+__device__ __forceinline__ void emit_tile(const i32x16 (&acc)[TM][TN], int32_t* stage, int lane, int rbase, int cbase,
+                                          int wcol, int M, int N, float scale, float* __restrict__ Y, int64_t ldy,
+                                          int32_t* __restrict__ acc_out, int64_t ldacc, const Requant& rq, float inv,
+                                          const int* dup_list, int dup_n, bool pad_writer) {
+    constexpr int WN = 32 * TN;
+    const bool vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && (ldy % 4 == 0);
+    const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) && (ldacc % 4 == 0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        if constexpr (RQ) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    i32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e];
+                    *reinterpret_cast<i32x4*>(&stage[(lane & 31) * kCodeStride + q * 8 + (lane >> 5) * 4]) = v;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                emit_staged_rows<32, 32, kCodeStride>(stage, lane, rbase + i * 32, cbase + j * 32, wcol + j * 32, M, N,
+                                                      scale, Y, ldy, acc_out, ldacc, vec_y, vec_a, rq, inv, dup_list,
+                                                      dup_n, pad_writer && j == TN - 1);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();   // the reads are issued before the next block's writes
+            }
+        } else {
+            constexpr int Q = 4 * SROWS / 32;      // accumulator quads of a lane per staged block
+#pragma unroll
+            for (int q0 = 0; q0 < 4; q0 += Q) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int q = 0; q < Q; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            stage[(q * 8 + (lane >> 5) * 4 + e) * WN + j * 32 + (lane & 31)] = acc[i][j][(q0 + q) * 4 + e];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                emit_staged_rows<SROWS, WN>(stage, lane, rbase + i * 32 + q0 * 8, cbase, wcol, M, N, scale, Y, ldy, acc_out,
+                                            ldacc, vec_y, vec_a, Requant{}, 0.0f, nullptr, 0, false);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+    }
+}
+
+// one product of the tile: the operand that leads decides what a lane of the result holds (see emit_tile)
+template <bool RQ>
+__device__ __forceinline__ i32x16 mfma_tile(i32x4 x, i32x4 w, i32x16 acc) {
+    return RQ ? __builtin_amdgcn_mfma_i32_32x32x32_i8(w, x, acc, 0, 0, 0)
+              : __builtin_amdgcn_mfma_i32_32x32x32_i8(x, w, acc, 0, 0, 0);
 }
 
 __device__ __forceinline__ float requant_inv(const Requant& rq, bool writer) {
@@ -225,8 +304,8 @@ __device__ __align__(16) int8_t zero_chunk[16] = {};   // (not declared const: i
 
 // MASK: the pitches may end inside the last K-step (see zero_chunk); every request then checks
 // its piece against the pitch.
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NBUF, bool CONV = false, bool SPLIT = false,
-          bool MASK = false>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NBUF, bool RQ = false, bool CONV = false,
+          bool SPLIT = false, bool MASK = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     const int8_t* __restrict__ Xq, int64_t ldx, const int8_t* __restrict__ Wq, int64_t ldw, int M,
     int N, int ksteps_all, const float* __restrict__ scale_x, const float* __restrict__ scale_w,
@@ -251,7 +330,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     // one array: the A ring, then the B ring; the epilogue reuses all of it
     constexpr int RING_BYTES = NBUF * (BM + BN) * BK;
     __shared__ __align__(1024) int8_t lds[RING_BYTES];
-    __shared__ int dup_list[kDupCap];
+    __shared__ int dup_list[RQ ? kDupCap : 1];
     __shared__ int dup_count;
     int8_t (*lds_a)[BM * BK] = reinterpret_cast<int8_t (*)[BM * BK]>(&lds[0]);
     int8_t (*lds_b)[BN * BK] = reinterpret_cast<int8_t (*)[BN * BK]>(&lds[NBUF * BM * BK]);
@@ -413,7 +492,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+                acc[i][j] = mfma_tile<RQ>(a[i], b[j], acc[i][j]);
     };
 
     // Step kt multiplies out of buffer kt % NBUF.  At its start it requests step kt+NBUF-1 into
@@ -439,7 +518,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
 
 #pragma unroll
     for (int p = 0; p < NBUF - 1; ++p) fetch(p, p);
-    build_dup_list<NT>(rq, N, col0, BN, dup_list, &dup_count);   // behind the first requests
+    if constexpr (RQ) build_dup_list<NT>(rq, N, col0, BN, dup_list, &dup_count);   // behind the first requests
     wait_vmcnt<(NBUF - 2) * LPS>();
     __syncthreads();
     read_slice(0, 0, af[0], bf[0]);
@@ -521,39 +600,15 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
         }
     }
 
-    // Epilogue.  An accumulator block leaves the MFMA with lane l holding ONE column and 16
-    // rows, which as stores would be 4 bytes per lane (measured: a CU retires such stores at
-    // ~16 B/clk, which made the output-bound shapes run at half the HBM write rate).  Each wave
-    // therefore turns its accumulators through a private piece of the free ring, 32 rows at a
-    // time, and reads them back with each lane holding four consecutive columns of one row:
-    // 16-byte stores, whole 128-byte lines per row.  Only this wave touches its piece and a
-    // wave's LDS accesses execute in issue order, so no barrier is needed.
-    constexpr int WAVE_STAGE = RING_BYTES / NW;          // bytes of LDS per wave
-    static_assert(WAVE_STAGE >= 32 * WN * 4, "ring too small to stage 32 rows of a wave's tile");
-    static_assert(WAVE_STAGE % 16 == 0, "staging area must keep 16-byte alignment");
-    int32_t* stage = reinterpret_cast<int32_t*>(&lds[wave * WAVE_STAGE]);
+    // epilogue, through a private piece of the free ring
+    constexpr int STAGE = RING_BYTES / NW / 16 * 16;     // (far apart: a wave's piece of the ring)
+    static_assert(STAGE >= stage_bytes<RQ, WN, 32>(), "ring too small for the staging areas");
+    int32_t* stage = reinterpret_cast<int32_t*>(&lds[wave * STAGE]);
     const float scale = scale_x[1] * scale_w[1];
-    const float inv = requant_inv(rq, (SPLIT ? tile == 0 : blockIdx.x == 0) && threadIdx.x == 0);
-    const int dup_n = (rq.Yq != nullptr && rq.s_next > 0) ? (dup_count < kDupCap ? dup_count : kDupCap) : 0;
-    const bool vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && (ldy % 4 == 0);
-    const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) &&
-                       (ldacc % 4 == 0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                stage[((v >> 2) * 8 + (lane >> 5) * 4 + (v & 3)) * WN + j * 32 + (lane & 31)] =
-                    acc[i][j][v];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        emit_staged_rows<32, WN>(stage, lane, row0 + wm * WM + i * 32, col0 + wn * WN, wn * WN, M, N,
-                                 scale, Y, ldy, acc_out, ldacc, vec_y, vec_a, rq, inv, dup_list, dup_n,
-                                 rq.Yq != nullptr && bn == tiles_n - 1 && wn == 0);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        __builtin_amdgcn_wave_barrier();   // the reads are issued before the next block's writes
-    }
+    const float inv = RQ ? requant_inv(rq, (SPLIT ? tile == 0 : blockIdx.x == 0) && threadIdx.x == 0) : 0.0f;
+    const int dup_n = RQ && rq.s_next > 0 ? (dup_count < kDupCap ? dup_count : kDupCap) : 0;
+    emit_tile<RQ, TM, TN, 32>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -578,7 +633,7 @@ __device__ __forceinline__ void lds_dma16(const int8_t* g, unsigned lds_addr) {
 #endif
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool RQ>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_wholek_kernel(
     const int8_t* __restrict__ Xq, int64_t ldx, const int8_t* __restrict__ Wq, int64_t ldw, int M,
     int N, int ksteps, const float* __restrict__ scale_x, const float* __restrict__ scale_w,
@@ -644,7 +699,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_wholek_kernel(
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
 
-    if (dup_off > 0) build_dup_list<NW * 64>(rq, N, col0, BN, dup_list, dup_count);   // behind the requests
+    if (RQ && dup_off > 0) build_dup_list<NW * 64>(rq, N, col0, BN, dup_list, dup_count);   // behind the requests
     wait_vmcnt<0>();
     __syncthreads();
 
@@ -670,38 +725,18 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_wholek_kernel(
             for (int i = 0; i < TM; ++i)
 #pragma unroll
                 for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+                    acc[i][j] = mfma_tile<RQ>(a[i], b[j], acc[i][j]);
         }
     }
     __syncthreads();  // the operands are dead: their LDS becomes the staging area
 
-    // Epilogue as in the ring kernel (each wave turns its accumulators through a private piece
-    // of LDS into rows of 16-byte stores), 8 rows at a time to keep the footprint small.
-    int32_t* stage = reinterpret_cast<int32_t*>(&dlds[wave * (8 * WN * 4)]);
+    // epilogue as in the ring kernel
+    int32_t* stage = reinterpret_cast<int32_t*>(&dlds[wave * stage_bytes<RQ, WN, 8>()]);
     const float scale = scale_x[1] * scale_w[1];
-    const float inv = requant_inv(rq, blockIdx.x == 0 && tid == 0);
-    const int dup_n = dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
-    const bool vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && (ldy % 4 == 0);
-    const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) &&
-                       (ldacc % 4 == 0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    stage[((lane >> 5) * 4 + e) * WN + j * 32 + (lane & 31)] = acc[i][j][q * 4 + e];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            emit_staged_rows<8, WN>(stage, lane, row0 + wm * WM + i * 32 + q * 8, col0 + wn * WN, wn * WN,
-                                    M, N, scale, Y, ldy, acc_out, ldacc, vec_y, vec_a, rq, inv, dup_list,
-                                    dup_n, rq.Yq != nullptr && bn == tiles_n - 1 && wn == 0);
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
-    }
+    const float inv = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
+    const int dup_n = RQ && dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
+    emit_tile<RQ, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -870,6 +905,190 @@ __global__ __launch_bounds__(NW * 64) void qgemm_slice_kernel(
     const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) && (ldacc % 4 == 0);
     emit_staged_rows<ROWS, BN>(stage, lane, row0 + wave * ROWS, col0, 0, M, N, scale, Y, ldy, acc_out, ldacc, vec_y,
                                vec_a, rq, inv, dup_list, dup_n, rq.Yq != nullptr && bn == tiles_n - 1);
+}
+
+// ---------------------------------------------------------------------------------------------
+// Convolution of unit stride whose output has the input's size (kh = 2 pad + 1 = kw, the body of the
+// paper's networks): the lowering as address arithmetic in LDS.  The BM output pixels of a tile are
+// consecutive in the flattened image, so the input pixels that all taps together need are one
+// contiguous run of BM + 2 pad (W + 1) pixels.  The workgroup fetches that run once (the ring kernel
+// above fetches every pixel once per tap, 9 times for a 3x3) and keeps it; a tap of an output row is
+// then the run's pixel (row + ky W + kx), read straight into the matrix cores' operand.  Taps outside
+// the image read 16 zero bytes instead: one bit per tap and row, worked out once.  K runs tap by tap in
+// 16-byte pieces as in the tap-major weights, which pass through a ring of 128-byte K-steps (one
+// barrier each); a pixel takes an odd number of pieces in LDS, so that consecutive pixels start in
+// different banks.
+// What bounds it: latency (fill, epilogue) and the address arithmetic of a slice, about as many vector
+// instructions as its products take cycles; several workgroups per compute unit hide one another's.
+// ---------------------------------------------------------------------------------------------
+constexpr int kPatchMaxTaps = 25;
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NBUF, bool RQ>
+__global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qconv_patch_kernel(
+    const int8_t* __restrict__ Aq, const int8_t* __restrict__ Wt, int64_t ldw, int M, int N, int ksteps,
+    int H, int W, int kw, int pad, int cpp, int P16, unsigned magic_p16, int pixels,
+    const float* __restrict__ scale_x, const float* __restrict__ scale_w, int32_t* __restrict__ acc_out,
+    int64_t ldacc, float* __restrict__ Y, int64_t ldy, int tiles_n, unsigned total_tiles, int ring_off,
+    int dup_off, Requant rq) {
+    // cpp: 16-byte pieces of a pixel in memory; P16 >= cpp: in LDS; pixels: length of the run
+    constexpr int NW = WAVES_M * WAVES_N;
+    constexpr int BK = 128, KS = BK / 32;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+    constexpr int B_LOADS = BN * (BK / 16) / (NW * 64);
+    static_assert(B_LOADS >= 1 && B_LOADS * NW * 64 == BN * (BK / 16), "the waves tile a step of the weights");
+    static_assert(NBUF >= 3 && (NBUF - 2) * B_LOADS < 64, "ring of at least three buffers");
+    static_assert(TM >= 1 && TN >= 1 && TM * 32 * WAVES_M == BM && TN * 32 * WAVES_N == BN, "32 x 32 blocks");
+    extern __shared__ __align__(1024) int8_t plds[];
+    int* dup_list = reinterpret_cast<int*>(plds + dup_off);       // only with copies to write
+    int* dup_count = dup_list + kDupCap;
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(3))) int8_t* lptr_t;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lptr_t)&plds[0];
+#else
+    const unsigned lds0 = 0;
+#endif
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+    const unsigned tile = xcd_remap(blockIdx.x, total_tiles);
+    const int bm = (int)(tile / (unsigned)tiles_n), bn = (int)(tile % (unsigned)tiles_n);
+    const int row0 = bm * BM, col0 = bn * BN;
+    const int kh = kw, taps = kh * kw;
+
+    // weights first (the multiply waits for both): request u of a step as in the ring kernel
+    const int8_t* b_src[B_LOADS];
+    int b_piece[B_LOADS];
+    const int b_pieces = (int)(ldw / 16);
+#pragma unroll
+    for (int u = 0; u < B_LOADS; ++u) {
+        const int pslot = (u * NW + wave) * 64 + lane, r = pslot / (BK / 16), c = pslot % (BK / 16);
+        b_src[u] = Wt + (int64_t)col_clamp(col0 + r, N) * ldw;    // (rows past the edge are never stored)
+        b_piece[u] = swz<BK>(r, c);
+    }
+    auto fetch = [&](int kt, int buf) {     // surplus steps (past the last) come from zero_chunk
+        const unsigned base = lds0 + (unsigned)(ring_off + buf * (BN * BK));
+#pragma unroll
+        for (int u = 0; u < B_LOADS; ++u) {
+            const int piece = kt * (BK / 16) + b_piece[u];
+            lds_dma16(piece < b_pieces ? b_src[u] + (int64_t)piece * 16 : zero_chunk, base + (unsigned)(u * NW + wave) * 1024);
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < NBUF - 1; ++p) fetch(p, p);
+    // the run of input pixels: piece i of the image in LDS = piece i % P16 of pixel i / P16 of the run
+    // (pixels before the first or past the last one of the tensor are clamped: no valid tap reads them)
+    const int lo = row0 - pad * W - pad;
+    const int pieces = pixels * P16;
+    for (int b = wave; b * 64 < pieces; b += NW) {
+        const unsigned i = (unsigned)(b * 64 + lane);
+        unsigned q = __umulhi(i, magic_p16);                      // floor(i / P16), at most one low
+        unsigned c = i - q * (unsigned)P16;
+        if (c >= (unsigned)P16) { ++q; c -= (unsigned)P16; }
+        const bool ok = (int)q < pixels && (int)c < cpp;
+        lds_dma16(ok ? Aq + ((int64_t)col_clamp(lo + (int)q, M) * cpp + c) * 16 : zero_chunk, lds0 + (unsigned)b * 1024);
+    }
+    const int zero_off = ring_off - 16;                           // 16 zero bytes behind the run
+    if (tid < 4) *reinterpret_cast<int*>(plds + zero_off + 4 * tid) = 0;
+
+    // per row of this lane: one bit per tap that lies inside the image
+    const int frag_row = lane & 31, frag_half = lane >> 5;
+    unsigned ok_taps[TM];
+    int row_off[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int r = wm * WM + i * 32 + frag_row;
+        const int gr = col_clamp(row0 + r, M);
+        const int yx = gr % (H * W), y = yx / W, x = yx - y * W;
+        unsigned m = 0;
+        for (int t = 0, ky = 0, kx = 0; t < taps; ++t) {
+            if ((unsigned)(y + ky - pad) < (unsigned)H && (unsigned)(x + kx - pad) < (unsigned)W) m |= 1u << t;
+            if (++kx == kw) { kx = 0; ++ky; }
+        }
+        ok_taps[i] = m;
+        row_off[i] = r * P16 * 16;
+    }
+    if (RQ && dup_off > 0) build_dup_list<NW * 64>(rq, N, col0, BN, dup_list, dup_count);   // behind the requests
+
+    i32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+
+    // This lane's piece of the K extent: piece `frag_half` of the first slice, two further on with every
+    // slice; `off` = its place relative to the row's first pixel of the run.
+    int tap = 0, kx = 0, cin = frag_half, off = frag_half * 16;
+    const int next_pixel = (P16 - cpp) * 16, next_row = (W - kw) * P16 * 16;
+    auto advance = [&]() {
+        cin += 2;
+        off += 32;
+        if (cin >= cpp) {                                         // (cpp >= 2: at most one tap further)
+            cin -= cpp;
+            off += next_pixel;
+            ++tap;
+            if (++kx == kw) { kx = 0; off += next_row; }
+        }
+    };
+    i32x4 af[2][TM], bf[2][TN];
+    auto read_slice = [&](int buf, int ks, i32x4 (&a)[TM], i32x4 (&b)[TN]) {
+        // (taps past the last one, where K is padded to whole steps: no bit set)
+        const bool in = tap < taps;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const bool ok = in && ((ok_taps[i] >> (tap & 31)) & 1u);
+            a[i] = *reinterpret_cast<const i32x4*>(plds + (ok ? row_off[i] + off : zero_off));
+        }
+        const int8_t* bb = plds + ring_off + buf * (BN * BK);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int r = wn * WN + j * 32 + frag_row;
+            b[j] = *reinterpret_cast<const i32x4*>(&bb[r * BK + swz<BK>(r, ks * 2 + frag_half) * 16]);
+        }
+        advance();
+    };
+    wait_vmcnt<0>();
+    __syncthreads();
+    read_slice(0, 0, af[0], bf[0]);
+    // Step kt as in the ring kernel: its weights' successor NBUF-1 steps on is requested into the buffer
+    // of step kt-1, the fragments of a slice are read while the slice before it is multiplied, and the
+    // barrier in front of the next step's first slice comes before the last multiply of this one.
+    for (int kt0 = 0; kt0 < ksteps; kt0 += NBUF) {
+#pragma unroll
+        for (int p = 0; p < NBUF; ++p) {
+            const int kt = kt0 + p;
+            if (kt >= ksteps) break;
+            fetch(kt + NBUF - 1, (p + NBUF - 1) % NBUF);
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if (ks + 1 < KS) {
+                    read_slice(p, ks + 1, af[(ks + 1) & 1], bf[(ks + 1) & 1]);
+                } else {
+                    wait_vmcnt<(NBUF - 2) * B_LOADS>();
+                    __syncthreads();
+                    read_slice((p + 1) % NBUF, 0, af[0], bf[0]);      // (after the last step: zeros, not used)
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = mfma_tile<RQ>(af[ks & 1][i], bf[ks & 1][j], acc[i][j]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    wait_vmcnt<0>();    // surplus requests must land before their LDS is reused
+    __syncthreads();
+
+    // epilogue as in the ring kernel
+    int32_t* stage = reinterpret_cast<int32_t*>(&plds[wave * stage_bytes<RQ, WN, 8>()]);
+    const float scale = scale_x[1] * scale_w[1];
+    const float inv = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
+    const int dup_n = RQ && dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
+    emit_tile<RQ, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
 }
 
 constexpr int64_t kWholeKMaxLds = 160 * 1024;  // LDS of one CU
@@ -1242,7 +1461,7 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 template <int BM, int BN, int WAVES_M, int WAVES_N>
 static int64_t wholek_lds_bytes(int64_t Kpad, const Requant& rq, int* dup_off = nullptr) {
     const int64_t operands = (Kpad / 64) * (BM + BN) * 64;
-    const int64_t staging = (int64_t)WAVES_M * WAVES_N * 8 * (BN / WAVES_N) * 4;
+    const int64_t staging = (int64_t)WAVES_M * WAVES_N * (rq.Yq != nullptr ? stage_bytes<true, BN / WAVES_N, 8>() : stage_bytes<false, BN / WAVES_N, 8>());
     int64_t lds = operands > staging ? operands : staging;
     int off = 0;
     if (rq.Yq != nullptr && rq.s_next > 0) {
@@ -1253,8 +1472,8 @@ static int64_t wholek_lds_bytes(int64_t Kpad, const Requant& rq, int* dup_off = 
     return lds;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N>
-static hipError_t run_wholek(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw,
+template <int BM, int BN, int WAVES_M, int WAVES_N, bool RQ>
+static hipError_t run_wholek_as(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw,
                              int64_t M, int64_t N, int64_t Kpad, const float* scale_x,
                              const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y,
                              int64_t ldy, hipStream_t stream, const Requant& rq) {
@@ -1271,7 +1490,7 @@ static hipError_t run_wholek(const int8_t* Xq, int64_t ldx, const int8_t* Wq, in
         if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
             e = hipFuncSetAttribute(
-                reinterpret_cast<const void*>(&qgemm_wholek_kernel<BM, BN, WAVES_M, WAVES_N>),
+                reinterpret_cast<const void*>(&qgemm_wholek_kernel<BM, BN, WAVES_M, WAVES_N, RQ>),
                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
@@ -1280,10 +1499,18 @@ static hipError_t run_wholek(const int8_t* Xq, int64_t ldx, const int8_t* Wq, in
     const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
     const int64_t total = tiles_m * tiles_n;
     if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
-    return launch_kernel(kTimeGemm, qgemm_wholek_kernel<BM, BN, WAVES_M, WAVES_N>,
+    return launch_kernel(kTimeGemm, qgemm_wholek_kernel<BM, BN, WAVES_M, WAVES_N, RQ>,
                          dim3((unsigned)total), dim3(WAVES_M * WAVES_N * 64), (unsigned)lds, stream,
                          Xq, ldx, Wq, ldw, (int)M, (int)N, (int)(Kpad / 64), scale_x, scale_w,
                          acc_out, ldacc, Y, ldy, (int)tiles_n, (unsigned)total, dup_off, rq);
+}
+template <int BM, int BN, int WAVES_M, int WAVES_N>
+static hipError_t run_wholek(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw,
+                             int64_t M, int64_t N, int64_t Kpad, const float* scale_x,
+                             const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y,
+                             int64_t ldy, hipStream_t stream, const Requant& rq) {
+    const auto run = rq.Yq != nullptr ? run_wholek_as<BM, BN, WAVES_M, WAVES_N, true> : run_wholek_as<BM, BN, WAVES_M, WAVES_N, false>;
+    return run(Xq, ldx, Wq, ldw, M, N, Kpad, scale_x, scale_w, acc_out, ldacc, Y, ldy, stream, rq);
 }
 
 // The K extent dealt over the waves.  Any K extent and pitch the GEMM accepts.
@@ -1327,7 +1554,9 @@ static hipError_t run_dma(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64
     const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
     const int64_t total = tiles_m * tiles_n;
     if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
-    return launch_kernel(kTimeGemm, qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, MASK>,
+    const auto kernel = rq.Yq != nullptr ? qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, true, false, false, MASK>
+                                         : qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, false, MASK>;
+    return launch_kernel(kTimeGemm, kernel,
                          dim3((unsigned)total), dim3(WAVES_M * WAVES_N * 64), 0, stream, Xq, ldx, Wq, ldw, (int)M,
                          (int)N, (int)(Kpad / BK), scale_x, scale_w, acc_out, ldacc, Y, ldy,
                          (int)tiles_n, (unsigned)total, ConvGeom{}, rq, SplitK{});
@@ -1389,7 +1618,7 @@ static hipError_t run_dma_split(const int8_t* Xq, int64_t ldx, const int8_t* Wq,
     sk.parts = parts;
     hipError_t e = splitk_counter_slot(&sk.counters);
     if (e != hipSuccess) return e;
-    return launch_kernel(kTimeGemm, qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, true>,
+    return launch_kernel(kTimeGemm, qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, true>,
                          dim3((unsigned)(total * parts)), dim3(WAVES_M * WAVES_N * 64), 0, stream, Xq, ldx, Wq,
                          ldw, (int)M, (int)N, (int)(Kpad / BK), scale_x, scale_w, acc_out, ldacc, Y, ldy,
                          (int)tiles_n, (unsigned)total, ConvGeom{}, rq, sk);
@@ -1406,10 +1635,69 @@ static hipError_t run_dma_conv(const int8_t* Aq, const int8_t* Wt, int64_t ldw, 
     const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
     const int64_t total = tiles_m * tiles_n;
     if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
-    return launch_kernel(kTimeGemm, qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, true>,
+    const auto kernel = rq.Yq != nullptr ? qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, true, true>
+                                         : qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, true>;
+    return launch_kernel(kTimeGemm, kernel,
                          dim3((unsigned)total), dim3(WAVES_M * WAVES_N * 64), 0, stream, Aq, cg.ldc, Wt,
                          ldw, (int)M, (int)N, (int)(Kpad / BK), scale_x, scale_w, acc_out, ldacc, Y,
                          ldy, (int)tiles_n, (unsigned)total, cg, rq, SplitK{});
+}
+
+// The convolution whose taps are read from one run of pixels in LDS: unit stride, output of the input's
+// size, at least two 16-byte pieces per pixel.  LDS = the run, 16 zero bytes, the ring of weight steps, the
+// table of the next layer's copies.
+struct PatchPlan {
+    int P16 = 0, pixels = 0, ring_off = 0, dup_off = 0;
+    int64_t lds = 0;
+};
+template <int BM, int BN, int NW, int NBUF>
+static PatchPlan patch_plan(int W, int pad, int cpp, const Requant& rq) {
+    PatchPlan p;
+    const int64_t pixels = (int64_t)BM + 2 * (int64_t)pad * (W + 1), P16 = cpp | 1;
+    if (pixels * P16 * 16 > kWholeKMaxLds) return p;              // lds == 0: does not fit
+    p.P16 = (int)P16;
+    p.pixels = (int)pixels;
+    p.ring_off = (int)(round_up(pixels * P16, 64) * 16 + 1024);   // whole requests, then a block that ends in the zeros
+    int64_t lds = (int64_t)p.ring_off + NBUF * BN * 128;
+    const int64_t staging = (int64_t)NW * stage_bytes<true, BN, 8>() > (int64_t)NW * stage_bytes<false, BN, 8>()
+                                ? (int64_t)NW * stage_bytes<true, BN, 8>() : (int64_t)NW * stage_bytes<false, BN, 8>();
+    if (lds < staging) lds = staging;
+    if (rq.Yq != nullptr && rq.s_next > 0) {
+        p.dup_off = (int)lds;
+        lds += (kDupCap + 1) * 4;
+    }
+    if (lds <= kWholeKMaxLds) p.lds = lds;
+    return p;
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int NBUF, bool RQ>
+static hipError_t run_patch(const int8_t* Aq, const int8_t* Wt, int64_t ldw, int64_t M, int64_t N, const ConvGeom& cg,
+                            const PatchPlan& p, const float* scale_x, const float* scale_w, int32_t* acc_out,
+                            int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream, const Requant& rq) {
+    if (p.lds <= 0 || p.lds > kWholeKMaxLds || cg.cpp < 2 || cg.kh != cg.kw || cg.kh * cg.kw > kPatchMaxTaps)
+        return hipErrorInvalidValue;
+    if (p.lds > 65536) {
+        static std::atomic<bool> opted_in[kMaxDevices];
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+        if (!opted_in[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&qconv_patch_kernel<BM, BN, WAVES_M, WAVES_N, NBUF, RQ>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
+            if (e != hipSuccess) return e;
+            opted_in[dev].store(true, std::memory_order_release);
+        }
+    }
+    const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
+    const int64_t total = tiles_m * tiles_n;
+    if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
+    const int ksteps = (int)ceil_div((int64_t)cg.kh * cg.kw * cg.ldc, 128);
+    const unsigned magic = (unsigned)((((uint64_t)1) << 32) / (uint64_t)p.P16);   // P16 >= 3
+    return launch_kernel(kTimeGemm, qconv_patch_kernel<BM, BN, WAVES_M, WAVES_N, NBUF, RQ>, dim3((unsigned)total),
+                         dim3(WAVES_M * WAVES_N * 64), (unsigned)p.lds, stream, Aq, Wt, ldw, (int)M, (int)N, ksteps,
+                         cg.H, cg.W, cg.kw, cg.pad, cg.cpp, p.P16, magic, p.pixels, scale_x, scale_w, acc_out, ldacc, Y,
+                         ldy, (int)tiles_n, (unsigned)total, p.ring_off, p.dup_off, rq);
 }
 
 hipError_t launch_qconv(const int8_t* Aq, int64_t ldc, int B, int H, int W, int kh, int kw, int stride,
@@ -1432,12 +1720,44 @@ hipError_t launch_qconv(const int8_t* Aq, int64_t ldc, int B, int H, int W, int 
     const int64_t Kpad = ldw;          // kh*kw*ldc rounded up to a whole K-step
     if (Kpad < (int64_t)kh * kw * ldc) return hipErrorInvalidValue;
     int tile = tuning().gemm_tile;
-    // measured on the stem and the 3x3 layers of the paper's networks: the 128x128 tile is level
+#define OCS_CONV_ARGS Aq, Wt, ldw, M, N, Kpad, cg, scale_x, scale_w, acc_out, ldacc, Y, ldy, stream, rq
+#define OCS_PATCH(BM_, BN_, WM_, WN_, NB_)                                                                          \
+    do {                                                                                                            \
+        const PatchPlan pp = patch_plan<BM_, BN_, WM_ * WN_, NB_>(W, pad, cg.cpp, rq);                              \
+        if (pp.lds > 0)                                                                                             \
+            return (rq.Yq != nullptr ? run_patch<BM_, BN_, WM_, WN_, NB_, true>                                     \
+                                     : run_patch<BM_, BN_, WM_, WN_, NB_, false>)(                                  \
+                Aq, Wt, ldw, M, N, cg, pp, scale_x, scale_w, acc_out, ldacc, Y, ldy, stream, rq);                   \
+    } while (0)
+    if (tile < 0 && kh == 1 && kw == 1 && stride == 1 && pad == 0)
+        // nothing to lower: the GEMM's own kernels (what a weight row holds past the pixel's codes is zero)
+        return launch_qgemm(Aq, ldc, Wt, ldw, M, N, Kpad, scale_x, scale_w, acc_out, ldacc, Y, ldy, stream, rq);
+    // Measured on 3x3 layers (us, ring 128 x 128 of before -> now).  Up to one 64 x 64 tile per compute
+    // unit (two, for more than 64 outputs) that ring tile: 2 x 28 x 28 x 128 -> 128 11.8 -> 9.0, 4 x 7 x 7 x 512 -> 512
+    // 27.1 -> 20.8.  Up to 64 outputs the run in LDS: 32 x 56 x 56 x 64 -> 64 19.7 -> 13.8 (fp32 out), 24.7 -> 16.5
+    // (codes out), with 256 rows a tile once that gives every compute unit one, 128 below (16 images: 13.5 -> 10.9).
+    // More outputs: the run's tile of 256 x 128 while it gives each compute unit at most one (128 x 14 x 14 x 256
+    // -> 256 30.9 -> 27.9; 19.1 against 12.4 with 98 of them), else the ring, which is level with it.
+    const int64_t cus = compute_units();
+    const bool patch = stride == 1 && kh == kw && kh == 2 * pad + 1 && kh * kw <= kPatchMaxTaps && cg.cpp >= 2;
+    if (tile < 0) {
+        const int64_t t64 = ceil_div(M, 64) * ceil_div(N, 64), t256 = ceil_div(M, 256) * ceil_div(N, 128);
+        if (t64 <= (N <= 64 ? cus : 2 * cus)) tile = 7;
+        else if (patch && N <= 64) tile = ceil_div(M, 256) >= cus ? 31 : 30;
+        else if (patch && 2 * t256 > cus && t256 <= cus) tile = 32;
+    }
+    if (patch) {       // (a run too long for LDS: the ring)
+        if (tile == 30) OCS_PATCH(128, 64, 4, 2, 3);
+        if (tile == 31) OCS_PATCH(256, 64, 4, 2, 3);
+        if (tile == 32) OCS_PATCH(256, 128, 4, 2, 3);
+    }
+    if (tile >= 30) tile = -1;
+#undef OCS_PATCH
+    // measured on the stem and the 3x3 layers of the paper's networks: the 128x128 ring tile is level
     // with or ahead of the larger ones (the loader's per-lane tap bookkeeping grows with the rows
     // a lane loads; a 128-byte K-step, which doubles them, was 15-90 % slower) and, from 64
     // output channels on, ahead of the 128x64 one as well
     if (tile < 0) tile = N < 64 ? 6 : 9;
-#define OCS_CONV_ARGS Aq, Wt, ldw, M, N, Kpad, cg, scale_x, scale_w, acc_out, ldacc, Y, ldy, stream, rq
     switch (tile) {
         case 6: return run_dma_conv<128, 64, 2, 2, 6>(OCS_CONV_ARGS);
         case 7: return run_dma_conv<64, 64, 2, 2, 6>(OCS_CONV_ARGS);
@@ -1508,8 +1828,16 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
     // A pitch that is not a whole number of 64-byte K-steps, or shorter than the K extent rounded
     // up to one (allowed up to 320 bytes of K), is something only the whole-K kernel and the sliced ones walk.
     const bool ring_ok = ldx % 64 == 0 && ldw % 64 == 0 && ldx >= Kpad && ldw >= Kpad;
-    if (!ring_ok) {
-        if (Kpad > 320) return hipErrorInvalidValue;
+    if (!ring_ok && !(tile >= 26 && tile <= 29) && Kpad > 320) {
+        // (a 1x1 convolution on pixels of any number of 16-byte pieces: the ring tiles that check every
+        // request against the pitch)
+        const int64_t K128 = round_up(Kpad, 128);
+        if (tile == 7) return run_dma<64, 64, 2, 2, 64, 6, true>(OCS_GEMM_ARGS);
+        if (N <= 64) return run_dma<128, 64, 2, 2, 128, 3, true>(OCS_GEMM_ARGS128);
+        if (ceil_div(M, 256) * ceil_div(N, 128) >= 128) return run_dma<256, 128, 4, 2, 128, 3, true>(OCS_GEMM_ARGS128);
+        return run_dma<128, 128, 4, 2, 128, 3, true>(OCS_GEMM_ARGS128);
+    }
+    if (!ring_ok && Kpad <= 320) {
         // (the 128 x 128 ring variant checks its requests against the pitch for this case: a very
         // wide N is better served by the ring kernel's tile order, see below)
         if (tile == 9 || (tile < 0 && N >= 1024))

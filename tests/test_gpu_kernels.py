@@ -731,6 +731,47 @@ def test_qconv(tile, Bn, H, W, Cn, N, kh, kw, stride, pad, s):
     assert_y_close(got["Y"], exp["Y"])
 
 
+@pytest.mark.parametrize("tile", [30, 31, 32, -1])
+@pytest.mark.parametrize("Bn,H,W,Cn,N,k,s", [
+    (3, 9, 7, 33, 33, 3, 2),          # images end inside a tile; ragged columns; an odd number of pieces per pixel
+    (1, 1, 1, 40, 5, 3, 1),           # a single pixel: eight taps outside
+    (2, 1, 13, 60, 70, 3, 4),         # one row
+    (2, 13, 1, 16, 64, 5, 1),         # one column, 25 taps
+    (1, 16, 16, 64, 64, 3, 0),        # whole tiles, no copies, an even number of pieces
+    (2, 17, 15, 130, 129, 3, 7),      # column tiles, odd pieces
+    (5, 11, 11, 20, 65, 1, 1),        # a 1x1 on pixels of 32 bytes (with the ids: one tap)
+    (2, 12, 12, 500, 100, 1, 25),     # a 1x1 whose pixels are not whole K-steps
+    (1, 40, 40, 500, 40, 1, 20),
+    (1, 3, 700, 200, 40, 3, 10),      # a run longer than LDS
+])
+def test_qconv_taps_from_lds(tile, Bn, H, W, Cn, N, k, s):
+    """Convolutions of unit stride and unchanged size, fp32 out and as the next layer's codes with copies
+    and pad columns, against the lowered codes through the oracle."""
+    rng = np.random.default_rng(Bn + H + W + Cn + N + k + s)
+    A = _tensor(rng, Bn * H * W, Cn, "heavy").reshape(Bn, H, W, Cn)
+    Wm = _tensor(rng, N, Cn * k * k, "heavy")
+    exp = _conv_reference(A, Wm, Cn, k, k, 1, k // 2, s, 8, 6, None)
+    s_next = 3
+    cs = _next_layer_list(rng, N, s_next)
+    T = float(np.float32(0.5 * np.abs(exp["Y"]).max()))
+    B.ocs_tune("gemm_tile", tile)
+    try:
+        got = gpu_conv_layer(A, Wm, Cn, k, k, 1, k // 2, s, bits_x=8, bits_w=6)
+        assert np.array_equal(got["acc"], exp["acc"])
+        assert_y_close(got["Y"], exp["Y"])
+        for relu, extra in ((True, 0), (False, 16)):
+            ldy = B.ocs_padded_channels(N + s_next) + extra
+            q_ref, sc_ref = ref.requantize(exp["acc"], exp["sx"][1], exp["sw"][1], T, 5, cs, s_next, relu=relu, ldq=ldy)
+            Yq = torch.full((Bn * H * W, ldy), 77, dtype=torch.int8, device="cuda")
+            sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+            thr = torch.tensor([T], dtype=torch.float32, device="cuda")
+            B.ocs_qconv_requant(dev(got["Aq"]), got["ldc"], Bn, H, W, Cn + s, k, k, 1, k // 2, dev(got["Wt"]), N, 8, 6,
+                                dev(got["sx"]), dev(got["sw"]), relu, thr, 5, dev(cs), s_next, Yq, ldy, sc)
+            assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
+    finally:
+        B.ocs_tune("gemm_tile", -1)
+
+
 def test_qconv_equals_the_lowered_gemm_path():
     # same layer through ocs_split_act on the im2col matrix + ocs_qgemm, with a static grid
     rng = np.random.default_rng(99)
