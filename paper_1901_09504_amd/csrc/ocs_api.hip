@@ -316,6 +316,11 @@ int ocs_quantize(const float* x, int64_t rows, int64_t cols, int64_t ldx, int bi
         float* colmax = reinterpret_cast<float*>(base + w.colmax_off);
         float* partial = reinterpret_cast<float*>(base + w.partial_off);
         (void)colmax;
+        if (act_self_max_serves(rows, (int)cols, 1, 0, ldx, ldq, nullptr)) {
+            e = launch_expand_quantize(x, ldx, rows, (int)cols, 1, 0, nullptr, nullptr, nullptr, qmax, q, ldq, scale_out,
+                                       st, nullptr, 0, clip_ratio, false, rows * cols);
+            return e == hipSuccess ? OCS_OK : hip_fail(e);
+        }
         int n = 0;
         e = launch_absmax_partials(x, rows, cols, ldx, partial, &n, st);
         if (e != hipSuccess) return hip_fail(e);
@@ -420,14 +425,20 @@ int ocs_split_act(const float* X, int64_t M, int C, int g, int64_t ldx, const in
         Workspace w = plan_workspace(M, (int64_t)C * g);
         float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
         int n = 0;
-        hipError_t e = launch_absmax_partials(X, M, (int64_t)C * g, ldx, partial, &n, st);
+        hipError_t e;
+        if (act_self_max_serves(M, C, g, num_splits, ldx, ldq, chan_src)) {
+            e = launch_expand_quantize(X, ldx, M, C, g, num_splits, chan_src, nullptr, nullptr, qmax, Xq, ldq, scale_out,
+                                       st, nullptr, 0, clip_ratio, false, M * (int64_t)C * g);
+            return e == hipSuccess ? OCS_OK : hip_fail(e);
+        }
+        e = launch_absmax_partials(X, M, (int64_t)C * g, ldx, partial, &n, st);
         if (e != hipSuccess) return hip_fail(e);
         // From 160 MB on the maxima are folded into one word by a launch of its own: the streaming
         // pass then takes its one-shot form, whose workgroups are far too many and too short to fold
         // a few hundred maxima each (config 5's per-batch pass: 13.4 -> 13.1 ms; on a 116 MB tensor the
         // extra launch costs what the faster pass gains).
         const int64_t cap = (int64_t)(w.total - w.partial_off) / 4;
-        if (n > 1 && n < cap && (tuning().max_flat == 2 || M * (int64_t)C * g >= ((int64_t)40 << 20))) {   // (max_flat 2: always, for tests)
+        if (n > 1 && n < cap && tuning().max_flat == 2) {   // (max_flat 2: always, for tests)
             e = launch_fold_max(partial, n, partial + n, st);
             if (e != hipSuccess) return hip_fail(e);
             partial += n;

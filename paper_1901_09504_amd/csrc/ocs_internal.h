@@ -92,7 +92,10 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
                                   const float* thr, float qmax, int8_t* Xq, int64_t ldq,
                                   float* scale_out, hipStream_t stream,
                                   const float* partials = nullptr, int n_partials = 0,
-                                  float clip_ratio = 1.0f, bool stepwise = false);
+                                  float clip_ratio = 1.0f, bool stepwise = false, int64_t self = 0);
+// Whether the pass can find a per-batch grid's maximum by itself (small contiguous X, un-scaled copies):
+// launch_expand_quantize then takes self = M * C * g, with neither thr nor partials.
+bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ldq, const int32_t* chan_src);
 
 // Per-workgroup maxima of |T| (stage 1 of the scalar reduction only): partial[0 .. *entries).
 hipError_t launch_fold_max(const float* in, int n, float* out, hipStream_t stream);

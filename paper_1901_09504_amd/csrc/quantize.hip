@@ -262,10 +262,9 @@ __global__ __launch_bounds__(kThreads) void expand_quantize_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
-// The pass in one shot, for a static grid with un-scaled copies (the activation side of Eq. 3): a
-// workgroup takes R whole rows (a few KB of X), requests all of its input at once (U 16-byte loads
-// per lane), turns it into codes, and is done: no loop, no look-ahead registers, one barrier.  The
-// chip's dispatcher hands such workgroups out in order, so the chip works inside one tight window
+// The pass in one shot: a workgroup takes R whole rows (a few KB of X), requests all of its input at
+// once (U 16-byte loads per lane), turns it into codes, and is done: no loop, no look-ahead registers.
+// The chip's dispatcher hands such workgroups out in order, so the chip works inside one tight window
 // that slides over X, tighter than persistent workgroups keep it (they drift apart): a plain copy
 // written this way moves 6.0 TB/s on this chip against 5.5 TB/s for the grid-stride form, and this
 // pass's pattern of 16 bytes in and 4 out per lane 6.1 against 5.5 (the library's measurement
@@ -273,42 +272,96 @@ __global__ __launch_bounds__(kThreads) void expand_quantize_kernel(
 //   Main items: dword d < Qc = ceil(K/4) of a row, 16 bytes of X each; their codes go straight to
 //   memory (d < Q = floor(K/4)) and into an image of the rows in LDS.
 //   Tail: dwords Q .. D-1 of a row (left-over columns of X, the appended columns, zero padding)
-//   are assembled afterwards from the image, byte by byte: the copy of a column is the code just
-//   written, so the appended columns cost no second trip to memory.  Their source columns do not
-//   depend on the row: a table of 4 * TD entries, looked up in chan_src behind the requests for X.
+//   are assembled afterwards.  Un-scaled copies (the activation side of Eq. 3) come from the image, byte
+//   by byte: the copy of a column is the code just written, so the appended columns cost no second trip
+//   to memory.  Their source columns do not depend on the row: a table of 4 * TD entries, looked up in
+//   chan_src behind the requests for X.
+//   SCALE (G1: one column per channel): every expanded channel j is multiplied by 2^-chan_depth[j] first (1: Eq. 4, one multiply;
+//   2: the weights of Eq. 3, halved split by split).  A copy that carries another depth than its source
+//   (one of the two was split again) gathers its value anew, from the row this workgroup has just pulled
+//   through the caches; all others are the code just written.
+//   The threshold: a given device float; or, for a per-batch grid, clip times the largest of the
+//   per-workgroup maxima that the pass before left behind, folded here behind the requests for X
+//   (FOLD_NOTE); or clip times the largest magnitude of a small contiguous X that every workgroup reads
+//   through for itself (kSelfMax).
 // ---------------------------------------------------------------------------------------------
 constexpr int kShotNT = 256;
 constexpr int kShotTabPer = 2;                       // table entries per lane
 constexpr int kShotMaxTail = kShotNT * kShotTabPer;  // tail columns 4 * TD served
 
-template <int U>
+struct ShotMax {
+    const float* partials = nullptr;   // per-workgroup maxima (n of them), or
+    int n = 0;
+    int64_t self = 0;                  // values of contiguous X to look through (0: none)
+    float clip = 1.0f;
+};
+
+// Threshold of the pass as all lanes see it; `red`: 4 floats of LDS.  A barrier unless it is given.
+template <int MAX>
+__device__ __forceinline__ float shot_threshold(const float* thr, const ShotMax& mx, float part, const float* X, float* red) {
+    if constexpr (MAX == 0) return *thr;
+    float m = part;                                           // this lane's first of the maxima (requested early)
+    for (int i = (int)threadIdx.x + kShotNT; i < mx.n; i += kShotNT) m = fmaxf(m, mx.partials[i]);
+    if constexpr (MAX == 2) {
+        const f32x4u* x4 = reinterpret_cast<const f32x4u*>(X);
+        const int n4 = (int)(mx.self / 4);
+        constexpr int UN = 8;                                 // requests in flight per lane
+        for (int i0 = (int)threadIdx.x; i0 < n4; i0 += UN * kShotNT) {
+            f32x4 v[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int i = i0 + u * kShotNT;
+                v[u] = x4[i < n4 ? i : n4 - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                m = fmaxf(fmaxf(fmaxf(m, fabsf(v[u][0])), fmaxf(fabsf(v[u][1]), fabsf(v[u][2]))), fabsf(v[u][3]));
+        }
+        if ((int64_t)threadIdx.x < mx.self - 4 * (int64_t)n4) m = fmaxf(m, fabsf(X[4 * n4 + threadIdx.x]));
+    }
+    const unsigned w = wave_umax32(__float_as_uint(m));      // magnitudes: non-negative, order like unsigned
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = __uint_as_float(w);
+    __syncthreads();
+    return mx.clip * fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+template <int U, int SCALE, int MAX, bool G1>
 __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
     const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
-    const int32_t* __restrict__ chan_src, const float* __restrict__ thr, float qmax,
-    int8_t* __restrict__ Xq, int64_t ldq, int R, unsigned magic_qc, unsigned magic_td,
-    float* __restrict__ scale_out, float clip) {
-    // clip: the threshold is clip * *thr (1 for a given threshold; the clip ratio when *thr is the
-    // tensor's largest magnitude, left behind by the pass before this one)
+    const int32_t* __restrict__ chan_src, const int32_t* __restrict__ chan_depth, const float* __restrict__ thr,
+    float qmax, int8_t* __restrict__ Xq, int64_t ldq, int R, unsigned magic_qc, unsigned magic_td,
+    unsigned magic_g, float* __restrict__ scale_out, ShotMax mx) {
     extern __shared__ __align__(16) int8_t slds[];
+    __shared__ float red[kShotNT / 64];
     const int K = C * g, Q = K / 4, rem = K - 4 * Q, Qc = Q + (rem > 0 ? 1 : 0);
     const int D = (int)(ldq / 4), TD = D - Q, Ke = (C + s) * g;
     const int P = (int)ldq + 4;                       // image pitch: consecutive rows start one bank apart
     int8_t* img = slds;
     int* tcol = reinterpret_cast<int*>(slds + ((R * P + 15) & ~15));
+    int* tdep = tcol + 4 * TD;                        // SCALE only: depth, -1 where it is the source's own
     const int tid = (int)threadIdx.x;
     const int row0 = (int)blockIdx.x * R;
     const int rows = M - row0 < R ? M - row0 : R;
 
-    // the table's look-ups first: they come back from the L2 while the rows are on their way
-    int tsrc[kShotTabPer];
+    // the maxima and the table's look-ups first: they come back from the L2 while the rows are on their way
+    auto channel_of = [&](int k) {                    // k / g
+        unsigned q = __umulhi((unsigned)k, magic_g);  // at most one low
+        if ((unsigned)k - q * (unsigned)g >= (unsigned)g) ++q;
+        return (int)q;
+    };
+    float part = 0.0f;
+    if constexpr (MAX == 1) part = tid < mx.n ? mx.partials[tid] : 0.0f;
+    int tsrc[kShotTabPer], tdp[kShotTabPer];
 #pragma unroll
     for (int i = 0; i < kShotTabPer; ++i) {
         const int k = 4 * Q + tid + i * kShotNT;
         const bool app = k >= K && k < Ke;
-        tsrc[i] = chan_src != nullptr ? chan_src[app ? k / g : 0] : 0;     // (no list: no appended columns)
+        tsrc[i] = chan_src != nullptr ? chan_src[app ? channel_of(k) : 0] : 0;     // (no list: no appended columns)
+        if constexpr (SCALE != 0) tdp[i] = chan_depth[k < Ke ? channel_of(k) : 0];
     }
     // main items: item i = (row i / Qc, dword i % Qc)
     f32x4 v[U];
+    i32x4 dep[SCALE ? U : 1];
     int r_[U], d_[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -321,8 +374,28 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
         d_[u] = (int)d;
         // a row's last dword may hold fewer than four columns of X: it is fetched as the row's last
         // four floats and shifted into place when used (nothing is read past the row)
-        const float* src = X + (int64_t)(row0 + (ok ? (int)q : 0)) * ldx + (ok ? ((int)d < Q ? 4 * (int)d : K - 4) : 0);
+        const int col0 = ok ? ((int)d < Q ? 4 * (int)d : K - 4) : 0;
+        const float* src = X + (int64_t)(row0 + (ok ? (int)q : 0)) * ldx + col0;
         v[u] = *reinterpret_cast<const f32x4u*>(src);
+        // (no condition around any load, or the compiler waits for those under way)
+        if constexpr (SCALE != 0 && G1) {
+            typedef int i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+            dep[u] = *reinterpret_cast<const i32x4u*>(chan_depth + col0);
+        } else if constexpr (SCALE != 0) {
+            int j = channel_of(col0), t = col0 - j * g;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                dep[u][e] = chan_depth[j];
+                const bool next = ++t == g;
+                t = next ? 0 : t;
+                j += next ? 1 : 0;
+            }
+        }
+    }
+    int sdep[kShotTabPer];
+    if constexpr (SCALE != 0) {
+#pragma unroll
+        for (int i = 0; i < kShotTabPer; ++i) sdep[i] = chan_depth[tsrc[i] < 0 ? 0 : (tsrc[i] >= C ? C - 1 : tsrc[i])];
     }
 #pragma unroll
     for (int i = 0; i < kShotTabPer; ++i) {
@@ -331,23 +404,32 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
             int col = -1;
             if (k < K) col = k;
             else if (k < Ke) {
-                const int j = k / g, t = k - j * g;
+                const int j = channel_of(k), t = k - j * g;
                 const int c = tsrc[i] < 0 ? 0 : (tsrc[i] >= C ? C - 1 : tsrc[i]);
                 col = c * g + t;
             }
             tcol[e] = col;
+            // (a left-over column is its own source)
+            if constexpr (SCALE != 0) tdep[e] = k < K || k >= Ke || tdp[i] == sdep[i] ? -1 : tdp[i];
         }
     }
-    const float T = clip * *thr;
+    const float T = shot_threshold<MAX>(thr, mx, part, X, red);
     const float inv = inv_step_of(T, qmax);
     if (scale_out != nullptr && blockIdx.x == 0 && tid == 0) {
         scale_out[0] = T;
         scale_out[1] = T / qmax;
     }
+    auto scaled = [](float x, int d) { return SCALE == 2 ? halved(x, d) : x * ldexpf(1.0f, -d); };
     unsigned* __restrict__ out = reinterpret_cast<unsigned*>(Xq);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         if (r_[u] < 0) continue;
+        if constexpr (SCALE != 0) {
+            if ((dep[u][0] | dep[u][1] | dep[u][2] | dep[u][3]) != 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[u][e] = scaled(v[u][e], dep[u][e]);
+            }
+        }
         unsigned q4 = pack4(code_bits(v[u][0], inv, qmax), code_bits(v[u][1], inv, qmax),
                             code_bits(v[u][2], inv, qmax), code_bits(v[u][3], inv, qmax));
         if (d_[u] < Q) out[(int64_t)(row0 + r_[u]) * D + d_[u]] = q4;
@@ -360,12 +442,26 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
         unsigned td = (unsigned)it - r * (unsigned)TD;
         if (td >= (unsigned)TD) { ++r; td -= (unsigned)TD; }
         const i32x4 cols = *reinterpret_cast<const i32x4*>(&tcol[4 * td]);
-        const int8_t* irow = img + (int)r * P;
         unsigned q4 = 0;
+        const int8_t* irow = img + (int)r * P;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const unsigned byte = (unsigned)(unsigned char)irow[cols[e] < 0 ? 0 : cols[e]];
             q4 |= (cols[e] < 0 ? 0u : byte) << (8 * e);
+        }
+        if constexpr (SCALE != 0) {
+            const i32x4 dd = *reinterpret_cast<const i32x4*>(&tdep[4 * td]);
+            if ((dd[0] & dd[1] & dd[2] & dd[3]) >= 0) {          // some copy with a depth of its own
+                const float* xrow = X + (int64_t)(row0 + (int)r) * ldx;
+                float x[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[e] = xrow[cols[e] < 0 ? 0 : cols[e]];   // requested together
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const unsigned byte = code_bits(scaled(x[e], dd[e] < 0 ? 0 : dd[e]), inv, qmax) & 0xFFu;
+                    if (dd[e] >= 0) q4 = (q4 & ~(0xFFu << (8 * e))) | (byte << (8 * e));
+                }
+            }
         }
         out[(int64_t)(row0 + (int)r) * D + Q + (int)td] = q4;
     }
@@ -380,7 +476,7 @@ struct ShotPlan {
 // row whatever it needs, up to 8 loads per lane.  force_u > 0: that many loads per lane, with as
 // many rows as they hold (tests and tuning).
 constexpr int kShotMaxU = 8;
-static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0) {
+static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0, bool scaled = false) {
     ShotPlan p;
     if (M < 1 || M > 0x7FFFFFFF - 4096 || K < 4 || K > 4 * kShotNT * kShotMaxU || ldq % 16 != 0) return p;
     const int64_t Q = K / 4, Qc = (K + 3) / 4, TD = ldq / 4 - Q;
@@ -393,6 +489,8 @@ static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0) {
         R = 512 / Qc;
         if (R * Qc < 448) R = 768 / Qc;
         if (R < 1) R = 1;
+        // scaled, single rows that leave a quarter of the third load's lanes idle with their look-ups: two
+        if (scaled && R == 1 && Qc > 512 && Qc <= 640) R = 2;
     }
     if (R > 64) R = 64;
     p.R = (int)R;
@@ -401,10 +499,11 @@ static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0) {
     return p;
 }
 
-template <int U>
+template <int U, int SCALE, int MAX, bool G1>
 static hipError_t run_expand_quantize_shot(const ShotPlan& p, const float* X, int64_t ldx, int64_t M, int C, int g,
-                                           int s, const int32_t* chan_src, const float* thr, float qmax, int8_t* Xq,
-                                           int64_t ldq, float* scale_out, hipStream_t stream, float clip) {
+                                           int s, const int32_t* chan_src, const int32_t* chan_depth, const float* thr,
+                                           float qmax, int8_t* Xq, int64_t ldq, float* scale_out, hipStream_t stream,
+                                           const ShotMax& mx) {
     const int64_t K = (int64_t)C * g, Q = K / 4, Qc = (K + 3) / 4, TD = ldq / 4 - Q;
     // floor(2^32 / n), or 2^32 - 1 for n = 1: the quotient estimate is then at most one low, which
     // the kernel's correction step absorbs
@@ -414,10 +513,30 @@ static hipError_t run_expand_quantize_shot(const ShotPlan& p, const float* X, in
     };
     const unsigned magic_qc = magic_of(Qc);
     const unsigned magic_td = TD > 0 ? magic_of(TD) : 0u;
-    const unsigned lds = (unsigned)(((p.R * (ldq + 4) + 15) & ~(int64_t)15) + (TD > 0 ? 4 * TD : 1) * 4);
-    return launch_kernel(kTimeSplitQuantize, expand_quantize_shot_kernel<U>, dim3((unsigned)ceil_div(M, p.R)),
-                         dim3(kShotNT), lds, stream, X, ldx, (int)M, C, g, s, chan_src, thr, qmax, Xq, ldq, p.R,
-                         magic_qc, magic_td, scale_out, clip);
+    const int64_t image = (p.R * (ldq + 4) + 15) & ~(int64_t)15;
+    const unsigned lds = (unsigned)(image + (TD > 0 ? 4 * TD : 1) * (SCALE ? 8 : 4));
+    return launch_kernel(kTimeSplitQuantize, expand_quantize_shot_kernel<U, SCALE, MAX, G1>, dim3((unsigned)ceil_div(M, p.R)),
+                         dim3(kShotNT), lds, stream, X, ldx, (int)M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq,
+                         p.R, magic_qc, magic_td, magic_of(g), scale_out, mx);
+}
+template <int SCALE, int MAX, bool G1 = false>
+static hipError_t launch_shot(const ShotPlan& p, const float* X, int64_t ldx, int64_t M, int C, int g, int s,
+                              const int32_t* chan_src, const int32_t* chan_depth, const float* thr, float qmax,
+                              int8_t* Xq, int64_t ldq, float* scale_out, hipStream_t stream, const ShotMax& mx) {
+#define OCS_SHOT(U_) \
+    case U_: return run_expand_quantize_shot<U_, SCALE, MAX, G1>(p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx)
+    switch (p.U) {
+        OCS_SHOT(1);
+        OCS_SHOT(2);
+        OCS_SHOT(3);
+        OCS_SHOT(4);
+        OCS_SHOT(5);
+        OCS_SHOT(6);
+        OCS_SHOT(7);
+        OCS_SHOT(8);
+        default: return hipErrorInvalidValue;
+    }
+#undef OCS_SHOT
 }
 
 // The same pass with the lanes dealt over the INPUT instead: one lane per 16-byte group of X,
@@ -582,11 +701,11 @@ static TileLds tile_lds(int BM, int64_t ldq, int ksteps_main, int T) {
     return l;
 }
 
-template <int BM, int WPE, int SETS>
+template <int BM, int WPE, int SETS, int MAX>
 __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
     const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
     const int32_t* __restrict__ chan_src, const float* __restrict__ thr, float qmax,
-    int8_t* __restrict__ Xq, int64_t ldq, int ksteps_main, int rem, float* __restrict__ scale_out, TileLds L) {
+    int8_t* __restrict__ Xq, int64_t ldq, int ksteps_main, int rem, float* __restrict__ scale_out, TileLds L, ShotMax mx) {
     // ksteps_main: whole 64-column steps of X; rem: columns of X left over after them (< 64)
     constexpr int NT = kTileNT, A_PER = BM * 16 / NT;
     static_assert(A_PER >= 1 && A_PER * NT == BM * 16, "the threads tile a step of X");
@@ -612,6 +731,10 @@ __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
         a_src[i] = X + (int64_t)gr * ldx + f4 * 4;
         a_dst[i] = r * P + f4 * 4;
     }
+    static_assert(NT == kShotNT, "shot_threshold's lanes");
+    __shared__ float red[NT / 64];
+    float part_max = 0.0f;
+    if constexpr (MAX == 1) part_max = tid < mx.n ? mx.partials[tid] : 0.0f;    // ahead of the requests for X
     f32x4 av[SETS][A_PER];   // SETS register sets in rotation: SETS-1 steps are on their way while one is processed
     auto load_step = [&](int kt, f32x4 (&a)[A_PER]) {
         // every lane issues the same loads at every step (a lane with nothing to fetch reads the 16
@@ -669,7 +792,7 @@ __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
         }
         // (the first step's barrier completes the table before anyone reads it)
     }
-    const float Tx = *thr;
+    const float Tx = shot_threshold<MAX>(thr, mx, part_max, X, red);
     const float inv = inv_step_of(Tx, qmax);
     if (scale_out != nullptr && blockIdx.x == 0 && tid == 0) {
         scale_out[0] = Tx;
@@ -735,10 +858,10 @@ static bool tile_fits(int64_t M, int64_t K, int64_t T, int64_t ldq) {
     return tile_lds(64, ldq, (int)(K / 64), (int)T).total <= kTileMaxLds;
 }
 
-template <int BM, int SETS>
+template <int BM, int SETS, int MAX>
 static hipError_t run_expand_quantize_tile(const float* X, int64_t ldx, int64_t M, int C, int g, int s,
                                            const int32_t* chan_src, const float* thr, float qmax, int8_t* Xq,
-                                           int64_t ldq, float* scale_out, hipStream_t stream) {
+                                           int64_t ldq, float* scale_out, hipStream_t stream, const ShotMax& mx) {
     const int64_t K = (int64_t)C * g;
     const int ksteps_main = (int)(K / 64), rem = (int)(K - (int64_t)ksteps_main * 64);
     const TileLds L = tile_lds(BM, ldq, ksteps_main, s * g);
@@ -749,22 +872,46 @@ static hipError_t run_expand_quantize_tile(const float* X, int64_t ldx, int64_t 
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_quantize_tile_kernel<BM, 4, SETS>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_quantize_tile_kernel<BM, 4, SETS, MAX>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    return launch_kernel(kTimeSplitQuantize, expand_quantize_tile_kernel<BM, 4, SETS>, dim3((unsigned)ceil_div(M, BM)),
+    return launch_kernel(kTimeSplitQuantize, expand_quantize_tile_kernel<BM, 4, SETS, MAX>, dim3((unsigned)ceil_div(M, BM)),
                          dim3(kTileNT), (unsigned)L.total, stream, X, ldx, (int)M, C, g, s, chan_src, thr, qmax, Xq, ldq,
-                         ksteps_main, rem, scale_out, L);
+                         ksteps_main, rem, scale_out, L, mx);
+}
+
+// The one-shot pass wherever it serves the shape (static grid, measured against the tile-ordered and the
+// flat passes below on the paper's layer shapes at batch 256: 1-13 % ahead on every one of them), except
+// rows of fewer than 256 values that are not whole 16-byte groups, the 7x7 stem's 147: a third of such a
+// workgroup's items are tail dwords, and the tile-ordered pass, which writes its image out in 16-byte
+// pieces, is 6 % ahead there.
+static bool act_shot_serves(int64_t M, int64_t K, int s, int g, int64_t ldq, const int32_t* chan_src) {
+    const int np_mode = tuning().act_np;
+    if (np_mode == 0 || tuning().act_tile > 0 || (chan_src == nullptr && s != 0)) return false;
+    if (np_mode < 0 && K % 4 != 0 && K < 256 && tile_fits(M, K, (int64_t)s * g, ldq)) return false;
+    return shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0).U > 0;
+}
+
+// Largest tensor whose maximum every workgroup of the one-shot pass finds for itself instead of a pass
+// ahead of it.  SELF_NOTE
+constexpr int64_t kSelfMax = 32768;
+bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ldq, const int32_t* chan_src) {
+    const int64_t K = (int64_t)C * g;
+    const Tuning& tn = tuning();
+    if (tn.act_grid > 0 || tn.act_un > 0 || tn.act_wide > 0 || tn.act_dep >= 0 || tn.act_map >= 0 || tn.max_flat >= 0 ||
+        tn.max_grid > 0 || tn.max_un >= 0 || tn.max_bt >= 0)
+        return false;      // (a launch shape asked of the passes this replaces: those)
+    return ldx == K && M * K <= kSelfMax && act_shot_serves(M, K, s, g, ldq, chan_src);
 }
 
 hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C, int g, int s,
                                   const int32_t* chan_src, const int32_t* chan_depth,
                                   const float* thr, float qmax, int8_t* Xq, int64_t ldq,
                                   float* scale_out, hipStream_t stream, const float* partials,
-                                  int n_partials, float clip_ratio, bool stepwise) {
+                                  int n_partials, float clip_ratio, bool stepwise, int64_t self) {
     const int64_t K = (int64_t)C * g;
     const bool vec_ok = true;   // 16-byte loads need only the float's own alignment
     const int main_units = (int)(K / 4);
@@ -782,32 +929,25 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     int64_t grid = 256 * 8;  // 8 workgroups of 4 waves on each of the 256 CUs
     if (tuning().act_grid > 0) grid = tuning().act_grid;
     if (grid > ceil_div(total, kThreads)) grid = ceil_div(total, kThreads);
-    // Static grid, un-scaled copies: the one-shot pass wherever it serves the shape (measured against
-    // the tile-ordered and the flat passes below on the paper's layer shapes at batch 256: 1-13 % ahead
-    // on every one of them)
-    // (except rows of fewer than 256 values that are not whole 16-byte groups, the 7x7 stem's 147: a
-    // third of such a workgroup's items are tail dwords, and the tile-ordered pass below, which writes
-    // its image out in 16-byte pieces, is 6 % ahead there)
     const int np_mode = tuning().act_np;
-    const bool odd_narrow = K % 4 != 0 && K < 256 && tile_fits(M, K, (int64_t)s * g, ldq);
-    // (a per-batch grid whose pass before this one left the maximum itself behind, one entry, is served
-    // too: the threshold is then the clip ratio times that entry)
-    const bool given = thr != nullptr && partials == nullptr, one_max = thr == nullptr && partials != nullptr && n_partials == 1;
-    if ((given || one_max) && !halve && (chan_src != nullptr || s == 0) && np_mode != 0 && tuning().act_tile <= 0 &&
-        tuning().act_map < 0 && (np_mode > 0 || !odd_narrow)) {
-        const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0);
-#define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, given ? thr : partials, qmax, Xq, ldq, scale_out, stream, given ? 1.0f : clip_ratio
-        switch (p.U) {
-            case 1: return run_expand_quantize_shot<1>(OCS_SHOT_ARGS);
-            case 2: return run_expand_quantize_shot<2>(OCS_SHOT_ARGS);
-            case 3: return run_expand_quantize_shot<3>(OCS_SHOT_ARGS);
-            case 4: return run_expand_quantize_shot<4>(OCS_SHOT_ARGS);
-            case 5: return run_expand_quantize_shot<5>(OCS_SHOT_ARGS);
-            case 6: return run_expand_quantize_shot<6>(OCS_SHOT_ARGS);
-            case 7: return run_expand_quantize_shot<7>(OCS_SHOT_ARGS);
-            case 8: return run_expand_quantize_shot<8>(OCS_SHOT_ARGS);
-            default: break;     // a shape it does not serve: the passes below
-        }
+    const bool given = thr != nullptr && partials == nullptr;
+    // (a launch shape asked of the flat passes: those)
+    const bool tuned = tuning().act_grid > 0 || tuning().act_un > 0 || tuning().act_wide > 0 || tuning().act_dep >= 0 || tuning().act_map >= 0;
+    ShotMax mx;
+    if (!given) {
+        mx.partials = partials;
+        mx.n = partials != nullptr ? n_partials : 0;
+        mx.self = self;
+        mx.clip = clip_ratio;
+    }
+    if (act_shot_serves(M, K, s, g, ldq, chan_src) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve)) {
+        const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve);
+#define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx
+        if (mx.self > 0) return launch_shot<0, 2>(OCS_SHOT_ARGS);
+        if (!given) return launch_shot<0, 1>(OCS_SHOT_ARGS);
+        if (!halve) return launch_shot<0, 0>(OCS_SHOT_ARGS);
+        if (g == 1) return stepwise ? launch_shot<2, 0, true>(OCS_SHOT_ARGS) : launch_shot<1, 0, true>(OCS_SHOT_ARGS);
+        return stepwise ? launch_shot<2, 0>(OCS_SHOT_ARGS) : launch_shot<1, 0>(OCS_SHOT_ARGS);
 #undef OCS_SHOT_ARGS
     }
     // Static grid, un-scaled copies: the tile-ordered pass.  Measured against the flat orders below on
@@ -817,11 +957,12 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     // 512-value rows on shorter X, level at 1152, behind from 1024-value 1x1 rows on.
     // Two steps of look-ahead (level with one), one for rows of a single step.
     const int tile_mode = tuning().act_tile;
-    if (thr != nullptr && partials == nullptr && !halve && tile_mode != 0 &&
-        tile_fits(M, K, (int64_t)s * g, ldq) &&
+    if ((given || (partials != nullptr && !tuned)) && !halve && tile_mode != 0 && tile_fits(M, K, (int64_t)s * g, ldq) &&
         (tile_mode > 0 || ldq <= 320 || (ldq <= 768 && M >= 400000))) {
-        if (K < 128) return run_expand_quantize_tile<64, 2>(X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream);
-        return run_expand_quantize_tile<64, 3>(X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream);
+#define OCS_TILE_ARGS X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream, mx
+        if (given) return K < 128 ? run_expand_quantize_tile<64, 2, 0>(OCS_TILE_ARGS) : run_expand_quantize_tile<64, 3, 0>(OCS_TILE_ARGS);
+        return K < 128 ? run_expand_quantize_tile<64, 2, 1>(OCS_TILE_ARGS) : run_expand_quantize_tile<64, 3, 1>(OCS_TILE_ARGS);
+#undef OCS_TILE_ARGS
     }
 
     // Lanes dealt over the input when its rows allow it (see expand_quantize_in_kernel)
