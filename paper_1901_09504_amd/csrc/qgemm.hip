@@ -94,10 +94,26 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
                                                  float* __restrict__ Y, int64_t ldy,
                                                  int32_t* __restrict__ acc_out, int64_t ldacc,
                                                  bool vec_y, bool vec_a, const Requant& rq, float inv,
-                                                 const int* dup_list, int dup_n, bool pad_writer) {
+                                                 const int* dup_list, int dup_n, bool pad_writer, bool whole = false) {
     constexpr int LPR = WN / 4;            // lanes per row (8, 16 or 32)
     constexpr int SLOTS = ROWS * LPR;      // 16-byte reads of the block
     static_assert(SLOTS % 64 == 0, "whole waves of slots");
+    // whole: the workgroup's tile lies inside the output, as nearly all of a large one's do: no bounds, no
+    // branch between the stores (for the tile, not per wave: where the last columns of a row share a line
+    // with the next row's first, waves that run ahead of each other cost more, 100000 x 100 19 against 16.5 us)
+    if (whole && rq.Yq == nullptr && acc_out == nullptr && vec_y) {
+        float* yp = Y + (int64_t)(rbase + lane / LPR) * ldy + cbase + (lane % LPR) * 4;
+        const int64_t step = (int64_t)(64 / LPR) * ldy;
+#pragma unroll
+        for (int it = 0; it < SLOTS / 64; ++it) {
+            const i32x4 a = *reinterpret_cast<const i32x4*>(&stage[(it * (64 / LPR) + lane / LPR) * STRIDE + (lane % LPR) * 4]);
+            f32x4 y;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = (float)a[e] * scale;
+            __builtin_nontemporal_store(y, reinterpret_cast<f32x4*>(yp + it * step));
+        }
+        return;
+    }
     if (rq.Yq == nullptr || acc_out != nullptr) {
 #pragma unroll
         for (int it = 0; it < SLOTS / 64; ++it) {
@@ -208,7 +224,7 @@ template <bool RQ, int TM, int TN, int SROWS>
 __device__ __forceinline__ void emit_tile(const i32x16 (&acc)[TM][TN], int32_t* stage, int lane, int rbase, int cbase,
                                           int wcol, int M, int N, float scale, float* __restrict__ Y, int64_t ldy,
                                           int32_t* __restrict__ acc_out, int64_t ldacc, const Requant& rq, float inv,
-                                          const int* dup_list, int dup_n, bool pad_writer) {
+                                          const int* dup_list, int dup_n, bool pad_writer, bool whole) {
     constexpr int WN = 32 * TN;
     const bool vec_y = (reinterpret_cast<uintptr_t>(Y) % 16 == 0) && (ldy % 4 == 0);
     const bool vec_a = acc_out != nullptr && (reinterpret_cast<uintptr_t>(acc_out) % 16 == 0) && (ldacc % 4 == 0);
@@ -246,7 +262,7 @@ __device__ __forceinline__ void emit_tile(const i32x16 (&acc)[TM][TN], int32_t* 
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 emit_staged_rows<SROWS, WN>(stage, lane, rbase + i * 32 + q0 * 8, cbase, wcol, M, N, scale, Y, ldy, acc_out,
-                                            ldacc, vec_y, vec_a, Requant{}, 0.0f, nullptr, 0, false);
+                                            ldacc, vec_y, vec_a, Requant{}, 0.0f, nullptr, 0, false, whole);
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
@@ -608,7 +624,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     const float inv = RQ ? requant_inv(rq, (SPLIT ? tile == 0 : blockIdx.x == 0) && threadIdx.x == 0) : 0.0f;
     const int dup_n = RQ && rq.s_next > 0 ? (dup_count < kDupCap ? dup_count : kDupCap) : 0;
     emit_tile<RQ, TM, TN, 32>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
-                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0, row0 + BM <= M && col0 + BN <= N);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -736,7 +752,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_wholek_kernel(
     const float inv = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
     const int dup_n = RQ && dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
     emit_tile<RQ, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
-                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0, row0 + BM <= M && col0 + BN <= N);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1088,7 +1104,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qconv_patch_kernel(
     const float inv = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
     const int dup_n = RQ && dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
     emit_tile<RQ, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
-                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0);
+                      inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0, row0 + BM <= M && col0 + BN <= N);
 }
 
 constexpr int64_t kWholeKMaxLds = 160 * 1024;  // LDS of one CU
@@ -1459,10 +1475,16 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 // when the output goes to the next layer as codes with copies, the table of those copies
 // behind them (*dup_off = its byte offset, 0 = none).
 template <int BM, int BN, int WAVES_M, int WAVES_N>
-static int64_t wholek_lds_bytes(int64_t Kpad, const Requant& rq, int* dup_off = nullptr) {
+static int64_t wholek_lds_bytes(int64_t N, int64_t Kpad, const Requant& rq, int* dup_off = nullptr) {
     const int64_t operands = (Kpad / 64) * (BM + BN) * 64;
     const int64_t staging = (int64_t)WAVES_M * WAVES_N * (rq.Yq != nullptr ? stage_bytes<true, BN / WAVES_N, 8>() : stage_bytes<false, BN / WAVES_N, 8>());
     int64_t lds = operands > staging ? operands : staging;
+    // Three of the 128 x 128 workgroups per compute unit, not four, and two where one tile holds a row of the
+    // output: the store streams of more cost more than they hide (inside the pass, behind the launch that
+    // wrote the codes: 802816 x 256 from 64 channels 189 us with three, 191 with four, 196 with two; 300000 x
+    // 100 from 64 channels 54 with two, 58 with three, 60 with four).
+    const int64_t floor = N <= 128 ? 54 * 1024 : 41 * 1024;
+    if (BM == 128 && BN == 128 && lds < floor) lds = floor;
     int off = 0;
     if (rq.Yq != nullptr && rq.s_next > 0) {
         off = (int)round_up(lds, 16);
@@ -1478,7 +1500,7 @@ static hipError_t run_wholek_as(const int8_t* Xq, int64_t ldx, const int8_t* Wq,
                              const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y,
                              int64_t ldy, hipStream_t stream, const Requant& rq) {
     int dup_off = 0;
-    const int64_t lds = wholek_lds_bytes<BM, BN, WAVES_M, WAVES_N>(Kpad, rq, &dup_off);
+    const int64_t lds = wholek_lds_bytes<BM, BN, WAVES_M, WAVES_N>(N, Kpad, rq, &dup_off);
     if (Kpad < 64 || Kpad % 64 != 0 || lds > kWholeKMaxLds) return hipErrorInvalidValue;
     // more than 64 KB of dynamic LDS has to be opted into, once per kernel and device (setting
     // it twice from two threads is harmless)
@@ -1859,14 +1881,26 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
                                         // 128 channels: the 128 x 64 tile, 70 against 83 us at M = 200,704)
         else if (N <= 64) tile = 24;    // 128 x 64 with whole-line (128-byte) K-steps: 134 against 155 us on
                                         // the 64 -> 64 3x3 layers at M = 802,816
-        else if (N >= 256 && t256sq >= 192 && Kpad >= 1024) tile = 12;
-        else if (N >= 1024 && Kpad < 1024) tile = 9;     // (launched alone on cold operands the 256 x 256 tile
+        else if (Kpad >= 1024) {
+            // Long K: rounds of the chip times what a tile costs.  A compute unit holds one workgroup of any of
+            // these tiles, so the launch takes as many rounds as tiles / compute units, rounded up; a 256 x 256
+            // tile takes 1.75 times as long as a 256 x 128 one, a 128 x 128 one 0.6 times (inside the pass, us:
+            // 2000 x 2000 x 2000 22.4 -> 17.9 with 256 of the small ones; 6000 x 3000 x 3000 112 -> 94 with three
+            // rounds of the middle ones instead of two of the large; 25088 x 256 x 1076 40.6 / 41.7 / 46.5, 50176 x 256
+            // x 1076 78 / 81 / 76, 12544 x 256 x 2358 62 / 58 / 77 for middle / small / large).
+            const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128), cus = compute_units();
+            const int64_t large = 35 * ceil_div(t256sq, cus), middle = 20 * ceil_div(t256, cus), small = 12 * ceil_div(t128, cus);
+            if (N >= 256 && large < middle && large <= small) tile = 12;
+            else if (middle <= small)
+                // the middle size as 128 x 256 for a very long K and fewer tiles than compute units: X rows asked for
+                // by two tiles, not four (43-46 against 45-47 us on the 512 -> 512 3x3 layers at M = 12544)
+                tile = N >= 512 && t256 < cus && Kpad >= 4096 ? 25 : 11;
+            else tile = 23;       // 128-byte K-steps when the operands allow them
+        }
+        else if (N >= 1024) tile = 9;     // (launched alone on cold operands the 256 x 256 tile
                                                          // is ahead here; behind the pass that wrote the codes
                                                          // it is 7-18 % behind)
         else if (N >= 512 && t256sq >= 512) tile = 12;
-        else if (N >= 512 && t256 >= 128 && t256 < 256 && Kpad >= 4096) tile = 25;   // fewer tiles than compute units and a very long K:
-                                        // 128 x 256 (X rows asked for by two tiles, not four; 43-46 against 45-47 us
-                                        // on the 512 -> 512 3x3 layers at M = 12544; behind at half that K)
         else if (t256 >= 128) tile = 11;                 // N = 256 with K below 1024 included (89 against 92 us)
         else tile = 23;   // 128-byte K-steps when the operands allow them
     }
@@ -1888,7 +1922,7 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
         case 14: return run_dma<256, 256, 4, 4, 64, 4>(OCS_GEMM_ARGS);   // 16 waves
         // whole-K variants; a K extent too long for them falls back to a ring variant
 #define OCS_WHOLEK(BM_, BN_, WM_, WN_, FALLBACK)                                                   \
-    (wholek_lds_bytes<BM_, BN_, WM_, WN_>(Kpad, rq) <= kWholeKMaxLds                                   \
+    (wholek_lds_bytes<BM_, BN_, WM_, WN_>(N, Kpad, rq) <= kWholeKMaxLds                                   \
          ? run_wholek<BM_, BN_, WM_, WN_>(OCS_GEMM_ARGS)                                            \
          : FALLBACK)
         case 16: return OCS_WHOLEK(128, 128, 4, 2, (run_dma<128, 128, 4, 2, 64, 4>(OCS_GEMM_ARGS)));

@@ -440,6 +440,62 @@ def test_split_act_one_shot(M, C, g, s, ld_extra, loads):
     assert np.array_equal(q, q_ref)
 
 
+@pytest.mark.parametrize("M,C,g,s,ld_extra", [(64, 64, 1, 9, 0), (33, 67, 1, 40, 48), (300, 3, 49, 5, 0), (17, 301, 2, 30, 0),
+                                              (40, 100, 3, 33, 16), (9, 240, 9, 12, 0), (21, 2300, 1, 60, 0),
+                                              (1000, 16, 1, 20, 0), (5, 1, 4, 3, 0), (7, 1013, 4, 20, 0)])
+@pytest.mark.parametrize("loads", [-1, 1, 2, 5, 8])
+def test_one_shot_with_channel_depths(M, C, g, s, ld_extra, loads):
+    """Scaled channels through the one-shot pass: channels split again and again, so that copies carry
+    another depth than their source, left-over columns, every number of columns per channel at which the
+    depth look-ups differ; the weights' halving split by split on values that leave the normal range."""
+    rng = np.random.default_rng(M + C + g + s + 5)
+    X = _tensor(rng, M, C * g, "heavy")
+    X[:, :g] *= 64.0                                   # one channel that is split over and over
+    sel = ref.split_weights(X, C, g, s)
+    assert s < 3 or sel["chan_depth"].max() >= 2
+    ldq = B.ocs_padded_cols((C + s) * g) + ld_extra
+    q_ref, s_ref, _ = ref.split_act(X, C, g, sel["chan_src"], sel["chan_depth"], s, 8, threshold=2.0, ldq=ldq)
+    W = (X * np.float32(3e-39)).astype(np.float32)     # denormals among them: every halving rounds
+    wsp = ref.split_weights(W, C, g, s)
+    wq_ref, ws_ref = ref.quantize(wsp["T_out"], 6, ldq=B.ocs_padded_cols((C + s) * g))
+    B.ocs_tune("act_np", loads)
+    B.ocs_tune("sel_inline", 0)
+    try:
+        q, sc = gpu_split_act(X, C, g, sel["chan_src"], sel["chan_depth"], s, 8, threshold=2.0, ldq=ldq)
+        got = gpu_split_weights(W, C, g, s, bits=6, want_f32=False)
+    finally:
+        B.ocs_tune("act_np", -1)
+        B.ocs_tune("sel_inline", -1)
+    assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+    assert np.array_equal(got["scale"], ws_ref) and np.array_equal(got["Wq"], wq_ref)
+
+
+@pytest.mark.parametrize("M,K", [(1, 4), (1, 1023), (7, 9), (64, 256), (3, 2731), (128, 256), (16, 2048), (331, 99), (331, 100),
+                                 (127, 259), (5, 6553), (5, 6554)])
+@pytest.mark.parametrize("where", ["first", "last", "nowhere"])
+def test_per_batch_grid_of_small_tensors(M, K, where):
+    """The maximum found by the pass itself (up to 32768 contiguous values) and by the pass ahead of it
+    (more, or rows at a pitch), with the largest magnitude at either end of the tensor and with none."""
+    rng = np.random.default_rng(M * K)
+    X = np.zeros((M, K), np.float32) if where == "nowhere" else rng.standard_normal((M, K)).astype(np.float32)
+    if where == "first":
+        X[0, 0] = -77.0
+    if where == "last":
+        X[-1, -1] = 77.0
+    s = min(5, K)
+    cs = np.concatenate([np.arange(K), rng.integers(0, K, s)]).astype(np.int32)
+    ldq = B.ocs_padded_cols(K + s)
+    q_ref, s_ref, _ = ref.split_act(X, K, 1, cs, None, s, 8, clip_ratio=0.9, ldq=ldq)
+    q, sc = gpu_split_act(X, K, 1, cs, None, s, 8, clip_ratio=0.9)
+    assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+    wide = torch.full((M, K + 3), 1e9, dtype=torch.float32, device="cuda")     # what lies between the rows is not read
+    wide[:, :K] = dev(X)
+    q2 = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+    sc2 = torch.zeros(2, dtype=torch.float32, device="cuda")
+    B.ocs_split_act(wide, M, K, 1, K + 3, dev(cs), None, s, 8, None, 0.9, q2, ldq, sc2, B.alloc_workspace(M, K))
+    assert np.array_equal(host(sc2), s_ref) and np.array_equal(host(q2), q_ref)
+
+
 @pytest.mark.parametrize("M,C,g,s", [(5, 8, 1, 3), (70, 64, 9, 4), (300, 3, 49, 1), (1000, 16, 1, 1), (77, 2048, 1, 103),
                                      (9, 512, 9, 26), (2100, 512, 1, 26), (4100, 1030, 1, 5)])
 @pytest.mark.parametrize("clip", [1.0, 0.7])
