@@ -289,6 +289,7 @@ __global__ __launch_bounds__(kThreads) void expand_quantize_kernel(
 constexpr int kShotNT = 256;
 constexpr int kShotTabPer = 2;                       // table entries per lane
 constexpr int kShotMaxTail = kShotNT * kShotTabPer;  // tail columns 4 * TD served
+constexpr int kSourceDepth = -0x7FFFFFFF - 1;        // a copy whose depth is its source's (no depth list holds this)
 
 struct ShotMax {
     const float* partials = nullptr;   // per-workgroup maxima (n of them), or
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
     const int P = (int)ldq + 4;                       // image pitch: consecutive rows start one bank apart
     int8_t* img = slds;
     int* tcol = reinterpret_cast<int*>(slds + ((R * P + 15) & ~15));
-    int* tdep = tcol + 4 * TD;                        // SCALE only: depth, -1 where it is the source's own
+    int* tdep = tcol + 4 * TD;                        // SCALE only: depth, kSourceDepth where it is the source's own
     const int tid = (int)threadIdx.x;
     const int row0 = (int)blockIdx.x * R;
     const int rows = M - row0 < R ? M - row0 : R;
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
             }
             tcol[e] = col;
             // (a left-over column is its own source)
-            if constexpr (SCALE != 0) tdep[e] = k < K || k >= Ke || tdp[i] == sdep[i] ? -1 : tdp[i];
+            if constexpr (SCALE != 0) tdep[e] = k < K || k >= Ke || tdp[i] == sdep[i] ? kSourceDepth : tdp[i];
         }
     }
     const float T = shot_threshold<MAX>(thr, mx, part, X, red);
@@ -455,15 +456,16 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
         }
         if constexpr (SCALE != 0) {
             const i32x4 dd = *reinterpret_cast<const i32x4*>(&tdep[4 * td]);
-            if ((dd[0] & dd[1] & dd[2] & dd[3]) >= 0) {          // some copy with a depth of its own
+            if (dd[0] != kSourceDepth || dd[1] != kSourceDepth || dd[2] != kSourceDepth || dd[3] != kSourceDepth) {
                 const float* xrow = X + (int64_t)(row0 + (int)r) * ldx;
                 float x[4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) x[e] = xrow[cols[e] < 0 ? 0 : cols[e]];   // requested together
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const unsigned byte = code_bits(scaled(x[e], dd[e] < 0 ? 0 : dd[e]), inv, qmax) & 0xFFu;
-                    if (dd[e] >= 0) q4 = (q4 & ~(0xFFu << (8 * e))) | (byte << (8 * e));
+                    const bool own = dd[e] != kSourceDepth;
+                    const unsigned byte = code_bits(scaled(x[e], own ? dd[e] : 0), inv, qmax) & 0xFFu;
+                    if (own) q4 = (q4 & ~(0xFFu << (8 * e))) | (byte << (8 * e));
                 }
             }
         }

@@ -566,6 +566,25 @@ def test_split_act_deep_halvings(act_dep):
     assert np.array_equal(q, q_ref)
 
 
+@pytest.mark.parametrize("M,C,g", [(40, 96, 1), (33, 68, 3)])
+def test_split_act_depths_below_zero(M, C, g):
+    """f_j = 2^-chan_depth[j] whatever the list holds: depths below zero (factors above one), on channels
+    and on copies, equal to their source's depth and not."""
+    rng = np.random.default_rng(M + C + g)
+    s = 12
+    chan_src = np.concatenate([np.arange(C), rng.integers(0, C, s)]).astype(np.int32)
+    chan_depth = rng.integers(-3, 3, C + s).astype(np.int32)
+    chan_depth[C:C + 4] = -1
+    chan_depth[C + 4] = chan_depth[chan_src[C + 4]]
+    X = _tensor(rng, M, C * g, "normal")
+    cols = (chan_src[:, None] * g + np.arange(g)[None, :]).reshape(-1)
+    Xe = X[:, cols] * np.repeat(np.exp2(-chan_depth.astype(np.float32)), g)[None, :].astype(np.float32)
+    ldq = B.ocs_padded_cols((C + s) * g)
+    q_ref, s_ref = ref.quantize(Xe, 8, threshold=6.0, ldq=ldq)
+    q, sc = gpu_split_act(X, C, g, chan_src, chan_depth, s, 8, threshold=6.0)
+    assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+
+
 def test_split_weights_halvings_that_leave_the_normal_range():
     """Weights of a few 1e-38: the halvings of Eq. 3 push them below the normal range, where every
     halving rounds; the expanded fp32 weights and the codes equal the oracle's (which halves split by
