@@ -186,19 +186,20 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
             rq.Yq[(int64_t)r * rq.ldyq + N + (e >> 8)] = (int8_t)out_code_bits(stage[rr * STRIDE + local], scale, lo, inv, rq.qmax);
     }
     // the pad columns of the code tensor (past the last copy) are zero codes: written by one wave
-    // of the last tile column, (row, dword) pairs over the lanes; the first dword of a row may begin
+    // of the last tile column, a lane walking the dwords of its row; the first dword of a row may begin
     // with the last copies, and then takes its bytes one by one
     if (pad_writer) {
-        const int64_t c0 = (int64_t)N + rq.s_next, d0 = c0 & ~(int64_t)3;
-        const int dwords = (int)((rq.ldyq - d0) / 4);
-        for (int idx = lane; idx < ROWS * dwords; idx += 64) {
-            const int r = rbase + idx % ROWS, d = idx / ROWS;
-            if (r >= M) continue;
-            int8_t* qp = rq.Yq + (int64_t)r * rq.ldyq + d0 + 4 * d;      // ldyq % 16 == 0: aligned
-            if (d0 + 4 * d >= c0) {
-                *reinterpret_cast<int*>(qp) = 0;
-            } else {
-                for (int e = (int)(c0 - d0); e < 4; ++e) qp[e] = 0;
+        static_assert(64 % ROWS == 0, "whole rows of lanes");
+        const int64_t c0 = (int64_t)N + rq.s_next;
+        const int r = rbase + lane % ROWS;
+        if (r < M) {
+            int8_t* row = rq.Yq + (int64_t)r * rq.ldyq;                  // ldyq % 16 == 0: whole dwords
+            for (int64_t c = (c0 & ~(int64_t)3) + 4 * (lane / ROWS); c < rq.ldyq; c += 4 * (64 / ROWS)) {
+                if (c >= c0) {
+                    *reinterpret_cast<int*>(row + c) = 0;
+                } else {
+                    for (int64_t e = c0; e < c + 4; ++e) row[e] = 0;
+                }
             }
         }
     }

@@ -926,6 +926,27 @@ def test_qgemm_requant(tile, M, N, K, s_next, relu):
     assert np.array_equal(host(Yq), q_ref)
 
 
+@pytest.mark.parametrize("tile", [6, 16])
+def test_qgemm_requant_pad_columns_of_a_long_row(tile):
+    """A pitch of 2^28 + 128 bytes: every column past the last copy is a zero code (32 staged rows times the
+    row's dwords do not fit 31 bits)."""
+    N, K, s_next, ldy = 33, 64, 1, (1 << 28) + 128
+    Xq = torch.full((1, K), 3, dtype=torch.int8, device="cuda")
+    Wq = torch.full((N, K), 2, dtype=torch.int8, device="cuda")
+    one = torch.tensor([1.0, 1.0], dtype=torch.float32, device="cuda")
+    thr = torch.tensor([1000.0], dtype=torch.float32, device="cuda")
+    cs = dev(np.append(np.arange(N), 5).astype(np.int32))
+    Yq = torch.full((1, ldy), 77, dtype=torch.int8, device="cuda")
+    sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+    B.ocs_tune("gemm_tile", tile)
+    try:
+        B.ocs_qgemm_requant(Xq, K, Wq, K, 1, N, K, 8, 6, one, one, False, thr, 8, cs, s_next, Yq, ldy, sc)
+    finally:
+        B.ocs_tune("gemm_tile", -1)
+    assert torch.all(Yq[0, :N + s_next] == 49)          # 3 * 2 * 64 = 384 on a grid of 1000 / 127: 48.8
+    assert not Yq[0, N + s_next:].any()
+
+
 @pytest.mark.parametrize("tile", [26, 27, 28, 29])
 @pytest.mark.parametrize("steps", [1, 2, 5, 7, 8, 9, 15, 16, 17, 24, 25, 32, 33, 40, 41])
 @pytest.mark.parametrize("M,N", [(1, 1), (31, 65), (33, 32), (64, 64), (65, 63), (97, 130)])
