@@ -914,6 +914,17 @@ bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ld
     return ldx == K && M * K <= kSelfMax && act_shot_serves(M, K, s, g, ldq, chan_src);
 }
 
+// Per-workgroup maxima that the short workgroups of the one-shot and tile passes fold for themselves.  Up to
+// 256, one per lane, always (what a contiguous X leaves behind).  A strided X leaves a few thousand (8 column
+// strips x 256 row blocks): every workgroup then reads as many bytes of maxima as of X, which pays only while
+// the tensor is small (40000 x 100 at a pitch of 116 12.2 against 15.2 us for the persistent workgroups of
+// the flat passes, 15000 x 300 15.7 against 16.1; 2500 x 2304 16.6 against 15.5, 25088 x 1024 52.1 against 44.1).
+constexpr int kFoldPerLane = 256;
+constexpr int64_t kFoldManyMax = (int64_t)5 << 20;
+static bool folds_maxima(int64_t values, int n_partials) {
+    return n_partials <= kFoldPerLane || values < kFoldManyMax;
+}
+
 hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C, int g, int s,
                                   const int32_t* chan_src, const int32_t* chan_depth,
                                   const float* thr, float qmax, int8_t* Xq, int64_t ldq,
@@ -947,7 +958,8 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
         mx.self = self;
         mx.clip = clip_ratio;
     }
-    if (act_shot_serves(M, K, s, g, ldq, chan_src) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve)) {
+    const bool folds = given || folds_maxima(M * K, mx.n);
+    if (act_shot_serves(M, K, s, g, ldq, chan_src) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && folds) {
         const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve);
 #define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx
         if (mx.self > 0) return launch_shot<0, 2>(OCS_SHOT_ARGS);
@@ -964,7 +976,7 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     // 512-value rows on shorter X, level at 1152, behind from 1024-value 1x1 rows on.
     // Two steps of look-ahead (level with one), one for rows of a single step.
     const int tile_mode = tuning().act_tile;
-    if ((given || (partials != nullptr && !tuned)) && !halve && tile_mode != 0 && tile_fits(M, K, (int64_t)s * g, ldq) &&
+    if ((given || (partials != nullptr && !tuned)) && folds && !halve && tile_mode != 0 && tile_fits(M, K, (int64_t)s * g, ldq) &&
         (tile_mode > 0 || ldq <= 320 || (ldq <= 768 && M >= 400000))) {
 #define OCS_TILE_ARGS X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream, mx
         if (given) return K < 128 ? run_expand_quantize_tile<64, 2, 0>(OCS_TILE_ARGS) : run_expand_quantize_tile<64, 3, 0>(OCS_TILE_ARGS);

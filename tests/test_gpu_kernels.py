@@ -519,6 +519,32 @@ def test_split_act_per_batch_grid_one_shot(M, C, g, s, clip):
         B.ocs_tune("max_flat", -1)
 
 
+@pytest.mark.parametrize("M,C,ld", [(300, 64, 80), (2600, 300, 316), (17470, 300, 301), (17480, 300, 301), (139820, 300, 316)])
+def test_per_batch_grid_of_strided_tensors(M, C, ld):
+    """Rows at a pitch: the max|X| pass leaves a few maxima, or thousands (folded by every workgroup of the
+    streaming pass below 5 * 2^20 values, by its persistent workgroups from there on, by a launch of their own from
+    40 * 2^20 on); the largest magnitude in the last column, larger values between the rows."""
+    rng = np.random.default_rng(M + C)
+    X = rng.standard_normal((M, C), dtype=np.float32)
+    X[M - 1, C - 1] = -9.0
+    s = 5
+    cs = np.concatenate([np.arange(C), rng.integers(0, C, s)]).astype(np.int32)
+    wide = torch.full((M, ld), 1e9, dtype=torch.float32, device="cuda")
+    wide[:, :C] = dev(X)
+    ws = B.alloc_workspace(M, C)
+    for split in (True, False):
+        ldq = B.ocs_padded_cols(C + (s if split else 0))
+        q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+        sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+        if split:
+            q_ref, s_ref, _ = ref.split_act(X, C, 1, cs, None, s, 8, clip_ratio=0.9, ldq=ldq)
+            B.ocs_split_act(wide, M, C, 1, ld, dev(cs), None, s, 8, None, 0.9, q, ldq, sc, ws)
+        else:
+            q_ref, s_ref = ref.quantize(X, 8, clip_ratio=0.9, ldq=ldq)
+            B.ocs_quantize(wide, M, C, ld, 8, None, 0.9, q, ldq, sc, ws)
+        assert np.array_equal(host(sc), s_ref) and np.array_equal(host(q), q_ref)
+
+
 @pytest.mark.parametrize("seed", list(range(24)))
 def test_split_act_static_grid_random_shapes(seed):
     """The static-grid pass as the library dispatches it (one-shot, tile-ordered or flat, by shape) on
