@@ -34,7 +34,8 @@ struct ReducePlan {
     int rows_per_block; // rows each workgroup walks
 };
 
-ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok);
+// scalar: one value per workgroup is wanted (the tensor's maximum), not one per column.
+ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok, bool scalar);
 
 // Workspace layout (byte offsets from a 256-byte aligned base).
 struct Workspace {

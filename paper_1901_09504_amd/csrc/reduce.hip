@@ -10,7 +10,7 @@
 
 namespace ocs {
 
-ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok) {
+ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok, bool scalar) {
     ReducePlan p;
     p.vec = (vec_ok && cols >= 4) ? 4 : 1;
     int64_t units = cols / p.vec;
@@ -31,8 +31,11 @@ ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok) {
     // enough workgroups by themselves, and with a single row block stage 1 writes the column
     // maxima directly: one launch instead of two launch-latency-bound ones.  With up to 512 rows (16
     // per lane) that is so for any number of strips: 256 x 256 weights 2.9 + 2.1 us and the gap
-    // between them -> 3.4 us in one launch.
-    if (p.vec == 4 && rows <= 2048 && (ceil_div(units, 8) >= 32 || rows <= 512)) {
+    // between them -> 3.4 us in one launch.  (Not when one value per workgroup is wanted, `scalar`: there is
+    // no second launch to save, and the few strips take longer than the row blocks: per-batch grid of 400 x 512
+    // at a pitch of 528
+    // 6.40 -> 6.05 us, 4 x 300 5.43 -> 5.14.)
+    if (p.vec == 4 && rows <= 2048 && (ceil_div(units, 8) >= 32 || (rows <= 512 && !scalar))) {
         p.tx = 8;                                  // 8 lanes x 16 B = one 128-byte line per row
         p.ty = kThreads / p.tx;
         p.col_strips = (int)ceil_div(units, p.tx);
@@ -46,8 +49,8 @@ ReducePlan plan_reduce(int64_t rows, int64_t cols, bool vec_ok) {
 Workspace plan_workspace(int64_t rows, int64_t cols) {
     Workspace w;
     // the plan with the most row blocks bounds both the vector and the scalar variant
-    ReducePlan a = plan_reduce(rows, cols, true);
-    ReducePlan b = plan_reduce(rows, cols, false);
+    ReducePlan a = plan_reduce(rows, cols, true, true);
+    ReducePlan b = plan_reduce(rows, cols, false, true);
     int64_t rb = a.row_blocks > b.row_blocks ? a.row_blocks : b.row_blocks;
     w.colmax_off = 0;
     w.partial_off = (size_t)round_up(round_up(cols, 64) * 4, 256);
@@ -252,7 +255,7 @@ static hipError_t launch_partials(const float* T, int64_t rows, int64_t cols, in
 hipError_t launch_colmax(const float* T, int64_t rows, int64_t cols, int64_t ld, float* colmax,
                          float* partial, hipStream_t stream) {
     const bool vec_ok = true;   // 16-byte loads at the float's own alignment (f32x4u)
-    ReducePlan p = plan_reduce(rows, cols, vec_ok);
+    ReducePlan p = plan_reduce(rows, cols, vec_ok, false);
     if (p.row_blocks == 1)   // a single row block: stage 1's output is the result
         return launch_partials(T, rows, cols, ld, colmax, false, p, nullptr, stream);
     hipError_t e = launch_partials(T, rows, cols, ld, partial, false, p, nullptr, stream);
@@ -311,7 +314,7 @@ hipError_t launch_absmax_partials(const float* T, int64_t rows, int64_t cols, in
     hipError_t fe = hipSuccess;
     if (launch_absmax_flat(T, rows, cols, ld, partial, entries, stream, &fe)) return fe;
     const bool vec_ok = true;   // 16-byte loads at the float's own alignment (f32x4u)
-    ReducePlan p = plan_reduce(rows, cols, vec_ok);
+    ReducePlan p = plan_reduce(rows, cols, vec_ok, true);
     return launch_partials(T, rows, cols, ld, partial, true, p, entries, stream);
 }
 
@@ -319,7 +322,7 @@ hipError_t launch_absmax_threshold(const float* T, int64_t rows, int64_t cols, i
                                    float* partial, float clip_ratio, float qmax, float* scale_out,
                                    hipStream_t stream) {
     const bool vec_ok = true;   // 16-byte loads at the float's own alignment (f32x4u)
-    ReducePlan p = plan_reduce(rows, cols, vec_ok);
+    ReducePlan p = plan_reduce(rows, cols, vec_ok, true);
     int n = 0;
     hipError_t e = hipSuccess;
     if (!launch_absmax_flat(T, rows, cols, ld, partial, &n, stream, &e))
