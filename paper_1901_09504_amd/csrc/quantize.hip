@@ -707,11 +707,11 @@ static TileLds tile_lds(int BM, int64_t ldq, int ksteps_main, int T) {
     return l;
 }
 
-template <int BM, int WPE, int SETS, int MAX>
+template <int BM, int WPE, int SETS>
 __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
     const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
     const int32_t* __restrict__ chan_src, const float* __restrict__ thr, float qmax,
-    int8_t* __restrict__ Xq, int64_t ldq, int ksteps_main, int rem, float* __restrict__ scale_out, TileLds L, ShotMax mx) {
+    int8_t* __restrict__ Xq, int64_t ldq, int ksteps_main, int rem, float* __restrict__ scale_out, TileLds L) {
     // ksteps_main: whole 64-column steps of X; rem: columns of X left over after them (< 64)
     constexpr int NT = kTileNT, A_PER = BM * 16 / NT;
     static_assert(A_PER >= 1 && A_PER * NT == BM * 16, "the threads tile a step of X");
@@ -737,10 +737,6 @@ __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
         a_src[i] = X + (int64_t)gr * ldx + f4 * 4;
         a_dst[i] = r * P + f4 * 4;
     }
-    static_assert(NT == kShotNT, "shot_threshold's lanes");
-    __shared__ float red[NT / 64];
-    float part_max = 0.0f;
-    if constexpr (MAX == 1) part_max = tid < mx.n ? mx.partials[tid] : 0.0f;    // ahead of the requests for X
     f32x4 av[SETS][A_PER];   // SETS register sets in rotation: SETS-1 steps are on their way while one is processed
     auto load_step = [&](int kt, f32x4 (&a)[A_PER]) {
         // every lane issues the same loads at every step (a lane with nothing to fetch reads the 16
@@ -798,7 +794,7 @@ __global__ __launch_bounds__(kTileNT, WPE) void expand_quantize_tile_kernel(
         }
         // (the first step's barrier completes the table before anyone reads it)
     }
-    const float Tx = shot_threshold<MAX>(thr, mx, part_max, X, red);
+    const float Tx = *thr;
     const float inv = inv_step_of(Tx, qmax);
     if (scale_out != nullptr && blockIdx.x == 0 && tid == 0) {
         scale_out[0] = Tx;
@@ -864,10 +860,10 @@ static bool tile_fits(int64_t M, int64_t K, int64_t T, int64_t ldq) {
     return tile_lds(64, ldq, (int)(K / 64), (int)T).total <= kTileMaxLds;
 }
 
-template <int BM, int SETS, int MAX>
+template <int BM, int SETS>
 static hipError_t run_expand_quantize_tile(const float* X, int64_t ldx, int64_t M, int C, int g, int s,
                                            const int32_t* chan_src, const float* thr, float qmax, int8_t* Xq,
-                                           int64_t ldq, float* scale_out, hipStream_t stream, const ShotMax& mx) {
+                                           int64_t ldq, float* scale_out, hipStream_t stream) {
     const int64_t K = (int64_t)C * g;
     const int ksteps_main = (int)(K / 64), rem = (int)(K - (int64_t)ksteps_main * 64);
     const TileLds L = tile_lds(BM, ldq, ksteps_main, s * g);
@@ -878,26 +874,28 @@ static hipError_t run_expand_quantize_tile(const float* X, int64_t ldx, int64_t 
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_quantize_tile_kernel<BM, 4, SETS, MAX>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&expand_quantize_tile_kernel<BM, 4, SETS>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kTileMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    return launch_kernel(kTimeSplitQuantize, expand_quantize_tile_kernel<BM, 4, SETS, MAX>, dim3((unsigned)ceil_div(M, BM)),
+    return launch_kernel(kTimeSplitQuantize, expand_quantize_tile_kernel<BM, 4, SETS>, dim3((unsigned)ceil_div(M, BM)),
                          dim3(kTileNT), (unsigned)L.total, stream, X, ldx, (int)M, C, g, s, chan_src, thr, qmax, Xq, ldq,
-                         ksteps_main, rem, scale_out, L, mx);
+                         ksteps_main, rem, scale_out, L);
 }
 
-// The one-shot pass wherever it serves the shape (static grid, measured against the tile-ordered and the
-// flat passes below on the paper's layer shapes at batch 256: 1-13 % ahead on every one of them), except
+// The one-shot pass wherever it serves the shape (measured against the tile-ordered and the flat passes below
+// on the paper's layer shapes at batch 256: 1-13 % ahead on every one of them), except, on a given threshold,
 // rows of fewer than 256 values that are not whole 16-byte groups, the 7x7 stem's 147: a third of such a
 // workgroup's items are tail dwords, and the tile-ordered pass, which writes its image out in 16-byte
-// pieces, is 6 % ahead there.
-static bool act_shot_serves(int64_t M, int64_t K, int s, int g, int64_t ldq, const int32_t* chan_src) {
+// pieces, is 6 % ahead there.  With a per-batch grid the tile order has to know the threshold before its first
+// step and its set-up stands in front of that: 1000 x 147 with the max|X| pass 9.5 us in tile order, 5.5 in one
+// shot, 50176 x 147 19.2 against 15.8, 401408 x 147 108 against 106.
+static bool act_shot_serves(int64_t M, int64_t K, int s, int g, int64_t ldq, const int32_t* chan_src, bool per_batch) {
     const int np_mode = tuning().act_np;
     if (np_mode == 0 || tuning().act_tile > 0 || (chan_src == nullptr && s != 0)) return false;
-    if (np_mode < 0 && K % 4 != 0 && K < 256 && tile_fits(M, K, (int64_t)s * g, ldq)) return false;
+    if (np_mode < 0 && !per_batch && K % 4 != 0 && K < 256 && tile_fits(M, K, (int64_t)s * g, ldq)) return false;
     return shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0).U > 0;
 }
 
@@ -911,7 +909,7 @@ bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ld
     if (tn.act_grid > 0 || tn.act_un > 0 || tn.act_wide > 0 || tn.act_dep >= 0 || tn.act_map >= 0 || tn.max_flat >= 0 ||
         tn.max_grid > 0 || tn.max_un >= 0 || tn.max_bt >= 0)
         return false;      // (a launch shape asked of the passes this replaces: those)
-    return ldx == K && M * K <= kSelfMax && act_shot_serves(M, K, s, g, ldq, chan_src);
+    return ldx == K && M * K <= kSelfMax && act_shot_serves(M, K, s, g, ldq, chan_src, true);
 }
 
 // Per-workgroup maxima that the short workgroups of the one-shot and tile passes fold for themselves.  Up to
@@ -959,7 +957,7 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
         mx.clip = clip_ratio;
     }
     const bool folds = given || folds_maxima(M * K, mx.n);
-    if (act_shot_serves(M, K, s, g, ldq, chan_src) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && folds) {
+    if (act_shot_serves(M, K, s, g, ldq, chan_src, !given) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && folds) {
         const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve);
 #define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx
         if (mx.self > 0) return launch_shot<0, 2>(OCS_SHOT_ARGS);
@@ -976,12 +974,10 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     // 512-value rows on shorter X, level at 1152, behind from 1024-value 1x1 rows on.
     // Two steps of look-ahead (level with one), one for rows of a single step.
     const int tile_mode = tuning().act_tile;
-    if ((given || (partials != nullptr && !tuned)) && folds && !halve && tile_mode != 0 && tile_fits(M, K, (int64_t)s * g, ldq) &&
+    if (given && !halve && tile_mode != 0 && tile_fits(M, K, (int64_t)s * g, ldq) &&
         (tile_mode > 0 || ldq <= 320 || (ldq <= 768 && M >= 400000))) {
-#define OCS_TILE_ARGS X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream, mx
-        if (given) return K < 128 ? run_expand_quantize_tile<64, 2, 0>(OCS_TILE_ARGS) : run_expand_quantize_tile<64, 3, 0>(OCS_TILE_ARGS);
-        return K < 128 ? run_expand_quantize_tile<64, 2, 1>(OCS_TILE_ARGS) : run_expand_quantize_tile<64, 3, 1>(OCS_TILE_ARGS);
-#undef OCS_TILE_ARGS
+        if (K < 128) return run_expand_quantize_tile<64, 2>(X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream);
+        return run_expand_quantize_tile<64, 3>(X, ldx, M, C, g, s, chan_src, thr, qmax, Xq, ldq, scale_out, stream);
     }
 
     // Lanes dealt over the input when its rows allow it (see expand_quantize_in_kernel)

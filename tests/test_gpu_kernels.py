@@ -519,6 +519,22 @@ def test_split_act_per_batch_grid_one_shot(M, C, g, s, clip):
         B.ocs_tune("max_flat", -1)
 
 
+@pytest.mark.parametrize("M,C,g", [(100, 147, 1), (700, 3, 49), (1000, 65, 1), (517, 255, 1), (300, 27, 9), (200, 66, 1), (64, 63, 1),
+                                   (3000, 253, 1)])
+def test_per_batch_grid_of_narrow_odd_rows(M, C, g):
+    """Rows of fewer than 256 values that are not whole groups of four: a given threshold takes the tile-ordered
+    pass, a per-batch grid the one-shot pass; both grids, the same largest magnitude, the same codes."""
+    rng = np.random.default_rng(M + C + g)
+    X = _tensor(rng, M, C * g, "heavy")
+    s = max(1, C // 20)
+    sel = ref.split_weights(_tensor(rng, 9, C * g, "heavy"), C, g, s)
+    ldq = B.ocs_padded_cols((C + s) * g)
+    q_ref, s_ref, _ = ref.split_act(X, C, g, sel["chan_src"], None, s, 8, clip_ratio=0.25, ldq=ldq)
+    for threshold in (None, float(s_ref[0])):
+        q, sc = gpu_split_act(X, C, g, sel["chan_src"], None, s, 8, threshold=threshold, clip_ratio=0.25)
+        assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+
+
 @pytest.mark.parametrize("M,C,ld", [(300, 64, 80), (2600, 300, 316), (17470, 300, 301), (17480, 300, 301), (139820, 300, 316)])
 def test_per_batch_grid_of_strided_tensors(M, C, ld):
     """Rows at a pitch: the max|X| pass leaves a few maxima, or thousands (folded by every workgroup of the
