@@ -433,12 +433,13 @@ int ocs_split_act(const float* X, int64_t M, int C, int g, int64_t ldx, const in
         }
         e = launch_absmax_partials(X, M, (int64_t)C * g, ldx, partial, &n, st);
         if (e != hipSuccess) return hip_fail(e);
-        // The maxima of a strided tensor from 160 MB on, a few thousand, are folded into one word by a launch
-        // of its own: the streaming pass then takes its one-shot form, whose workgroups are far too many and
-        // too short to fold that many each (400000 x 300 at a pitch of 316: 249 -> 222 us; below, the launch costs
-        // what the faster pass gains).  A contiguous tensor leaves 256, which they do fold: a launch for it costs more at any size.
-        const int64_t cap = (int64_t)(w.total - w.partial_off) / 4;
-        const bool fold = n > 256 && M * (int64_t)C * g >= ((int64_t)40 << 20);
+        // From 160 MB on the maxima are folded into one word by a launch of their own where the streaming pass's
+        // one-shot workgroups, far too many and too short there, had better not fold them: the few thousand of a
+        // strided tensor (400000 x 300 at a pitch of 316: 249 -> 222 us; below that size the launch costs what the
+        // faster pass gains), and for the narrowest rows (5 million x 12 120 -> 114 us).  Other contiguous
+        // tensors leave 256 that cost their workgroups less than a launch.
+        const int64_t cap = (int64_t)(w.total - w.partial_off) / 4, K = (int64_t)C * g;
+        const bool fold = (n > 256 || K < 24) && M * K >= ((int64_t)40 << 20);
         if (n > 1 && n < cap && (fold || tuning().max_flat == 2)) {   // (max_flat 2: always, for tests)
             e = launch_fold_max(partial, n, partial + n, st);
             if (e != hipSuccess) return hip_fail(e);

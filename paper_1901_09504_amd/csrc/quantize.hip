@@ -298,10 +298,11 @@ struct ShotMax {
     float clip = 1.0f;
 };
 
-// Threshold of the pass as all lanes see it; `red`: 4 floats of LDS.  A barrier unless it is given.
+// Threshold of the pass as all lanes see it; `red`: 4 floats of LDS.  A barrier unless it is one word (MAX 0: a given
+// threshold, clip 1, or the only maximum).
 template <int MAX>
 __device__ __forceinline__ float shot_threshold(const float* thr, const ShotMax& mx, float part, const float* X, float* red) {
-    if constexpr (MAX == 0) return *thr;
+    if constexpr (MAX == 0) return mx.clip * *thr;
     float m = part;                                           // this lane's first of the maxima (requested early)
     for (int i = (int)threadIdx.x + kShotNT; i < mx.n; i += kShotNT) m = fmaxf(m, mx.partials[i]);
     if constexpr (MAX == 2) {
@@ -482,7 +483,20 @@ struct ShotPlan {
 // row whatever it needs, up to 8 loads per lane.  force_u > 0: that many loads per lane, with as
 // many rows as they hold (tests and tuning).
 constexpr int kShotMaxU = 8;
-static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0, bool scaled = false) {
+// Per-batch grid: X comes from the memory-side cache, where the max|X| pass left it, and every workgroup folds the
+// maxima first, so larger workgroups, and fewer of them, are ahead while X fits that cache (256 MB): 7812 x 512
+// 10.5 -> 9.7 us (both passes), 65104 x 384 41.8 -> 39.9, 98958 x 384 64.3 -> 60.8, 401408 x 147 106 -> 103; beyond it
+// three loads' worth, or what a given threshold takes (390625 x 384 249 -> 246).  (Not with the thousands of maxima of
+// a strided X: 40000 x 100 12.4 -> 13.4, nor with a single one.)
+static int per_batch_loads(int64_t M, int64_t K) {
+    const int64_t n = M * K, million = 1 << 20;
+    if (n < 3 * million / 2) return 0;                  // by the row's length alone
+    if (K < 320) return n < 10 * million ? 4 : (n < 64 * million ? 3 : 0);
+    if (n < 8 * million) return 4;
+    if (n < 64 * million) return 6;
+    return K <= 2304 ? 3 : 0;
+}
+static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0, bool scaled = false, bool per_batch = false) {
     ShotPlan p;
     if (M < 1 || M > 0x7FFFFFFF - 4096 || K < 4 || K > 4 * kShotNT * kShotMaxU || ldq % 16 != 0) return p;
     const int64_t Q = K / 4, Qc = (K + 3) / 4, TD = ldq / 4 - Q;
@@ -497,6 +511,8 @@ static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0, bo
         if (R < 1) R = 1;
         // scaled, single rows that leave a quarter of the third load's lanes idle with their look-ups: two
         if (scaled && R == 1 && Qc > 512 && Qc <= 640) R = 2;
+        const int64_t loads = per_batch ? per_batch_loads(M, K) : 0;
+        if (kShotNT * loads >= Qc) R = kShotNT * loads / Qc;
     }
     if (R > 64) R = 64;
     p.R = (int)R;
@@ -912,15 +928,21 @@ bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ld
     return ldx == K && M * K <= kSelfMax && act_shot_serves(M, K, s, g, ldq, chan_src, true);
 }
 
-// Per-workgroup maxima that the short workgroups of the one-shot and tile passes fold for themselves.  Up to
-// 256, one per lane, always (what a contiguous X leaves behind).  A strided X leaves a few thousand (8 column
-// strips x 256 row blocks): every workgroup then reads as many bytes of maxima as of X, which pays only while
-// the tensor is small (40000 x 100 at a pitch of 116 12.2 against 15.2 us for the persistent workgroups of
-// the flat passes, 15000 x 300 15.7 against 16.1; 2500 x 2304 16.6 against 15.5, 25088 x 1024 52.1 against 44.1).
-constexpr int kFoldPerLane = 256;
-constexpr int64_t kFoldManyMax = (int64_t)5 << 20;
-static bool folds_maxima(int64_t values, int n_partials) {
-    return n_partials <= kFoldPerLane || values < kFoldManyMax;
+// Whether a per-batch grid's pass takes the one-shot form, every workgroup of which folds the maxima for itself.
+//  Many maxima: a contiguous X leaves at most 256 behind, one per lane; a strided one leaves a few thousand (8 column
+//   strips x 256 row blocks), and every workgroup then reads as many bytes of maxima as of X.  That pays only
+//   while the tensor is small (40000 x 100 at a pitch of 116 12.2 against 15.2 us for the persistent workgroups of the
+//   flat passes, 15000 x 300 15.7 against 16.1; 2500 x 2304 16.6 against 15.5, 25088 x 1024 52.1 against 44.1).
+//  Rows of fewer than 24 values: a workgroup's 64 rows are less than its lanes could request (4 values: 250,000 rows
+//   9.3 against 9.1 us, 3 million 53 against 41; 16 values: 437,500 rows 17.1 against 16.7, 1.6 million 47 against 44).
+//  A few of the longest rows: one workgroup each, and a fold and a table per workgroup (71 x 7000 6.4 against 6.05 us,
+//   24 x 4096 5.8 against 5.6; level from about 160 rows on).
+static bool per_batch_one_shot(int64_t M, int64_t K, int n_partials) {
+    const int64_t n = M * K, million = 1 << 20;
+    if (n_partials == 1) return true;
+    if (n_partials > 256 && n >= 5 * million) return false;
+    if (K < 24 && n >= (K <= 8 ? million : 6 * million)) return false;
+    return K < 4096 || M >= 160;
 }
 
 hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C, int g, int s,
@@ -956,12 +978,13 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
         mx.self = self;
         mx.clip = clip_ratio;
     }
-    const bool folds = given || folds_maxima(M * K, mx.n);
-    if (act_shot_serves(M, K, s, g, ldq, chan_src, !given) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && folds) {
-        const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve);
+    const bool one_shot = given || mx.self > 0 || per_batch_one_shot(M, K, mx.n);
+    if (act_shot_serves(M, K, s, g, ldq, chan_src, !given) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && one_shot) {
+        const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve, !given && mx.n > 1 && mx.n <= 256);
 #define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx
         if (mx.self > 0) return launch_shot<0, 2>(OCS_SHOT_ARGS);
-        if (!given) return launch_shot<0, 1>(OCS_SHOT_ARGS);
+        if (!given && mx.n > 1) return launch_shot<0, 1>(OCS_SHOT_ARGS);
+        if (!given) thr = mx.partials;
         if (!halve) return launch_shot<0, 0>(OCS_SHOT_ARGS);
         if (g == 1) return stepwise ? launch_shot<2, 0, true>(OCS_SHOT_ARGS) : launch_shot<1, 0, true>(OCS_SHOT_ARGS);
         return stepwise ? launch_shot<2, 0>(OCS_SHOT_ARGS) : launch_shot<1, 0>(OCS_SHOT_ARGS);

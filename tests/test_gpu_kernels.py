@@ -535,6 +535,23 @@ def test_per_batch_grid_of_narrow_odd_rows(M, C, g):
         assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
 
 
+@pytest.mark.parametrize("M,K", [(6143, 256), (6144, 256), (40961, 256), (3933, 400), (20972, 400), (167773, 400), (131071, 8),
+                                 (131073, 8), (393217, 16), (3495254, 12), (159, 4100), (160, 4100), (700, 2305)])
+def test_per_batch_grid_of_contiguous_tensors(M, K):
+    """Sizes on either side of the lines at which the pass after max|X| changes its rows per workgroup (1.5, 8 and 64
+    times 2^20 values, other lines for rows of fewer than 320 values) or its form (the narrowest rows, a few of the longest), and of
+    the launch that folds the maxima; the largest magnitude in the last value."""
+    rng = np.random.default_rng(M + K)
+    X = rng.standard_normal((M, K), dtype=np.float32)
+    X[M - 1, K - 1] = 9.0
+    s = 3
+    cs = np.concatenate([np.arange(K), rng.integers(0, K, s)]).astype(np.int32)
+    ldq = B.ocs_padded_cols(K + s)
+    q_ref, s_ref, _ = ref.split_act(X, K, 1, cs, None, s, 8, clip_ratio=0.5, ldq=ldq)
+    q, sc = gpu_split_act(X, K, 1, cs, None, s, 8, clip_ratio=0.5)
+    assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+
+
 @pytest.mark.parametrize("M,C,ld", [(300, 64, 80), (2600, 300, 316), (17470, 300, 301), (17480, 300, 301), (139820, 300, 316)])
 def test_per_batch_grid_of_strided_tensors(M, C, ld):
     """Rows at a pitch: the max|X| pass leaves a few maxima, or thousands (folded by every workgroup of the
