@@ -298,11 +298,13 @@ struct ShotMax {
     float clip = 1.0f;
 };
 
-// Threshold of the pass as all lanes see it; `red`: 4 floats of LDS.  A barrier unless it is one word (MAX 0: a given
-// threshold, clip 1, or the only maximum).
+// Threshold of the pass as all lanes see it; `red`: 4 floats of LDS.  MAX: 0 given, 1 from the maxima (clip times the
+// largest), 2 looked for in X, 3 from a single maximum; a barrier in 1 and 2.  (The factor in an instance of its own: with
+// clip = 1 in instance 0 a given threshold took 1-1.5 % longer on every shape.)
 template <int MAX>
 __device__ __forceinline__ float shot_threshold(const float* thr, const ShotMax& mx, float part, const float* X, float* red) {
-    if constexpr (MAX == 0) return mx.clip * *thr;
+    if constexpr (MAX == 0) return *thr;
+    if constexpr (MAX == 3) return mx.clip * *thr;
     float m = part;                                           // this lane's first of the maxima (requested early)
     for (int i = (int)threadIdx.x + kShotNT; i < mx.n; i += kShotNT) m = fmaxf(m, mx.partials[i]);
     if constexpr (MAX == 2) {
@@ -978,13 +980,16 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
         mx.self = self;
         mx.clip = clip_ratio;
     }
-    const bool one_shot = given || mx.self > 0 || per_batch_one_shot(M, K, mx.n);
+    const bool one_shot = given || mx.self > 0 || np_mode > 0 || per_batch_one_shot(M, K, mx.n);
     if (act_shot_serves(M, K, s, g, ldq, chan_src, !given) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && one_shot) {
         const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve, !given && mx.n > 1 && mx.n <= 256);
 #define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx
         if (mx.self > 0) return launch_shot<0, 2>(OCS_SHOT_ARGS);
         if (!given && mx.n > 1) return launch_shot<0, 1>(OCS_SHOT_ARGS);
-        if (!given) thr = mx.partials;
+        if (!given) {
+            thr = mx.partials;
+            return launch_shot<0, 3>(OCS_SHOT_ARGS);
+        }
         if (!halve) return launch_shot<0, 0>(OCS_SHOT_ARGS);
         if (g == 1) return stepwise ? launch_shot<2, 0, true>(OCS_SHOT_ARGS) : launch_shot<1, 0, true>(OCS_SHOT_ARGS);
         return stepwise ? launch_shot<2, 0>(OCS_SHOT_ARGS) : launch_shot<1, 0>(OCS_SHOT_ARGS);
