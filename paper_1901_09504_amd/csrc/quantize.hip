@@ -980,7 +980,11 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
         mx.self = self;
         mx.clip = clip_ratio;
     }
-    const bool one_shot = given || mx.self > 0 || np_mode > 0 || per_batch_one_shot(M, K, mx.n);
+    // Scaled channels of several columns take four look-ups per 16 bytes: with rows beyond 2048 values, four loads per lane and
+    // more, that chain is longer than the rest of a launch of few workgroups (49 x 256 x 9 4.2 against 3.65 us for the flat
+    // passes, 64 x 900 x 9 5.2 against 4.2; level at about 1.8 million values, 12544 x 256 x 9 26 against 29).
+    const bool few_scaled = halve && g > 1 && K > 2048 && M * K < ((int64_t)7 << 18);
+    const bool one_shot = np_mode > 0 || (given ? !few_scaled : mx.self > 0 || per_batch_one_shot(M, K, mx.n));
     if (act_shot_serves(M, K, s, g, ldq, chan_src, !given) && (given && !halve ? tuning().act_map < 0 : !tuned) && (given || !halve) && one_shot) {
         const ShotPlan p = shot_plan(M, K, ldq, np_mode > 0 && np_mode <= kShotMaxU ? np_mode : 0, halve, !given && mx.n > 1 && mx.n <= 256);
 #define OCS_SHOT_ARGS p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx

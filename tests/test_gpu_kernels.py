@@ -470,6 +470,27 @@ def test_one_shot_with_channel_depths(M, C, g, s, ld_extra, loads):
     assert np.array_equal(got["scale"], ws_ref) and np.array_equal(got["Wq"], wq_ref)
 
 
+@pytest.mark.parametrize("M,C,g", [(1, 256, 9), (64, 900, 9), (796, 256, 9), (797, 256, 9), (5, 1025, 2), (300, 512, 4)])
+def test_channel_depths_of_few_long_rows(M, C, g):
+    """Scaled channels of several columns on either side of the line (rows beyond 2048 values, about 1.8 million values)
+    between the one-shot pass and the flat ones; weights, split by split, through the same dispatch."""
+    rng = np.random.default_rng(M + C + g)
+    s = C // 20
+    X = _tensor(rng, M, C * g, "heavy")
+    sel = ref.split_weights(X, C, g, s)
+    ldq = B.ocs_padded_cols((C + s) * g)
+    q_ref, s_ref, _ = ref.split_act(X, C, g, sel["chan_src"], sel["chan_depth"], s, 8, threshold=2.0, ldq=ldq)
+    q, sc = gpu_split_act(X, C, g, sel["chan_src"], sel["chan_depth"], s, 8, threshold=2.0, ldq=ldq)
+    assert np.array_equal(sc, s_ref) and np.array_equal(q, q_ref)
+    wq_ref, ws_ref = ref.quantize(sel["T_out"], 5, clip_ratio=0.9, ldq=ldq)
+    B.ocs_tune("sel_inline", 0)
+    try:
+        got = gpu_split_weights(X, C, g, s, bits=5, clip_ratio=0.9, want_f32=False)
+    finally:
+        B.ocs_tune("sel_inline", -1)
+    assert np.array_equal(got["scale"], ws_ref) and np.array_equal(got["Wq"], wq_ref)
+
+
 @pytest.mark.parametrize("M,K", [(1, 4), (1, 1023), (7, 9), (64, 256), (3, 2731), (128, 256), (16, 2048), (331, 99), (331, 100),
                                  (127, 259), (5, 6553), (5, 6554)])
 @pytest.mark.parametrize("where", ["first", "last", "nowhere"])
