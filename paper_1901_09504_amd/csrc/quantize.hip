@@ -1074,6 +1074,7 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
 // expanded channel j is scaled by 2^-dep[j]; Eq. 1 on the grid of clip_ratio * max|W'|), with
 // the arithmetic of expand_quantize_kernel.  Workgroup 0 also writes the lists, the maximum
 // and the grid for the caller.  32-bit indices.
+template <bool FEW>
 __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     const float* __restrict__ W, int64_t ldw, int64_t N, int C, int g, int s,
     const float* __restrict__ colmax, int32_t* __restrict__ split_src,
@@ -1112,7 +1113,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     fetch(o, cur, row, d);
 
     channel_maxima_to_lds<kThreads>(colmax, C, g, vals, src, dep);
-    greedy_rounds<kThreads>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
+    greedy_select<kThreads, FEW>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
     unsigned m = 0;   // bit pattern of the largest entry (all entries are non-negative)
     for (int j = tid; j < E; j += kThreads) {
         if (first) {
@@ -1173,10 +1174,10 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
 // Whether the one-launch form serves this shape: a list short enough that 256 lanes are through its rounds
 // about as fast as the selector's wide workgroup is (measured over the whole weight path, one launch against
 // two: 512 channels with 26 or 52 splits 14 against 16 us, 2048 x 512 with 26 17.0 against 17.4, 512 x 512 x 9
-// 15.7 against 16.1; 2048 x 1000 with 10 splits 22 against 19), 32-bit item indices.
+// 15.7 against 16.1; 2048 x 1000 with 10 splits 22 against 19) or taken step by step, 32-bit item indices.
 bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq) {
     const int limit = tuning().sel_inline < 0 ? 64 : tuning().sel_inline;
-    if (C + s > 640 || s > limit || limit == 0) return false;
+    if ((C + s > 640 && !few_steps(C, s)) || s > limit || limit == 0) return false;
     return N * (ldq / 4) + 2 * 2048 * (int64_t)kThreads < ((int64_t)1 << 32);
 }
 
@@ -1194,9 +1195,10 @@ hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N,
     if (tuning().act_grid > 0) grid = tuning().act_grid;
     if (grid > ceil_div(total, kThreads)) grid = ceil_div(total, kThreads);
     const unsigned magic = (unsigned)((((uint64_t)1) << 32) / (uint64_t)D);  // D >= 16
-    return launch_kernel(kTimeSplitQuantize, select_expand_quantize_kernel, dim3((unsigned)grid), dim3(kThreads),
-                         greedy_list_bytes(E), stream, W, ldw, N, C, g, s, colmax, split_src, chan_src, chan_depth,
-                         max_out, clip_ratio, qmax, scale_out, Wq, D, main_units, magic);
+    const auto kernel = few_steps(C, s) ? select_expand_quantize_kernel<true> : select_expand_quantize_kernel<false>;
+    return launch_kernel(kTimeSplitQuantize, kernel, dim3((unsigned)grid), dim3(kThreads), greedy_list_bytes(E), stream,
+                         W, ldw, N, C, g, s, colmax, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax,
+                         scale_out, Wq, D, main_units, magic);
 }
 
 // fp32 expanded tensor (Eq. 3 with halve != 0, the weight side of Eq. 4 with halve == 0).

@@ -14,9 +14,9 @@ namespace ocs {
 
 // What bounds it: the latency of one workgroup's passes over LDS, its barriers and one trip to memory.
 // 3000 channels, 150 splits: 78 -> 11 us against one split per step (0.2 us a step on one wave, 0.5 us on
-// four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; with few splits on few channels level
-// with it.  NT: sixteen waves where the list or its column maxima give every lane something to do.
-template <int NT>
+// four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
+// taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
+template <int NT, bool FEW>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ colmax, int C, int g, int s, int mode,
     const int32_t* split_in, int32_t* split_src,
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     channel_maxima_to_lds<NT>(colmax, C, g, vals, src, dep);
 
     if (mode == 0) {
-        greedy_rounds<NT>(vals, src, dep, cand, sc, C, s, split_src);
+        greedy_select<NT, FEW>(vals, src, dep, cand, sc, C, s, split_src);
     } else {
         if (tid == 0) {
             for (int i = 0; i < s; ++i) {
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
 constexpr unsigned kSelectMaxLds = 128 * 1024;   // holds the list of kMaxExpanded channels
 
-template <int NT>
+template <int NT, bool FEW>
 static hipError_t run_select(const float* colmax, int C, int g, int s, int mode, const int32_t* split_in,
                              int32_t* split_src, int32_t* chan_src, int32_t* chan_depth, float* max_out,
                              float clip_ratio, float qmax, float* scale_out, hipStream_t stream) {
@@ -86,13 +86,13 @@ static hipError_t run_select(const float* colmax, int C, int g, int s, int mode,
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT, FEW>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    select_kernel<NT><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
+    select_kernel<NT, FEW><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
                                               max_out, clip_ratio, qmax, scale_out);
     return hipGetLastError();
 }
@@ -102,11 +102,12 @@ hipError_t launch_select(const float* colmax, int C, int g, int s, int mode,
                          int32_t* chan_depth, float* max_out, float clip_ratio, float qmax,
                          float* scale_out, hipStream_t stream) {
     // E = C + s <= kMaxExpanded is checked by the caller
-    if (C + s <= 512 && (int64_t)C * g <= 1024)
-        return run_select<256>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out,
-                               clip_ratio, qmax, scale_out, stream);
-    return run_select<1024>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out, clip_ratio,
-                            qmax, scale_out, stream);
+    const bool few = mode == 0 && few_steps(C, s);
+    const bool narrow = C + s <= 512 && (int64_t)C * g <= 1024;
+    const auto run = narrow ? (few ? run_select<256, true> : run_select<256, false>)
+                            : (few ? run_select<1024, true> : run_select<1024, false>);
+    return run(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax, scale_out,
+               stream);
 }
 
 }  // namespace ocs

@@ -160,6 +160,10 @@ def _maxima(kind, C, rng):
         m = np.where(rng.random(C) < 0.5, np.float32(0.5), np.nextafter(np.float32(0.5), np.float32(1)))
         m[C // 2] = 1.0
         return m.astype(np.float32)
+    if kind == "infinite":                    # an infinite channel is split by every step, the lowest of two
+        m = np.exp(rng.uniform(-3, 3, C)).astype(np.float32)
+        m[[C // 3, C - 1]] = np.inf
+        return m
     if kind == "denormal":                    # halving rounds, then reaches zero
         return (rng.integers(0, 9, C) * 1.4e-45).astype(np.float32)
     return np.exp(rng.uniform(-12, 12, C)).astype(np.float32)
@@ -167,9 +171,9 @@ def _maxima(kind, C, rng):
 
 @pytest.mark.parametrize("C,s", [(1, 1), (1, 40), (7, 6), (256, 1), (256, 255), (256, 256), (300, 301), (1100, 37),
                                  (4000, 4000), (7000, 600), (7999, 1)])
-@pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread"])
+@pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread", "infinite"])
 def test_select_rounds(C, s, kind):
-    """Rounds cut at every digit of the sort key, rounds that end in zeros, the largest list."""
+    """Rounds cut at every digit of the sort key, rounds that end in zeros or never leave an infinite channel, the largest list."""
     m = _maxima(kind, C, np.random.default_rng(C + s))
     T = np.ascontiguousarray(np.stack([m * np.float32(0.25), -m]))
     exp = ref.split_weights(T, C, 1, s)
@@ -177,6 +181,32 @@ def test_select_rounds(C, s, kind):
     for k in ("split_src", "chan_src", "chan_depth"):
         assert np.array_equal(got[k], exp[k]), k
     assert got["max"] == exp["max"]
+
+
+@pytest.mark.parametrize("C", [2, 64, 65, 96, 97, 256, 257, 320, 321, 512, 513, 640, 641, 1024, 1025])
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 6, 7])
+def test_select_a_few_splits(C, s):
+    """Few splits, step by step on one wave or in rounds: either side of every list length at which the registers per lane
+    or the form change; one dominant channel (copies of copies), equals, zeros, an infinite channel; through the selector
+    and through the code pass."""
+    rng = np.random.default_rng(C + s)
+    for kind in ("dominant", "equal", "octaves", "denormal", "infinite", "spread"):
+        m = _maxima(kind, C, rng)
+        if kind == "dominant":
+            m = np.full(C, 0.5, np.float32)
+            m[C - 1] = 8.0
+        T = np.ascontiguousarray(np.stack([m * np.float32(0.25), -m]))
+        exp = ref.split_weights(T, C, 1, s)
+        got = gpu_select(T, C, 1, s)
+        for k in ("split_src", "chan_src", "chan_depth"):
+            assert np.array_equal(got[k], exp[k]), (k, kind)
+        assert got["max"] == exp["max"]
+        if kind != "infinite":
+            got = gpu_split_weights(T, C, 1, s, bits=6, want_f32=False)
+            for k in ("split_src", "chan_src", "chan_depth"):
+                assert np.array_equal(got[k], exp[k]), (k, kind)
+            q_ref, s_ref = ref.quantize(exp["T_out"], 6, ldq=B.ocs_padded_cols(C + s))
+            assert np.array_equal(got["scale"], s_ref) and np.array_equal(got["Wq"], q_ref)
 
 
 def test_select_resplits_one_dominant_channel():
