@@ -1723,6 +1723,22 @@ static hipError_t run_patch(const int8_t* Aq, const int8_t* Wt, int64_t ldw, int
                          ldy, (int)tiles_n, (unsigned)total, p.ring_off, p.dup_off, rq);
 }
 
+// Whether the run's 256 x 128 tile is ahead of the 128 x 128 ring tile: at most one per compute unit, most of the units
+// busy, and taps of enough 16-byte pieces (cpp) that the address arithmetic per tap weighs little; an even number of pieces
+// takes one more in LDS, an odd one none.  3x3 layers at 14 x 14, 256 outputs, fp32 / codes out, run against ring in us:
+//   cpp 17 (256 channels) 170 tiles 23.1 / 25.9 against 25.2 / 27.1, 246 tiles 25.9 / 27.7 against 30.2 / 32.8
+//   cpp 13 (190)          150 tiles 19.8 / 22.5 against 21.0 / 22.1, 246 tiles 21.9 / 23.1 against 24.3 / 26.8
+//   cpp 16 (240)          170 tiles 21.8 / 24.3 against 20.5 / 22.5, 200 tiles 22.6 / 24.8 against 22.5 / 24.5
+//   cpp 9  (128, 28 x 28) 190 tiles 17.2 / 19.3 against 16.4 / 17.6, 245 tiles 18.2 / 20.1 against 18.6 / 20.2
+//   cpp 5  (64, 28 x 28)  190 tiles 14.2 / 15.8 against 13.6 / 13.8, 245 tiles 14.5 / 16.2 against 13.4 / 14.5
+static bool run_pays(int64_t tiles, int64_t cus, int64_t cpp, int64_t N, bool codes) {
+    if (tiles > cus) return false;
+    if (cpp < 13) return cpp >= 9 && 20 * tiles >= 19 * cus;
+    if (4 * tiles >= 3 * cus) return true;
+    if (cpp % 2 == 0 || N % 128 != 0) return false;
+    return codes ? (cpp >= 17 ? 9 * tiles >= 5 * cus : 5 * tiles >= 3 * cus) : 2 * tiles > cus;
+}
+
 hipError_t launch_qconv(const int8_t* Aq, int64_t ldc, int B, int H, int W, int kh, int kw, int stride,
                         int pad, const int8_t* Wt, int64_t ldw, int64_t N, const float* scale_x,
                         const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy,
@@ -1758,16 +1774,20 @@ hipError_t launch_qconv(const int8_t* Aq, int64_t ldc, int B, int H, int W, int 
     // Measured on 3x3 layers (us, ring 128 x 128 of before -> now).  Up to one 64 x 64 tile per compute
     // unit (two, for more than 64 outputs) that ring tile: 2 x 28 x 28 x 128 -> 128 11.8 -> 9.0, 4 x 7 x 7 x 512 -> 512
     // 27.1 -> 20.8.  Up to 64 outputs the run in LDS: 32 x 56 x 56 x 64 -> 64 19.7 -> 13.8 (fp32 out), 24.7 -> 16.5
-    // (codes out), with 256 rows a tile once that gives every compute unit one, 128 below (16 images: 13.5 -> 10.9).
-    // More outputs: the run's tile of 256 x 128 while it gives each compute unit at most one (128 x 14 x 14 x 256
-    // -> 256 30.9 -> 27.9; 19.1 against 12.4 with 98 of them), else the ring, which is level with it.
+    // (codes out), with 256 rows a tile once that gives every compute unit one, 128 below (16 images: 13.5 -> 10.9);
+    // 256 as well where the run of 128 rows is so long that a compute unit holds one workgroup and there are more
+    // of them than units (16 x 56 x 56 x 256 -> 64 ring 23.2, 128 rows 24.9, 256 rows 19.0; where those do not fit, the ring).
+    // More outputs: the run's tile of 256 x 128 where run_pays() says so, else the ring.
     const int64_t cus = compute_units();
     const bool patch = stride == 1 && kh == kw && kh == 2 * pad + 1 && kh * kw <= kPatchMaxTaps && cg.cpp >= 2;
     if (tile < 0) {
         const int64_t t64 = ceil_div(M, 64) * ceil_div(N, 64), t256 = ceil_div(M, 256) * ceil_div(N, 128);
         if (t64 <= (N <= 64 ? cus : 2 * cus)) tile = 7;
-        else if (patch && N <= 64) tile = ceil_div(M, 256) >= cus ? 31 : 30;
-        else if (patch && 2 * t256 > cus && t256 <= cus) tile = 32;
+        else if (patch && N <= 64) {
+            const bool one_each = 2 * patch_plan<128, 64, 8, 3>(W, pad, cg.cpp, rq).lds > kWholeKMaxLds;
+            tile = ceil_div(M, 256) >= cus || (one_each && ceil_div(M, 128) > cus) ? 31 : 30;
+        }
+        else if (patch && run_pays(t256, cus, cg.cpp, N, rq.Yq != nullptr)) tile = 32;
     }
     if (patch) {       // (a run too long for LDS: the ring)
         if (tile == 30) OCS_PATCH(128, 64, 4, 2, 3);

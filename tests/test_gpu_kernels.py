@@ -957,6 +957,34 @@ def test_qconv_taps_from_lds(tile, Bn, H, W, Cn, N, k, s):
         B.ocs_tune("gemm_tile", -1)
 
 
+@pytest.mark.parametrize("Bn,H,W,Cn,N,k,s", [
+    (17, 3, 700, 30, 40, 3, 2),       # long run, one workgroup per compute unit and more 128-row tiles than units: 256 rows
+    (15, 3, 700, 30, 40, 3, 2),       # the same with fewer tiles than units
+    (17, 3, 700, 120, 40, 3, 2),      # ... whose 256-row run does not fit
+    (32, 28, 28, 190, 129, 3, 2),     # 196 tiles of 256 x 128, twelve or more pieces a pixel
+    (30, 28, 28, 40, 129, 3, 2),      # as many, few pieces: the ring
+])
+def test_qconv_routes_by_tiles_and_pieces(Bn, H, W, Cn, N, k, s):
+    """The forms a 3x3 layer takes by its number of tiles (of 256 compute units) and its pieces per pixel, fp32 and codes out."""
+    rng = np.random.default_rng(Bn + H + W + Cn + N)
+    A = _tensor(rng, Bn * H * W, Cn, "normal").reshape(Bn, H, W, Cn)
+    Wm = _tensor(rng, N, Cn * k * k, "normal")
+    exp = _conv_reference(A, Wm, Cn, k, k, 1, k // 2, s, 8, 6, None)
+    got = gpu_conv_layer(A, Wm, Cn, k, k, 1, k // 2, s, bits_x=8, bits_w=6)
+    assert np.array_equal(got["acc"], exp["acc"])
+    assert_y_close(got["Y"], exp["Y"])
+    T = float(np.float32(0.5 * np.abs(exp["Y"]).max()))
+    cs = _next_layer_list(rng, N, 3)
+    ldy = B.ocs_padded_channels(N + 3)
+    q_ref, sc_ref = ref.requantize(exp["acc"], exp["sx"][1], exp["sw"][1], T, 5, cs, 3, relu=True, ldq=ldy)
+    Yq = torch.full((Bn * H * W, ldy), 77, dtype=torch.int8, device="cuda")
+    sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+    thr = torch.tensor([T], dtype=torch.float32, device="cuda")
+    B.ocs_qconv_requant(dev(got["Aq"]), got["ldc"], Bn, H, W, Cn + s, k, k, 1, k // 2, dev(got["Wt"]), N, 8, 6, dev(got["sx"]),
+                        dev(got["sw"]), True, thr, 5, dev(cs), 3, Yq, ldy, sc)
+    assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
+
+
 def test_qconv_equals_the_lowered_gemm_path():
     # same layer through ocs_split_act on the im2col matrix + ocs_qgemm, with a static grid
     rng = np.random.default_rng(99)
