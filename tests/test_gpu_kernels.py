@@ -753,6 +753,29 @@ def test_qgemm(tile, pitch, M, N, K):
     assert np.array_equal(Y, Y2)
 
 
+@pytest.mark.parametrize("K", [384, 385, 512, 513])
+@pytest.mark.parametrize("M,N", [(130, 300), (257, 2047), (128, 2048), (257, 2100)])
+def test_qgemm_stores_of_the_128_ring_tile(M, N, K):
+    """128 x 128 tiles with 64-byte steps: 6, 7, 8 and 9 steps, below and from 2048 outputs, whole tiles beside
+    ragged ones - the stores go with or without bounds by all three."""
+    rng = np.random.default_rng(M + N + K)
+    ld = -(-K // 128) * 128
+    Xq = np.zeros((M, ld), dtype=np.int8)
+    Wq = np.zeros((N, ld), dtype=np.int8)
+    Xq[:, :K] = rng.integers(-127, 128, (M, K))
+    Wq[:, :K] = rng.integers(-127, 128, (N, K))
+    sx = np.array([3.0, 3.0 / 127], dtype=np.float32)
+    sw = np.array([0.7, 0.7 / 127], dtype=np.float32)
+    acc_ref, y_ref = ref.qgemm(Xq, Wq, K, sx[1], sw[1])
+    B.ocs_tune("gemm_tile", 9)
+    try:
+        acc, Y = gpu_qgemm(Xq, Wq, K, sx, sw)
+    finally:
+        B.ocs_tune("gemm_tile", -1)
+    assert np.array_equal(acc, acc_ref)
+    assert_y_close(Y, y_ref)
+
+
 @pytest.mark.parametrize("parts", [2, 3, 4, 7])
 @pytest.mark.parametrize("M,N,K", [(1, 1, 500), (130, 70, 448), (257, 129, 1035), (700, 300, 1035), (300, 520, 2358),
                                    (1000, 512, 4842)])
