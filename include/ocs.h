@@ -314,7 +314,9 @@ int ocs_qgemm(const int8_t *Xq, int64_t ldx, const int8_t *Wq, int64_t ldw, int6
  * two calls do the same work.
  */
 int ocs_split_act_qgemm_fits(int64_t M, int C, int g, int num_splits, int64_t N, int64_t ldx);
-/* 1 where it fits and was measured ahead of the two calls (rows of X of 256 values and more). */
+/* 1 where it fits and was measured ahead of the two calls.  Rows of X of 128 values and more; N <= 128: from 448
+ * values only with rows to fill the device (64 per compute unit, 128 from 768 values); N > 128: up to 256
+ * values with at most 64 rows per compute unit, longer rows from 156 on. */
 int ocs_split_act_qgemm_pays(int64_t M, int C, int g, int num_splits, int64_t N, int64_t ldx);
 int ocs_split_act_qgemm(const float *X, int64_t M, int C, int g, int64_t ldx, const int32_t *chan_src,
                         int num_splits, int bits_x, const float *threshold, const int8_t *Wq, int64_t ldw,

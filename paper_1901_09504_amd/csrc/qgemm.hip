@@ -1401,10 +1401,19 @@ __global__ __launch_bounds__(NT, WPE) void split_act_qgemm_kernel(
     }
 }
 
-// Where the one launch is ahead of the two (measured on the same shapes): from 256 columns of X
-// on.  With 64 the pass over X is short either way and the output dominates.
+// Where the one launch is ahead of the two (graph replays of the same shape, two launches / one).  It walks a
+// row tile serially, so it needs tiles for every compute unit, the more the longer the rows and the more
+// outputs the plain GEMM can spread instead:
+//   N <= 128   K = 512, N = 64: 1.07 at 16384 rows; shorter rows are ahead from the smallest call on.  From 448 values
+//              64 rows per compute unit, from 768 values 128.
+//   N > 128    K = 1024, N = 256: 0.91 at 32768 rows, 1.10 at 50176; K = 2304: 0.25 at 1000.  More than 256 values:
+//              156 rows per compute unit; up to 256 it is the short calls that save (their launch), 64 rows each.
+// Below 128 values the pass over X is short either way and the output dominates.
 bool split_act_qgemm_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
-    return split_act_qgemm_fits(M, C, g, s, N, ldx) && (int64_t)C * g >= 128;
+    const int64_t K = (int64_t)C * g, cus = compute_units();
+    if (!split_act_qgemm_fits(M, C, g, s, N, ldx) || K < 128) return false;
+    if (N <= 128) return K < 448 || M >= (K < 768 ? 64 : 128) * cus;
+    return K <= 256 ? M <= 64 * cus : M >= 156 * cus;
 }
 
 bool split_act_qgemm_fits(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {

@@ -193,6 +193,22 @@ def test_one_launch_entry_point_says_what_it_serves_and_checks_on_the_host():
     assert call(sxo=A, thr=A) == -9
 
 
+@pytest.mark.parametrize("C,g,s,N,below,from_", [
+    (64, 1, 4, 64, (1, 802816), ()), (127, 1, 4, 256, (1, 802816), ()),               # too narrow at any size
+    (128, 1, 4, 128, (), (1, 802816)), (447, 1, 4, 64, (), (1, 802816)),              # ahead at any size
+    (448, 1, 4, 128, (1, 64 * 256 - 1), (64 * 256, 802816)), (767, 1, 4, 64, (64 * 256 - 1,), (64 * 256,)),
+    (256, 3, 4, 128, (1000, 128 * 256 - 1), (128 * 256,)), (1024, 1, 52, 64, (128 * 256 - 1,), (128 * 256,)),
+    (256, 1, 13, 129, (64 * 256 + 1, 802816), (1, 64 * 256)), (128, 1, 4, 256, (64 * 256 + 1,), (64 * 256,)),
+    (257, 1, 4, 129, (1, 156 * 256 - 1), (156 * 256, 802816)), (256, 9, 13, 256, (1000, 156 * 256 - 1), (156 * 256,))])
+def test_one_launch_pays_by_rows_columns_and_outputs(C, g, s, N, below, from_):
+    """Few long rows leave most compute units without a tile: there the two launches are ahead, up to four times
+    (rows per compute unit, of which there are 256)."""
+    for M in below:
+        assert B.ocs_split_act_qgemm_fits(M, C, g, s, N, C * g) and not B.ocs_split_act_qgemm_pays(M, C, g, s, N, C * g)
+    for M in from_:
+        assert B.ocs_split_act_qgemm_pays(M, C, g, s, N, C * g)
+
+
 def test_binding_raises_on_error():
     with pytest.raises(B.OcsError) as e:
         B._check(-4, "ocs_quantize")
