@@ -136,8 +136,8 @@ def test_select_channels(rows, C, g, s, kind):
 @pytest.mark.parametrize("E", [64, 65, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
 @pytest.mark.parametrize("kind", ["heavy", "ties"])
 def test_select_at_the_list_layout_boundaries(E, kind):
-    """C + s on either side of every size at which the selector changes how it deals the list
-    over its lanes (slots per lane, one wave or four)."""
+    """C + s on either side of the sizes at which the lanes of a workgroup get one entry more each, and of the
+    list and column lengths from which the selector's workgroup has sixteen waves instead of four."""
     s = 40
     rng = np.random.default_rng(E)
     T = _tensor(rng, 3, E - s, kind)
@@ -239,17 +239,24 @@ def test_split_weights_halve(N, C, g, s, bits, clip):
     assert np.array_equal(got["Wq"], q_ref)
 
 
-@pytest.mark.parametrize("sel_inline", [-1, 0, 64])   # default limit / selector launch / selection in the code pass
+@pytest.mark.parametrize("sel_inline", [-1, 0, 1000])   # up to 64 splits inside the code pass / a selector launch / any number inside
 @pytest.mark.parametrize("N,C,g,s,kind", [
     (7, 12, 1, 5, "heavy"), (40, 64, 9, 4, "heavy"), (256, 256, 9, 6, "normal"), (100, 37, 4, 16, "heavy"),
     (100, 37, 4, 17, "heavy"), (64, 3, 49, 1, "normal"), (33, 130, 1, 0, "normal"), (20, 250, 1, 6, "ties"),
     (20, 251, 1, 6, "ties"), (9, 500, 2, 12, "heavy"), (9, 501, 1, 12, "heavy"), (5, 1010, 1, 14, "normal"),
-    (5, 1010, 1, 15, "normal"), (12, 16, 3, 40, "heavy"), (300, 8, 1, 9, "zero")])
+    (5, 1010, 1, 15, "normal"), (12, 16, 3, 40, "heavy"), (300, 8, 1, 9, "zero"),
+    (20, 620, 1, 20, "heavy"), (20, 621, 1, 20, "heavy"),               # lists of 640 and 641
+    (5, 1010, 1, 4, "heavy"), (5, 1010, 1, 5, "heavy"),                 # ... longer ones only for a few steps
+    (30, 100, 3, 64, "heavy"), (30, 100, 3, 65, "heavy"), (6, 540, 2, 100, "heavy"),
+    (9, 576, 1, 64, "last_digits"), (9, 500, 1, 140, "last_digits"), (9, 300, 1, 60, "equal")])   # cut rounds of hundreds of entries
 def test_split_weights_codes_only_routes(N, C, g, s, kind, sel_inline):
     """Codes only (no fp32 copy): with few splits the selection runs inside the code pass, one launch
     instead of two; both routes must write the same lists, maximum, grid and codes."""
     rng = np.random.default_rng(N + C + g + s)
-    W = (_tensor(rng, N, C * g, kind) * 0.05).astype(np.float32)
+    if kind in ("last_digits", "equal"):
+        W = np.outer(np.linspace(-1, 1, N), _maxima(kind, C * g, rng)).astype(np.float32)
+    else:
+        W = (_tensor(rng, N, C * g, kind) * 0.05).astype(np.float32)
     exp = ref.split_weights(W, C, g, s)
     B.ocs_tune("sel_inline", sel_inline)
     try:
@@ -551,9 +558,9 @@ def test_per_batch_grid_of_small_tensors(M, K, where):
                                      (9, 512, 9, 26), (2100, 512, 1, 26), (4100, 1030, 1, 5)])
 @pytest.mark.parametrize("clip", [1.0, 0.7])
 def test_split_act_per_batch_grid_one_shot(M, C, g, s, clip):
-    """The per-batch grid as large tensors take it: max|X| as one value per workgroup, folded into one
-    word by a launch of its own, then the split+quantize pass in its one-shot form with the clip ratio
-    times that word as its threshold.  Twice in a row on the same scratch space, the second tensor
+    """The per-batch grid with the maxima of the max|X| pass folded by a launch of their own (strided tensors and the
+    narrowest rows from 160 MB on; forced here), then the split+quantize pass in its one-shot form with the clip ratio
+    times that one word as its threshold.  Twice in a row on the same scratch space, the second tensor
     with a smaller maximum (anything left over from the first call would show)."""
     rng = np.random.default_rng(M + 3 * C + g + s)
     sel = ref.split_weights(_tensor(rng, 9, C * g, "heavy"), C, g, s)
@@ -651,13 +658,15 @@ def test_split_act_static_grid_random_shapes(seed):
     assert np.array_equal(q, q_ref)
 
 
-@pytest.mark.parametrize("act_dep", [0, 1])
-def test_split_act_deep_halvings(act_dep):
+@pytest.mark.parametrize("g", [3, 1])
+@pytest.mark.parametrize("act_dep", [0, 1, -1])
+def test_split_act_deep_halvings(act_dep, g):
     """Eq. 4 with depth lists no greedy run would produce (the call takes any list): factors down to
-    2^-126, the denormal 2^-127 .. 2^-149, and zero beyond, on values up to 2^125.  The per-column depth table (one byte per column, 255 standing for anything
-    larger) and the look-up in global memory agree with the oracle."""
+    2^-126, the denormal 2^-127 .. 2^-149, and zero beyond, on values up to 2^125.  The one-shot pass (-1, what such a
+    call takes by default), the flat pass with its per-column depth table (one byte per column, 255 standing for anything
+    larger) and with the look-up in global memory agree with the oracle."""
     rng = np.random.default_rng(31)
-    M, C, g, s = 40, 12, 3, 4
+    M, C, s = 40, 12, 4
     chan_src = np.array(list(range(C)) + [2, 5, 7, 11], dtype=np.int32)
     chan_depth = np.array([0, 1, 50, 100, 126, 127, 130, 140, 150, 200, 255, 300, 50, 127, 140, 300], dtype=np.int32)
     X = _tensor(rng, M, C * g, "normal")
@@ -720,7 +729,9 @@ def test_split_weights_halvings_that_leave_the_normal_range():
 
 # ---- ocs_qgemm -------------------------------------------------------------------------------
 
-GEMM_TILES = [6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23, 24, 25]     # every tile variant of the library
+# The ring and whole-K tiles.  (26 to 29, with K dealt over the waves: test_qgemm_k_over_the_waves; 30 to 32, convolutions
+# with the taps from LDS: test_qconv_taps_from_lds.)
+GEMM_TILES = [6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23, 24, 25]
 
 
 @pytest.mark.parametrize("tile", [-1] + GEMM_TILES)
@@ -1006,6 +1017,67 @@ def test_qconv_routes_by_tiles_and_pieces(Bn, H, W, Cn, N, k, s):
     B.ocs_qconv_requant(dev(got["Aq"]), got["ldc"], Bn, H, W, Cn + s, k, k, 1, k // 2, dev(got["Wt"]), N, 8, 6, dev(got["sx"]),
                         dev(got["sw"]), True, thr, 5, dev(cs), 3, Yq, ldy, sc)
     assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
+
+
+@pytest.mark.parametrize("Cn,s", [(330, 9), (390, 5)])      # pixels of 352 and 400 bytes: the 128-byte K-steps pass their end
+@pytest.mark.parametrize("H,W,N", [(60, 100, 100), (85, 200, 40), (100, 100, 200), (85, 200, 200)])
+def test_qconv_1x1_on_the_ring_with_any_pitch(H, W, N, Cn, s):
+    """1x1 layers on pixels that are not whole K-steps, more of them than the sliced tiles take (256 compute units): the
+    64 x 64, 128 x 64, 128 x 128 and 256 x 128 ring tiles that check every request, fp32 and codes out; the last
+    pixels are followed by other bytes than zeros."""
+    rng = np.random.default_rng(H + W + N + Cn)
+    A = _tensor(rng, H * W, Cn, "normal").reshape(1, H, W, Cn)
+    Wm = _tensor(rng, N, Cn, "normal")
+    exp = _conv_reference(A, Wm, Cn, 1, 1, 1, 0, s, 8, 6, None)
+    got = gpu_conv_layer(A, Wm, Cn, 1, 1, 1, 0, s, bits_x=8, bits_w=6)
+    assert got["ldc"] % 64 != 0
+    assert np.array_equal(got["acc"], exp["acc"])
+    assert_y_close(got["Y"], exp["Y"])
+    T = float(np.float32(0.5 * np.abs(exp["Y"]).max()))
+    cs = _next_layer_list(rng, N, 3)
+    ldy = B.ocs_padded_channels(N + 3)
+    q_ref, sc_ref = ref.requantize(exp["acc"], exp["sx"][1], exp["sw"][1], T, 5, cs, 3, relu=True, ldq=ldy)
+    padded = torch.full((H * W + 64, got["ldc"]), 77, dtype=torch.int8, device="cuda")
+    padded[:H * W] = dev(got["Aq"])
+    Yq = torch.full((H * W, ldy), 77, dtype=torch.int8, device="cuda")
+    sc = torch.zeros(2, dtype=torch.float32, device="cuda")
+    thr = torch.tensor([T], dtype=torch.float32, device="cuda")
+    B.ocs_qconv_requant(padded, got["ldc"], 1, H, W, Cn + s, 1, 1, 1, 0, dev(got["Wt"]), N, 8, 6, dev(got["sx"]),
+                        dev(got["sw"]), True, thr, 5, dev(cs), 3, Yq, ldy, sc)
+    assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (4096, 1024, 1030), (4097, 1024, 1030),       # 256 / 264 tiles of 128 x 128: the small tile / the middle one
+    (8192, 1024, 1030), (8193, 1024, 1030),       # 256 / 264 tiles of 256 x 128: the middle tile / the large one
+    (4097, 1024, 4100), (4097, 500, 4100),        # the middle tile lying down (512 outputs and more, a very long K)
+    (1024, 1030, 1030), (16500, 129, 1000)])      # 64 x 64 tiles just beyond one per compute unit; K below 1024
+def test_qgemm_tile_by_rounds_of_the_chip(M, N, K):
+    """The default tile on either side of the sizes at which it changes (256 compute units): accumulators and outputs those
+    of a fixed tile, whose first, last and a few rows between are the oracle's."""
+    gen = torch.Generator(device="cuda").manual_seed(M + N + K)
+    ld = B.ocs_padded_cols(K)
+    Xq = torch.zeros((M, ld), dtype=torch.int8, device="cuda")
+    Wq = torch.zeros((N, ld), dtype=torch.int8, device="cuda")
+    Xq[:, :K] = torch.randint(-127, 128, (M, K), generator=gen, device="cuda", dtype=torch.int8)
+    Wq[:, :K] = torch.randint(-127, 128, (N, K), generator=gen, device="cuda", dtype=torch.int8)
+    sx = torch.tensor([3.0, 3.0 / 127], dtype=torch.float32, device="cuda")
+    sw = torch.tensor([0.7, 0.7 / 127], dtype=torch.float32, device="cuda")
+    out = []
+    for tile in (-1, 6):
+        acc = torch.full((M, N), -7, dtype=torch.int32, device="cuda")
+        Y = torch.full((M, N), -7.0, dtype=torch.float32, device="cuda")
+        B.ocs_tune("gemm_tile", tile)
+        try:
+            B.ocs_qgemm(Xq, ld, Wq, ld, M, N, K, 8, 8, sx, sw, acc, N, Y, N)
+        finally:
+            B.ocs_tune("gemm_tile", -1)
+        out.append((acc, Y))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    rows = [0, 1, M // 3, M // 2, M - 2, M - 1]
+    acc_ref, y_ref = ref.qgemm(host(Xq[rows]), host(Wq), K, host(sx)[1], host(sw)[1])
+    assert np.array_equal(host(out[0][0][rows]), acc_ref)
+    assert_y_close(host(out[0][1][rows]), y_ref)
 
 
 def test_qconv_equals_the_lowered_gemm_path():

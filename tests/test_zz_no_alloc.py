@@ -52,8 +52,8 @@ def test_static_scratch_matches_workspace_call_twice_in_a_row():
 
 
 def test_static_scratch_with_the_maxima_folded_by_a_launch_of_their_own():
-    """The per-batch grid as tensors from 160 MB on take it (the maxima of the max|X| pass folded into
-    one word of the scratch space, the one-shot pass behind it), forced here on small tensors: same
+    """The per-batch grid as strided tensors and the narrowest rows take it from 160 MB on (the maxima of the max|X| pass
+    folded into one word of the scratch space by a launch of their own), forced here on small tensors: same
     bits from both entry points and from the oracle, twice in a row, the second input smaller."""
     G.require_gpu()
     B.ocs_tune("max_flat", 2)
