@@ -488,12 +488,14 @@ int ocs_calib_mfma(const void *operands, int iters, int workgroups, void *sink, 
 /*
  * Launch-shape overrides for benchmarking (no passage of the paper; results never depend
  * on them).  Keys: "act_grid", "act_nt", "act_un", "act_map", "act_wide", "act_dep", "act_tile",
- * "act_np" (the split+quantize pass; act_tile: the tile-ordered variant never (0) / wherever it
- * fits (1); act_np: the one-shot variant never (0) / with 1..8 loads per lane wherever that many
- * hold a row (1..8) / wherever it serves the shape (9); default: by shape), "max_flat", "max_grid",
- * "max_un", "max_bt" (the whole-tensor max|x|
- * pass; max_flat 2: the flat pass, and ocs_split_act folds its maxima in a launch of its own whatever the tensor's size), "sel_inline" (most splits for which ocs_split_weights runs the selection inside its
- * code pass instead of as a launch of its own; 0: never), "gemm_tile" (tile variant of
+ * "act_np" (the split+quantize pass; act_tile, on a given threshold with un-scaled copies: the tile-ordered
+ * variant never (0) / wherever it fits (1); act_np: the one-shot variant never (0) / with 1..8 loads per lane
+ * wherever that many hold a row (1..8) / wherever it serves the shape (9); act_grid, act_un, act_map, act_wide and
+ * act_dep shape the flat variants and, with scaled copies or a per-batch grid, ask for them; default: by shape),
+ * "max_flat", "max_grid", "max_un", "max_bt" (the whole-tensor max|x| pass; max_flat 2: the flat pass, and
+ * ocs_split_act folds its maxima in a launch of its own whatever the tensor's size), "sel_inline" (most splits for
+ * which ocs_split_weights runs the selection inside its code pass, where the list is short enough, instead of as a
+ * launch of its own; 0: never), "gemm_tile" (tile variant of
  * ocs_qgemm / ocs_qconv: 6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23 to 29, for ocs_qconv 30 to 32; an id a shape cannot use falls
  * back to one it can), "fused_variant" (ocs_split_act_qgemm with more than 128 output columns:
  * 1 = 64-row workgroups, 2 = 128-row ones), "fused_stride" (rows between that kernel's workgroups: 0 = a

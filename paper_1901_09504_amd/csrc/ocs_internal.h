@@ -274,18 +274,19 @@ struct Tuning {
     int act_map = -1;   // lanes of that pass dealt over the output (0), over the input (1), by row shape (-1)
     int act_un = -1;    // items in flight per lane in that pass (1, 2 or 4)
     int act_wide = 0;   // force the 64-bit index variant of that pass (tests: tensors of 2^32 dwords do not fit a test)
-    int act_dep = -1;   // Eq. 4 pass: per-column depths from a table in LDS (1), from global memory (0), by tensor size (-1)
+    int act_dep = -1;   // Eq. 4 through the flat passes: per-column depths from a table in LDS (1), from global memory (0); by shape (-1)
     int act_nt = 0;     // non-temporal loads of X in that pass (off: appended columns re-read X through L2)
-    int act_np = -1;    // static grid, un-scaled copies: the loop-free flat pass with this many pieces per XCD run (> 0), never (0), by shape (-1)
-    int act_tile = -1;  // static grid, un-scaled copies: tile-ordered pass always (1), never (0), by shape (-1)
+    int act_np = -1;    // one-shot pass: with this many loads per lane (1 .. 8), wherever it serves (9), never (0), by shape (-1)
+    int act_tile = -1;  // given threshold, un-scaled copies: tile-ordered pass wherever it fits (1), never (0), by shape (-1)
     int gemm_tile = -1;
     int fused_stride = -1;   // rows between the one-launch kernel's workgroups: forced (> 0), a whole tile always (0), by shape (-1)
     int fused_variant = -1;  // workgroup shape / pipeline depth of the split+quantize+GEMM launch (default: by shape)
-    int max_flat = -1;  // whole-tensor max|x| of a contiguous tensor as one flat stream (1), by columns (0), default (-1)
+    int max_flat = -1;  // whole-tensor max|x| of a contiguous tensor as one flat stream (1), by columns (0), default (-1);
+                        // 2: flat, and a per-batch grid's maxima always folded by a launch of their own
     int max_grid = -1;  // workgroups of the flat pass
     int max_un = -1;    // 16-byte loads in flight per lane in the flat pass (1, 2 or 4)
     int max_bt = -1;    // threads per workgroup of the flat pass (256 or 1024)
-    int sel_inline = -1; // most splits for which the weight pass runs the selection itself (0: never; default 64)
+    int sel_inline = -1; // most splits for which the weight pass runs the selection itself where its list allows it (0: never; default 64)
 };
 Tuning& tuning();
 

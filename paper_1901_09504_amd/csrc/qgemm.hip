@@ -1498,7 +1498,9 @@ static int64_t wholek_lds_bytes(int64_t N, int64_t Kpad, const Requant& rq, int*
     // Three of the 128 x 128 workgroups per compute unit, not four, and two where one tile holds a row of the
     // output: the store streams of more cost more than they hide (inside the pass, behind the launch that
     // wrote the codes: 802816 x 256 from 64 channels 189 us with three, 191 with four, 196 with two; 300000 x
-    // 100 from 64 channels 54 with two, 58 with three, 60 with four).
+    // 100 from 64 channels 54 with two, 58 with three, 60 with four; the GEMM alone, this floor against none:
+    // 400000 x 200 x 68 109.9 / 114 us, 802816 x 256 x 68 133.2 / 135.2, 300000 x 128 x 68 29.1 / 29.5 and 300000 x 70 x 68
+    // 39.9 / 39.6, 128 x 135 31.5 / 31.7, 128 x 269 52.8 / 52.6, 100000 x 256 x 269 level).
     const int64_t floor = N <= 128 ? 54 * 1024 : 41 * 1024;
     if (BM == 128 && BN == 128 && lds < floor) lds = floor;
     int off = 0;
@@ -1945,7 +1947,7 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
     // on both operands (the producers' contract) and the walk may include them.
     const int64_t K128 = round_up(Kpad, 128);
     const bool k128 = K128 == Kpad || (ldx >= K128 && ldw >= K128);
-    // Tile variants by id (the dispatcher above picks 7, 9, 11, 12, 16, 17, 19 or 23 to 29; the others
+    // Tile variants by id (the dispatcher above picks 7, 9, 11, 12, 16, 17, 19 or 23 to 29, a convolution 30 to 32 as well; the others
     // are kept selectable because the parity tests run every kernel family through them).
     switch (tile) {
         case 6: return run_dma<128, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);

@@ -82,12 +82,13 @@ __device__ __forceinline__ f32x4 load4(const f32x4u* p) {
     return *p;
 }
 
+// The flat pass, for what neither the one-shot nor the tile-ordered form below takes.
 // One lane per packed output dword, the whole output walked as ONE flat range with a grid
 // stride: lane i of the grid produces dwords i, i + G, i + 2G, ...  Consecutive lanes read
-// consecutive 16-byte groups of X and write consecutive dwords of Xq, and at any moment the
-// whole chip works inside one compact window that slides over X front to back, which is the
-// access pattern HBM serves fastest (measured against row-per-wave and row-per-workgroup
-// layouts with LDS staging of the appended columns; those were 10-15 % slower).
+// consecutive 16-byte groups of X and write consecutive dwords of Xq, and the whole chip works
+// inside one window that slides over X front to back (measured against row-per-wave and
+// row-per-workgroup layouts of persistent workgroups with LDS staging of the appended columns; those
+// were 10-15 % slower.  The one-shot form keeps that window tighter).
 //   d <  main_units: the dword's four inputs are the contiguous X[r, 4d .. 4d+3], one 16-byte
 //                    load at whatever alignment the row has (main_units = K / 4);
 //   d >= main_units: leftover columns, appended channels (their source values were fetched
@@ -282,9 +283,10 @@ __global__ __launch_bounds__(kThreads) void expand_quantize_kernel(
 //   through the caches; all others are the code just written.
 //   The threshold: a given device float; or, for a per-batch grid, clip times the largest of the
 //   per-workgroup maxima that the pass before left behind, folded here behind the requests for X
-//   (a launch of its own for that costs 3 us and more at any size: 12544 x 512 x 9, both passes 89.9 -> 86.9 us;
-//   200704 x 64 against the flat pass that folded them 24.1 -> 22.6); or clip times the largest
-//   magnitude of a small contiguous X that every workgroup reads through for itself (kSelfMax).
+//   (up to 256 of them, one per lane: 12544 x 512 x 9, both passes, 89.9 us with a launch that folds them, 86.9 so;
+//   200704 x 64 against the flat pass that folded them 24.1 -> 22.6; where they are more, or the workgroups very
+//   short, per_batch_one_shot() and the caller decide); or clip times the one word such a launch left; or clip times
+//   the largest magnitude of a small contiguous X that every workgroup reads through for itself (kSelfMax).
 // ---------------------------------------------------------------------------------------------
 constexpr int kShotNT = 256;
 constexpr int kShotTabPer = 2;                       // table entries per lane
@@ -511,7 +513,8 @@ static ShotPlan shot_plan(int64_t M, int64_t K, int64_t ldq, int force_u = 0, bo
         R = 512 / Qc;
         if (R * Qc < 448) R = 768 / Qc;
         if (R < 1) R = 1;
-        // scaled, single rows that leave a quarter of the third load's lanes idle with their look-ups: two
+        // scaled, single rows that leave most of the third load's lanes idle: two (12544 x 2304 27.7 against 29.5 us,
+        // 12544 x 256 x 9 26.0 against 29.6, 20000 x 2100 38.0 against 40.4; 2500 x 2304 level)
         if (scaled && R == 1 && Qc > 512 && Qc <= 640) R = 2;
         const int64_t loads = per_batch ? per_batch_loads(M, K) : 0;
         if (kShotNT * loads >= Qc) R = kShotNT * loads / Qc;
@@ -959,9 +962,11 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     const int64_t total = M * D;
     const bool nt = tuning().act_nt != 0;
     const bool halve = chan_depth != nullptr;
-    // Eq. 4: the per-column depth table in LDS, one byte per column of the unexpanded row, when a
-    // lane has enough items for the table's set-up to pay (weights, with one or two items per lane,
-    // were 0.6-2.3 us slower with it; cfg 2's activations, with 14, are 5 us faster)
+    // Eq. 4 on what the one-shot form leaves to the flat passes (rows of more than 8192 values, more than 512
+    // appended and padded columns): the per-column depth table in LDS, one byte per column of the unexpanded row,
+    // when a lane has enough items for the table's set-up to pay (2000 x 1200 x 9, 11 items a lane, 35.5
+    // against 32.6 us; 8000 x 1200 x 9 102 against 117, 12544 x 512 x 9 with 103 splits 79 against 85; behind by 4 % where
+    // half the columns and more are copies: 400000 x 64 x 9 with 64 splits 402 against 385)
     const bool dep_pays = tuning().act_dep < 0 ? M * (ldq / 4) >= (int64_t)8 * 2048 * kThreads : tuning().act_dep != 0;
     const int dep_table = halve && !stepwise && K <= kDepthTableMax && dep_pays ? 1 : 0;
     const unsigned dep_lds = dep_table ? (unsigned)round_up(K, 16) : 0;

@@ -13,8 +13,8 @@
 namespace ocs {
 
 // What bounds it: the latency of one workgroup's passes over LDS, its barriers and one trip to memory.
-// 3000 channels, 150 splits: 78 -> 11 us against one split per step (0.2 us a step on one wave, 0.5 us on
-// four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
+// 3000 channels, 150 splits: 78 -> 11 us with the column maxima in the caches, 14 without, against one split per
+// step (0.2 us a step on one wave, 0.5 us on four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
 // taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
 template <int NT, bool FEW>
 __global__ __launch_bounds__(NT) void select_kernel(
