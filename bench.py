@@ -43,13 +43,13 @@ STATIC_T = 5.0               # the static activation grid's range (inputs are |N
 # reads for the plain copy kernel of known size that runs after the timed region
 # (profiles/bench_config5_headline.md).  Valid only for the kernel source it was measured on:
 # reported as null once that file changes.
-X2_TRAFFIC = {"quantize_hip_sha256": "af4bb4e0e029d50a5d0fd005ad943fb80f02f0f7054c896d3ab774679a02eb2c",
-              "bytes_per_step": 28940640069}
+X2_TRAFFIC = {"quantize_hip_sha256": "fb9c9efb91a71a63426f23713b7ed1e63a75329940caa2d814f41db189d5eea5",
+              "bytes_per_step": 28942891898}
 
 
 # The same for the launches of the one-launch pass (`--extras fused`), keyed on the GEMM source.
-FUSED_TRAFFIC = {"qgemm_hip_sha256": "e877844785df958f9fab9f298e8557ced25473f8f65d32942d078a62d6984872",
-                 "bytes_per_step": 22973502667}
+FUSED_TRAFFIC = {"qgemm_hip_sha256": "86a33c94d20e3307a07edeabc6e8a2e2d47760fd90fb8af64bb410783945fc58",
+                 "bytes_per_step": 22973719517}
 
 
 def fused_traffic():

@@ -941,8 +941,9 @@ __global__ __launch_bounds__(NW * 64) void qgemm_slice_kernel(
 // 16-byte pieces as in the tap-major weights, which pass through a ring of 128-byte K-steps (one
 // barrier each); a pixel takes an odd number of pieces in LDS, so that consecutive pixels start in
 // different banks.
-// What bounds it: latency (fill, epilogue) and the address arithmetic of a slice, about as many vector
-// instructions as its products take cycles; several workgroups per compute unit hide one another's.
+// What bounds it (32 x 56 x 56 x 64 -> 64 with codes out, 16.8 us): 33 vector instructions per matrix instruction, the
+// addresses of the taps and the epilogue, fill 61 % of the busy compute units' cycles, the matrix cores 15 %, waits
+// 23 % of the waves'; several workgroups per compute unit hide one another's fill and epilogue.
 // ---------------------------------------------------------------------------------------------
 constexpr int kPatchMaxTaps = 25;
 
