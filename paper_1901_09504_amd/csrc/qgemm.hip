@@ -251,6 +251,10 @@ __device__ __forceinline__ void emit_tile(const i32x16 (&acc)[TM][TN], int32_t* 
             }
         } else {
             constexpr int Q = 4 * SROWS / 32;      // accumulator quads of a lane per staged block
+            // (one address and constant offsets; with the lane's part inside the index the compiler formed eight addresses by
+            // OR and half of the writes came singly: 1x1 1024 -> 256 at 25088 rows, both launches, 40.35 us so, 40.30 now,
+            // convolutions of 28 x 28 and 16 channels up to 4 %)
+            int32_t* at = stage + (lane >> 5) * 4 * WN + (lane & 31);
 #pragma unroll
             for (int q0 = 0; q0 < 4; q0 += Q) {
 #pragma unroll
@@ -259,7 +263,7 @@ __device__ __forceinline__ void emit_tile(const i32x16 (&acc)[TM][TN], int32_t* 
                     for (int q = 0; q < Q; ++q)
 #pragma unroll
                         for (int e = 0; e < 4; ++e)
-                            stage[(q * 8 + (lane >> 5) * 4 + e) * WN + j * 32 + (lane & 31)] = acc[i][j][(q0 + q) * 4 + e];
+                            at[(q * 8 + e) * WN + j * 32] = acc[i][j][(q0 + q) * 4 + e];
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 emit_staged_rows<SROWS, WN>(stage, lane, rbase + i * 32 + q0 * 8, cbase, wcol, M, N, scale, Y, ldy, acc_out,
