@@ -629,11 +629,12 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     const float inv = RQ ? requant_inv(rq, (SPLIT ? tile == 0 : blockIdx.x == 0) && threadIdx.x == 0) : 0.0f;
     const int dup_n = RQ && rq.s_next > 0 ? (dup_count < kDupCap ? dup_count : kDupCap) : 0;
     // Whole tiles without bounds, but for the 128 x 128 tile with 64-byte steps (1024 outputs and more), whose waves then run their
-    // stores ahead of each other: ahead up to 384 bytes of K (50176 x 1024 x 330 50.7 against 54.0 us, 100000 x 1024 x 330 90 against
-    // 97), behind at 448 and 512 (8192 x 2048 x 400 20.3 against 19.4, 50176 x 1024 x 450 56.7 against 55.4) and, for 2048 outputs
-    // and more, from there on (8192 x 8192 x 600 99 against 94; 100000 x 1024 x 800 189 against 206 the other way).
+    // stores ahead of each other.  With bounds / without, us: up to 384 bytes of K ahead without (50176 x 1024 x 330 54.0 / 50.7);
+    // longer, behind (8192 x 8192 x 538 89.6 / 93.4, 50176 x 1024 x 538 60.3 / 61.9, 16384 x 8192 x 900 251 / 262) until the codes
+    // of X are some 56 MB (100000 x 1024 x 538, 58 MB, 117.6 / 118.9, by 2048 229 / 224; x 660 194 / 181; 70000 x 1024 x 900 151 /
+    // 142, x 660 95.9 / 97.6).
     constexpr bool HELD = !CONV && !MASK && BM == 128 && BN == 128 && BK == 64;
-    const bool whole = row0 + BM <= M && col0 + BN <= N && (!HELD || ksteps_all <= 6 || (ksteps_all >= 9 && N < 2048));
+    const bool whole = row0 + BM <= M && col0 + BN <= N && (!HELD || ksteps_all <= 6 || (int64_t)M * ksteps_all >= 900000);
     emit_tile<RQ, TM, TN, 32>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
                       inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0, whole);
 }

@@ -1047,6 +1047,32 @@ def test_qconv_1x1_on_the_ring_with_any_pitch(H, W, N, Cn, s):
     assert np.array_equal(host(Yq), q_ref) and np.array_equal(host(sc), sc_ref)
 
 
+def test_qgemm_stores_of_the_128_ring_tile_on_a_tall_operand():
+    """... and 8 steps on codes of X beyond 56 MB, where the stores go without bounds again: against the oracle on the
+    first, last and some rows, and against a tile without the rule everywhere."""
+    M, N, K = 112513, 130, 449
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    ld = B.ocs_padded_cols(K)
+    Xq = torch.zeros((M, ld), dtype=torch.int8, device="cuda")
+    Wq = torch.zeros((N, ld), dtype=torch.int8, device="cuda")
+    Xq[:, :K] = torch.randint(-127, 128, (M, K), generator=gen, device="cuda", dtype=torch.int8)
+    Wq[:, :K] = torch.randint(-127, 128, (N, K), generator=gen, device="cuda", dtype=torch.int8)
+    one = torch.tensor([3.0, 3.0 / 127], dtype=torch.float32, device="cuda")
+    out = []
+    for tile in (9, 6):
+        Y = torch.full((M, N + 2), -7.0, dtype=torch.float32, device="cuda")
+        B.ocs_tune("gemm_tile", tile)
+        try:
+            B.ocs_qgemm(Xq, ld, Wq, ld, M, N, K, 8, 8, one, one, None, 0, Y, N + 2)
+        finally:
+            B.ocs_tune("gemm_tile", -1)
+        out.append(Y)
+    assert torch.equal(out[0], out[1]) and torch.all(out[0][:, N:] == -7.0)
+    rows = [0, 127, 128, M // 2, M - 2, M - 1]
+    _, y_ref = ref.qgemm(host(Xq[rows]), host(Wq), K, host(one)[1], host(one)[1])
+    assert_y_close(host(out[0][rows, :N].contiguous()), y_ref)
+
+
 @pytest.mark.parametrize("M,N,K", [
     (4096, 1024, 1030), (4097, 1024, 1030),       # 256 / 264 tiles of 128 x 128: the small tile / the middle one
     (8192, 1024, 1030), (8193, 1024, 1030),       # 256 / 264 tiles of 256 x 128: the middle tile / the large one
