@@ -325,8 +325,9 @@ __device__ __align__(16) int8_t zero_chunk[16] = {};   // (not declared const: i
 
 // MASK: the pitches may end inside the last K-step (see zero_chunk); every request then checks
 // its piece against the pitch.
+// BOUNDED: stores with bounds whatever the tile, in an instance of its own (see run_dma).
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NBUF, bool RQ = false, bool CONV = false,
-          bool SPLIT = false, bool MASK = false>
+          bool SPLIT = false, bool MASK = false, bool BOUNDED = false>
 __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     const int8_t* __restrict__ Xq, int64_t ldx, const int8_t* __restrict__ Wq, int64_t ldw, int M,
     int N, int ksteps_all, const float* __restrict__ scale_x, const float* __restrict__ scale_w,
@@ -634,7 +635,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qgemm_dma_kernel(
     // of X are some 56 MB (100000 x 1024 x 538, 58 MB, 117.6 / 118.9, by 2048 229 / 224; x 660 194 / 181; 70000 x 1024 x 900 151 /
     // 142, x 660 95.9 / 97.6).
     constexpr bool HELD = !CONV && !MASK && BM == 128 && BN == 128 && BK == 64;
-    const bool whole = row0 + BM <= M && col0 + BN <= N && (!HELD || ksteps_all <= 6 || (int64_t)M * ksteps_all >= 900000);
+    const bool whole = !BOUNDED && row0 + BM <= M && col0 + BN <= N && (!HELD || ksteps_all <= 6 || (int64_t)M * ksteps_all >= 900000);
     emit_tile<RQ, TM, TN, 32>(acc, stage, lane, row0 + wm * WM, col0 + wn * WN, wn * WN, M, N, scale, Y, ldy, acc_out, ldacc, rq,
                       inv, dup_list, dup_n, RQ && bn == tiles_n - 1 && wn == 0, whole);
 }
@@ -1600,8 +1601,13 @@ static hipError_t run_dma(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64
     const int64_t tiles_m = ceil_div(M, BM), tiles_n = ceil_div(N, BN);
     const int64_t total = tiles_m * tiles_n;
     if (total > 0x7FFFFFFF) return hipErrorInvalidValue;   // one workgroup per tile: grid.x
-    const auto kernel = rq.Yq != nullptr ? qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, true, false, false, MASK>
-                                         : qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, false, MASK>;
+    // A single round of 256 x 128 tiles gains nothing from stores without bounds and pays for the code of both forms
+    // (1x1 1024 -> 256 at 25088 rows, both launches, 40.17 against 40.30 us, LSTM gates at 700 rows 29.06 against 29.25); in
+    // several rounds they hide behind the next tile (100000 x 512 x 500 65.3 with, 63.6 without, 40000 x 256 x 1500 32.6 / 31.2).
+    constexpr bool BOTH = BM == 256 && BN == 128 && BK == 128 && !MASK;
+    const auto plain = BOTH && total <= compute_units() ? qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, false, MASK, BOTH>
+                                                        : qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, false, false, false, MASK>;
+    const auto kernel = rq.Yq != nullptr ? qgemm_dma_kernel<BM, BN, WAVES_M, WAVES_N, BK, NBUF, true, false, false, MASK> : plain;
     return launch_kernel(kTimeGemm, kernel,
                          dim3((unsigned)total), dim3(WAVES_M * WAVES_N * 64), 0, stream, Xq, ldx, Wq, ldw, (int)M,
                          (int)N, (int)(Kpad / BK), scale_x, scale_w, acc_out, ldacc, Y, ldy,

@@ -1077,7 +1077,8 @@ def test_qgemm_stores_of_the_128_ring_tile_on_a_tall_operand():
     (4096, 1024, 1030), (4097, 1024, 1030),       # 256 / 264 tiles of 128 x 128: the small tile / the middle one
     (8192, 1024, 1030), (8193, 1024, 1030),       # 256 / 264 tiles of 256 x 128: the middle tile / the large one
     (4097, 1024, 4100), (4097, 500, 4100),        # the middle tile lying down (512 outputs and more, a very long K)
-    (1024, 1030, 1030), (16500, 129, 1000)])      # 64 x 64 tiles just beyond one per compute unit; K below 1024
+    (1024, 1030, 1030), (16500, 129, 1000),       # 64 x 64 tiles just beyond one per compute unit; K below 1024
+    (32768, 256, 700), (32769, 256, 700)])        # 256 / 258 tiles of 256 x 128: stores with bounds / whole tiles without
 def test_qgemm_tile_by_rounds_of_the_chip(M, N, K):
     """The default tile on either side of the sizes at which it changes (256 compute units): accumulators and outputs those
     of a fixed tile, whose first, last and a few rows between are the oracle's."""
