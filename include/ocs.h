@@ -297,6 +297,20 @@ int ocs_qgemm(const int8_t *Xq, int64_t ldx, const int8_t *Wq, int64_t ldw, int6
               size_t ws_bytes, void *stream);
 
 /*
+ * One quantized layer as one call: ocs_split_act (copies un-scaled, as on the activation side of Eq. 3) and ocs_qgemm on
+ * its codes, with the arguments those take.  threshold: device float, or NULL for the batch's own maximum times
+ * clip_ratio (workspace as for ocs_split_act then; it may be NULL with a threshold).  Leaves what the two calls leave:
+ * Xq [M, ldq] with its padding, scale_x_out {T, T / qmax}, Y and, if given, acc_out, bit for bit.  Layers of few output tiles run
+ * as one launch (plus the max|X| pass where it has to be one); where Y, acc_out or Xq share memory with X or the
+ * threshold, and on every other shape, the two launches run.
+ */
+int ocs_forward(const float *X, int64_t M, int C, int g, int64_t ldx, const int32_t *chan_src,
+                int num_splits, int bits_x, const float *threshold, float clip_ratio, int8_t *Xq,
+                int64_t ldq, float *scale_x_out, const int8_t *Wq, int64_t ldw, int64_t N, int bits_w,
+                const float *scale_w, int32_t *acc_out, int64_t ldacc, float *Y, int64_t ldy,
+                void *workspace, size_t ws_bytes, void *stream);
+
+/*
  * ocs_split_act (static grid, copies un-scaled: the activation side of Eq. 3) and ocs_qgemm as ONE
  * launch: the GEMM's loader reads the fp32 rows of X [M, C*g] itself, puts them on the grid of
  * `threshold` (Eq. 1, the arithmetic of ocs_split_act: the codes are the same), and takes the

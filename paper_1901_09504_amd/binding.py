@@ -100,6 +100,9 @@ def lib():
     L.ocs_qgemm_split_k.restype = _i32
     L.ocs_qgemm_split_k.argtypes = [_vp, _i64, _vp, _i64, _i64, _i64, _i64, _i32, _i32, _vp, _vp, _vp, _i64, _vp,
                                     _i64, _i32, _vp, _sz, _vp]
+    L.ocs_forward.restype = _i32
+    L.ocs_forward.argtypes = [_vp, _i64, _i32, _i32, _i64, _vp, _i32, _i32, _vp, _f32, _vp, _i64, _vp, _vp, _i64, _i64,
+                              _i32, _vp, _vp, _i64, _vp, _i64, _vp, _sz, _vp]
     L.ocs_split_act_qgemm_fits.restype = _i32
     L.ocs_split_act_qgemm_fits.argtypes = [_i64, _i32, _i32, _i32, _i64, _i64]
     L.ocs_split_act_qgemm_pays.restype = _i32
@@ -345,6 +348,14 @@ def ocs_qgemm(Xq, ldx, Wq, ldw, M, N, Kexp, bits_x, bits_w, scale_x, scale_w, ac
     _check(lib().ocs_qgemm(_ptr(Xq), ldx, _ptr(Wq), ldw, M, N, Kexp, bits_x, bits_w, _ptr(scale_x),
                            _ptr(scale_w), _ptr(acc_out), ldacc, _ptr(Y), ldy, w, wb,
                            _stream(stream)), "ocs_qgemm")
+
+
+def ocs_forward(X, M, Cn, g, ldx, chan_src, num_splits, bits_x, threshold, clip_ratio, Xq, ldq, scale_x_out, Wq, ldw, N,
+                bits_w, scale_w, acc_out, ldacc, Y, ldy, workspace, stream=None):
+    w, wb = _ws(workspace)
+    _check(lib().ocs_forward(_ptr(X), M, Cn, g, ldx, _ptr(chan_src), num_splits, bits_x, _ptr(threshold), clip_ratio,
+                             _ptr(Xq), ldq, _ptr(scale_x_out), _ptr(Wq), ldw, N, bits_w, _ptr(scale_w), _ptr(acc_out),
+                             ldacc, _ptr(Y), ldy, w, wb, _stream(stream)), "ocs_forward")
 
 
 def ocs_split_act_qgemm_fits(M, C, g, num_splits, N, ldx):

@@ -524,6 +524,63 @@ int ocs_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t ldw, int6
     return OCS_OK;
 }
 
+// Whether [a, a + an) and [b, b + bn) share a byte.
+static bool overlap(const void* a, int64_t an, const void* b, int64_t bn) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return a != nullptr && b != nullptr && x < y + (uint64_t)bn && y < x + (uint64_t)an;
+}
+
+int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int32_t* chan_src, int num_splits, int bits_x,
+                const float* threshold, float clip_ratio, int8_t* Xq, int64_t ldq, float* scale_x_out, const int8_t* Wq,
+                int64_t ldw, int64_t N, int bits_w, const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y,
+                int64_t ldy, void* workspace, size_t ws_bytes, void* stream) {
+    if (!Wq || !scale_w || !Y) return OCS_E_NULL;
+    int rc = check_split_act(X, M, C, g, ldx, chan_src, num_splits, bits_x, threshold, clip_ratio, Xq, ldq, scale_x_out);
+    if (rc) return rc;
+    const int64_t K = (int64_t)C * g, Kexp = (int64_t)(C + num_splits) * g;
+    rc = check_gemm_operands(Xq, ldq, Wq, ldw, M, N, Kexp, bits_x, bits_w, acc_out, ldacc);
+    if (rc) return rc;
+    if (ldy < N) return OCS_E_SHAPE;
+    if (threshold == nullptr) {
+        rc = check_workspace(workspace, ws_bytes, M, K);
+        if (rc) return rc;
+    }
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // One launch reads X while outputs are being written: an output that shares memory with X or with the threshold (a
+    // layer applied to its own output) keeps the two, the first of which has read both before the second begins.
+    const int64_t xb = 4 * ((M - 1) * ldx + K), yb = 4 * ((M - 1) * ldy + N), ab = 4 * ((M - 1) * ldacc + N), qb = M * ldq;
+    const bool apart = !overlap(X, xb, Y, yb) && !overlap(X, xb, acc_out, ab) && !overlap(X, xb, Xq, qb) && !overlap(X, xb, scale_x_out, 8) &&
+                       !overlap(threshold, 4, Y, yb) && !overlap(threshold, 4, acc_out, ab) && !overlap(threshold, 4, Xq, qb) &&
+                       !overlap(threshold, 4, scale_x_out, 8);
+    const Tuning& tn = tuning();
+    const bool tuned = tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0;   // (launch shapes of the two)
+    if (apart && !tuned && slice_layer_pays(M, C, g, num_splits, N, ldx)) {
+        const float* thr = threshold;
+        int n = 0;
+        int64_t self = 0;
+        hipError_t e = hipSuccess;
+        if (threshold == nullptr) {
+            Workspace w = plan_workspace(M, K);
+            float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
+            if (act_self_max_serves(M, C, g, num_splits, ldx, ldq, chan_src)) {
+                self = M * K;
+            } else {
+                e = launch_absmax_partials(X, M, K, ldx, partial, &n, st);
+                if (e != hipSuccess) return hip_fail(e);
+                thr = partial;
+            }
+        }
+        e = launch_slice_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, self, clip_ratio, qmax_of(bits_x), Xq, ldq,
+                               scale_x_out, Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
+        return e == hipSuccess ? OCS_OK : hip_fail(e);
+    }
+    rc = ocs_split_act(X, M, C, g, ldx, chan_src, nullptr, num_splits, bits_x, threshold, clip_ratio, Xq, ldq, scale_x_out,
+                       workspace, ws_bytes, stream);
+    if (rc) return rc;
+    return ocs_qgemm(Xq, ldq, Wq, ldw, M, N, Kexp, bits_x, bits_w, scale_x_out, scale_w, acc_out, ldacc, Y, ldy, nullptr, 0,
+                     stream);
+}
+
 int ocs_split_act_qgemm_fits(int64_t M, int C, int g, int num_splits, int64_t N, int64_t ldx) {
     if (M <= 0 || C <= 0 || g <= 0 || num_splits < 0 || N <= 0) return 0;
     if ((int64_t)C * g > (int64_t)1 << 30 || (int64_t)C + num_splits > OCS_MAX_EXPANDED_CHANNELS) return 0;
@@ -785,6 +842,7 @@ int ocs_tune(const char* key, int value) {
     else if (!strcmp(key, "gemm_tile")) t.gemm_tile = value;
     else if (!strcmp(key, "fused_variant")) t.fused_variant = value;
     else if (!strcmp(key, "fused_stride")) t.fused_stride = value;
+    else if (!strcmp(key, "slice_layer")) t.slice_layer = value;
     else if (!strcmp(key, "max_flat")) t.max_flat = value;
     else if (!strcmp(key, "max_grid")) t.max_grid = value;
     else if (!strcmp(key, "max_un")) t.max_un = value;

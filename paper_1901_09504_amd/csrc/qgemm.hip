@@ -10,6 +10,7 @@
 // in different banks.  K is padded with zero codes to a multiple of 64 by the producers, so the
 // K loop has no tail; zeros add nothing to an integer sum.
 #include <atomic>
+#include <type_traits>
 
 #include "ocs_internal.h"
 
@@ -937,6 +938,316 @@ __global__ __launch_bounds__(NW * 64) void qgemm_slice_kernel(
 }
 
 // ---------------------------------------------------------------------------------------------
+// A whole layer of few tiles as one launch: the sliced kernel above with X2 in its loader.  A wave's
+// step of the activations is 64 floats of the tile's rows, requested as 16 bytes per lane (16 lanes
+// share a row's 256 bytes) into registers, NBUF - 1 steps ahead like the weight codes' ring; it is
+// put on the grid with X2's arithmetic (code_bits, pack4), written as dwords into a piece of LDS that
+// only this wave uses, in the layout the matrix cores read, and multiplied.  Appended columns, the
+// columns that do not fill a last step and the padding come through a table of their source columns,
+// built in LDS behind the first requests: such a step gathers its floats one by one (5 % of K at the
+// paper's ratios).  The codes also go to memory as ocs_split_act leaves them, every K-step written by
+// one of the workgroups that share the rows.  A per-batch grid's threshold is folded from the max|X|
+// pass's maxima, or, for small contiguous X, looked for by every workgroup, behind the same requests.
+// Tiles are 32 rows high: the workgroups of a row of tiles each repeat the quantization of its rows, so
+// width is what saves work.
+// What bounds it: the smallest by latency (requests, the gather behind the table, the sum over the
+// waves), the longest by the floats every workgroup draws again (rows x K x 4 bytes a compute unit).
+// Passes one after the other, two launches / one, us: 64 x 256 -> 256 per batch 9.2 / 6.4, 1 x 3000 -> 6000 8.9 / 6.3, 700 x
+// 256 -> 256 8.9 / 6.3, 1000 x 147 -> 64 per batch 11.3 / 8.6; the kernels alone, in a graph, 6.4 / 5.3, 7.1 / 5.6, 5.9 / 4.9,
+// 7.9 / 7.2.  Accumulators, codes, scales and outputs are bit for bit those of the two calls.
+// ---------------------------------------------------------------------------------------------
+struct SliceLayer {
+    const float* X;
+    int64_t ldx;
+    int M, N, K, C, g, Kexp;
+    const int32_t* chan_src;
+    const float* thr;          // n_max == 0 and self == 0: the threshold; else the n_max maxima
+    int n_max;
+    int64_t self;              // values of contiguous X to look through (0: none)
+    float clip, qmax;
+    int8_t* Xq;
+    int64_t ldq;
+    float* scale_x;
+    const int8_t* Wq;
+    int64_t ldw;
+    const float* scale_w;
+    int32_t* acc_out;
+    int64_t ldacc;
+    float* Y;
+    int64_t ldy;
+    int ksteps, kmain;         // K-steps of 64 columns; those that lie inside X's rows
+    int tiles_m, tiles_n, rows_first;
+};
+// LDS of a wave: slots of weight codes and the step's activation codes, then its partial tile
+template <int TN, int SLOTS>
+constexpr int slice_layer_wave_bytes() {
+    const int operands = SLOTS * 32 * TN * 64 + 32 * 64, partial = 32 * 32 * TN * 4;
+    return operands > partial ? operands : partial;
+}
+// A_PER: requests of a step of X, four rows each (the rows above 4 A_PER of a tile are not there).  NBUF: steps in the ring.
+// EARLY: the first step of appended columns has a slot of its own and is requested ahead of the others.
+template <int TN, int A_PER, int NW, int NBUF, bool EARLY>
+__global__ __launch_bounds__(NW * 64) void slice_layer_kernel(SliceLayer p) {
+    constexpr int BM = 32, BN = 32 * TN;
+    constexpr int LPS = BN / 16;                                  // requests of a step of W: 16 rows each
+    constexpr int RING = slice_layer_wave_bytes<TN, NBUF + (EARLY ? 1 : 0)>();
+    constexpr int EW = BM * BN / 256 < NW ? BM * BN / 256 : NW;   // waves that store (see the sliced kernel)
+    constexpr int ROWS = BM / EW;
+    static_assert(EW * ROWS == BM && ROWS * BN % 256 == 0, "whole waves of 16-byte outputs");
+    static_assert((NBUF - 1) * (LPS + A_PER) < 64, "look-ahead exceeds the vmcnt range");
+    static_assert(A_PER >= 1 && A_PER <= 8 && (NBUF == 2 || NBUF == 3), "rows of the tile, ring");
+    extern __shared__ __align__(1024) int8_t slds[];
+    int* tail_col = reinterpret_cast<int*>(slds + NW * RING);     // source column of every column past the whole steps (-1: zero code)
+    const int tail_cols = (p.ksteps - p.kmain) * 64;
+    float* red = reinterpret_cast<float*>(tail_col + tail_cols);  // NW floats
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(3))) int8_t* lptr_t;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lptr_t)&slds[0];
+#else
+    const unsigned lds0 = 0;
+#endif
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const unsigned tile = xcd_remap(blockIdx.x, (unsigned)p.tiles_m * (unsigned)p.tiles_n);
+    const int bm = p.rows_first ? (int)(tile % (unsigned)p.tiles_m) : (int)(tile / (unsigned)p.tiles_n);
+    const int bn = p.rows_first ? (int)(tile / (unsigned)p.tiles_m) : (int)(tile % (unsigned)p.tiles_n);
+    const int row0 = bm * BM, col0 = bn * BN;
+
+    // weight codes: as in the sliced kernel (rows past the edge are never stored; pieces past the pitch are zeros)
+    const int piece = swz<64>(lane >> 2, lane & 3);
+    const int8_t* wsrc[LPS];
+#pragma unroll
+    for (int q = 0; q < LPS; ++q) wsrc[q] = p.Wq + (int64_t)col_clamp(col0 + q * 16 + (lane >> 2), p.N) * p.ldw;
+    const int w_end = (int)(p.ldw / 16);
+    int8_t* ring = slds + wave * RING;
+    int8_t* codes = ring + (RING - BM * 64) / 16 * 16;            // behind the slots
+    const unsigned ring0 = lds0 + (unsigned)wave * RING;
+    // activations: request u of a step is row 4u + lane / 16, columns 4 (lane % 16) .. + 3.  Offsets from the tile's first
+    // row in floats: below 2^29 (the caller's limit on ldx)
+    const float* xb = p.X + (int64_t)row0 * p.ldx;
+    const int c4 = (lane & 15) * 4;
+    unsigned xrow[A_PER];
+#pragma unroll
+    for (int u = 0; u < A_PER; ++u) xrow[u] = (unsigned)(col_clamp(row0 + u * 4 + (lane >> 4), p.M) - row0) * (unsigned)p.ldx;
+    // this wave's steps: those inside X's rows, kt = wave, wave + NW, ... below kmain, then the others
+    const int trips = p.kmain > wave ? (p.kmain - wave + NW - 1) / NW : 0;
+    const int tail0 = trips * NW + wave;
+
+    auto fetch_w = [&](int kt, int slot) {
+        const int q0 = kt * 4 + piece;
+#pragma unroll
+        for (int q = 0; q < LPS; ++q)
+            lds_dma16(q0 < w_end ? wsrc[q] + (int64_t)q0 * 16 : zero_chunk, ring0 + (unsigned)(slot * BN * 64 + q * 1024));
+    };
+    // (surplus requests repeat the wave's last step: no condition around a load, or the compiler waits for those under way.
+    // The weight codes first: requests return in order, so whoever has a step's activations has its weight codes.)
+    auto fetch = [&](int it, int slot, f32x4 (&a)[A_PER]) {
+        const int kt = (it < trips ? it : trips - 1) * NW + wave;
+        fetch_w(kt, slot);
+#pragma unroll
+        for (int u = 0; u < A_PER; ++u) a[u] = *reinterpret_cast<const f32x4u*>(xb + (xrow[u] + (unsigned)(kt * 64 + c4)));
+    };
+
+    f32x4 av[NBUF][A_PER];
+    if (trips > 0) {
+#pragma unroll
+        for (int u = 0; u + 1 < NBUF; ++u) fetch(u, u, av[u]);
+    }
+    if (EARLY && tail0 < p.ksteps) fetch_w(tail0, NBUF);
+    // the table, and the threshold, behind the first requests
+    for (int e = tid; e < tail_cols; e += NW * 64) {
+        const int k = p.kmain * 64 + e;
+        int col = -1;
+        if (k < p.K) col = k;
+        else if (k < p.Kexp) {
+            const int j = k / p.g;
+            col = col_clamp(p.chan_src[j], p.C) * p.g + (k - j * p.g);
+        }
+        tail_col[e] = col;
+    }
+    float T;
+    if (p.n_max == 0 && p.self == 0) {
+        T = *p.thr;
+    } else {
+        float m = 0.0f;
+        for (int i = tid; i < p.n_max; i += NW * 64) m = fmaxf(m, p.thr[i]);
+        const int n4 = (int)(p.self / 4);
+        constexpr int UN = 8;
+        for (int i0 = tid; i0 < n4; i0 += UN * NW * 64) {
+            f32x4 v[UN];
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                const int i = i0 + u * NW * 64;
+                v[u] = reinterpret_cast<const f32x4u*>(p.X)[i < n4 ? i : n4 - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                m = fmaxf(fmaxf(fmaxf(m, fabsf(v[u][0])), fmaxf(fabsf(v[u][1]), fabsf(v[u][2]))), fabsf(v[u][3]));
+        }
+        if ((int64_t)tid < p.self - 4 * (int64_t)n4) m = fmaxf(m, fabsf(p.X[4 * n4 + tid]));
+        const unsigned w = wave_umax32(__float_as_uint(m));
+        if (lane == 0) red[wave] = __uint_as_float(w);
+        T = 0.0f;
+    }
+    __syncthreads();
+    if (p.n_max != 0 || p.self != 0) {
+        float m = red[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) m = fmaxf(m, red[w]);
+        T = p.clip * m;
+    }
+    const float inv = inv_step_of(T, p.qmax);
+    if (blockIdx.x == 0 && tid == 0) {
+        p.scale_x[0] = T;
+        p.scale_x[1] = T / p.qmax;
+    }
+
+    i32x16 acc[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0;
+
+    const int frag_row = lane & 31, frag_half = lane >> 5;
+    int8_t* qrow = p.Xq + (int64_t)row0 * p.ldq;
+    // A step's floats onto the grid, into LDS and, by one of the workgroups that share the rows, to memory.
+    // keep: the bytes that are codes (the others are zero)
+    auto quantize = [&](int kt, const f32x4 (&a)[A_PER], unsigned keep) {
+        unsigned q4[A_PER];
+#pragma unroll
+        for (int q = 0; q < A_PER; ++q) {
+            q4[q] = keep & pack4(code_bits(a[q][0], inv, p.qmax), code_bits(a[q][1], inv, p.qmax),
+                                 code_bits(a[q][2], inv, p.qmax), code_bits(a[q][3], inv, p.qmax));
+            const int r = q * 4 + (lane >> 4);
+            *reinterpret_cast<unsigned*>(codes + r * 64 + swz<64>(r, (lane & 15) >> 2) * 16 + (lane & 3) * 4) = q4[q];
+        }
+        if (kt % p.tiles_n == bn && kt * 64 + c4 < p.ldq) {
+#pragma unroll
+            for (int q = 0; q < A_PER; ++q) {
+                const int r = q * 4 + (lane >> 4);
+                if (row0 + r < p.M) *reinterpret_cast<unsigned*>(qrow + (int64_t)r * p.ldq + kt * 64 + c4) = q4[q];
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    auto multiply = [&](int slot) {
+        const int8_t* base = ring + slot * (BN * 64);
+        i32x4 a[2], b[2][TN];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            a[ks] = *reinterpret_cast<const i32x4*>(&codes[frag_row * 64 + swz<64>(frag_row, ks * 2 + frag_half) * 16]);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int r = j * 32 + frag_row;
+                b[ks][j] = *reinterpret_cast<const i32x4*>(&base[r * 64 + swz<64>(r, ks * 2 + frag_half) * 16]);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        __builtin_amdgcn_wave_barrier();                          // the reads are issued before the next step's writes
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[ks], b[ks][j], acc[j], 0, 0, 0);
+    };
+    auto gather = [&](int kt, f32x4 (&a)[A_PER], unsigned& keep) {
+        const i32x4 cols = *reinterpret_cast<const i32x4*>(&tail_col[(kt - p.kmain) * 64 + c4]);
+        keep = 0xFFFFFFFFu;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (cols[e] < 0) keep &= ~(0xFFu << (8 * e));
+#pragma unroll
+        for (int u = 0; u < A_PER; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[u][e] = xb[xrow[u] + (unsigned)(cols[e] < 0 ? 0 : cols[e])];
+    };
+
+    f32x4 at[A_PER];
+    unsigned keep = 0;
+    if (EARLY && tail0 < p.ksteps) gather(tail0, at, keep);
+    auto step = [&](int it, auto slot) {
+        constexpr int u = decltype(slot)::value, next = (u + NBUF - 1) % NBUF;
+        // the slot requested into was read by the step before: its reads have returned
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));   // lgkmcnt(0)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);                        // (no arithmetic on the step's floats ahead of the requests)
+        fetch(it + NBUF - 1, next, av[next]);
+        wait_vmcnt<(NBUF - 1) * (LPS + A_PER)>();                 // this step's requests are back
+        asm volatile("" ::: "memory");                            // no read of the step above its wait
+        __builtin_amdgcn_sched_barrier(0);
+        quantize(it * NW + wave, av[u], 0xFFFFFFFFu);
+        multiply(u);
+    };
+    // (whole rounds of the ring without a way out, or the compiler's own waits assume the shortest way through)
+    int it0 = 0;
+    for (; it0 + NBUF <= trips; it0 += NBUF) {
+        step(it0, std::integral_constant<int, 0>{});
+        step(it0 + 1, std::integral_constant<int, 1>{});
+        if constexpr (NBUF > 2) step(it0 + 2, std::integral_constant<int, NBUF - 1>{});
+    }
+    if (it0 < trips) {
+        step(it0, std::integral_constant<int, 0>{});
+        if constexpr (NBUF > 2)
+            if (it0 + 1 < trips) step(it0 + 1, std::integral_constant<int, 1>{});
+    }
+    for (int kt = tail0; kt < p.ksteps; kt += NW) {
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));       // lgkmcnt(0): the slot's last reads have returned
+        asm volatile("" ::: "memory");
+        const bool early = EARLY && kt == tail0;
+        if (!early) {
+            wait_vmcnt<0>();                                      // (surplus requests into the slot)
+            fetch_w(kt, NBUF - 1);
+            gather(kt, at, keep);
+        }
+        wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+        quantize(kt, at, keep);
+        multiply(early ? NBUF : NBUF - 1);
+    }
+    wait_vmcnt<0>();                              // surplus requests have landed: the slots take the partial tile
+    // the padding of the code rows past the last K-step
+    if (bn == 0) {
+        const int c0 = p.ksteps * 64, n4 = p.ldq > c0 ? (int)((p.ldq - c0) / 4) : 0;
+        const int rows = p.M - row0 < BM ? p.M - row0 : BM;
+        for (int i = tid; i < rows * n4; i += NW * 64) {
+            const int r = i / n4;
+            *reinterpret_cast<unsigned*>(qrow + (int64_t)r * p.ldq + c0 + 4 * (i - r * n4)) = 0u;
+        }
+    }
+    // every wave puts its partial tile over its own operands, whose reads have returned
+    constexpr int PSTRIDE = RING / 4;
+    int32_t* part = reinterpret_cast<int32_t*>(slds);
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            part[wave * PSTRIDE + ((v >> 2) * 8 + frag_half * 4 + (v & 3)) * BN + j * 32 + frag_row] = acc[j][v];
+    __syncthreads();
+    if (wave >= EW) return;                       // no barrier follows
+
+    int32_t* stage = part + wave * (ROWS * BN);   // this wave's rows of copy 0: the sum goes there
+#pragma unroll
+    for (int o = 0; o < ROWS * BN / 256; ++o) {
+        i32x4 sum = *reinterpret_cast<const i32x4*>(&stage[(o * 64 + lane) * 4]);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) {
+            const i32x4 v = *reinterpret_cast<const i32x4*>(&stage[w * PSTRIDE + (o * 64 + lane) * 4]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += v[e];
+        }
+        *reinterpret_cast<i32x4*>(&stage[(o * 64 + lane) * 4]) = sum;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const float scale = (T / p.qmax) * p.scale_w[1];
+    const bool vec_y = (reinterpret_cast<uintptr_t>(p.Y) % 16 == 0) && (p.ldy % 4 == 0);
+    const bool vec_a = p.acc_out != nullptr && (reinterpret_cast<uintptr_t>(p.acc_out) % 16 == 0) && (p.ldacc % 4 == 0);
+    emit_staged_rows<ROWS, BN>(stage, lane, row0 + wave * ROWS, col0, 0, p.M, p.N, scale, p.Y, p.ldy, p.acc_out, p.ldacc,
+                               vec_y, vec_a, Requant{}, 0.0f, nullptr, 0, false);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Convolution of unit stride whose output has the input's size (kh = 2 pad + 1 = kw, the body of the
 // paper's networks): the lowering as address arithmetic in LDS.  The BM output pixels of a tile are
 // consecutive in the flattened image, so the input pixels that all taps together need are one
@@ -1587,6 +1898,78 @@ static hipError_t run_slice(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int
     return launch_kernel(kTimeGemm, qgemm_slice_kernel<TM, TN, NW, NBUF>, dim3((unsigned)total), dim3(NW * 64), lds,
                          stream, Xq, ldx, Wq, ldw, (int)M, (int)N, (int)(Kpad / 64), scale_x, scale_w, acc_out,
                          ldacc, Y, ldy, (int)tiles_m, (int)tiles_n, N > M ? 1 : 0, rq);
+}
+
+template <int TN, int A_PER, int NW, int NBUF, bool EARLY>
+static hipError_t run_slice_layer(SliceLayer p, hipStream_t stream) {
+    const unsigned lds = (unsigned)(NW * slice_layer_wave_bytes<TN, NBUF + (EARLY ? 1 : 0)>() + (p.ksteps - p.kmain) * 64 * 4 + NW * 4);
+    if (lds > kWholeKMaxLds) return hipErrorInvalidValue;
+    if (lds > 65536) {
+        static std::atomic<bool> opted_in[kMaxDevices];
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+        if (!opted_in[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&slice_layer_kernel<TN, A_PER, NW, NBUF, EARLY>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
+            if (e != hipSuccess) return e;
+            opted_in[dev].store(true, std::memory_order_release);
+        }
+    }
+    p.tiles_m = (int)ceil_div(p.M, 32);
+    p.tiles_n = (int)ceil_div(p.N, 32 * TN);
+    p.rows_first = p.N > p.M ? 1 : 0;
+    return launch_kernel(kTimeGemm, slice_layer_kernel<TN, A_PER, NW, NBUF, EARLY>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(NW * 64),
+                         lds, stream, p);
+}
+
+// Columns of the one-launch layer's tile in units of 32 (0: more tiles than compute units).
+static int slice_layer_tile(int64_t M, int64_t N) {
+    const int64_t cus = compute_units(), tiles_m = ceil_div(M, 32);
+    for (int tn = 1; tn <= 4; tn *= 2)
+        if (tiles_m * ceil_div(N, 32 * tn) <= cus) return tn;
+    return 0;
+}
+constexpr int kSliceLayerTail = 4096;      // columns of the table in LDS (16 KB)
+
+// Up to 32768 values of X per row of tiles: what a workgroup draws again grows with them, what the launch saves does not.
+// Two launches / one, passes one after the other (host time included) and the kernels alone in a graph, us: 1024 values
+// 9.7 / 6.7 and 5.9 / 4.4; 8192 9.6 / 6.5 and 5.7 / 4.8; 16384 9.6 / 6.5 and 5.9 / 5.8; 28544 (526 x 892 -> 40, per batch) 12.0 / 10.4
+// and 9.5 / 10.3; 32768 9.0 / 6.5 and 6.4 / 7.0; 60000 (20 x 3000 -> 6000) 8.9 / 11.0 and 7.8 / 11.0.
+bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
+    const int64_t K = (int64_t)C * g, Kexp = (int64_t)(C + s) * g;
+    const Tuning& tn = tuning();
+    if (tn.slice_layer == 0) return false;
+    const int tile = slice_layer_tile(M, N);
+    if (tile == 0 || ldx >= ((int64_t)1 << 23) || K >= ((int64_t)1 << 23) || round_up(Kexp, 64) - K / 64 * 64 > kSliceLayerTail) return false;
+    if (tn.slice_layer > 0) return true;
+    return (M < 32 ? M : 32) * K <= 32768;
+}
+
+hipError_t launch_slice_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
+                              const float* thr, int n_max, int64_t self, float clip, float qmax, int8_t* Xq, int64_t ldq,
+                              float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
+                              int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream) {
+    SliceLayer p;
+    p.X = X; p.ldx = ldx; p.M = (int)M; p.N = (int)N;
+    p.K = C * g; p.C = C; p.g = g; p.Kexp = (C + s) * g;
+    p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.self = self; p.clip = clip; p.qmax = qmax;
+    p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.scale_w = scale_w;
+    p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
+    p.ksteps = (int)ceil_div(p.Kexp, 64);
+    p.kmain = p.K / 64;
+    const int rows = (int)(M < 32 ? M : 32);
+    switch (slice_layer_tile(M, N)) {
+        case 1:
+            if (rows <= 8) return run_slice_layer<1, 2, 8, 3, true>(p, stream);
+            if (rows <= 16) return run_slice_layer<1, 4, 8, 3, true>(p, stream);
+            if (rows <= 24) return run_slice_layer<1, 6, 8, 3, true>(p, stream);
+            return run_slice_layer<1, 8, 8, 3, true>(p, stream);
+        case 2: return run_slice_layer<2, 8, 8, 3, true>(p, stream);
+        case 4: return run_slice_layer<4, 8, 8, 2, false>(p, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NBUF, bool MASK = false>

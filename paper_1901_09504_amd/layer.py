@@ -133,8 +133,10 @@ class ExpandedLayer:
         """X fp32 [M, C*g] -> Y fp32 [M, N].  threshold: device float tensor for a static
         activation grid (Sec. 5: fixed from profiling), None for a per-batch dynamic one."""
         M = X.shape[0]
-        self.split_act(X, threshold, stream)
-        self.qgemm(M, acc_out, stream)
+        self._ensure_rows(M)
+        B.ocs_forward(X, M, self.C, self.g, X.stride(0), self.chan_src, self.s, self.bits_x, threshold, self.clip_ratio_x,
+                      self.Xq, self.ldq, self.scale_x, self.Wq, self.ldq, self.N, self.bits_w, self.scale_w, acc_out,
+                      0 if acc_out is None else acc_out.stride(0), self.Y, self.N, self.ws_x, stream)
         return self.Y[:M]
 
     def forward_act_ocs(self, W, X, acc_out=None, stream=None, qa=False):

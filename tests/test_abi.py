@@ -213,3 +213,21 @@ def test_binding_raises_on_error():
     with pytest.raises(B.OcsError) as e:
         B._check(-4, "ocs_quantize")
     assert "2..8" in str(e.value) and e.value.code == -4
+
+
+def test_forward_reports_what_its_two_steps_report():
+    L = B.lib()
+    ws = 1 << 24
+
+    def fwd(X=A, M=4, C=8, g=1, ldx=8, src=A, s=2, bx=8, thr=A, clip=1.0, Xq=A, ldq=16, sx=A, Wq=A, ldw=16, N=4, bw=8, sw=A,
+            acc=None, ldacc=0, Y=A, ldy=4, w=A, wb=ws):
+        return L.ocs_forward(X, M, C, g, ldx, src, s, bx, thr, clip, Xq, ldq, sx, Wq, ldw, N, bw, sw, acc, ldacc, Y, ldy, w, wb, None)
+
+    for name in ("X", "src", "Xq", "sx", "Wq", "sw", "Y"):
+        assert fwd(**{name: None}) == -1, name
+    assert fwd(M=0) == -2 and fwd(ldx=7) == -2 and fwd(N=0) == -2 and fwd(ldq=0) == -2 and fwd(ldy=3) == -2
+    assert fwd(ldw=0) == -2 and fwd(acc=A, ldacc=3) == -2
+    assert fwd(Xq=A + 1) == -3 and fwd(ldq=24) == -3 and fwd(Wq=A + 4) == -3 and fwd(thr=None, w=A + 16) == -3
+    assert fwd(bx=9) == -4 and fwd(bw=1) == -4 and fwd(s=-1) == -5
+    assert fwd(C=7000, ldx=140000, g=20, s=0, ldq=140032, ldw=140032) == -6
+    assert fwd(thr=None, w=None, wb=0) == -7 and fwd(thr=None, clip=0.0) == -10

@@ -1433,3 +1433,78 @@ def test_activation_ocs_with_qa_members_end_to_end():
     acc_ref, y_ref = ref.qgemm(Xq_ref, Wq_ref, L.Ke, sx_ref[1], sw_ref[1])
     assert np.array_equal(host(acc), acc_ref)
     assert_y_close(host(Y), y_ref)
+
+
+# ---- ocs_forward: the layer as one call -------------------------------------------------------------
+
+def _forward_once(M, C, g, s, N, ld_extra, threshold, clip, mode, seed=0, bits_w=5, ldq_extra=0):
+    """One ocs_forward call with dirty outputs against the oracle's two steps, all outputs bit for bit."""
+    rng = np.random.default_rng(1000 * M + C + 7 * N + s + seed)
+    K, Ke = C * g, (C + s) * g
+    X, W = _tensor(rng, M, K, "heavy"), _tensor(rng, N, K, "normal")
+    sp = ref.split_weights(W, C, g, s)
+    ldq = B.ocs_padded_cols(Ke) + ldq_extra
+    Wq, sw = ref.quantize(sp["T_out"], bits_w, ldq=ldq)
+    Xd = torch.zeros((M, K + ld_extra), dtype=torch.float32, device="cuda")
+    Xd[:, :K] = dev(X)
+    q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+    sx = torch.full((2,), -1.0, dtype=torch.float32, device="cuda")
+    Y = torch.full((M, N), -1.0, dtype=torch.float32, device="cuda")
+    acc = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+    th = None if threshold is None else torch.tensor([threshold], dtype=torch.float32, device="cuda")
+    B.ocs_tune("slice_layer", mode)
+    try:
+        B.ocs_forward(Xd, M, C, g, Xd.stride(0), dev(sp["chan_src"].astype(np.int32)), s, 8, th, clip, q, ldq, sx, dev(Wq),
+                      ldq, N, bits_w, dev(sw), acc, N, Y, N, B.alloc_workspace(M, K))
+    finally:
+        B.ocs_tune("slice_layer", -1)
+    q_ref, sx_ref, _ = ref.split_act(X, C, g, sp["chan_src"], None, s, 8, threshold=threshold, clip_ratio=clip, ldq=ldq)
+    acc_ref, y_ref = ref.qgemm(q_ref, Wq, Ke, sx_ref[1], sw[1])
+    assert np.array_equal(host(sx).view(np.uint32), sx_ref.view(np.uint32))
+    assert np.array_equal(host(q), q_ref)
+    assert np.array_equal(host(acc), acc_ref)
+    assert_y_close(host(Y), y_ref)
+
+
+# Few tiles as one launch: every count of rows in a tile's groups of four and of row groups requested (8, 16, 24, 32), no
+# whole K-step (C g < 64), steps around the waves and the ring (8 waves, ring of 3 and of 2: 7, 8, 9, 16, 17, 24, 25
+# whole steps), rows that end on a step, tails of several steps (more appended columns than the waves' first), padding past
+# the last step, the three widths of tile (N = 300: 32 columns; 8190 rows: 64; 4090 rows of 256: 128).
+@pytest.mark.parametrize("mode", [1, 0])
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra", [
+    (1, 1, 1, 0, 1, 0), (3, 5, 1, 4, 33, 1), (8, 63, 1, 2, 31, 0), (9, 64, 1, 0, 32, 0), (16, 65, 1, 7, 100, 3),
+    (17, 448, 1, 9, 64, 0), (24, 512, 1, 1, 33, 0), (25, 576, 1, 0, 40, 5), (31, 1024, 1, 60, 300, 0),
+    (32, 1088, 1, 52, 65, 0), (33, 1536, 1, 15, 300, 2), (40, 1600, 1, 30, 20, 0), (65, 40, 9, 36, 70, 0),
+    (20, 3, 49, 1, 64, 0), (12, 100, 9, 100, 35, 0), (8190, 64, 1, 3, 64, 0), (4090, 20, 9, 2, 256, 0)])
+def test_forward_of_few_tiles(M, C, g, s, N, ld_extra, mode):
+    if mode == 0 and M > 1000:
+        pytest.skip("the two launches at this size have tests of their own")
+    _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, mode)
+
+
+# Per-batch grids: looked for by every workgroup up to 32768 contiguous values (whole and ragged counts of four, and one
+# value more), folded from the maxima of a pass of its own beyond and for strided rows; code rows with more padding than asked for.
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip,ldq_extra", [
+    (1, 3, 1, 1, 5, 0, 1.0, 0), (64, 256, 1, 13, 256, 0, 0.9, 0), (128, 256, 1, 13, 64, 0, 1.0, 128), (129, 257, 1, 3, 64, 0, 0.8, 0),
+    (257, 64, 9, 4, 70, 0, 1.0, 64), (33, 300, 1, 15, 40, 4, 0.7, 0), (4000, 64, 1, 4, 64, 1, 1.0, 16)])
+def test_forward_of_few_tiles_per_batch(M, C, g, s, N, ld_extra, clip, ldq_extra):
+    _forward_once(M, C, g, s, N, ld_extra, None, clip, 1, ldq_extra=ldq_extra)
+
+
+def test_forward_over_its_own_input():
+    """Y on top of X (a layer applied to its own output): X has been read as a whole before any output is written."""
+    M, C, N, s = 70, 256, 256, 8
+    rng = np.random.default_rng(3)
+    X, W = _tensor(rng, M, C, "heavy"), _tensor(rng, N, C, "normal")
+    sp = ref.split_weights(W, C, 1, s)
+    ldq = B.ocs_padded_cols(C + s)
+    Wq, sw = ref.quantize(sp["T_out"], 6, ldq=ldq)
+    buf = dev(X)
+    q = torch.empty((M, ldq), dtype=torch.int8, device="cuda")
+    sx = torch.empty(2, dtype=torch.float32, device="cuda")
+    B.ocs_forward(buf, M, C, 1, C, dev(sp["chan_src"].astype(np.int32)), s, 8, None, 1.0, q, ldq, sx, dev(Wq), ldq, N, 6,
+                  dev(sw), None, 0, buf, N, B.alloc_workspace(M, C))
+    q_ref, sx_ref, _ = ref.split_act(X, C, 1, sp["chan_src"], None, s, 8, threshold=None, clip_ratio=1.0, ldq=ldq)
+    _, y_ref = ref.qgemm(q_ref, Wq, C + s, sx_ref[1], sw[1])
+    assert np.array_equal(host(q), q_ref)
+    assert_y_close(host(buf), y_ref)
