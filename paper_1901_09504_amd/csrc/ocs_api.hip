@@ -164,9 +164,11 @@ int ocs_select_channels(const float* T, int64_t rows, int C, int g, int64_t ld, 
     float* colmax = reinterpret_cast<float*>(base + w.colmax_off);
     float* partial = reinterpret_cast<float*>(base + w.partial_off);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipError_t e = launch_colmax(T, rows, K, ld, colmax, partial, st);
+    int blocks = 1;
+    const float* maxima = nullptr;
+    hipError_t e = launch_colmax_blocks(T, rows, K, ld, colmax, partial, kSelectFold, &maxima, &blocks, st);
     if (e != hipSuccess) return hip_fail(e);
-    e = launch_select(colmax, C, g, num_splits, 0, nullptr, split_src, chan_src, chan_depth,
+    e = launch_select(maxima, blocks, C, g, num_splits, 0, nullptr, split_src, chan_src, chan_depth,
                       max_out, 1.0f, 1.0f, nullptr, st);
     if (e != hipSuccess) return hip_fail(e);
     return OCS_OK;
@@ -201,17 +203,20 @@ int ocs_split_weights(const float* W, int64_t N, int C, int g, int64_t ldw, int 
 
     // W1: channel maxima.  W2: selection (or replay of the given list).  The selector also
     // emits max|W'| and, when codes are wanted, the threshold and step of the weight grid.
-    hipError_t e = launch_colmax(W, N, K, ldw, colmax, partial, st);
+    const bool inlined = Wq && !W_out && mode == OCS_MODE_HALVE && select_expand_quantize_fits(C, num_splits, N, ldq);
+    int blocks = 1;
+    const float* maxima = nullptr;
+    hipError_t e = launch_colmax_blocks(W, N, K, ldw, colmax, partial, inlined ? kInlineFold : kSelectFold, &maxima, &blocks, st);
     if (e != hipSuccess) return hip_fail(e);
     const float qmax = Wq ? qmax_of(bits) : 1.0f;
-    if (Wq && !W_out && mode == OCS_MODE_HALVE && select_expand_quantize_fits(C, num_splits, N, ldq)) {
+    if (inlined) {
         // few splits, codes only: W2 and W3 as one launch
-        e = launch_select_expand_quantize(W, ldw, N, C, g, num_splits, colmax, split_src, chan_src,
+        e = launch_select_expand_quantize(W, ldw, N, C, g, num_splits, maxima, blocks, split_src, chan_src,
                                           chan_depth, wmax_out, clip_ratio, qmax, scale_w_out, Wq,
                                           ldq, st);
         return e == hipSuccess ? OCS_OK : hip_fail(e);
     }
-    e = launch_select(colmax, C, g, num_splits, mode, split_src, split_src, chan_src, chan_depth,
+    e = launch_select(maxima, blocks, C, g, num_splits, mode, split_src, split_src, chan_src, chan_depth,
                       wmax_out, clip_ratio, qmax, Wq ? scale_w_out : nullptr, st);
     if (e != hipSuccess) return hip_fail(e);
 
@@ -259,10 +264,12 @@ int ocs_split_weights_qa(const float* W, int64_t N, int C, int g, int64_t ldw, i
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     // selection and threshold exactly as for plain halving; then the histories; then the members
-    hipError_t e = launch_colmax(W, N, K, ldw, colmax, partial, st);
+    int blocks = 1;
+    const float* maxima = nullptr;
+    hipError_t e = launch_colmax_blocks(W, N, K, ldw, colmax, partial, kSelectFold, &maxima, &blocks, st);
     if (e != hipSuccess) return hip_fail(e);
     const float qmax = qmax_of(bits);
-    e = launch_select(colmax, C, g, num_splits, OCS_MODE_HALVE, split_src, split_src, chan_src,
+    e = launch_select(maxima, blocks, C, g, num_splits, OCS_MODE_HALVE, split_src, split_src, chan_src,
                       chan_depth, nullptr, clip_ratio, qmax, scale_w_out, st);
     if (e != hipSuccess) return hip_fail(e);
     e = launch_qa_paths(split_src, C, num_splits, chan_path, st);

@@ -51,6 +51,13 @@ Workspace plan_workspace(int64_t rows, int64_t cols);
 hipError_t launch_colmax(const float* T, int64_t rows, int64_t cols, int64_t ld, float* colmax,
                          float* partial, hipStream_t stream);
 
+// Most values of colmax[blocks][C*g] the selector folds (in its own launch; repeated by every workgroup of the weight pass).
+constexpr int64_t kSelectFold = 49152, kInlineFold = 16384;
+// The same for a reader that folds row blocks itself: (*out)[b * cols + c], b < *blocks, hold the column maxima of the
+// blocks (at most `most` values in all, unless it is a single row of them).
+hipError_t launch_colmax_blocks(const float* T, int64_t rows, int64_t cols, int64_t ld, float* colmax, float* partial,
+                                int64_t most, const float** out, int* blocks, hipStream_t stream);
+
 // scale_out = {T, T/qmax} with T = clip_ratio * max|T| over the whole tensor: the column pass
 // with one value per workgroup, then one small reduction (no per-column result).
 hipError_t launch_absmax_threshold(const float* T, int64_t rows, int64_t cols, int64_t ld,
@@ -58,9 +65,9 @@ hipError_t launch_absmax_threshold(const float* T, int64_t rows, int64_t cols, i
                                    hipStream_t stream);
 
 // Greedy channel selection (mode 0) or replay of a given split list (mode 1) on the C
-// channel maxima derived from colmax[C*g].  Optionally writes max_out and
+// channel maxima derived from colmax[blocks][C*g].  Optionally writes max_out and
 // scale_out = {clip*max, clip*max/qmax}.
-hipError_t launch_select(const float* colmax, int C, int g, int s, int mode,
+hipError_t launch_select(const float* colmax, int blocks, int C, int g, int s, int mode,
                          const int32_t* split_in, int32_t* split_src, int32_t* chan_src,
                          int32_t* chan_depth, float* max_out, float clip_ratio, float qmax,
                          float* scale_out, hipStream_t stream);
@@ -76,7 +83,7 @@ hipError_t launch_threshold(const float* colmax, int C, int g, int s, const int3
 // what launch_select and launch_expand_quantize together would.
 bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq);
 hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N, int C, int g, int s,
-                                         const float* colmax, int32_t* split_src, int32_t* chan_src,
+                                         const float* colmax, int blocks, int32_t* split_src, int32_t* chan_src,
                                          int32_t* chan_depth, float* max_out, float clip_ratio,
                                          float qmax, float* scale_out, int8_t* Wq, int64_t ldq,
                                          hipStream_t stream);

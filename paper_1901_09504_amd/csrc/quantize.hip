@@ -1079,10 +1079,10 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
 // expanded channel j is scaled by 2^-dep[j]; Eq. 1 on the grid of clip_ratio * max|W'|), with
 // the arithmetic of expand_quantize_kernel.  Workgroup 0 also writes the lists, the maximum
 // and the grid for the caller.  32-bit indices.
-template <bool FEW>
+template <bool FEW, bool BLOCKS>
 __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     const float* __restrict__ W, int64_t ldw, int64_t N, int C, int g, int s,
-    const float* __restrict__ colmax, int32_t* __restrict__ split_src,
+    const float* __restrict__ colmax, int blocks, int32_t* __restrict__ split_src,
     int32_t* __restrict__ chan_src, int32_t* __restrict__ chan_depth, float* __restrict__ max_out,
     float clip_ratio, float qmax, float* __restrict__ scale_out, int8_t* __restrict__ Wq, int D,
     int main_units, unsigned magic) {
@@ -1117,7 +1117,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     int d = 0, nd = 0;
     fetch(o, cur, row, d);
 
-    channel_maxima_to_lds<kThreads>(colmax, C, g, vals, src, dep);
+    channel_maxima_to_lds<kThreads, BLOCKS>(colmax, blocks, C, g, vals, src, dep);
     greedy_select<kThreads, FEW>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
     unsigned m = 0;   // bit pattern of the largest entry (all entries are non-negative)
     for (int j = tid; j < E; j += kThreads) {
@@ -1187,7 +1187,7 @@ bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq) {
 }
 
 hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N, int C, int g, int s,
-                                         const float* colmax, int32_t* split_src, int32_t* chan_src,
+                                         const float* colmax, int blocks, int32_t* split_src, int32_t* chan_src,
                                          int32_t* chan_depth, float* max_out, float clip_ratio,
                                          float qmax, float* scale_out, int8_t* Wq, int64_t ldq,
                                          hipStream_t stream) {
@@ -1200,9 +1200,10 @@ hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N,
     if (tuning().act_grid > 0) grid = tuning().act_grid;
     if (grid > ceil_div(total, kThreads)) grid = ceil_div(total, kThreads);
     const unsigned magic = (unsigned)((((uint64_t)1) << 32) / (uint64_t)D);  // D >= 16
-    const auto kernel = few_steps(C, s) ? select_expand_quantize_kernel<true> : select_expand_quantize_kernel<false>;
+    const auto kernel = blocks > 1 ? (few_steps(C, s) ? select_expand_quantize_kernel<true, true> : select_expand_quantize_kernel<false, true>)
+                                   : (few_steps(C, s) ? select_expand_quantize_kernel<true, false> : select_expand_quantize_kernel<false, false>);
     return launch_kernel(kTimeSplitQuantize, kernel, dim3((unsigned)grid), dim3(kThreads), greedy_list_bytes(E), stream,
-                         W, ldw, N, C, g, s, colmax, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax,
+                         W, ldw, N, C, g, s, colmax, blocks, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax,
                          scale_out, Wq, D, main_units, magic);
 }
 

@@ -265,6 +265,90 @@ hipError_t launch_colmax(const float* T, int64_t rows, int64_t cols, int64_t ld,
     return hipGetLastError();
 }
 
+// Stage 1 where the rows are cut into blocks: one workgroup of sixteen waves per compute unit, eight 16-byte requests of
+// a lane on their way at a time, and so few blocks that the selector folds their partial rows itself (no stage 2, one
+// launch less).  TX lanes share a row (512 bytes with 32), 1024 / TX rows at a time; the last group of a row is its last four
+// columns, which may be another group's as well: both find the same maxima.
+// What bounds it: HBM (6000 x 3000, 72 MB, 15 us either way); what it saves is stage 2 and its launch.  Selection with its
+// maxima, us, with stage 2 / without: 6000 x 3000 28.4 / 25.4, 2048 x 512 13.1 / 10.2, 6272 x 2048 20.2 / 18.3.
+constexpr int kStripThreads = 1024;
+template <int TX>
+__global__ __launch_bounds__(kStripThreads) void colmax_strip_kernel(const float* __restrict__ T, int64_t ld, int64_t rows,
+                                                                    int cols, int rows_per_block,
+                                                                    float* __restrict__ partial) {
+    constexpr int TY = kStripThreads / TX, UN = 8;
+    __shared__ f32x4 red[kStripThreads];
+    const int tx = (int)threadIdx.x % TX, ty = (int)threadIdx.x / TX;
+    const int u = (int)blockIdx.x * TX + tx;
+    const bool in = 4 * u < cols;
+    const int col = 4 * u < cols - 4 ? 4 * u : cols - 4;      // (cols >= 4; lanes past the row repeat its end and store nothing)
+    const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
+    const int64_t r1 = r0 + rows_per_block < rows ? r0 + rows_per_block : rows;
+    const float* base = T + col;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int64_t r = r0 + ty; r < r1; r += UN * TY) {
+        f32x4 v[UN] = {};
+#pragma unroll
+        for (int q = 0; q < UN; ++q)
+            if (r + q * TY < r1) v[q] = *reinterpret_cast<const f32x4u*>(base + (r + q * TY) * ld);
+#pragma unroll
+        for (int q = 0; q < UN; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], fabsf(v[q][e]));
+    }
+    red[threadIdx.x] = acc;
+    __syncthreads();
+#pragma unroll
+    for (int w = TY / 2; w > 0; w >>= 1) {
+        if (ty < w) {
+            const f32x4 o = red[threadIdx.x + w * TX];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], o[e]);
+            red[threadIdx.x] = acc;
+        }
+        __syncthreads();
+    }
+    if (ty == 0 && in) *reinterpret_cast<f32x4u*>(partial + (int64_t)blockIdx.y * cols + col) = acc;
+}
+
+// Weights of up to 2048 long rows go through one launch of strips that run down all rows (plan_reduce): from 1.5 million values on
+// the blocks are ahead of it (selection with its maxima, us: 1024 x 1024 10.0 against 10.6, 1000 x 2048 a whole preparation
+// 18.4 against 16.6, 2000 x 2000 16.7 against 13.5), never up to 512 rows.
+static bool direct_strips(const ReducePlan& p, int64_t rows, int64_t cols) {
+    return p.row_blocks == 1 && (rows <= 512 || rows * cols < (int64_t)3 << 19);
+}
+hipError_t launch_colmax_blocks(const float* T, int64_t rows, int64_t cols, int64_t ld, float* colmax, float* partial,
+                                int64_t most, const float** out, int* blocks, hipStream_t stream) {
+    *out = colmax;
+    *blocks = 1;
+    const Workspace ws = plan_workspace(rows, cols);      // (what the caller's workspace holds at least)
+    const int64_t room = (int64_t)(ws.total - ws.partial_off) / 4;
+    if (room < most) most = room;
+    const ReducePlan p = plan_reduce(rows, cols, true, false);
+    if (direct_strips(p, rows, cols) || (p.row_blocks == 1 && most < 2 * cols))
+        return launch_partials(T, rows, cols, ld, colmax, false, p, nullptr, stream);
+    if (cols < 4 || cols > 0x7FFFFFFF / 4) return launch_colmax(T, rows, cols, ld, colmax, partial, stream);
+    const int64_t units = ceil_div(cols, 4);
+    const int tx = units <= 8 ? 8 : (units <= 16 ? 16 : 32), ty = kStripThreads / tx;
+    const int64_t strips = ceil_div(units, tx);
+    // a workgroup per compute unit, of at least four rows a lane; no more partial rows than the caller's reader folds and
+    // the workspace has room for
+    int64_t rb = 256 / strips;
+    if (rb > ceil_div(rows, 4 * ty)) rb = ceil_div(rows, 4 * ty);
+    if (rb > most / cols) rb = most / cols;
+    if (rb < 1) rb = 1;
+    const int per = (int)ceil_div(rows, rb);
+    rb = ceil_div(rows, per);
+    float* dst = rb == 1 ? colmax : partial;
+    const dim3 grid((unsigned)strips, (unsigned)rb);
+    if (tx == 8) colmax_strip_kernel<8><<<grid, kStripThreads, 0, stream>>>(T, ld, rows, (int)cols, per, dst);
+    else if (tx == 16) colmax_strip_kernel<16><<<grid, kStripThreads, 0, stream>>>(T, ld, rows, (int)cols, per, dst);
+    else colmax_strip_kernel<32><<<grid, kStripThreads, 0, stream>>>(T, ld, rows, (int)cols, per, dst);
+    *out = dst;
+    *blocks = (int)rb;
+    return hipGetLastError();
+}
+
 // scale_out = {T, T/qmax}, T = clip_ratio * max(v[0..n)).  One workgroup.
 __global__ __launch_bounds__(kThreads) void threshold_scalar_kernel(const float* __restrict__ v, int n,
                                                                     float clip_ratio, float qmax,

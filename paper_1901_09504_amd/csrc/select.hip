@@ -16,9 +16,9 @@ namespace ocs {
 // 3000 channels, 150 splits: 78 -> 11 us with the column maxima in the caches, 14 without, against one split per
 // step (0.2 us a step on one wave, 0.5 us on four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
 // taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
-template <int NT, bool FEW>
+template <int NT, bool FEW, bool BLOCKS>
 __global__ __launch_bounds__(NT) void select_kernel(
-    const float* __restrict__ colmax, int C, int g, int s, int mode,
+    const float* __restrict__ colmax, int blocks, int C, int g, int s, int mode,
     const int32_t* split_in, int32_t* split_src,
     int32_t* __restrict__ chan_src, int32_t* __restrict__ chan_depth, float* __restrict__ max_out,
     float clip_ratio, float qmax, float* __restrict__ scale_out) {
@@ -31,7 +31,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     __shared__ GreedyScratch sc;
     const int tid = threadIdx.x;
 
-    channel_maxima_to_lds<NT>(colmax, C, g, vals, src, dep);
+    channel_maxima_to_lds<NT, BLOCKS>(colmax, blocks, C, g, vals, src, dep);
 
     if (mode == 0) {
         greedy_select<NT, FEW>(vals, src, dep, cand, sc, C, s, split_src);
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
 constexpr unsigned kSelectMaxLds = 128 * 1024;   // holds the list of kMaxExpanded channels
 
-template <int NT, bool FEW>
-static hipError_t run_select(const float* colmax, int C, int g, int s, int mode, const int32_t* split_in,
+template <int NT, bool FEW, bool BLOCKS>
+static hipError_t run_select(const float* colmax, int blocks, int C, int g, int s, int mode, const int32_t* split_in,
                              int32_t* split_src, int32_t* chan_src, int32_t* chan_depth, float* max_out,
                              float clip_ratio, float qmax, float* scale_out, hipStream_t stream) {
     const unsigned lds = greedy_list_bytes(C + s);
@@ -86,27 +86,29 @@ static hipError_t run_select(const float* colmax, int C, int g, int s, int mode,
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT, FEW>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT, FEW, BLOCKS>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    select_kernel<NT, FEW><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
-                                              max_out, clip_ratio, qmax, scale_out);
+    select_kernel<NT, FEW, BLOCKS><<<1, NT, lds, stream>>>(colmax, blocks, C, g, s, mode, split_in, split_src, chan_src,
+                                              chan_depth, max_out, clip_ratio, qmax, scale_out);
     return hipGetLastError();
 }
 
-hipError_t launch_select(const float* colmax, int C, int g, int s, int mode,
+hipError_t launch_select(const float* colmax, int blocks, int C, int g, int s, int mode,
                          const int32_t* split_in, int32_t* split_src, int32_t* chan_src,
                          int32_t* chan_depth, float* max_out, float clip_ratio, float qmax,
                          float* scale_out, hipStream_t stream) {
     // E = C + s <= kMaxExpanded is checked by the caller
     const bool few = mode == 0 && few_steps(C, s);
-    const bool narrow = C + s <= 512 && (int64_t)C * g <= 1024;
-    const auto run = narrow ? (few ? run_select<256, true> : run_select<256, false>)
-                            : (few ? run_select<1024, true> : run_select<1024, false>);
-    return run(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax, scale_out,
+    const bool narrow = C + s <= 512 && (int64_t)C * g <= 1024 && (int64_t)blocks * C * g <= 8192;
+    const auto run = blocks > 1 ? (narrow ? (few ? run_select<256, true, true> : run_select<256, false, true>)
+                                          : (few ? run_select<1024, true, true> : run_select<1024, false, true>))
+                                : (narrow ? (few ? run_select<256, true, false> : run_select<256, false, false>)
+                                          : (few ? run_select<1024, true, false> : run_select<1024, false, false>));
+    return run(colmax, blocks, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax, scale_out,
                stream);
 }
 

@@ -16,11 +16,15 @@
 
 namespace ocs {
 
-// Channel maxima from the K = C * g column maxima into vals[0 .. C), src/dep set to the identity.
-// One coalesced, independent load per column, folded per channel with LDS atomics on the bit
-// pattern.  Called by all NT lanes of the workgroup; contains barriers, and ends with one.
-template <int NT>
-__device__ __forceinline__ void channel_maxima_to_lds(const float* __restrict__ colmax, int C, int g,
+// Channel maxima from the column maxima of `blocks` row blocks, colmax[blocks][K = C * g], into vals[0 .. C), src/dep set to
+// the identity.  Independent 16-byte loads, a lane's eight or sixteen on their way together (the maxima were written a moment ago by
+// other CUs and every load waits a whole trip through the fabric), folded per channel with LDS atomics on the bit
+// pattern.  Lanes are dealt over a block's groups of four columns first, then over the blocks; the last group of a block is
+// its last four columns, some of which may be another group's as well (K >= 4 with several blocks).  Called by all NT lanes of the workgroup;
+// contains barriers, and ends with one.
+// BLOCKS: more than one, in an instance of its own.
+template <int NT, bool BLOCKS>
+__device__ __forceinline__ void channel_maxima_to_lds(const float* __restrict__ colmax, int blocks, int C, int g,
                                                       float* vals, unsigned short* src, unsigned short* dep) {
     const int tid = threadIdx.x;
     for (int j = tid; j < C; j += NT) {
@@ -31,22 +35,46 @@ __device__ __forceinline__ void channel_maxima_to_lds(const float* __restrict__ 
     __syncthreads();
     const int K = C * g;
     unsigned* vbits = reinterpret_cast<unsigned*>(vals);
-    // Sixteen loads per lane (four in the wide workgroup) are requested before the first value is
-    // used: the column maxima were written a moment ago by other CUs and every load waits a whole
-    // trip through the fabric.  (The compiler keeps a load behind the LDS atomic that precedes it in
-    // program order, so a plain loop, unrolled or not, makes one trip per column of a lane.)
-    constexpr int UN = NT >= 1024 ? 4 : 16;
-    for (int k0 = tid; k0 < K; k0 += UN * NT) {
-        float v[UN];
+    if constexpr (!BLOCKS) {
+        // (a column per lane: four atomics behind one 16-byte load are longer than the loads, 256 x 256 x 9 7.1 against 7.6 us.
+        // The compiler keeps a load behind the LDS atomic that precedes it in program order, so a plain loop, unrolled or
+        // not, makes one trip per column of a lane: several are requested before the first value is used.)
+        constexpr int U1 = NT >= 1024 ? 4 : 16;
+        for (int k0 = tid; k0 < K; k0 += U1 * NT) {
+            float v[U1];
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = k0 + u * NT;
-            v[u] = colmax[k < K ? k : K - 1];
+            for (int u = 0; u < U1; ++u) {
+                const int k = k0 + u * NT;
+                v[u] = colmax[k < K ? k : K - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < U1; ++u) {
+                const int k = k0 + u * NT;
+                if (k < K) atomicMax(&vbits[k / g], __float_as_uint(v[u]));
+            }
         }
+    } else {
+        constexpr int UN = NT >= 1024 ? 16 : 8;
+        const int units = (K + 3) / 4;
+        const int groups = units < NT ? NT / units : 1;           // blocks walked side by side
+        const int b0 = units < NT ? tid / units : 0, u0 = tid - b0 * units;
+        if (b0 < groups) {
+            for (int u = u0; u < units; u += NT) {                // (one trip where units < NT)
+                const int col = 4 * u < K - 4 ? 4 * u : K - 4;
+                f32x4 m = {0.0f, 0.0f, 0.0f, 0.0f};
+                for (int b = b0; b < blocks; b += UN * groups) {
+                    f32x4 v[UN] = {};
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            const int k = k0 + u * NT;
-            if (k < K) atomicMax(&vbits[k / g], __float_as_uint(v[u]));
+                    for (int q = 0; q < UN; ++q)
+                        if (b + q * groups < blocks) v[q] = *reinterpret_cast<const f32x4u*>(colmax + (int64_t)(b + q * groups) * K + col);
+#pragma unroll
+                    for (int q = 0; q < UN; ++q)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) m[e] = fmaxf(m[e], v[q][e]);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) atomicMax(&vbits[(col + e) / g], __float_as_uint(m[e]));
+            }
         }
     }
     __syncthreads();

@@ -1508,3 +1508,35 @@ def test_forward_over_its_own_input():
     _, y_ref = ref.qgemm(q_ref, Wq, C + s, sx_ref[1], sw[1])
     assert np.array_equal(host(q), q_ref)
     assert_y_close(host(buf), y_ref)
+
+
+# ---- channel maxima in row blocks that the selector folds itself ------------------------------------
+
+# Rows and columns around the blocks' edges: a row's last group of four overlaps the one before (5, 7, 33, 130 columns, 8, 16 and
+# 32 lanes a row), a single column per channel and several, blocks of a row more or less, more blocks than a lane
+# requests at once (64 columns: 256 blocks), weights-shaped tensors past the single-launch strips, rows too few for a second block.
+@pytest.mark.parametrize("rows,C,g,s,ld_extra", [
+    (2049, 1, 4, 3, 0), (700, 5, 1, 2, 0), (5000, 7, 1, 4, 3), (4100, 33, 1, 5, 0), (9000, 64, 1, 7, 0), (2500, 13, 10, 4, 1),
+    (70000, 16, 2, 3, 0), (2111, 300, 1, 30, 0), (1030, 1600, 1, 12, 0), (800, 2000, 1, 20, 0), (3000, 40, 9, 4, 0)])
+def test_selection_on_row_blocks(rows, C, g, s, ld_extra):
+    rng = np.random.default_rng(rows + C)
+    K = C * g
+    T = _tensor(rng, rows, K, "heavy")
+    T[rows - 1, K - 1] = 11.5                        # the last row and column count
+    T[rows // 2, 0] = -12.5
+    exp = ref.split_weights(T, C, g, s)
+    buf = torch.zeros((rows, K + ld_extra), dtype=torch.float32, device="cuda")
+    buf[:, :K] = dev(T)
+    buf[:, K:] = 99.0                                # not part of the tensor
+    ws = B.alloc_workspace(rows, K)
+    ws.fill_(0x7F)
+    ss = torch.full((max(s, 1),), -7, dtype=torch.int32, device="cuda")
+    cs = torch.full((C + s,), -7, dtype=torch.int32, device="cuda")
+    cd = torch.full((C + s,), -7, dtype=torch.int32, device="cuda")
+    mx = torch.zeros(1, dtype=torch.float32, device="cuda")
+    B.ocs_select_channels(buf, rows, C, g, K + ld_extra, s, ss, cs, cd, mx, ws)
+    assert np.array_equal(host(ss)[:s], exp["split_src"]) and np.array_equal(host(cs), exp["chan_src"])
+    assert np.array_equal(host(cd), exp["chan_depth"]) and float(host(mx)[0]) == float(np.float32(exp["max"]))
+    got = gpu_split_weights(T, C, g, s, bits=6, want_f32=False)        # the weight pass with the selection in its prologue
+    q_ref, sw_ref = ref.quantize(exp["T_out"], 6, ldq=B.ocs_padded_cols((C + s) * g))
+    assert np.array_equal(got["Wq"], q_ref) and np.array_equal(got["scale"], sw_ref)
