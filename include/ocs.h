@@ -311,6 +311,20 @@ int ocs_forward(const float *X, int64_t M, int C, int g, int64_t ldx, const int3
                 void *workspace, size_t ws_bytes, void *stream);
 
 /*
+ * Activation OCS (Eq. 4) with the channels chosen on the batch itself (Sec. 5.3), as one call: ocs_select_channels on X
+ * (max_out required: with clip_ratio 1 it is the grid's threshold), ocs_duplicate_weight_codes, ocs_split_act with
+ * the depths and ocs_qgemm, with the arguments those take and leaving what they leave, bit for bit.  Wq holds the weights'
+ * own codes in its first C*g columns (ocs_quantize), scale_w their grid; its other columns are written here.  max_out must
+ * not lie in scale_x_out.  workspace as for ocs_select_channels.
+ */
+int ocs_forward_act(const float *X, int64_t M, int C, int g, int64_t ldx, int num_splits, int bits_x,
+                    float clip_ratio, int32_t *split_src, int32_t *chan_src, int32_t *chan_depth,
+                    float *max_out, int8_t *Xq, int64_t ldq, float *scale_x_out, int8_t *Wq,
+                    int64_t ldw, int64_t N, int bits_w, const float *scale_w, int32_t *acc_out,
+                    int64_t ldacc, float *Y, int64_t ldy, void *workspace, size_t ws_bytes,
+                    void *stream);
+
+/*
  * ocs_split_act (static grid, copies un-scaled: the activation side of Eq. 3) and ocs_qgemm as ONE
  * launch: the GEMM's loader reads the fp32 rows of X [M, C*g] itself, puts them on the grid of
  * `threshold` (Eq. 1, the arithmetic of ocs_split_act: the codes are the same), and takes the

@@ -103,6 +103,9 @@ def lib():
     L.ocs_forward.restype = _i32
     L.ocs_forward.argtypes = [_vp, _i64, _i32, _i32, _i64, _vp, _i32, _i32, _vp, _f32, _vp, _i64, _vp, _vp, _i64, _i64,
                               _i32, _vp, _vp, _i64, _vp, _i64, _vp, _sz, _vp]
+    L.ocs_forward_act.restype = _i32
+    L.ocs_forward_act.argtypes = [_vp, _i64, _i32, _i32, _i64, _i32, _i32, _f32, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp,
+                                  _i64, _i64, _i32, _vp, _vp, _i64, _vp, _i64, _vp, _sz, _vp]
     L.ocs_split_act_qgemm_fits.restype = _i32
     L.ocs_split_act_qgemm_fits.argtypes = [_i64, _i32, _i32, _i32, _i64, _i64]
     L.ocs_split_act_qgemm_pays.restype = _i32
@@ -356,6 +359,15 @@ def ocs_forward(X, M, Cn, g, ldx, chan_src, num_splits, bits_x, threshold, clip_
     _check(lib().ocs_forward(_ptr(X), M, Cn, g, ldx, _ptr(chan_src), num_splits, bits_x, _ptr(threshold), clip_ratio,
                              _ptr(Xq), ldq, _ptr(scale_x_out), _ptr(Wq), ldw, N, bits_w, _ptr(scale_w), _ptr(acc_out),
                              ldacc, _ptr(Y), ldy, w, wb, _stream(stream)), "ocs_forward")
+
+
+def ocs_forward_act(X, M, Cn, g, ldx, num_splits, bits_x, clip_ratio, split_src, chan_src, chan_depth, max_out, Xq, ldq,
+                    scale_x_out, Wq, ldw, N, bits_w, scale_w, acc_out, ldacc, Y, ldy, workspace, stream=None):
+    w, wb = _ws(workspace)
+    _check(lib().ocs_forward_act(_ptr(X), M, Cn, g, ldx, num_splits, bits_x, clip_ratio, _ptr(split_src), _ptr(chan_src),
+                                 _ptr(chan_depth), _ptr(max_out), _ptr(Xq), ldq, _ptr(scale_x_out), _ptr(Wq), ldw, N,
+                                 bits_w, _ptr(scale_w), _ptr(acc_out), ldacc, _ptr(Y), ldy, w, wb, _stream(stream)),
+           "ocs_forward_act")
 
 
 def ocs_split_act_qgemm_fits(M, C, g, num_splits, N, ldx):

@@ -588,6 +588,39 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
                      stream);
 }
 
+int ocs_forward_act(const float* X, int64_t M, int C, int g, int64_t ldx, int num_splits, int bits_x, float clip_ratio,
+                    int32_t* split_src, int32_t* chan_src, int32_t* chan_depth, float* max_out, int8_t* Xq, int64_t ldq,
+                    float* scale_x_out, int8_t* Wq, int64_t ldw, int64_t N, int bits_w, const float* scale_w,
+                    int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, void* workspace, size_t ws_bytes, void* stream) {
+    if (!max_out || !chan_depth || !Wq || !scale_w || !Y) return OCS_E_NULL;
+    int rc = check_split_act(X, M, C, g, ldx, chan_src, num_splits, bits_x, max_out, clip_ratio, Xq, ldq, scale_x_out);
+    if (rc) return rc;
+    if (!clip_ok(clip_ratio)) return OCS_E_CLIP;
+    const int64_t Kexp = (int64_t)(C + num_splits) * g;
+    rc = check_gemm_operands(Xq, ldq, Wq, ldw, M, N, Kexp, bits_x, bits_w, acc_out, ldacc);
+    if (rc) return rc;
+    if (ldy < N) return OCS_E_SHAPE;
+    if (max_out == scale_x_out || max_out == scale_x_out + 1) return OCS_E_MODE;   // the pass reads one while writing the other
+    rc = ocs_select_channels(X, M, C, g, ldx, num_splits, split_src, chan_src, chan_depth, max_out, workspace, ws_bytes, stream);
+    if (rc) return rc;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    hipError_t e = hipSuccess;
+    if (clip_ratio == 1.0f) {
+        // the selection's own maximum is the threshold: the pass over X with the weights' copies in its last workgroups
+        e = launch_expand_quantize(X, ldx, M, C, g, num_splits, chan_src, chan_depth, max_out, qmax_of(bits_x), Xq, ldq,
+                                   scale_x_out, st, nullptr, 0, 1.0f, false, 0, Wq, ldw, N);
+        if (e != hipSuccess) return hip_fail(e);
+    } else {
+        e = launch_dup_code_columns(Wq, ldw, N, C, g, num_splits, chan_src, st);
+        if (e != hipSuccess) return hip_fail(e);
+        rc = ocs_split_act(X, M, C, g, ldx, chan_src, chan_depth, num_splits, bits_x, nullptr, clip_ratio, Xq, ldq, scale_x_out,
+                           workspace, ws_bytes, stream);
+        if (rc) return rc;
+    }
+    return ocs_qgemm(Xq, ldq, Wq, ldw, M, N, Kexp, bits_x, bits_w, scale_x_out, scale_w, acc_out, ldacc, Y, ldy, nullptr, 0,
+                     stream);
+}
+
 int ocs_split_act_qgemm_fits(int64_t M, int C, int g, int num_splits, int64_t N, int64_t ldx) {
     if (M <= 0 || C <= 0 || g <= 0 || num_splits < 0 || N <= 0) return 0;
     if ((int64_t)C * g > (int64_t)1 << 30 || (int64_t)C + num_splits > OCS_MAX_EXPANDED_CHANNELS) return 0;

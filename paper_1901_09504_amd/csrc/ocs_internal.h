@@ -100,7 +100,9 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
                                   const float* thr, float qmax, int8_t* Xq, int64_t ldq,
                                   float* scale_out, hipStream_t stream,
                                   const float* partials = nullptr, int n_partials = 0,
-                                  float clip_ratio = 1.0f, bool stepwise = false, int64_t self = 0);
+                                  float clip_ratio = 1.0f, bool stepwise = false, int64_t self = 0,
+                                  int8_t* dup_codes = nullptr, int64_t ldw = 0, int64_t N = 0);
+// dup_codes: weight codes [N, ldw] whose appended and padding columns this call fills as well (launch_dup_code_columns).
 // Whether the pass can find a per-batch grid's maximum by itself (small contiguous X, un-scaled copies):
 // launch_expand_quantize then takes self = M * C * g, with neither thr nor partials.
 bool act_self_max_serves(int64_t M, int C, int g, int s, int64_t ldx, int64_t ldq, const int32_t* chan_src);
@@ -281,6 +283,23 @@ __device__ __forceinline__ unsigned pack4(unsigned a, unsigned b, unsigned c, un
 __device__ __forceinline__ float inv_step_of(float T, float qmax) {
     if (!(T > 0.0f)) return 0.0f;
     return __builtin_fminf(__fdiv_rn(qmax, T), 3.402823466e+38f);
+}
+
+// Byte o of the appended and padding columns of weight codes: the copy of its source's code, or a zero code.
+__device__ __forceinline__ void dup_code_byte(int8_t* __restrict__ Wq, int64_t ldq, int64_t N, int C, int g, int s,
+                                              const int32_t* __restrict__ chan_src, int64_t o) {
+    const int tail = (int)(ldq - (int64_t)C * g);                // appended + padding columns per row
+    if (o >= N * tail) return;
+    const int64_t n = o / tail;
+    const int k = C * g + (int)(o - n * tail);
+    int8_t code = 0;
+    if (k < (C + s) * g) {
+        const int j = k / g, t = k - j * g;
+        int src = chan_src[j];
+        src = src < 0 ? 0 : (src >= C ? C - 1 : src);
+        code = Wq[n * ldq + (int64_t)src * g + t];
+    }
+    Wq[n * ldq + k] = code;
 }
 
 // Launch-shape overrides (benchmarking only); < 0 means "use the default".

@@ -362,19 +362,7 @@ hipError_t launch_expand_quantize_qa(const float* W, int64_t ldw, int64_t N, int
 __global__ __launch_bounds__(kThreads) void dup_code_columns_kernel(int8_t* __restrict__ Wq, int64_t ldq,
                                                                     int64_t N, int C, int g, int s,
                                                                     const int32_t* __restrict__ chan_src) {
-    const int tail = (int)(ldq - (int64_t)C * g);                // appended + padding columns per row
-    const int64_t o = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (o >= N * tail) return;
-    const int64_t n = o / tail;
-    const int k = C * g + (int)(o - n * tail);
-    int8_t code = 0;
-    if (k < (C + s) * g) {
-        const int j = k / g, t = k - j * g;
-        int src = chan_src[j];
-        src = src < 0 ? 0 : (src >= C ? C - 1 : src);
-        code = Wq[n * ldq + (int64_t)src * g + t];
-    }
-    Wq[n * ldq + k] = code;
+    dup_code_byte(Wq, ldq, N, C, g, s, chan_src, (int64_t)blockIdx.x * kThreads + threadIdx.x);
 }
 
 hipError_t launch_dup_code_columns(int8_t* Wq, int64_t ldq, int64_t N, int C, int g, int s,

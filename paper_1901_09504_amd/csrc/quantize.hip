@@ -333,11 +333,11 @@ __device__ __forceinline__ float shot_threshold(const float* thr, const ShotMax&
 }
 
 template <int U, int SCALE, int MAX, bool G1>
-__global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
+__device__ __forceinline__ void expand_quantize_shot(
     const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
     const int32_t* __restrict__ chan_src, const int32_t* __restrict__ chan_depth, const float* __restrict__ thr,
     float qmax, int8_t* __restrict__ Xq, int64_t ldq, int R, unsigned magic_qc, unsigned magic_td,
-    unsigned magic_g, float* __restrict__ scale_out, ShotMax mx) {
+    unsigned magic_g, float* __restrict__ scale_out, const ShotMax& mx) {
     extern __shared__ __align__(16) int8_t slds[];
     __shared__ float red[kShotNT / 64];
     const int K = C * g, Q = K / 4, rem = K - 4 * Q, Qc = Q + (rem > 0 ? 1 : 0);
@@ -478,6 +478,38 @@ __global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
     }
 }
 
+template <int U, int SCALE, int MAX, bool G1>
+__global__ __launch_bounds__(kShotNT) void expand_quantize_shot_kernel(
+    const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
+    const int32_t* __restrict__ chan_src, const int32_t* __restrict__ chan_depth, const float* __restrict__ thr,
+    float qmax, int8_t* __restrict__ Xq, int64_t ldq, int R, unsigned magic_qc, unsigned magic_td,
+    unsigned magic_g, float* __restrict__ scale_out, ShotMax mx) {
+    expand_quantize_shot<U, SCALE, MAX, G1>(X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, R, magic_qc,
+                                            magic_td, magic_g, scale_out, mx);
+}
+
+// Eq. 4's pass over the activations (depths given) with the weights' side of it in its last workgroups: the codes of the
+// channels split on this batch, copied behind the weight codes (dup_code_columns_kernel's work, one byte per lane).  By itself that is
+// a launch of 64 K lanes between two that wait for each other: 6272 x 2048 -> 512, the whole layer, 44.0 us with it, 40.5 so.
+struct DupTail {
+    int8_t* Wq;
+    int64_t ldw, N;
+    unsigned first;          // first workgroup of the copies
+};
+template <int U, bool G1>
+__global__ __launch_bounds__(kShotNT) void expand_quantize_shot_dup_kernel(
+    const float* __restrict__ X, int64_t ldx, int M, int C, int g, int s,
+    const int32_t* __restrict__ chan_src, const int32_t* __restrict__ chan_depth, const float* __restrict__ thr,
+    float qmax, int8_t* __restrict__ Xq, int64_t ldq, int R, unsigned magic_qc, unsigned magic_td,
+    unsigned magic_g, float* __restrict__ scale_out, ShotMax mx, DupTail dt) {
+    if (blockIdx.x >= dt.first) {
+        dup_code_byte(dt.Wq, dt.ldw, dt.N, C, g, s, chan_src, (int64_t)(blockIdx.x - dt.first) * kShotNT + threadIdx.x);
+        return;
+    }
+    expand_quantize_shot<U, 1, 0, G1>(X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, R, magic_qc, magic_td,
+                                      magic_g, scale_out, mx);
+}
+
 struct ShotPlan {
     int U = 0, R = 0;
 };
@@ -530,7 +562,7 @@ template <int U, int SCALE, int MAX, bool G1>
 static hipError_t run_expand_quantize_shot(const ShotPlan& p, const float* X, int64_t ldx, int64_t M, int C, int g,
                                            int s, const int32_t* chan_src, const int32_t* chan_depth, const float* thr,
                                            float qmax, int8_t* Xq, int64_t ldq, float* scale_out, hipStream_t stream,
-                                           const ShotMax& mx) {
+                                           const ShotMax& mx, const DupTail* dup) {
     const int64_t K = (int64_t)C * g, Q = K / 4, Qc = (K + 3) / 4, TD = ldq / 4 - Q;
     // floor(2^32 / n), or 2^32 - 1 for n = 1: the quotient estimate is then at most one low, which
     // the kernel's correction step absorbs
@@ -542,6 +574,16 @@ static hipError_t run_expand_quantize_shot(const ShotPlan& p, const float* X, in
     const unsigned magic_td = TD > 0 ? magic_of(TD) : 0u;
     const int64_t image = (p.R * (ldq + 4) + 15) & ~(int64_t)15;
     const unsigned lds = (unsigned)(image + (TD > 0 ? 4 * TD : 1) * (SCALE ? 8 : 4));
+    if constexpr (SCALE == 1 && MAX == 0) {
+        if (dup != nullptr) {
+            DupTail dt = *dup;
+            dt.first = (unsigned)ceil_div(M, p.R);
+            const int64_t grid = dt.first + ceil_div(dt.N * (dt.ldw - K), kShotNT);
+            return launch_kernel(kTimeSplitQuantize, expand_quantize_shot_dup_kernel<U, G1>, dim3((unsigned)grid), dim3(kShotNT),
+                                 lds, stream, X, ldx, (int)M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, p.R, magic_qc,
+                                 magic_td, magic_of(g), scale_out, mx, dt);
+        }
+    }
     return launch_kernel(kTimeSplitQuantize, expand_quantize_shot_kernel<U, SCALE, MAX, G1>, dim3((unsigned)ceil_div(M, p.R)),
                          dim3(kShotNT), lds, stream, X, ldx, (int)M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq,
                          p.R, magic_qc, magic_td, magic_of(g), scale_out, mx);
@@ -549,9 +591,10 @@ static hipError_t run_expand_quantize_shot(const ShotPlan& p, const float* X, in
 template <int SCALE, int MAX, bool G1 = false>
 static hipError_t launch_shot(const ShotPlan& p, const float* X, int64_t ldx, int64_t M, int C, int g, int s,
                               const int32_t* chan_src, const int32_t* chan_depth, const float* thr, float qmax,
-                              int8_t* Xq, int64_t ldq, float* scale_out, hipStream_t stream, const ShotMax& mx) {
+                              int8_t* Xq, int64_t ldq, float* scale_out, hipStream_t stream, const ShotMax& mx,
+                              const DupTail* dup = nullptr) {
 #define OCS_SHOT(U_) \
-    case U_: return run_expand_quantize_shot<U_, SCALE, MAX, G1>(p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx)
+    case U_: return run_expand_quantize_shot<U_, SCALE, MAX, G1>(p, X, ldx, M, C, g, s, chan_src, chan_depth, thr, qmax, Xq, ldq, scale_out, stream, mx, dup)
     switch (p.U) {
         OCS_SHOT(1);
         OCS_SHOT(2);
@@ -954,7 +997,8 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
                                   const int32_t* chan_src, const int32_t* chan_depth,
                                   const float* thr, float qmax, int8_t* Xq, int64_t ldq,
                                   float* scale_out, hipStream_t stream, const float* partials,
-                                  int n_partials, float clip_ratio, bool stepwise, int64_t self) {
+                                  int n_partials, float clip_ratio, bool stepwise, int64_t self, int8_t* dup_codes,
+                                  int64_t ldw, int64_t N) {
     const int64_t K = (int64_t)C * g;
     const bool vec_ok = true;   // 16-byte loads need only the float's own alignment
     const int main_units = (int)(K / 4);
@@ -1000,9 +1044,21 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
             return launch_shot<0, 3>(OCS_SHOT_ARGS);
         }
         if (!halve) return launch_shot<0, 0>(OCS_SHOT_ARGS);
+        if (dup_codes != nullptr && !stepwise && N * (ldw - K) <= (int64_t)1 << 32) {    // (the grid's workgroups stay countable in 32 bits)
+            const DupTail dt = {dup_codes, ldw, N, 0};
+            return g == 1 ? launch_shot<1, 0, true>(OCS_SHOT_ARGS, &dt) : launch_shot<1, 0>(OCS_SHOT_ARGS, &dt);
+        }
+        if (dup_codes != nullptr) {
+            const hipError_t e = launch_dup_code_columns(dup_codes, ldw, N, C, g, s, chan_src, stream);
+            if (e != hipSuccess) return e;
+        }
         if (g == 1) return stepwise ? launch_shot<2, 0, true>(OCS_SHOT_ARGS) : launch_shot<1, 0, true>(OCS_SHOT_ARGS);
         return stepwise ? launch_shot<2, 0>(OCS_SHOT_ARGS) : launch_shot<1, 0>(OCS_SHOT_ARGS);
 #undef OCS_SHOT_ARGS
+    }
+    if (dup_codes != nullptr) {
+        const hipError_t e = launch_dup_code_columns(dup_codes, ldw, N, C, g, s, chan_src, stream);
+        if (e != hipSuccess) return e;
     }
     // Static grid, un-scaled copies: the tile-ordered pass.  Measured against the flat orders below on
     // the paper's layer shapes at batch 256 (inside the whole pass over the network): 4-17 % ahead for

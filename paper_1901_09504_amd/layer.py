@@ -38,6 +38,7 @@ class ExpandedLayer:
         self.scale_w = torch.empty(2, dtype=torch.float32, device=device)
         self.scale_x = torch.empty(2, dtype=torch.float32, device=device)
         self.wmax = torch.empty(1, dtype=torch.float32, device=device)
+        self.xmax = torch.empty(1, dtype=torch.float32, device=device)
         self.ws_w = B.alloc_workspace(self.N, self.K, device)
         self._rows = 0
         self.Xq = self.Y = self.ws_x = None
@@ -146,31 +147,27 @@ class ExpandedLayer:
         in-place change of W needs prepare_weights() or a new tensor to be seen)."""
         M = X.shape[0]
         self._ensure_rows(M)
-        xmax = torch.empty(1, dtype=torch.float32, device=self.device)
-        B.ocs_select_channels(X, M, self.C, self.g, X.stride(0), self.s, self.split_src,
-                              self.chan_src, self.chan_depth, xmax, self.ws_x, stream)
         if self._dup_base is not W:
             # once per weight tensor: its own codes in the first C*g columns (they do not depend
             # on the batch's choice); afterwards only the appended columns are rewritten per batch
             B.ocs_quantize(W, self.N, self.K, W.stride(0), self.bits_w, None, self.clip_ratio_w,
                            self.Wq, self.ldq, self.scale_w, self.ws_w, stream)
             self._dup_base = W
+        if not qa:
+            B.ocs_forward_act(X, M, self.C, self.g, X.stride(0), self.s, self.bits_x, self.clip_ratio_x, self.split_src,
+                              self.chan_src, self.chan_depth, self.xmax, self.Xq, self.ldq, self.scale_x, self.Wq,
+                              self.ldq, self.N, self.bits_w, self.scale_w, acc_out,
+                              0 if acc_out is None else acc_out.stride(0), self.Y, self.N, self.ws_x, stream)
+            return self.Y[:M]
+        B.ocs_select_channels(X, M, self.C, self.g, X.stride(0), self.s, self.split_src,
+                              self.chan_src, self.chan_depth, self.xmax, self.ws_x, stream)
         B.ocs_duplicate_weight_codes(self.Wq, self.ldq, self.N, self.C, self.g, self.s, self.chan_src,
                                      stream)
-        if qa:
-            if self.chan_path is None:
-                self.chan_path = torch.empty(self.C + self.s, dtype=torch.int32, device=self.device)
-            B.ocs_split_act_qa(X, M, self.C, self.g, X.stride(0), self.split_src, self.chan_src,
-                               self.chan_depth, self.chan_path, self.s, self.bits_x, xmax, self.Xq,
-                               self.ldq, self.scale_x, stream)
-            self.qgemm(M, acc_out, stream)
-            return self.Y[:M]
-        # the selector already returned the largest magnitude of the halved activations: with no
-        # clipping that is the threshold, and the pass over X that would recompute it is skipped
-        thr = xmax if self.clip_ratio_x == 1.0 else None
-        B.ocs_split_act(X, M, self.C, self.g, X.stride(0), self.chan_src, self.chan_depth, self.s,
-                        self.bits_x, thr, self.clip_ratio_x, self.Xq, self.ldq, self.scale_x,
-                        self.ws_x, stream)
+        if self.chan_path is None:
+            self.chan_path = torch.empty(self.C + self.s, dtype=torch.int32, device=self.device)
+        B.ocs_split_act_qa(X, M, self.C, self.g, X.stride(0), self.split_src, self.chan_src,
+                           self.chan_depth, self.chan_path, self.s, self.bits_x, self.xmax, self.Xq,
+                           self.ldq, self.scale_x, stream)
         self.qgemm(M, acc_out, stream)
         return self.Y[:M]
 

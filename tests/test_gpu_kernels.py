@@ -1540,3 +1540,40 @@ def test_selection_on_row_blocks(rows, C, g, s, ld_extra):
     got = gpu_split_weights(T, C, g, s, bits=6, want_f32=False)        # the weight pass with the selection in its prologue
     q_ref, sw_ref = ref.quantize(exp["T_out"], 6, ldq=B.ocs_padded_cols((C + s) * g))
     assert np.array_equal(got["Wq"], q_ref) and np.array_equal(got["scale"], sw_ref)
+
+
+# ---- ocs_forward_act: channels chosen on the batch, as one call ---------------------------------------
+
+# The weights' copies in the last workgroups of the pass over X (one and several columns per channel, rows that are not whole
+# groups of four, no split at all: only padding to clear), and as a launch of their own where that pass is another one (rows beyond
+# 8192 values, more appended columns than its table) or the threshold is not the selection's (clip).
+@pytest.mark.parametrize("M,C,g,s,N,clip", [
+    (70, 256, 1, 13, 64, 1.0), (33, 61, 1, 7, 100, 1.0), (40, 30, 9, 4, 17, 1.0), (9, 64, 1, 0, 5, 1.0), (5, 7900, 1, 9, 8, 1.0),
+    (17, 900, 10, 2, 6, 1.0), (50, 128, 9, 100, 33, 1.0), (64, 100, 1, 5, 48, 0.8), (1, 1, 1, 1, 1, 1.0)])
+def test_forward_act_as_one_call(M, C, g, s, N, clip):
+    rng = np.random.default_rng(M + C + N)
+    K, Ke, bits_w = C * g, (C + s) * g, 6
+    X, W = _tensor(rng, M, K, "heavy"), _tensor(rng, N, K, "normal")
+    sel = ref.split_weights(X, C, g, s)
+    cs, cd = sel["chan_src"].astype(np.int32), sel["chan_depth"].astype(np.int32)
+    ldq = B.ocs_padded_cols(Ke)
+    wq, sw = ref.quantize(W, bits_w, ldq=ldq)
+    Wq_ref = np.zeros((N, ldq), np.int8)
+    Wq_ref[:, :Ke] = wq[:, :K].reshape(N, C, g)[:, cs, :].reshape(N, Ke)
+    T = float(np.float32(sel["max"])) if clip == 1.0 else None
+    Xq_ref, sx_ref, _ = ref.split_act(X, C, g, cs, cd, s, 8, threshold=T, clip_ratio=clip, ldq=ldq)
+    acc_ref, y_ref = ref.qgemm(Xq_ref, Wq_ref, Ke, sx_ref[1], sw[1])
+    wd = torch.full((N, ldq), 55, dtype=torch.int8, device="cuda")
+    wd[:, :K] = dev(wq)[:, :K]
+    i32 = dict(dtype=torch.int32, device="cuda")
+    ss, csd, cdd = torch.full((max(s, 1),), -7, **i32), torch.full((C + s,), -7, **i32), torch.full((C + s,), -7, **i32)
+    mx, sx = torch.zeros(1, device="cuda"), torch.zeros(2, device="cuda")
+    q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+    Y, acc = torch.zeros((M, N), device="cuda"), torch.zeros((M, N), **i32)
+    B.ocs_forward_act(dev(X), M, C, g, K, s, 8, clip, ss, csd, cdd, mx, q, ldq, sx, wd, ldq, N, bits_w, dev(sw), acc, N, Y, N,
+                      B.alloc_workspace(M, K))
+    assert np.array_equal(host(ss)[:s], sel["split_src"]) and np.array_equal(host(csd), cs) and np.array_equal(host(cdd), cd)
+    assert np.array_equal(host(wd), Wq_ref) and np.array_equal(host(q), Xq_ref)
+    assert np.array_equal(host(sx).view(np.uint32), sx_ref.view(np.uint32))
+    assert np.array_equal(host(acc), acc_ref)
+    assert_y_close(host(Y), y_ref)
