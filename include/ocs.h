@@ -300,9 +300,10 @@ int ocs_qgemm(const int8_t *Xq, int64_t ldx, const int8_t *Wq, int64_t ldw, int6
  * One quantized layer as one call: ocs_split_act (copies un-scaled, as on the activation side of Eq. 3) and ocs_qgemm on
  * its codes, with the arguments those take.  threshold: device float, or NULL for the batch's own maximum times
  * clip_ratio (workspace as for ocs_split_act then; it may be NULL with a threshold).  Leaves what the two calls leave:
- * Xq [M, ldq] with its padding, scale_x_out {T, T / qmax}, Y and, if given, acc_out, bit for bit.  Layers of few output tiles run
- * as one launch (plus the max|X| pass where it has to be one); where Y, acc_out or Xq share memory with X or the
- * threshold, and on every other shape, the two launches run.
+ * Xq [M, ldq] with its padding, scale_x_out {T, T / qmax}, Y and, if given, acc_out, bit for bit.  Layers of few output tiles, and
+ * layers of many long rows with up to 256 outputs, run as one launch (plus the max|X| pass where it has to be one); where Y,
+ * acc_out, Xq or scale_x_out share memory with X, the threshold, chan_src or (for the batch's own maximum) the workspace, and on
+ * every other shape, the two launches run.
  */
 int ocs_forward(const float *X, int64_t M, int C, int g, int64_t ldx, const int32_t *chan_src,
                 int num_splits, int bits_x, const float *threshold, float clip_ratio, int8_t *Xq,
@@ -527,7 +528,8 @@ int ocs_calib_mfma(const void *operands, int iters, int workgroups, void *sink, 
  * ocs_qgemm / ocs_qconv: 6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23 to 29, for ocs_qconv 30 to 32; an id a shape cannot use falls
  * back to one it can), "fused_variant" (ocs_split_act_qgemm with more than 128 output columns:
  * 1 = 64-row workgroups, 2 = 128-row ones), "fused_stride" (rows between that kernel's workgroups: 0 = a
- * whole tile always, n > 0 = n).  value < 0 restores the default.  Returns OCS_OK or OCS_E_MODE for an
+ * whole tile always, n > 0 = n), "slice_layer" and "panel_layer" (ocs_forward as one launch, of few tiles and of many rows: 1 =
+ * wherever it serves, 0 = never).  value < 0 restores the default.  Returns OCS_OK or OCS_E_MODE for an
  * unknown key.  The settings belong to the calling thread and affect its own calls only.
  */
 int ocs_tune(const char *key, int value);

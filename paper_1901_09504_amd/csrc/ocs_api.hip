@@ -415,6 +415,30 @@ static int check_split_act(const float* X, int64_t M, int C, int g, int64_t ldx,
     return OCS_OK;
 }
 
+// The maxima a per-batch grid is folded from: *out[0 .. *n).
+static hipError_t per_batch_maxima(const float* X, int64_t M, int64_t K, int64_t ldx, void* workspace, hipStream_t st,
+                                   const float** out, int* n) {
+    Workspace w = plan_workspace(M, K);
+    float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
+    hipError_t e = launch_absmax_partials(X, M, K, ldx, partial, n, st);
+    if (e != hipSuccess) return e;
+    // From 160 MB on the maxima are folded into one word by a launch of their own where the streaming pass's
+    // one-shot workgroups, far too many and too short there, had better not fold them: the few thousand of a
+    // strided tensor (400000 x 300 at a pitch of 316: 249 -> 222 us; below that size the launch costs what the
+    // faster pass gains), and for the narrowest rows (5 million x 12 120 -> 114 us).  Other contiguous
+    // tensors leave 256 that cost their workgroups less than a launch.
+    const int64_t cap = (int64_t)(w.total - w.partial_off) / 4;
+    const bool fold = (*n > 256 || K < 24) && M * K >= ((int64_t)40 << 20);
+    if (*n > 1 && *n < cap && (fold || tuning().max_flat == 2)) {   // (max_flat 2: always, for tests)
+        e = launch_fold_max(partial, *n, partial + *n, st);
+        if (e != hipSuccess) return e;
+        partial += *n;
+        *n = 1;
+    }
+    *out = partial;
+    return hipSuccess;
+}
+
 int ocs_split_act(const float* X, int64_t M, int C, int g, int64_t ldx, const int32_t* chan_src,
                   const int32_t* chan_depth, int num_splits, int bits, const float* threshold,
                   float clip_ratio, int8_t* Xq, int64_t ldq, float* scale_out, void* workspace,
@@ -429,8 +453,7 @@ int ocs_split_act(const float* X, int64_t M, int C, int g, int64_t ldx, const in
         // X's own.  One pass leaves per-workgroup maxima, the streaming pass folds them itself.
         rc = check_workspace(workspace, ws_bytes, M, (int64_t)C * g);
         if (rc) return rc;
-        Workspace w = plan_workspace(M, (int64_t)C * g);
-        float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
+        const float* maxima = nullptr;
         int n = 0;
         hipError_t e;
         if (act_self_max_serves(M, C, g, num_splits, ldx, ldq, chan_src)) {
@@ -438,23 +461,10 @@ int ocs_split_act(const float* X, int64_t M, int C, int g, int64_t ldx, const in
                                        st, nullptr, 0, clip_ratio, false, M * (int64_t)C * g);
             return e == hipSuccess ? OCS_OK : hip_fail(e);
         }
-        e = launch_absmax_partials(X, M, (int64_t)C * g, ldx, partial, &n, st);
+        e = per_batch_maxima(X, M, (int64_t)C * g, ldx, workspace, st, &maxima, &n);
         if (e != hipSuccess) return hip_fail(e);
-        // From 160 MB on the maxima are folded into one word by a launch of their own where the streaming pass's
-        // one-shot workgroups, far too many and too short there, had better not fold them: the few thousand of a
-        // strided tensor (400000 x 300 at a pitch of 316: 249 -> 222 us; below that size the launch costs what the
-        // faster pass gains), and for the narrowest rows (5 million x 12 120 -> 114 us).  Other contiguous
-        // tensors leave 256 that cost their workgroups less than a launch.
-        const int64_t cap = (int64_t)(w.total - w.partial_off) / 4, K = (int64_t)C * g;
-        const bool fold = (n > 256 || K < 24) && M * K >= ((int64_t)40 << 20);
-        if (n > 1 && n < cap && (fold || tuning().max_flat == 2)) {   // (max_flat 2: always, for tests)
-            e = launch_fold_max(partial, n, partial + n, st);
-            if (e != hipSuccess) return hip_fail(e);
-            partial += n;
-            n = 1;
-        }
         e = launch_expand_quantize(X, ldx, M, C, g, num_splits, chan_src, nullptr, nullptr, qmax, Xq,
-                                   ldq, scale_out, st, partial, n, clip_ratio);
+                                   ldq, scale_out, st, maxima, n, clip_ratio);
         if (e != hipSuccess) return hip_fail(e);
         return OCS_OK;
     }
@@ -553,12 +563,16 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
         if (rc) return rc;
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // One launch reads X while outputs are being written: an output that shares memory with X or with the threshold (a
-    // layer applied to its own output) keeps the two, the first of which has read both before the second begins.
+    // One launch reads X while outputs are being written: an output that shares memory with X, the threshold, the sources or the
+    // maxima (a layer applied to its own output) keeps the two, the first of which has read them all before the second begins.
     const int64_t xb = 4 * ((M - 1) * ldx + K), yb = 4 * ((M - 1) * ldy + N), ab = 4 * ((M - 1) * ldacc + N), qb = M * ldq;
-    const bool apart = !overlap(X, xb, Y, yb) && !overlap(X, xb, acc_out, ab) && !overlap(X, xb, Xq, qb) && !overlap(X, xb, scale_x_out, 8) &&
-                       !overlap(threshold, 4, Y, yb) && !overlap(threshold, 4, acc_out, ab) && !overlap(threshold, 4, Xq, qb) &&
-                       !overlap(threshold, 4, scale_x_out, 8);
+    auto clear_of_outputs = [&](const void* in, int64_t bytes) {
+        return !overlap(in, bytes, Y, yb) && !overlap(in, bytes, acc_out, ab) && !overlap(in, bytes, Xq, qb) &&
+               !overlap(in, bytes, scale_x_out, 8);
+    };
+    const bool apart = clear_of_outputs(X, xb) && clear_of_outputs(threshold, 4) &&
+                       clear_of_outputs(num_splits > 0 ? chan_src : nullptr, 4 * (int64_t)(C + num_splits)) &&
+                       clear_of_outputs(threshold == nullptr ? workspace : nullptr, (int64_t)ws_bytes);
     const Tuning& tn = tuning();
     const bool tuned = tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0;   // (launch shapes of the two)
     if (apart && !tuned && slice_layer_pays(M, C, g, num_splits, N, ldx)) {
@@ -579,6 +593,18 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
         }
         e = launch_slice_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, self, clip_ratio, qmax_of(bits_x), Xq, ldq,
                                scale_x_out, Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
+        return e == hipSuccess ? OCS_OK : hip_fail(e);
+    }
+    if (apart && !tuned && panel_layer_pays(X, ldx, M, C, g, num_splits, ldq, ldw, N)) {
+        const float* thr = threshold;
+        int n = 0;
+        hipError_t e = hipSuccess;
+        if (threshold == nullptr) {
+            e = per_batch_maxima(X, M, K, ldx, workspace, st, &thr, &n);
+            if (e != hipSuccess) return hip_fail(e);
+        }
+        e = launch_panel_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, clip_ratio, qmax_of(bits_x), Xq, ldq, scale_x_out,
+                               Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
         return e == hipSuccess ? OCS_OK : hip_fail(e);
     }
     rc = ocs_split_act(X, M, C, g, ldx, chan_src, nullptr, num_splits, bits_x, threshold, clip_ratio, Xq, ldq, scale_x_out,
@@ -883,6 +909,7 @@ int ocs_tune(const char* key, int value) {
     else if (!strcmp(key, "fused_variant")) t.fused_variant = value;
     else if (!strcmp(key, "fused_stride")) t.fused_stride = value;
     else if (!strcmp(key, "slice_layer")) t.slice_layer = value;
+    else if (!strcmp(key, "panel_layer")) t.panel_layer = value;
     else if (!strcmp(key, "max_flat")) t.max_flat = value;
     else if (!strcmp(key, "max_grid")) t.max_grid = value;
     else if (!strcmp(key, "max_un")) t.max_un = value;

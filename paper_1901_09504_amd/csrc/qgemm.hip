@@ -1804,6 +1804,409 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 #undef OCS_FUSED_ARGS
 }
 
+// ---------------------------------------------------------------------------------------------
+// The layer of many rows as one launch with two kinds of waves (ocs_forward; codes included).  The two launches write every code
+// and read it back; in the row-tile kernel above every wave requests, quantizes, meets the others and multiplies in turn, one
+// step of X ahead, and with the codes written as well it is behind the two (25088 x 1024 -> 256 55.9 us against 39.4).  Here
+// NQ waves only quantize: they hold no accumulators, so a step of 128 columns of X is on its way in their registers, each
+// register requested again as soon as it is read (with two steps they spill: 57 us).  Floats through LDS instead cost it as much
+// again as the fragments do (25088 x 1024 -> 256 39.8 us).  The other waves multiply, and request the weight codes straight
+// into LDS a step ahead: neither kind waits for the other's memory, and a step costs one barrier.  A workgroup of 128 rows on
+// every compute unit; the next tile's first steps are requested before the last one's outputs are written.
+// The copies of the split channels are moved byte by byte, by the wave that quantizes their rows, into the steps that follow X's
+// whole ones (`tail`), next to the columns left over after those; the tail is multiplied last.
+// Bounded by what the compute units draw from memory: X, codes and outputs at 4.5 TB/s (25088 x 1024 -> 256 40.5 -> 34.7 us for
+// the layer), 4.9 (50176 x 2304 -> 256 150 -> 135), 5.5 behind a max|X| pass that left X in the last-level cache (50176 x 1024 ->
+// 256 99 -> 88 with that pass); with X's requests switched off 25 us of the first remain, with the weights' 36.
+// ---------------------------------------------------------------------------------------------
+struct PanelLayer {
+    const float* X;
+    int64_t ldx;
+    int M, C, g, s;
+    const int32_t* chan_src;
+    const float* thr;          // the threshold (n_max == 0), or n_max maxima
+    int n_max;
+    float clip, qmax;
+    int8_t* Xq;
+    int64_t ldq;
+    float* scale_x;
+    const int8_t* Wq;
+    int64_t ldw;
+    int N;
+    const float* scale_w;
+    int32_t* acc_out;
+    int64_t ldacc;
+    float* Y;
+    int64_t ldy;
+    int kmain, kall, rem;      // whole steps of X; steps with the tail; X's columns after the whole steps
+    int stride, rpw;           // rows of a workgroup (<= BM) and of each of its quantizing waves
+    int tail_off, list_off, stage_off, tiles;
+};
+
+constexpr int kPanelMaxTail = 256;     // appended columns s*g
+
+template <int BM, int BN, int BK, int NQ, int WAVES_M, int WAVES_N, int RA>
+__global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_kernel(PanelLayer p) {
+    constexpr int NM = WAVES_M * WAVES_N;
+    constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
+    constexpr int CPR = BK / 16, LG = BK == 64 ? 6 : 7;      // 16-byte pieces of a row of codes
+    constexpr int LPR = BK / 4, RPL = 64 / LPR;              // X: lanes per row, rows per request
+    constexpr int RPW = BM / NQ, LA = RPW / RPL;             // rows and requests of a step per quantizing wave
+    constexpr int LB = BN * BK / 1024 / NM;                  // requests of a step of W per multiplying wave
+    static_assert(BK == 64 || BK == 128, "steps of half or whole lines of codes");
+    static_assert(TM >= 1 && TN >= 1 && TM * 32 * WAVES_M == BM && TN * 32 * WAVES_N == BN && LA >= 1 && LB >= 1, "tile");
+    static_assert(NQ + NM <= 16, "waves of a workgroup");
+
+    extern __shared__ __align__(1024) int8_t plds[];
+    int8_t* codes = plds;
+    int8_t* wring = codes + 2 * BM * BK;
+    int8_t* tail = plds + p.tail_off;
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((address_space(3))) int8_t* lptr_t;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lptr_t)&plds[0];
+#else
+    const unsigned lds0 = 0;
+#endif
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tail_steps = p.kall - p.kmain, nx = p.kmain + (p.rem > 0 ? 1 : 0);
+    // Rows of whole 4096 bytes: from the same step on in every workgroup, all addresses under way are alike in their low bits, and
+    // meet on few of the memory's channels.  Each workgroup begins at another step (25088 x 1024 -> 256 37.9 -> 35.0 us), scattered,
+    // since the channel also depends on the higher bits: with step = workgroup mod steps 32768 x 2048, a megabyte apart, took 108 us
+    // for 75.  Other pitches spread by themselves and gain from rows read in one direction (200000 x 256 70.6 us, 89.4 turned).
+    const int turn = p.kmain > 0 && p.ldx % 1024 == 0 ? (int)((blockIdx.x * 2654435761u >> 16) % (unsigned)p.kmain) : 0;
+    auto step_of = [&](int it) -> int { return it >= p.kmain ? it : (it + turn < p.kmain ? it + turn : it + turn - p.kmain); };
+    const bool multiplier = wave >= NQ;
+    const int mw = multiplier ? wave - NQ : 0;
+
+    // the barrier of a step: LDS accesses of this wave done, requests to memory still on their way
+    auto step_barrier = [&]() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // the threshold, folded from its maxima by each wave for itself: no barrier before the first step
+    auto threshold = [&]() -> float {
+        if (p.n_max == 0) return *p.thr;
+        float m = 0.0f;
+        for (int i0 = lane; i0 < p.n_max; i0 += 256) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = p.thr[i0 + 64 * u < p.n_max ? i0 + 64 * u : p.n_max - 1];
+            m = fmaxf(fmaxf(fmaxf(m, v[0]), fmaxf(v[1], v[2])), v[3]);
+        }
+        return p.clip * __uint_as_float(wave_umax32(__float_as_uint(m)));
+    };
+
+    if (multiplier) {
+        // W: request u of multiplying wave f fills block u * NM + f of the step (the swizzle is the same for every u)
+        static_assert(BK == 64 || NM % 2 == 0, "the blocks of a wave begin at rows of one parity");
+        unsigned wsrc[LB];
+        const int w_end = (int)(p.ldw / 16);
+        const int wpiece = swz<BK>((mw * 64 + lane) / CPR, lane % CPR);
+#pragma unroll
+        for (int u = 0; u < LB; ++u)                         // (N <= 512 rows of at most kFusedMaxK + kFusedMaxTail codes and their padding)
+            wsrc[u] = (unsigned)col_clamp(((u * NM + mw) * 64 + lane) / CPR, p.N) * (unsigned)p.ldw;
+        const unsigned w0 = lds0 + (unsigned)(2 * BM * BK + mw * 1024);
+        auto fetch_w = [&](int kt) {
+            const int q = step_of(kt) * CPR + wpiece;
+            const int8_t* base = p.Wq + (int64_t)q * 16;
+            const unsigned slot = w0 + (unsigned)((kt & 1) * (BN * BK));
+#pragma unroll
+            for (int u = 0; u < LB; ++u) lds_dma16(q < w_end ? base + wsrc[u] : zero_chunk, slot + u * (NM * 1024));
+        };
+        fetch_w(0);
+        const int wm = mw / WAVES_N, wn = mw % WAVES_N;
+        const int frag_row = lane & 31, frag_half = lane >> 5;
+        int32_t* stage = reinterpret_cast<int32_t*>(plds + p.stage_off) + mw * (8 * WN);
+        i32x16 acc[TM][TN];
+        i32x4 fa[2][TM], fb[2][TN];
+        for (int tile = (int)blockIdx.x; tile < p.tiles; tile += (int)gridDim.x) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
+            for (int kt = 0; kt < p.kall; ++kt) {
+                wait_vmcnt<0>();                                 // this wave's part of the step's weight codes
+                step_barrier();
+                const int8_t* am = kt < p.kmain ? codes + (kt & 1) * (BM * BK) : tail + (kt - p.kmain) * (BM * BK);
+                const int8_t* wb = wring + (kt & 1) * (BN * BK);
+                auto read_slice = [&](int ks) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) {
+                        const int r = wm * WM + i * 32 + frag_row;
+                        fa[ks & 1][i] = *reinterpret_cast<const i32x4*>(&am[r * BK + swz<BK>(r, ks * 2 + frag_half) * 16]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int r = wn * WN + j * 32 + frag_row;
+                        fb[ks & 1][j] = *reinterpret_cast<const i32x4*>(&wb[r * BK + swz<BK>(r, ks * 2 + frag_half) * 16]);
+                    }
+                };
+                read_slice(0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (kt + 1 < p.kall) fetch_w(kt + 1);            // into the slot multiplied before this barrier
+#pragma unroll
+                for (int ks = 0; ks < BK / 32; ++ks) {
+                    if (ks + 1 < BK / 32) read_slice(ks + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = mfma_tile<false>(fa[ks & 1][i], fb[ks & 1][j], acc[i][j]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            step_barrier();                                      // the tile's operands have been read: the next one's may come
+            if (tile + (int)gridDim.x < p.tiles) fetch_w(0);
+            const int row0 = tile * p.stride, row_end = row0 + p.stride < p.M ? row0 + p.stride : p.M;
+            const float scale = (threshold() / p.qmax) * p.scale_w[1];
+            emit_tile<false, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, wn * WN, wn * WN, row_end, p.N, scale, p.Y, p.ldy,
+                                        p.acc_out, p.ldacc, Requant{}, 0.0f, nullptr, 0, false, row0 + BM <= row_end && BN <= p.N);
+        }
+        return;
+    }
+
+    // the appended columns' sources, up to ET a lane: expanded column C g + e is a copy of column col[e / 64] of lane e % 64
+    constexpr int ET = kPanelMaxTail / 64;
+    const int T = p.s * p.g;
+    int col[ET];
+#pragma unroll
+    for (int q = 0; q < ET; ++q) {
+        const int e = q * 64 + lane, j = e / p.g;
+        col[q] = e < T ? col_clamp(p.chan_src[p.C + j], p.C) * p.g + (e - j * p.g) : -1;
+    }
+    const float Tx = threshold();
+    const float inv = inv_step_of(Tx, p.qmax);
+    if (blockIdx.x == 0 && tid == 0) {
+        p.scale_x[0] = Tx;
+        p.scale_x[1] = Tx / p.qmax;
+    }
+    int* list = reinterpret_cast<int*>(plds + p.list_off) + wave * kPanelMaxTail;
+    const int c4 = (lane % LPR) * 4;
+    int own;                                                 // rows of the tile this wave quantizes (none: <= 0)
+    unsigned xoff[LA], qoff[LA];                             // bytes from the tile's first row of X, of the codes (ldx, ldq < 2^23)
+    int at[LA];                                              // this lane's four codes inside a step's buffer
+    const char* xbase;
+    char* qbase;
+    f32x4 av[RA][LA];
+    auto load_x = [&](int kt, int u) -> f32x4 {
+        const bool main_step = kt < p.kmain, rest = kt == p.kmain && c4 < p.rem;
+        // left-over columns: four floats that would cross the row's end start four before it (K >= 64) and are shifted into
+        // place when they are used; nothing to request: sixteen zero bytes
+        const int off = rest && c4 + 3 >= p.rem ? p.rem - 4 - c4 : 0;
+        const float* src = main_step || rest ? reinterpret_cast<const float*>(xbase + (int64_t)step_of(kt) * (4 * BK) + xoff[u]) + off
+                                             : reinterpret_cast<const float*>(zero_chunk);
+        return __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(src));
+    };
+    // X: request u of a step covers RPL rows of the wave, LPR lanes each.  Rows that do not exist repeat the last one that
+    // does, codes and all, so that no request and no write has a condition; a wave without any row does nothing.
+    auto begin = [&](int tile) {
+        const int row0 = tile * p.stride, row_end = row0 + p.stride < p.M ? row0 + p.stride : p.M;
+        own = row_end - row0 - wave * p.rpw;
+        own = own < p.rpw ? own : p.rpw;
+        xbase = reinterpret_cast<const char*>(p.X + (int64_t)row0 * p.ldx);
+        qbase = reinterpret_cast<char*>(p.Xq + (int64_t)row0 * p.ldq);
+        if (own <= 0) return;
+#pragma unroll
+        for (int u = 0; u < LA; ++u) {
+            int r = u * RPL + lane / LPR;
+            r = wave * p.rpw + (r < own ? r : own - 1);
+            xoff[u] = ((unsigned)r * (unsigned)p.ldx + (unsigned)c4) * 4u;
+            qoff[u] = (unsigned)r * (unsigned)p.ldq + (unsigned)c4;
+            at[u] = r * BK + swz<BK>(r, c4 >> 4) * 16 + (c4 & 15);
+        }
+#pragma unroll
+        for (int k = 0; k < RA; ++k)
+#pragma unroll
+            for (int u = 0; u < LA; ++u) av[k][u] = load_x(k, u);
+    };
+    auto code4 = [&](const f32x4& v) -> unsigned {
+        return pack4(code_bits(v[0], inv, p.qmax), code_bits(v[1], inv, p.qmax), code_bits(v[2], inv, p.qmax), code_bits(v[3], inv, p.qmax));
+    };
+    auto quantize = [&](int it, int u, const f32x4& v) {
+        const unsigned q4 = code4(v);
+        *reinterpret_cast<unsigned*>(codes + (it & 1) * (BM * BK) + at[u]) = q4;
+        __builtin_nontemporal_store(q4, reinterpret_cast<unsigned*>(qbase + (int64_t)step_of(it) * BK + qoff[u]));
+    };
+    // The copies of this wave's rows whose sources step it holds (a wave's LDS accesses execute in order: no barrier)
+    auto copies = [&](int it) {
+        const int step = step_of(it);
+        int n = 0;
+#pragma unroll
+        for (int q = 0; q < ET; ++q) {
+            const bool here = (col[q] >> LG) == step;          // (-1 >> LG is no step)
+            const unsigned long long m = __ballot(here);
+            const int to = n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+            if (here) list[to] = ((q * 64 + lane) << LG) | (col[q] & (BK - 1));
+            n += __popcll(m);
+        }
+        const int8_t* am = it < p.kmain ? codes + (it & 1) * (BM * BK) : tail;
+        for (int idx = lane; idx < n * RPW; idx += 64) {
+            const int en = list[idx / RPW], r = wave * p.rpw + idx % RPW, e = p.rem + (en >> LG), c = en & (BK - 1), te = e & (BK - 1);
+            if (idx % RPW < own)
+                tail[(e >> LG) * (BM * BK) + r * BK + swz<BK>(r, te >> 4) * 16 + (te & 15)] =
+                    am[r * BK + swz<BK>(r, c >> 4) * 16 + (c & 15)];
+        }
+    };
+
+    begin((int)blockIdx.x);
+    for (int tile = (int)blockIdx.x; tile < p.tiles; tile += (int)gridDim.x) {
+        const bool live = own > 0;
+        if (live) {                                          // this wave's rows of the tail
+            for (int o = lane; o < tail_steps * RPW * CPR; o += 64) {
+                const int k = o / (RPW * CPR), r = o / CPR % RPW, c = o % CPR;
+                const i32x4 z = {0, 0, 0, 0};
+                if (r < own) *reinterpret_cast<i32x4*>(&tail[k * (BM * BK) + (wave * p.rpw + r) * BK + c * 16]) = z;
+            }
+        }
+        int it0 = 0;
+        if (live && p.kmain >= 2 * RA) {
+            // steps whose requests ahead are whole ones, without a condition; the first RA of them by themselves: the requests
+            // and writes under way are then the same number on every way into the loop, and its waits no stricter than they must be
+            auto steps = [&]() {
+#pragma unroll
+                for (int k = 0; k < RA; ++k) {
+#pragma unroll
+                    for (int u = 0; u < LA; ++u) {
+                        quantize(it0 + k, u, av[k][u]);
+                        av[k][u] = __builtin_nontemporal_load(
+                            reinterpret_cast<const f32x4u*>(xbase + (int64_t)step_of(it0 + k + RA) * (4 * BK) + xoff[u]));
+                        __builtin_amdgcn_sched_barrier(0);   // (or the arithmetic of later steps, and its waits, move ahead)
+                    }
+                    copies(it0 + k);
+                    step_barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                it0 += RA;
+            };
+            steps();
+            while (it0 + 2 * RA <= p.kmain) steps();
+        }
+        for (; it0 < nx; it0 += RA) {
+#pragma unroll
+            for (int k = 0; k < RA; ++k) {
+                const int it = it0 + k;
+                if (it >= nx) break;
+                if (live && it < p.kmain) {
+#pragma unroll
+                    for (int u = 0; u < LA; ++u) {
+                        quantize(it, u, av[k][u]);
+                        av[k][u] = load_x(it + RA, u);
+                    }
+                    copies(it);
+                } else if (live) {
+#pragma unroll
+                    for (int u = 0; u < LA; ++u) {
+                        const unsigned q4 = code4(av[k][u]);
+                        if (c4 + 3 < p.rem) {
+                            *reinterpret_cast<unsigned*>(tail + at[u]) = q4;
+                        } else {
+                            const int d = c4 - (p.rem - 4);  // (fetched as columns rem - 4 .. rem - 1)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (c4 + e < p.rem) tail[at[u] + e] = (int8_t)((q4 >> (8 * (e + d))) & 0xFFu);
+                        }
+                    }
+                    copies(it);
+                }
+                step_barrier();
+            }
+        }
+        // what follows the whole steps of a row: left-over columns, copies, and zeros up to the pitch (this wave's rows of the
+        // tail are complete)
+        if (live) {
+            const int pieces = (int)(p.ldq / 16) - p.kmain * CPR;
+            for (int idx = lane; idx < own * pieces; idx += 64) {
+                const int r = wave * p.rpw + idx / pieces, c = idx % pieces;
+                i32x4 q = {0, 0, 0, 0};
+                if (c < tail_steps * CPR)
+                    q = *reinterpret_cast<const i32x4*>(&tail[(c / CPR) * (BM * BK) + r * BK + swz<BK>(r, c % CPR) * 16]);
+                *reinterpret_cast<i32x4*>(qbase + (int64_t)r * p.ldq + (int64_t)p.kmain * BK + c * 16) = q;
+            }
+        }
+        if (tile + (int)gridDim.x < p.tiles) begin(tile + (int)gridDim.x);
+        for (int it = nx; it < p.kall + 1; ++it) step_barrier();         // the tail's steps, and the last of the operands
+    }
+}
+
+template <int BM, int BN, int BK, int NQ, int WAVES_M>
+static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
+    const int64_t tail = 2 * (BM + BN) * BK, list = tail + tail_steps * BM * BK, stage = list + NQ * kPanelMaxTail * 4;
+    if (p != nullptr) {
+        p->tail_off = (int)tail;
+        p->list_off = (int)list;
+        p->stage_off = (int)stage;
+    }
+    return stage + WAVES_M * 8 * BN * 4;
+}
+
+template <int BM, int BN, int BK, int NQ, int WAVES_M, int WAVES_N, int RA>
+static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
+    const int64_t K = (int64_t)p.C * p.g, Kexp = (int64_t)(p.C + p.s) * p.g;
+    p.kmain = (int)(K / BK);
+    p.kall = (int)ceil_div(Kexp, BK);
+    p.rem = (int)(K - (int64_t)p.kmain * BK);
+    const int64_t o = panel_lds<BM, BN, BK, NQ, WAVES_M>(p.kall - p.kmain, &p);
+    if (o > kWholeKMaxLds) return hipErrorInvalidValue;
+    static std::atomic<bool> opted_in[kMaxDevices];
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    if (!opted_in[dev].load(std::memory_order_acquire)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, BK, NQ, WAVES_M, WAVES_N, RA>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
+        if (e != hipSuccess) return e;
+        opted_in[dev].store(true, std::memory_order_release);
+    }
+    // a workgroup on every compute unit, rounds of tiles as even as they can be, no more than half of a tile idle
+    const int64_t slots = compute_units(), rounds = ceil_div(p.M, slots * BM);
+    int64_t st = ceil_div(p.M, slots * rounds);
+    st = st < BM / 2 ? BM / 2 : (st > BM ? BM : st);
+    p.stride = (int)st;
+    p.rpw = (int)ceil_div(st, NQ);
+    p.tiles = (int)ceil_div(p.M, st);
+    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, BK, NQ, WAVES_M, WAVES_N, RA>,
+                         dim3((unsigned)(p.tiles < slots ? p.tiles : slots)), dim3((NQ + WAVES_M * WAVES_N) * 64), (unsigned)o, stream, p);
+}
+
+static bool panel_fits(int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq, int64_t ldw, int64_t N) {
+    const int64_t K = (int64_t)C * g, T = (int64_t)s * g, pitch = (int64_t)1 << 23;      // (offsets of 128 rows in 32 bits)
+    if (K < 64 || T > kPanelMaxTail || N > 256 || M > 0x7FFFFFFF - 256 || ldx >= pitch || ldq >= pitch || ldw >= pitch) return false;
+    const int64_t tail_steps = ceil_div(K + T, 128) - K / 128;
+    return panel_lds<128, 256, 128, 8, 2>(tail_steps, nullptr) <= kWholeKMaxLds;         // (the widest)
+}
+
+hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
+                              const float* thr, int n_max, float clip, float qmax, int8_t* Xq, int64_t ldq,
+                              float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
+                              int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream) {
+    PanelLayer p;
+    p.X = X; p.ldx = ldx; p.M = (int)M; p.C = C; p.g = g; p.s = s;
+    p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
+    p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
+    p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
+    if (N <= 64) return run_panel<128, 64, 128, 8, 4, 2, 1>(p, stream);
+    if (N <= 128) return run_panel<128, 128, 128, 8, 2, 4, 1>(p, stream);
+    return run_panel<128, 256, 128, 8, 2, 4, 1>(p, stream);
+}
+
+// Where the one launch is ahead of the two (two launches / one, passes one after the other, inputs rotating; static grid, per batch):
+//   rows per compute unit  K = 512, N = 64: 64 1.01, 0.90; 80 1.16, 1.10; 98 1.25, 1.15; 130 1.06, 1.05; 196 1.10, 1.08.  K = 1024,
+//                N = 256: 64 0.91, 0.96; 98 1.11, 1.12; 128 1.13, 1.16; 196 1.04, 1.13.  K = 2304, N = 256: 64 0.80, 0.94; 98 0.99,
+//                1.07; 130 0.96, 1.06; 165 1.05, 1.18; 260 1.08, 1.10.  A workgroup per compute unit and 128 rows of tile: with fewer
+//                than 96 rows, or just over 128 (two rounds of half a tile), the weights are read again for too little.
+//   columns      N = 64: K = 192 1.09, 0.97 at 98 rows and 0.87, 0.94 at 196; 256 1.10, 1.04 and 0.95, 0.98; 384 1.25, 1.13 and 1.09, 1.07.
+//   whole lines  rows that begin inside one share it with their neighbour's last step, which reads it again: K = 400, N = 64 1.00, 0.94 at
+//                165 rows, K = 1000 0.96, 0.99.
+bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq, int64_t ldw, int64_t N) {
+    const int mode = tuning().panel_layer;
+    if (mode == 0 || !panel_fits(ldx, M, C, g, s, ldq, ldw, N)) return false;
+    if (mode > 0) return true;
+    const int64_t K = (int64_t)C * g, cus = compute_units();
+    if (K < 384 || K % 64 != 0 || ldx % 32 != 0 || reinterpret_cast<uintptr_t>(X) % 128 != 0) return false;
+    return (M >= 96 * cus && M <= 128 * cus) || M >= 160 * cus;
+}
+
 
 // Dynamic LDS of a whole-K launch: operands (or the epilogue's staging area, if larger) and,
 // when the output goes to the next layer as codes with copies, the table of those copies

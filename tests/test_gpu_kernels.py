@@ -1510,6 +1510,65 @@ def test_forward_over_its_own_input():
     assert_y_close(host(buf), y_ref)
 
 
+# ---- ocs_forward on many rows: quantizing and multiplying waves in one launch ------------------------
+
+def _panel(mode, fn):
+    B.ocs_tune("panel_layer", mode)
+    try:
+        fn()
+    finally:
+        B.ocs_tune("panel_layer", -1)
+
+
+# Steps of 128 columns: none whole, one, two (the loop without conditions needs two), left-over columns of 1, 3, 4 and 127 that share
+# their step with copies, none left over; copies in one, two and three steps, none, the most (256); rows around the waves' sixteen,
+# the tile's 128 and half of it; outputs around 32, 64, 128, 256; strided rows, padded code rows; rows of 4096 bytes (another
+# first step per workgroup); more tiles than compute units.
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra,ldq_extra", [
+    (1, 64, 1, 0, 1, 0, 0), (17, 65, 1, 3, 33, 1, 0), (63, 127, 1, 60, 64, 0, 0), (64, 128, 1, 0, 65, 0, 0), (65, 129, 1, 127, 100, 2, 16),
+    (127, 131, 1, 10, 128, 0, 0), (128, 132, 1, 256, 129, 0, 128), (129, 255, 1, 1, 256, 0, 0), (130, 256, 1, 13, 200, 0, 0),
+    (200, 384, 1, 128, 31, 0, 0), (257, 57, 9, 28, 255, 3, 0), (300, 3, 49, 1, 64, 0, 0), (140, 1024, 1, 52, 256, 0, 0),
+    (300, 900, 1, 45, 70, 124, 0), (70, 2048, 4, 64, 20, 0, 0), (33001, 64, 1, 4, 64, 0, 0), (33001, 150, 1, 8, 130, 0, 0)])
+def test_forward_of_many_rows(M, C, g, s, N, ld_extra, ldq_extra):
+    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, ldq_extra=ldq_extra))
+
+
+# Per-batch grids: one maximum, 256 of them, the thousands of a strided tensor
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip", [
+    (1, 64, 1, 1, 5, 0, 1.0), (700, 256, 1, 13, 256, 0, 0.9), (3000, 257, 1, 3, 64, 3, 0.8), (33000, 128, 1, 7, 33, 0, 1.0)])
+def test_forward_of_many_rows_per_batch(M, C, g, s, N, ld_extra, clip):
+    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0))
+
+
+# What the rule sends there, against the two launches, bit for bit: the fewest and the most rows of one round, rows just over it
+# (which stay with the two), more than a round; rows that begin inside a line stay too.
+@pytest.mark.parametrize("per,extra,C,g,N,ld", [
+    (96, 0, 384, 1, 72, 0), (128, 0, 1024, 1, 256, 0), (128, 5, 512, 1, 64, 0), (160, 3, 448, 1, 128, 0), (100, 1, 64, 9, 40, 32),
+    (100, 0, 400, 1, 64, 0)])
+@pytest.mark.parametrize("threshold", [3.0, None])
+def test_forward_route_of_many_rows(per, extra, C, g, N, ld, threshold):
+    from paper_1901_09504_amd.layer import ExpandedLayer
+    M, K, s = per * 256 + extra, C * g, max(1, C // 20)
+    gen = torch.Generator(device="cuda").manual_seed(per + C)
+    X = torch.randn((M, K + ld), device="cuda", generator=gen)
+    L = ExpandedLayer(N, C, g, s / C, 6, 8, max_rows=M)
+    L.prepare_weights(torch.randn((N, K), device="cuda", generator=gen))
+    th = None if threshold is None else torch.tensor([threshold], device="cuda")
+    out = []
+    for mode in (0, -1, -1):          # (twice: nothing is left behind by a pass)
+        acc = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+        L.Xq.fill_(77)
+        L.scale_x.fill_(-1)
+        _panel(mode, lambda: L.forward(X[:, :K], th, acc_out=acc))
+        out.append((L.Xq.clone(), L.scale_x.clone(), acc, L.Y.clone()))
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+
+
+def test_forward_of_many_rows_over_its_own_input():
+    _panel(1, test_forward_over_its_own_input)
+
+
 # ---- channel maxima in row blocks that the selector folds itself ------------------------------------
 
 # Rows and columns around the blocks' edges: a row's last group of four overlaps the one before (5, 7, 33, 130 columns, 8, 16 and
