@@ -525,7 +525,7 @@ int ocs_calib_mfma(const void *operands, int iters, int workgroups, void *sink, 
  * ocs_split_act folds its maxima in a launch of its own whatever the tensor's size), "sel_inline" (most splits for
  * which ocs_split_weights runs the selection inside its code pass, where the list is short enough, instead of as a
  * launch of its own; 0: never), "gemm_tile" (tile variant of
- * ocs_qgemm / ocs_qconv: 6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23 to 29, for ocs_qconv 30 to 32; an id a shape cannot use falls
+ * ocs_qgemm / ocs_qconv: 6, 7, 9, 10, 11, 12, 14, 16, 17, 18, 19, 23 to 29, 33, for ocs_qconv 30 to 32; an id a shape cannot use falls
  * back to one it can), "fused_variant" (ocs_split_act_qgemm with more than 128 output columns:
  * 1 = 64-row workgroups, 2 = 128-row ones), "fused_stride" (rows between that kernel's workgroups: 0 = a
  * whole tile always, n > 0 = n), "slice_layer" and "panel_layer" (ocs_forward as one launch, of few tiles and of many rows: 1 =

@@ -98,7 +98,7 @@ __device__ __forceinline__ void emit_staged_rows(const int32_t* stage, int lane,
                                                  const int* dup_list, int dup_n, bool pad_writer, bool whole = false) {
     constexpr int LPR = WN / 4;            // lanes per row (8, 16 or 32)
     constexpr int SLOTS = ROWS * LPR;      // 16-byte reads of the block
-    static_assert(SLOTS % 64 == 0, "whole waves of slots");
+    static_assert(SLOTS % 64 == 0 && 64 % LPR == 0, "whole waves of slots, whole rows of lanes");
     // whole: the workgroup's tile lies inside the output, as nearly all of a large one's do: no bounds, no
     // branch between the stores (for the tile, not per wave: where the last columns of a row share a line
     // with the next row's first, waves that run ahead of each other cost more, 100000 x 100 19 against 16.5 us)
@@ -2727,6 +2727,13 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
             const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128), cus = compute_units();
             const int64_t large = 35 * ceil_div(t256sq, cus), middle = 20 * ceil_div(t256, cus), small = 12 * ceil_div(t128, cus);
             if (N >= 256 && large < middle && large <= small) tile = 12;
+            else if (middle <= small && ldx >= round_up(Kpad, 128) && ldw >= round_up(Kpad, 128) &&
+                     ceil_div(M, 192) * ceil_div(N, 128) <= cus && ceil_div(M, 192) * 192 <= ceil_div(M, 256) * 256)
+                // 192 x 128 where that is still one round and walks no more rows: the compute units the middle size leaves
+                // idle get a tile, each a quarter smaller (both launches, us: 700 x 6000 x 3150, 188 tiles for 141, 28.8 -> 25.1;
+                // 800 x 5000 x 4200 35.2 -> 30.8; 1400 x 3000 x 3150 29.6 -> 26.5; 9000 x 512 x 1076 22.9 -> 21.4; 40000 x 100 x
+                // 1575 68.3 -> 67.3; with 576 rows walked for 512, 400 x 8000 x 3150 22.5 -> 23.2)
+                tile = 33;
             else if (middle <= small)
                 // the middle size as 128 x 256 for a very long K and fewer tiles than compute units: X rows asked for
                 // by two tiles, not four (43-46 against 45-47 us on the 512 -> 512 3x3 layers at M = 12544)
@@ -2745,7 +2752,7 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
     // on both operands (the producers' contract) and the walk may include them.
     const int64_t K128 = round_up(Kpad, 128);
     const bool k128 = K128 == Kpad || (ldx >= K128 && ldw >= K128);
-    // Tile variants by id (the dispatcher above picks 7, 9, 11, 12, 16, 17, 19 or 23 to 29, a convolution 30 to 32 as well; the others
+    // Tile variants by id (the dispatcher above picks 7, 9, 11, 12, 16, 17, 19, 23 to 29 or 33, a convolution 30 to 32 as well; the others
     // are kept selectable because the parity tests run every kernel family through them).
     switch (tile) {
         case 6: return run_dma<128, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);
@@ -2772,6 +2779,7 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
                              : run_dma<128, 64, 2, 2, 64, 6>(OCS_GEMM_ARGS);
         case 25: return k128 ? run_dma<128, 256, 2, 4, 128, 3>(OCS_GEMM_ARGS128)
                              : run_dma<256, 128, 4, 2, 64, 4>(OCS_GEMM_ARGS);
+        case 33: return k128 ? run_dma<192, 128, 2, 4, 128, 3>(OCS_GEMM_ARGS128) : run_dma<128, 128, 4, 2, 64, 4>(OCS_GEMM_ARGS);
         // K dealt over eight waves; any pitch
         case 26: return run_slice<1, 1, 8, 4>(OCS_GEMM_ARGS);    // 32 x 32
         case 27: return run_slice<1, 2, 8, 3>(OCS_GEMM_ARGS);    // 32 x 64

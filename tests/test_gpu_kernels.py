@@ -1186,6 +1186,32 @@ def test_qgemm_requant(tile, M, N, K, s_next, relu):
     assert np.array_equal(host(Yq), q_ref)
 
 
+# The 192 x 128 tile: rows and outputs around one and two of it, K of fewer steps than the ring holds, around it and long; a pitch
+# that ends before a whole 128-byte step (K = 192: the tile of 64-byte steps)
+@pytest.mark.parametrize("M,N,K,ld", [(1, 1, 128, 128), (191, 127, 256, 256), (192, 128, 384, 384), (193, 129, 512, 512), (385, 300, 1100, 1152),
+                                      (200, 33, 3150, 3200), (97, 64, 192, 192)])
+def test_qgemm_tile_of_192_rows(M, N, K, ld):
+    rng = np.random.default_rng(M + N + K)
+    Xq, Wq = np.zeros((M, ld), dtype=np.int8), np.zeros((N, ld), dtype=np.int8)
+    Xq[:, :K] = rng.integers(-127, 128, (M, K))
+    Wq[:, :K] = rng.integers(-31, 32, (N, K))
+    sx, sw = np.array([3.0, 3.0 / 127], dtype=np.float32), np.array([0.7, 0.7 / 31], dtype=np.float32)
+    acc_ref, y_ref = ref.qgemm(Xq, Wq, K, sx[1], sw[1])
+    B.ocs_tune("gemm_tile", 33)
+    try:
+        for want_acc in (True, False):          # (without accumulators whole tiles are stored without bounds)
+            acc, Y = gpu_qgemm(Xq, Wq, K, sx, sw, bits_w=6, want_acc=want_acc)
+            assert acc is None or np.array_equal(acc, acc_ref)
+            assert_y_close(Y, y_ref)
+    finally:
+        B.ocs_tune("gemm_tile", -1)
+
+
+@pytest.mark.parametrize("M,N,K,s_next,relu", [(130, 70, 64, 9, True), (193, 129, 2358, 26, True), (400, 300, 1269, 15, False)])
+def test_qgemm_requant_tile_of_192_rows(M, N, K, s_next, relu):
+    test_qgemm_requant(33, M, N, K, s_next, relu)
+
+
 @pytest.mark.parametrize("tile", [6, 16])
 def test_qgemm_requant_pad_columns_of_a_long_row(tile):
     """A pitch of 2^28 + 128 bytes: every column past the last copy is a zero code (32 staged rows times the
@@ -1518,6 +1544,27 @@ def _panel(mode, fn):
         fn()
     finally:
         B.ocs_tune("panel_layer", -1)
+
+
+@pytest.mark.parametrize("M,N,K", [(700, 6000, 3150), (3000, 1500, 1575)])
+def test_qgemm_route_of_one_round_of_192_rows(M, N, K):
+    ld = B.ocs_padded_cols(K)
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    Xq, Wq = (torch.randint(-31, 32, (r, ld), device="cuda", generator=gen, dtype=torch.int8) for r in (M, N))
+    Xq[:, K:] = 0
+    Wq[:, K:] = 0
+    one = torch.ones(2, device="cuda")
+    out = []
+    for tile in (-1, 33, 11):
+        acc, Y = torch.empty((M, N), dtype=torch.int32, device="cuda"), torch.empty((M, N), device="cuda")
+        B.ocs_tune("gemm_tile", tile)
+        try:
+            B.ocs_qgemm(Xq, ld, Wq, ld, M, N, K, 8, 6, one, one, acc, N, Y, N)
+        finally:
+            B.ocs_tune("gemm_tile", -1)
+        out.append((acc, Y))
+    for o in out[1:]:
+        assert torch.equal(out[0][0], o[0]) and torch.equal(out[0][1], o[1])
 
 
 # Steps of 128 columns: none whole, one, two (the loop without conditions needs two), left-over columns of 1, 3, 4 and 127 that share
