@@ -43,13 +43,13 @@ STATIC_T = 5.0               # the static activation grid's range (inputs are |N
 # reads for the plain copy kernel of known size that runs after the timed region
 # (profiles/bench_config5_headline.md).  Valid only for the kernel source it was measured on:
 # reported as null once that file changes.
-X2_TRAFFIC = {"quantize_hip_sha256": "fb9c9efb91a71a63426f23713b7ed1e63a75329940caa2d814f41db189d5eea5",
-              "bytes_per_step": 28942891898}
+X2_TRAFFIC = {"quantize_hip_sha256": "e2b802a577991daaaba99bce1ce60e836e49dcd1ff20f46217196b803981f975",
+              "bytes_per_step": 28944930928}
 
 
 # The same for the launches of the one-launch pass (`--extras fused`), keyed on the GEMM source.
-FUSED_TRAFFIC = {"qgemm_hip_sha256": "28a1fdb8466a621aec1ad2cb4dbcacba64e69d5cefdc6329bb6a83c1157af751",
-                 "bytes_per_step": 22973462541}
+FUSED_TRAFFIC = {"qgemm_hip_sha256": "aef6f2f996ef5ec4626d7f3864cd3da6e3e339b3200163a584f359869642b092",
+                 "bytes_per_step": 22973685620}
 
 
 def fused_traffic():
