@@ -1623,7 +1623,8 @@ def test_forward_of_many_rows_over_its_own_input():
 # requests at once (64 columns: 256 blocks), weights-shaped tensors past the single-launch strips, rows too few for a second block.
 @pytest.mark.parametrize("rows,C,g,s,ld_extra", [
     (2049, 1, 4, 3, 0), (700, 5, 1, 2, 0), (5000, 7, 1, 4, 3), (4100, 33, 1, 5, 0), (9000, 64, 1, 7, 0), (2500, 13, 10, 4, 1),
-    (70000, 16, 2, 3, 0), (2111, 300, 1, 30, 0), (1030, 1600, 1, 12, 0), (800, 2000, 1, 20, 0), (3000, 40, 9, 4, 0)])
+    (70000, 16, 2, 3, 0), (2111, 300, 1, 30, 0), (1030, 1600, 1, 12, 0), (800, 2000, 1, 20, 0), (3000, 40, 9, 4, 0),
+    (520, 512, 9, 11, 0)])                                          # (too few workgroups left: two launches)
 def test_selection_on_row_blocks(rows, C, g, s, ld_extra):
     rng = np.random.default_rng(rows + C)
     K = C * g
