@@ -2303,10 +2303,17 @@ static hipError_t run_slice(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int
                          ldacc, Y, ldy, (int)tiles_m, (int)tiles_n, N > M ? 1 : 0, rq);
 }
 
+// The waves' parts, the table of the columns past the whole steps and the maxima of the waves.
+template <int TN, int NW, int NBUF, bool EARLY>
+static int64_t slice_layer_lds(int64_t tail_cols) {
+    return NW * slice_layer_wave_bytes<TN, NBUF + (EARLY ? 1 : 0)>() + tail_cols * 4 + NW * 4;
+}
+
 template <int TN, int A_PER, int NW, int NBUF, bool EARLY>
 static hipError_t run_slice_layer(SliceLayer p, hipStream_t stream) {
-    const unsigned lds = (unsigned)(NW * slice_layer_wave_bytes<TN, NBUF + (EARLY ? 1 : 0)>() + (p.ksteps - p.kmain) * 64 * 4 + NW * 4);
-    if (lds > kWholeKMaxLds) return hipErrorInvalidValue;
+    const int64_t bytes = slice_layer_lds<TN, NW, NBUF, EARLY>((p.ksteps - p.kmain) * 64);
+    if (bytes > kWholeKMaxLds) return hipErrorInvalidValue;
+    const unsigned lds = (unsigned)bytes;
     if (lds > 65536) {
         static std::atomic<bool> opted_in[kMaxDevices];
         int dev = 0;
@@ -2336,16 +2343,27 @@ static int slice_layer_tile(int64_t M, int64_t N) {
 }
 constexpr int kSliceLayerTail = 4096;      // columns of the table in LDS (16 KB)
 
+// Whether an instance of launch_slice_layer takes the shape: a tile, 32-bit offsets, and the LDS of the tile's instance (the
+// wider two have room for 4088 columns of the table).
+static bool slice_layer_fits(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
+    const int64_t K = (int64_t)C * g, tail = round_up((int64_t)(C + s) * g, 64) - K / 64 * 64, pitch = (int64_t)1 << 23;
+    if (ldx >= pitch || K >= pitch || tail > kSliceLayerTail) return false;
+    switch (slice_layer_tile(M, N)) {
+        case 1: return slice_layer_lds<1, 8, 3, true>(tail) <= kWholeKMaxLds;
+        case 2: return slice_layer_lds<2, 8, 3, true>(tail) <= kWholeKMaxLds;
+        case 4: return slice_layer_lds<4, 8, 2, false>(tail) <= kWholeKMaxLds;
+        default: return false;
+    }
+}
+
 // Up to 32768 values of X per row of tiles: what a workgroup draws again grows with them, what the launch saves does not.
 // Two launches / one, passes one after the other (host time included) and the kernels alone in a graph, us: 1024 values
 // 9.7 / 6.7 and 5.9 / 4.4; 8192 9.6 / 6.5 and 5.7 / 4.8; 16384 9.6 / 6.5 and 5.9 / 5.8; 28544 (526 x 892 -> 40, per batch) 12.0 / 10.4
 // and 9.5 / 10.3; 32768 9.0 / 6.5 and 6.4 / 7.0; 60000 (20 x 3000 -> 6000) 8.9 / 11.0 and 7.8 / 11.0.
 bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
-    const int64_t K = (int64_t)C * g, Kexp = (int64_t)(C + s) * g;
+    const int64_t K = (int64_t)C * g;
     const Tuning& tn = tuning();
-    if (tn.slice_layer == 0) return false;
-    const int tile = slice_layer_tile(M, N);
-    if (tile == 0 || ldx >= ((int64_t)1 << 23) || K >= ((int64_t)1 << 23) || round_up(Kexp, 64) - K / 64 * 64 > kSliceLayerTail) return false;
+    if (tn.slice_layer == 0 || !slice_layer_fits(M, C, g, s, N, ldx)) return false;
     if (tn.slice_layer > 0) return true;
     return (M < 32 ? M : 32) * K <= 32768;
 }

@@ -1517,6 +1517,35 @@ def test_forward_of_few_tiles_per_batch(M, C, g, s, N, ld_extra, clip, ldq_extra
     _forward_once(M, C, g, s, N, ld_extra, None, clip, 1, ldq_extra=ldq_extra)
 
 
+# The table of the columns past the whole steps at its largest (4096 columns: the wider tiles' LDS has no room for it, and the call
+# takes the two launches) and one step below, on tiles of 32, 64 and 128 columns.
+@pytest.mark.parametrize("mode", [1, -1])
+@pytest.mark.parametrize("M,C,g,s,N", [(3, 8, 9, 448, 40), (1, 8, 9, 441, 8200), (1, 8, 9, 448, 8200), (1, 8, 9, 441, 16400),
+                                       (1, 8, 9, 448, 16400)])
+def test_forward_of_few_tiles_with_the_longest_tails(M, C, g, s, N, mode):
+    rng = np.random.default_rng(s + N)
+    K, Ke = C * g, (C + s) * g
+    ldq = B.ocs_padded_cols(Ke)
+    X = _tensor(rng, M, K, "heavy")
+    cs = np.concatenate([np.arange(C), rng.integers(0, C, s)]).astype(np.int32)
+    Wq = np.zeros((N, ldq), np.int8)
+    Wq[:, :Ke] = rng.integers(-15, 16, (N, Ke))
+    sw, th = np.array([1.5, 0.1], np.float32), np.array([2.5], np.float32)
+    q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+    sx = torch.full((2,), -1.0, dtype=torch.float32, device="cuda")
+    Y, acc = torch.empty((M, N), device="cuda"), torch.empty((M, N), dtype=torch.int32, device="cuda")
+    B.ocs_tune("slice_layer", mode)
+    try:
+        B.ocs_forward(dev(X), M, C, g, K, dev(cs), s, 8, dev(th), 1.0, q, ldq, sx, dev(Wq), ldq, N, 5, dev(sw), acc, N, Y, N, None)
+    finally:
+        B.ocs_tune("slice_layer", -1)
+    q_ref, sx_ref, _ = ref.split_act(X, C, g, cs, None, s, 8, threshold=2.5, ldq=ldq)
+    acc_ref, y_ref = ref.qgemm(q_ref, Wq, Ke, sx_ref[1], sw[1])
+    assert np.array_equal(host(sx).view(np.uint32), sx_ref.view(np.uint32)) and np.array_equal(host(q), q_ref)
+    assert np.array_equal(host(acc), acc_ref)
+    assert_y_close(host(Y), y_ref)
+
+
 def test_forward_over_its_own_input():
     """Y on top of X (a layer applied to its own output): X has been read as a whole before any output is written."""
     M, C, N, s = 70, 256, 256, 8
