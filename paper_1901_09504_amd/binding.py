@@ -103,6 +103,8 @@ def lib():
     L.ocs_forward.restype = _i32
     L.ocs_forward.argtypes = [_vp, _i64, _i32, _i32, _i64, _vp, _i32, _i32, _vp, _f32, _vp, _i64, _vp, _vp, _i64, _i64,
                               _i32, _vp, _vp, _i64, _vp, _i64, _vp, _sz, _vp]
+    L.ocs_forward_one_launch.restype = _i32
+    L.ocs_forward_one_launch.argtypes = [_vp, _i64, _i32, _i32, _i64, _i32, _i64, _i64, _i64, _i32]
     L.ocs_forward_act.restype = _i32
     L.ocs_forward_act.argtypes = [_vp, _i64, _i32, _i32, _i64, _i32, _i32, _f32, _vp, _vp, _vp, _vp, _vp, _i64, _vp, _vp,
                                   _i64, _i64, _i32, _vp, _vp, _i64, _vp, _i64, _vp, _sz, _vp]
@@ -359,6 +361,11 @@ def ocs_forward(X, M, Cn, g, ldx, chan_src, num_splits, bits_x, threshold, clip_
     _check(lib().ocs_forward(_ptr(X), M, Cn, g, ldx, _ptr(chan_src), num_splits, bits_x, _ptr(threshold), clip_ratio,
                              _ptr(Xq), ldq, _ptr(scale_x_out), _ptr(Wq), ldw, N, bits_w, _ptr(scale_w), _ptr(acc_out),
                              ldacc, _ptr(Y), ldy, w, wb, _stream(stream)), "ocs_forward")
+
+
+def ocs_forward_one_launch(M, Cn, g, ldx, num_splits, ldq, ldw, N, captured=False, X=None):
+    """0: two kernels; 1: the one launch of few tiles; 2: that of many rows (X: tensor or address, for its alignment)."""
+    return int(lib().ocs_forward_one_launch(X if isinstance(X, int) else _ptr(X), M, Cn, g, ldx, num_splits, ldq, ldw, N, captured))
 
 
 def ocs_forward_act(X, M, Cn, g, ldx, num_splits, bits_x, clip_ratio, split_src, chan_src, chan_depth, max_out, Xq, ldq,

@@ -547,6 +547,24 @@ static bool overlap(const void* a, int64_t an, const void* b, int64_t bn) {
     return a != nullptr && b != nullptr && x < y + (uint64_t)bn && y < x + (uint64_t)an;
 }
 
+// The kernels ocs_forward takes: the two of ocs_split_act and ocs_qgemm, or the one launch of few tiles or of many rows.
+enum class ForwardRoute { two = 0, few_tiles = 1, many_rows = 2 };
+static ForwardRoute forward_route(const float* X, int64_t M, int C, int g, int64_t ldx, int s, int64_t ldq, int64_t ldw, int64_t N,
+                                  bool captured) {
+    const Tuning& tn = tuning();
+    if (tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0)   // launch shapes of the two
+        return ForwardRoute::two;
+    if (slice_layer_pays(M, C, g, s, N, ldx, captured)) return ForwardRoute::few_tiles;
+    if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) return ForwardRoute::many_rows;
+    return ForwardRoute::two;
+}
+
+int ocs_forward_one_launch(const float* X, int64_t M, int C, int g, int64_t ldx, int num_splits, int64_t ldq, int64_t ldw,
+                           int64_t N, int captured) {
+    if (check_layer(M, C, g, ldx, num_splits) || N <= 0) return 0;
+    return (int)forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, captured != 0);
+}
+
 int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int32_t* chan_src, int num_splits, int bits_x,
                 const float* threshold, float clip_ratio, int8_t* Xq, int64_t ldq, float* scale_x_out, const int8_t* Wq,
                 int64_t ldw, int64_t N, int bits_w, const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y,
@@ -573,9 +591,18 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
     const bool apart = clear_of_outputs(X, xb) && clear_of_outputs(threshold, 4) &&
                        clear_of_outputs(num_splits > 0 ? chan_src : nullptr, 4 * (int64_t)(C + num_splits)) &&
                        clear_of_outputs(threshold == nullptr ? workspace : nullptr, (int64_t)ws_bytes);
-    const Tuning& tn = tuning();
-    const bool tuned = tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0;   // (launch shapes of the two)
-    if (apart && !tuned && slice_layer_pays(M, C, g, num_splits, N, ldx)) {
+    ForwardRoute route = ForwardRoute::two;
+    if (apart) {
+        route = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, false);
+        if (route == ForwardRoute::few_tiles && st != nullptr) {       // (the null stream is never captured)
+            const ForwardRoute in_graph = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, true);
+            hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+            const hipError_t e = in_graph == route ? hipSuccess : hipStreamIsCapturing(st, &status);
+            if (e != hipSuccess) return hip_fail(e);
+            if (status != hipStreamCaptureStatusNone) route = in_graph;
+        }
+    }
+    if (route == ForwardRoute::few_tiles) {
         const float* thr = threshold;
         int n = 0;
         int64_t self = 0;
@@ -595,7 +622,7 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
                                scale_x_out, Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
         return e == hipSuccess ? OCS_OK : hip_fail(e);
     }
-    if (apart && !tuned && panel_layer_pays(X, ldx, M, C, g, num_splits, ldq, ldw, N)) {
+    if (route == ForwardRoute::many_rows) {
         const float* thr = threshold;
         int n = 0;
         hipError_t e = hipSuccess;

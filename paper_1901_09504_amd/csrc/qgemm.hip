@@ -2356,16 +2356,27 @@ static bool slice_layer_fits(int64_t M, int C, int g, int s, int64_t N, int64_t 
     }
 }
 
-// Up to 32768 values of X per row of tiles: what a workgroup draws again grows with them, what the launch saves does not.
-// Two launches / one, passes one after the other (host time included) and the kernels alone in a graph, us: 1024 values
-// 9.7 / 6.7 and 5.9 / 4.4; 8192 9.6 / 6.5 and 5.7 / 4.8; 16384 9.6 / 6.5 and 5.9 / 5.8; 28544 (526 x 892 -> 40, per batch) 12.0 / 10.4
-// and 9.5 / 10.3; 32768 9.0 / 6.5 and 6.4 / 7.0; 60000 (20 x 3000 -> 6000) 8.9 / 11.0 and 7.8 / 11.0.
-bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
-    const int64_t K = (int64_t)C * g;
+// Where the one launch is ahead of the two.  A workgroup draws and quantizes its rows of X again, and gathers the appended columns
+// value by value, each step of them past a wave's first waiting for its requests: both grow with the size, what the launch saves
+// does not.  A launch less saves 3 us of the host's time, so the line lies higher where the host launches than in a captured graph.
+// Two launches / one, the ratio: a graph on inputs outside the caches; a graph on the same input again; passes launched one after
+// the other (the range over static grid and per batch, 10 to 4000 outputs, copies 5 % of the channels):
+//   values of X in a row of tiles  8192: 0.98-1.30, 1.07-1.25, 1.29-1.50; 12288: 1.02-1.20, 1.04-1.22, 1.36-1.49; 16384: 0.89-1.06,
+//                0.95-1.12, 1.18-1.49; 24576: 0.81-1.05, 0.93-1.11, 1.12-1.49; 32000: 0.62-0.97, 0.77-1.08, 0.74-1.39
+//   tiles of 128 columns           8192: 1.10, 1.11, 1.28; 12288: 0.98, 1.01, 1.24; 16384: 0.86, 0.94, 1.11; 24576: 0.80, 0.91, 0.99
+//   a row of K = 4000: 0.97-1.15, 1.09-1.20, 1.29; 6000: 0.89-1.14, 1.01-1.19, 1.04; 8000: 0.84, 1.00, 1.01; 16000: 0.71, 0.83, 0.85
+//   copies, 8192 values: half of the channels 1.02, 1.04, 1.36, all of them 0.85, 0.86, 1.24 (tiles of 128 columns 0.96, 0.97, 1.25
+//                and 0.92, 0.92, 1.16); 12288: a quarter 0.90, 1.00, 1.22, half 0.88, 0.93, 1.12; four steps of them for a wave
+//                (2000 to 2048 columns) 0.77, 0.78, 0.91, eight 0.64, 0.55, 0.58
+// So an appended column counts as two, and a wave has at most two steps of them.
+bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx, bool captured) {
+    const int64_t K = (int64_t)C * g, rows = M < 32 ? M : 32;
     const Tuning& tn = tuning();
     if (tn.slice_layer == 0 || !slice_layer_fits(M, C, g, s, N, ldx)) return false;
     if (tn.slice_layer > 0) return true;
-    return (M < 32 ? M : 32) * K <= 32768;
+    const bool wide = slice_layer_tile(M, N) == 4;
+    const int64_t most = captured ? (wide ? 10240 : 13312) : (wide ? 13312 : 27648);
+    return rows * (K + 2 * (int64_t)s * g) <= most && K <= (captured ? 4096 : 6144) && round_up((int64_t)(C + s) * g, 64) - K / 64 * 64 <= 1024;
 }
 
 hipError_t launch_slice_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,

@@ -209,6 +209,34 @@ def test_one_launch_pays_by_rows_columns_and_outputs(C, g, s, N, below, from_):
         assert B.ocs_split_act_qgemm_pays(M, C, g, s, N, C * g)
 
 
+# 256 compute units.  Values of X in a row of tiles, a copy counted twice: up to 27648 (13312 with tiles of 128 columns) launched by
+# the host, 13312 (10240) in a captured graph; rows of up to 6144 (4096) values; up to 1024 columns past the whole steps.
+@pytest.mark.parametrize("M,C,g,s,N,eager,captured", [
+    (64, 256, 1, 13, 256, 1, 1), (1, 3000, 1, 150, 6000, 1, 1), (700, 256, 1, 13, 256, 1, 1), (1000, 3, 49, 1, 64, 1, 1),
+    (32, 416, 1, 0, 64, 1, 1), (32, 417, 1, 0, 64, 1, 0), (32, 864, 1, 0, 64, 1, 0), (32, 865, 1, 0, 64, 0, 0),
+    (64, 832, 1, 16, 64, 1, 0), (64, 832, 1, 17, 64, 0, 0), (27, 1024, 1, 0, 64, 1, 0), (28, 1024, 1, 0, 64, 0, 0),
+    (2, 4096, 1, 0, 64, 1, 1), (2, 4097, 1, 0, 64, 1, 0), (1, 682, 9, 0, 64, 1, 0), (1, 683, 9, 0, 64, 0, 0),
+    (1, 1024, 1, 1024, 64, 1, 1), (1, 1024, 1, 1025, 64, 0, 0), (1, 63, 1, 962, 64, 0, 0), (1, 63, 1, 961, 64, 1, 1),
+    (700, 320, 1, 0, 1000, 1, 1), (700, 321, 1, 0, 1000, 1, 0), (700, 416, 1, 0, 1000, 1, 0), (700, 417, 1, 0, 1000, 0, 0),
+    (20, 3000, 1, 150, 6000, 0, 0), (32, 1000, 1, 50, 64, 0, 0), (8200, 64, 1, 3, 300, 0, 0)])
+def test_forward_of_few_tiles_by_what_a_row_of_tiles_holds(M, C, g, s, N, eager, captured):
+    ld = B.ocs_padded_cols((C + s) * g)
+    assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, False) == eager
+    assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, True) == captured
+
+
+def test_forward_route_of_refused_shapes_and_forced_kernels():
+    assert B.ocs_forward_one_launch(0, 64, 1, 64, 1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 63, 1, 128, 128, 64) == 0
+    assert B.ocs_forward_one_launch(4, 64, 1, 64, -1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 0) == 0
+    assert B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 64) == 1
+    for key, value in (("gemm_tile", 7), ("act_grid", 8), ("slice_layer", 0)):
+        B.ocs_tune(key, value)
+        try:
+            assert B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 64) == 0, key
+        finally:
+            B.ocs_tune(key, -1)
+
+
 def test_binding_raises_on_error():
     with pytest.raises(B.OcsError) as e:
         B._check(-4, "ocs_quantize")

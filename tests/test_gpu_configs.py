@@ -414,3 +414,37 @@ def test_layer_replays_from_a_hip_graph():
         torch.cuda.synchronize()
         assert np.array_equal(sx_graph, host(L.scale_x)) and sx_graph[0] == np.float32(40.0 + rep)
         assert torch.equal(Xq_graph, L.Xq[:layer.M]) and torch.equal(Y_graph, Y_eager)
+
+
+# What a captured stream takes: the one launch of few tiles, static and per batch (maxima found by the launch itself, or by a pass of
+# its own: more than 32768 values); the two kernels where only the host's launches would make the one pay; the one launch of
+# many rows.
+@pytest.mark.parametrize("M,C,g,s,N,eager,captured", [
+    (64, 256, 1, 13, 256, 1, 1), (700, 256, 1, 13, 40, 1, 1), (32, 700, 1, 35, 100, 1, 0), (25088, 512, 1, 26, 64, 2, 2)])
+@pytest.mark.parametrize("static", [True, False])
+def test_one_launch_layers_replay_from_a_hip_graph(M, C, g, s, N, eager, captured, static):
+    L = ExpandedLayer(N, C, g, s / C, 6, 8, max_rows=M)
+    for cap, route in ((False, eager), (True, captured)):
+        assert B.ocs_forward_one_launch(M, C, g, C * g, L.s, L.ldq, L.ldq, N, cap) == route
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    L.prepare_weights(torch.randn((N, C * g), device="cuda", generator=gen))
+    X = torch.randn((M, C * g), device="cuda", generator=gen)
+    th = torch.tensor([2.0], device="cuda") if static else None
+    acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    L.forward(X, th, acc_out=acc)          # eager warm-up: buffers exist before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        L.forward(X, th, acc_out=acc)
+    for rep in range(4):
+        X.normal_(generator=gen)
+        X[rep, 3 * rep] = -9.0 - rep       # moves the per-batch grid
+        L.Xq.fill_(77)
+        acc.fill_(-1)
+        graph.replay()
+        got = [t.clone() for t in (L.Y[:M], L.Xq[:M], L.scale_x, acc)]
+        L.Xq.fill_(55)
+        L.forward(X, th, acc_out=acc)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, (L.Y[:M], L.Xq[:M], L.scale_x, acc)))
+        assert static or float(got[2][0]) == 9.0 + rep
