@@ -2190,23 +2190,30 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     return run_panel<128, 256, 128, 8, 2, 4, 1>(p, stream);
 }
 
-// Where the one launch is ahead of the two (two launches / one, passes one after the other, inputs rotating; static grid, per batch):
-//   rows per compute unit  K = 512, N = 64: 64 1.01, 0.90; 80 1.16, 1.10; 98 1.25, 1.15; 130 1.06, 1.05; 196 1.10, 1.08.  K = 1024,
-//                N = 256: 64 0.91, 0.96; 98 1.11, 1.12; 128 1.13, 1.16; 196 1.04, 1.13.  K = 2304, N = 256: 64 0.80, 0.94; 98 0.99,
-//                1.07; 130 0.96, 1.06; 165 1.05, 1.18; 260 1.08, 1.10.  A workgroup per compute unit and 128 rows of tile: with fewer
-//                than 96 rows, or just over 128 (two rounds of half a tile), the weights are read again for too little.
-//   columns      N = 64: K = 192 1.09, 0.97 at 98 rows and 0.87, 0.94 at 196; 256 1.10, 1.04 and 0.95, 0.98; 384 1.25, 1.13 and 1.09, 1.07.
+// Where the one launch is ahead of the two (two launches / one; in a graph on inputs outside the caches, in a graph on the same input
+// again, passes one after the other with the inputs rotating; 16 to 256 outputs, copies 5 % of the channels unless stated):
+//   rows per compute unit, static grid, K = 512: 64 1.01 in passes; 80 1.16; 98 to 128 1.21-1.44, 1.05-1.26, 1.10-1.27; 130 1.06; 160 and 176
+//                1.15-1.26, 0.96-1.04, 1.02-1.11; 192 to 400 1.16-1.41, 0.94-1.08, 1.04-1.15.  K = 1024: 64 0.91; 98 to 128 1.20-1.33,
+//                0.97-1.07, 1.04-1.15; 160 and 176 1.11-1.28, 0.88-0.98, 0.95-1.09; 192 to 400 1.21-1.38, 0.91-1.17, 1.01-1.17.  K = 2304:
+//                64 0.80; 96 1.26-1.34, 0.93-1.00, 0.97-1.03; 98 to 128 1.25-1.35, 0.99-1.11, 1.00-1.09; 130 0.96; 192 to 400 1.18-1.29,
+//                1.04-1.17, 1.06-1.18.  K = 4608: 98 to 400 1.21-1.27, 1.10-1.20, 1.10-1.20; 9216: 1.20-1.27, 1.15-1.23, 1.15-1.23.  Per batch 1.04-1.26, 0.99-1.27, 1.02-1.26 from
+//                98 rows on.  A workgroup per compute unit and 128 rows of tile: with fewer than 98 rows, or in two rounds of less than
+//                three quarters of a tile, the weights are read again for too little.
+//   columns      N = 64: K = 192 1.09 in passes, 0.97 per batch at 98 rows and 0.87, 0.94 at 196; 256 1.10, 1.04 and 0.95, 0.98.  16 to 64
+//                outputs 1.01-1.41, 0.93-1.31, 1.00-1.26; 100 to 128 0.99-1.47, 0.91-1.35, 1.00-1.34; 192 and 256 0.99-1.42, 0.93-1.25, 1.00-1.26.
+//   copies       moved byte by byte: more than a fifth of the columns 0.96-1.17 in passes, a third to two thirds 0.80-1.09.
 //   whole lines  rows that begin inside one share it with their neighbour's last step, which reads it again: K = 400, N = 64 1.00, 0.94 at
 //                165 rows, K = 1000 0.96, 0.99.
+//   pitch        rows that do not follow each other: K = 384 and 512 0.85-1.29 in passes, K = 1024 1.00-1.16.
 bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq, int64_t ldw, int64_t N) {
     const int mode = tuning().panel_layer;
     if (mode == 0 || !panel_fits(ldx, M, C, g, s, ldq, ldw, N)) return false;
     if (mode > 0) return true;
     const int64_t K = (int64_t)C * g, cus = compute_units();
     if (K < 384 || K % 64 != 0 || ldx % 32 != 0 || reinterpret_cast<uintptr_t>(X) % 128 != 0) return false;
-    return (M >= 96 * cus && M <= 128 * cus) || M >= 160 * cus;
+    if (5 * (int64_t)s * g > K || (ldx != K && K < 1024)) return false;
+    return (M >= 98 * cus && M <= 128 * cus) || M >= 192 * cus;
 }
-
 
 // Dynamic LDS of a whole-K launch: operands (or the epilogue's staging area, if larger) and,
 // when the output goes to the next layer as codes with copies, the table of those copies

@@ -225,6 +225,24 @@ def test_forward_of_few_tiles_by_what_a_row_of_tiles_holds(M, C, g, s, N, eager,
     assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, True) == captured
 
 
+# Rows per compute unit (98 to 128, or from 192 on), whole steps and lines, few copies, rows that follow each other, alignment of X.
+@pytest.mark.parametrize("C,g,s,N,extra,inside,outside", [
+    (512, 1, 26, 64, 0, (98 * 256, 25088 + 7, 128 * 256, 192 * 256, 802816), (96 * 256, 98 * 256 - 1, 128 * 256 + 1, 160 * 256, 192 * 256 - 1)),
+    (256, 9, 12, 256, 0, (98 * 256, 128 * 256, 200704), (97 * 256, 176 * 256)), (512, 9, 25, 1, 0, (98 * 256,), (97 * 256,)),
+    (384, 1, 76, 100, 0, (100 * 256,), ()), (384, 1, 77, 100, 0, (), (100 * 256,)), (1024, 1, 204, 64, 0, (200 * 256,), ()),
+    (1024, 1, 205, 64, 0, (), (200 * 256,)), (512, 1, 26, 64, 32, (), (100 * 256,)), (1024, 1, 51, 64, 32, (100 * 256,), ()),
+    (1024, 1, 51, 64, 8, (), (100 * 256,)), (320, 1, 16, 64, 0, (), (100 * 256, 802816)), (400, 1, 20, 64, 0, (), (100 * 256,)),
+    (512, 1, 26, 257, 0, (), (100 * 256,))])
+def test_forward_of_many_rows_by_rows_and_copies(C, g, s, N, extra, inside, outside):
+    ld = B.ocs_padded_cols((C + s) * g)
+    for M in inside:
+        assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=1 << 20) == 2, M
+        assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, captured=True, X=1 << 20) == 2, M
+        assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=(1 << 20) + 64) == 0, M
+    for M in outside:
+        assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=1 << 20) == 0, M
+
+
 def test_forward_route_of_refused_shapes_and_forced_kernels():
     assert B.ocs_forward_one_launch(0, 64, 1, 64, 1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 63, 1, 128, 128, 64) == 0
     assert B.ocs_forward_one_launch(4, 64, 1, 64, -1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 0) == 0
