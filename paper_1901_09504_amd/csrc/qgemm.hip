@@ -2760,15 +2760,20 @@ hipError_t launch_qgemm(const int8_t* Xq, int64_t ldx, const int8_t* Wq, int64_t
             // 2000 x 2000 x 2000 22.4 -> 17.9 with 256 of the small ones; 6000 x 3000 x 3000 112 -> 94 with three
             // rounds of the middle ones instead of two of the large; 25088 x 256 x 1076 40.6 / 41.7 / 46.5, 50176 x 256
             // x 1076 78 / 81 / 76, 12544 x 256 x 2358 62 / 58 / 77 for middle / small / large).
-            const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128), cus = compute_units();
+            const int64_t t128 = ceil_div(M, 128) * ceil_div(N, 128), t192 = ceil_div(M, 192) * ceil_div(N, 128), cus = compute_units();
             const int64_t large = 35 * ceil_div(t256sq, cus), middle = 20 * ceil_div(t256, cus), small = 12 * ceil_div(t128, cus);
             if (N >= 256 && large < middle && large <= small) tile = 12;
-            else if (middle <= small && ldx >= round_up(Kpad, 128) && ldw >= round_up(Kpad, 128) &&
-                     ceil_div(M, 192) * ceil_div(N, 128) <= cus && ceil_div(M, 192) * 192 <= ceil_div(M, 256) * 256)
+            else if (middle <= small && ldx >= round_up(Kpad, 128) && ldw >= round_up(Kpad, 128) && t192 <= cus &&
+                     ceil_div(M, 192) * 192 <= ceil_div(M, 256) * 256 &&
+                     (32 * t192 <= 29 * cus || Kpad >= (N <= 256 ? 2048 : 1344)))
                 // 192 x 128 where that is still one round and walks no more rows: the compute units the middle size leaves
                 // idle get a tile, each a quarter smaller (both launches, us: 700 x 6000 x 3150, 188 tiles for 141, 28.8 -> 25.1;
                 // 800 x 5000 x 4200 35.2 -> 30.8; 1400 x 3000 x 3150 29.6 -> 26.5; 9000 x 512 x 1076 22.9 -> 21.4; 40000 x 100 x
-                // 1575 68.3 -> 67.3; with 576 rows walked for 512, 400 x 8000 x 3150 22.5 -> 23.2)
+                // 1575 68.3 -> 67.3; with 576 rows walked for 512, 400 x 8000 x 3150 22.5 -> 23.2).  The tiles together ask for more than
+                // the middle size's: where nearly every compute unit has one and K is short, that is what counts, on some chips more than on
+                // others (24576 x 256 x 1110 36.6 -> 40.0, another 35.0 -> 34.0; 24576 x 256 x 2397 70 -> 70, 3932 x 1500 x 1260 22.9 -> 24.3,
+                // 16181 x 300 x 1257 level; 12167 x 512 x 1396 31.0 -> 30.2, 5729 x 1024 x 1381 23.5 -> 21.8, 22000 x 256 x 1575, 230 tiles,
+                // 45.3 -> 45.0)
                 tile = 33;
             else if (middle <= small)
                 // the middle size as 128 x 256 for a very long K and fewer tiles than compute units: X rows asked for

@@ -1575,7 +1575,8 @@ def _panel(mode, fn):
         B.ocs_tune("panel_layer", -1)
 
 
-@pytest.mark.parametrize("M,N,K", [(700, 6000, 3150), (3000, 1500, 1575)])
+# (the last two: nearly every compute unit a tile, on either side of the shortest K)
+@pytest.mark.parametrize("M,N,K", [(700, 6000, 3150), (3000, 1500, 1575), (12280, 500, 1400), (12280, 500, 1270)])
 def test_qgemm_route_of_one_round_of_192_rows(M, N, K):
     ld = B.ocs_padded_cols(K)
     gen = torch.Generator(device="cuda").manual_seed(M)
