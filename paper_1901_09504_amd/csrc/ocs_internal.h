@@ -45,6 +45,9 @@ struct Workspace {
 };
 Workspace plan_workspace(int64_t rows, int64_t cols);
 
+// Compute units of the current device (looked up once per device; 256 if the query fails).
+int compute_units();
+
 // ---- launchers (each returns the hipError_t of its launches) ---------------------------------
 
 // colmax[c] = max_r |T[r, c]| for c < cols.  Two stages, no atomics, deterministic.

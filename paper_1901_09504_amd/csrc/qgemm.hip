@@ -1435,8 +1435,7 @@ __global__ __launch_bounds__(WAVES_M * WAVES_N * 64) void qconv_patch_kernel(
 constexpr int64_t kWholeKMaxLds = 160 * 1024;  // LDS of one CU
 constexpr int kMaxDevices = 64;
 
-// Compute units of the current device (looked up once per device; 256 if the query fails).
-static int compute_units() {
+int compute_units() {
     static std::atomic<int> cached[kMaxDevices];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;

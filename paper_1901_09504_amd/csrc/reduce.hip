@@ -269,7 +269,8 @@ hipError_t launch_colmax(const float* T, int64_t rows, int64_t cols, int64_t ld,
 // a lane on their way at a time, and so few blocks that the selector folds their partial rows itself (no stage 2, one
 // launch less).  TX lanes share a row (512 bytes with 32), 1024 / TX rows at a time; the last group of a row is its last four
 // columns, which may be another group's as well: both find the same maxima.
-// What bounds it: HBM (6000 x 3000, 72 MB, 15 us either way); what it saves is stage 2 and its launch.  Selection with its
+// What bounds it: three batches of eight requests a lane at 6000 x 3000, each waited for as a whole (72 MB: 27.6 us on cold caches,
+// 2.6 TB/s, 15 partly from the last-level cache, with stage 2 as well); what it saves is stage 2 and its launch.  Selection with its
 // maxima, us, with stage 2 / without: 6000 x 3000 28.4 / 25.4, 2048 x 512 13.1 / 10.2, 6272 x 2048 20.2 / 18.3.
 constexpr int kStripThreads = 1024;
 template <int TX>
@@ -333,15 +334,24 @@ hipError_t launch_colmax_blocks(const float* T, int64_t rows, int64_t cols, int6
     const int64_t strips = ceil_div(units, tx);
     // a workgroup per compute unit, of at least four rows a lane; no more partial rows than the caller's reader folds and
     // the workspace has room for
-    int64_t rb = 256 / strips;
+    const int64_t cus = compute_units(), values = rows * cols;
+    int64_t rb = cus / strips;
     if (rb > ceil_div(rows, 4 * ty)) rb = ceil_div(rows, 4 * ty);
+    bool two = false;
     if (rb > most / cols) {
-        // what the reader folds leaves fewer than half of the compute units a workgroup: the two launches (the weights of 520
-        // rows of 4608 values prepared in 17.2 us, 18.0 with 108 workgroups)
-        if (most / cols * strips < 128) return launch_colmax(T, rows, cols, ld, colmax, partial, stream);
+        // What the reader folds leaves fewer than half of the compute units a workgroup, or the tensor is so large that the idle ones
+        // count for more than a launch (a whole preparation, two launches / one: 520 x 4608 17.2 us, 18.0 with 108 workgroups;
+        // 16000 x 512 40.5 / 36.5 with 128, 25000 x 512 54 / 51, 50000 x 512 89 / 91.5, 100000 x 512 160 / 174, 100000 x 576 161 / 177)
         rb = most / cols;
+        two = 2 * rb * strips < cus || values >= (int64_t)20 << 20;
     }
     if (rb < 1) rb = 1;
+    // Strips that divide the compute units badly: fewer than three quarters of them on a large tensor (4100 x 17000 161 / 163, 6000 x
+    // 19800 273 / 278; 2100 x 17000 82 / 79), or a second round that is less than half full (2100 x 33000 174 / 189, 6000 x 36000
+    // 484 / 519; 2100 x 45000 level, 2100 x 60000 321 / 313)
+    const int64_t last = strips % cus;
+    two = two || (4 * strips * rb < 3 * cus && values >= (int64_t)64 << 20) || (strips > cus && last > 0 && 2 * last < cus);
+    if (two) return launch_colmax(T, rows, cols, ld, colmax, partial, stream);
     const int per = (int)ceil_div(rows, rb);
     rb = ceil_div(rows, per);
     float* dst = rb == 1 ? colmax : partial;

@@ -1679,6 +1679,30 @@ def test_selection_on_row_blocks(rows, C, g, s, ld_extra):
     assert np.array_equal(got["Wq"], q_ref) and np.array_equal(got["scale"], sw_ref)
 
 
+# Tensors whose strips give the chip a badly filled last round, or whose fold would leave compute units idle: two launches.  One
+# split: the channel of the largest column maximum, and what is then the largest value of the list.
+@pytest.mark.parametrize("rows,C,g", [(2100, 3300, 10), (36500, 64, 9), (4200, 1600, 10), (2100, 1200, 50)])
+def test_selection_on_large_tensors(rows, C, g):
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    T = torch.randn((rows, C * g), device="cuda", generator=gen)
+    T[rows - 1, (C * g) // 3], T[rows // 2, C * g - 1] = -31.0, 27.0
+    chan = T.abs().amax(0).view(C, g).amax(1)
+    ws = B.alloc_workspace(rows, C * g)
+    ws.fill_(0x7F)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    ss, cs, cd, mx = torch.empty(1, **i32), torch.empty(C + 1, **i32), torch.empty(C + 1, **i32), torch.zeros(1, device="cuda")
+    B.ocs_select_channels(T, rows, C, g, C * g, 1, ss, cs, cd, mx, ws)
+    src = int(chan.argmax())
+    assert int(ss[0]) == src and int(cs[C]) == src and int(cd[src]) == 1 and int(cd[C]) == 1
+    chan[src] /= 2
+    assert float(mx[0]) == float(chan.max())
+    ldq, sw = B.ocs_padded_cols((C + 1) * g), torch.zeros(2, device="cuda")
+    Wq = torch.full((rows, ldq), 77, dtype=torch.int8, device="cuda")
+    ws.fill_(0x7F)
+    B.ocs_split_weights(T, rows, C, g, C * g, 1, B.MODE_HALVE, ss, cs, cd, None, 0, mx, 6, 1.0, Wq, ldq, sw, ws)
+    assert int(ss[0]) == src and float(mx[0]) == float(chan.max()) and float(sw[0]) == float(chan.max())
+
+
 # ---- ocs_forward_act: channels chosen on the batch, as one call ---------------------------------------
 
 # The weights' copies in the last workgroups of the pass over X (one and several columns per channel, rows that are not whole
