@@ -1138,10 +1138,10 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
 template <bool FEW, bool BLOCKS>
 __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     const float* __restrict__ W, int64_t ldw, int64_t N, int C, int g, int s,
-    const float* __restrict__ colmax, int blocks, int32_t* __restrict__ split_src,
+    const float* __restrict__ colmax, int32_t* __restrict__ split_src,
     int32_t* __restrict__ chan_src, int32_t* __restrict__ chan_depth, float* __restrict__ max_out,
     float clip_ratio, float qmax, float* __restrict__ scale_out, int8_t* __restrict__ Wq, int D,
-    int main_units, unsigned magic) {
+    int main_units, unsigned magic, int blocks) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int E = C + s, Ke = E * g;
     unsigned long long* cand = reinterpret_cast<unsigned long long*>(smem);
@@ -1259,8 +1259,8 @@ hipError_t launch_select_expand_quantize(const float* W, int64_t ldw, int64_t N,
     const auto kernel = blocks > 1 ? (few_steps(C, s) ? select_expand_quantize_kernel<true, true> : select_expand_quantize_kernel<false, true>)
                                    : (few_steps(C, s) ? select_expand_quantize_kernel<true, false> : select_expand_quantize_kernel<false, false>);
     return launch_kernel(kTimeSplitQuantize, kernel, dim3((unsigned)grid), dim3(kThreads), greedy_list_bytes(E), stream,
-                         W, ldw, N, C, g, s, colmax, blocks, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax,
-                         scale_out, Wq, D, main_units, magic);
+                         W, ldw, N, C, g, s, colmax, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax,
+                         scale_out, Wq, D, main_units, magic, blocks);
 }
 
 // fp32 expanded tensor (Eq. 3 with halve != 0, the weight side of Eq. 4 with halve == 0).
