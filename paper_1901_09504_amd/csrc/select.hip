@@ -18,10 +18,10 @@ namespace ocs {
 // taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
 template <int NT, bool FEW, bool BLOCKS>
 __global__ __launch_bounds__(NT) void select_kernel(
-    const float* __restrict__ colmax, int blocks, int C, int g, int s, int mode,
+    const float* __restrict__ colmax, int C, int g, int s, int mode,
     const int32_t* split_in, int32_t* split_src,
     int32_t* __restrict__ chan_src, int32_t* __restrict__ chan_depth, float* __restrict__ max_out,
-    float clip_ratio, float qmax, float* __restrict__ scale_out) {
+    float clip_ratio, float qmax, float* __restrict__ scale_out, int blocks) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int E = C + s;
     unsigned long long* cand = reinterpret_cast<unsigned long long*>(smem);
@@ -92,8 +92,8 @@ static hipError_t run_select(const float* colmax, int blocks, int C, int g, int 
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    select_kernel<NT, FEW, BLOCKS><<<1, NT, lds, stream>>>(colmax, blocks, C, g, s, mode, split_in, split_src, chan_src,
-                                              chan_depth, max_out, clip_ratio, qmax, scale_out);
+    select_kernel<NT, FEW, BLOCKS><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
+                                              max_out, clip_ratio, qmax, scale_out, blocks);
     return hipGetLastError();
 }
 
