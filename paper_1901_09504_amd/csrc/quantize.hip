@@ -1044,7 +1044,9 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
             return launch_shot<0, 3>(OCS_SHOT_ARGS);
         }
         if (!halve) return launch_shot<0, 0>(OCS_SHOT_ARGS);
-        if (dup_codes != nullptr && !stepwise && N * (ldw - K) <= (int64_t)1 << 32) {    // (the grid's workgroups stay countable in 32 bits)
+        // (a launch's lanes are counted in 32 bits; the copies that do not fit beside the pass do in a launch of their own)
+        const int64_t workgroups = ceil_div(M, p.R) + (dup_codes != nullptr ? ceil_div(N * (ldw - K), kShotNT) : 0);
+        if (dup_codes != nullptr && !stepwise && workgroups * kShotNT < (int64_t)1 << 32) {
             const DupTail dt = {dup_codes, ldw, N, 0};
             return g == 1 ? launch_shot<1, 0, true>(OCS_SHOT_ARGS, &dt) : launch_shot<1, 0>(OCS_SHOT_ARGS, &dt);
         }

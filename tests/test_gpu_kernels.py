@@ -1738,3 +1738,28 @@ def test_forward_act_as_one_call(M, C, g, s, N, clip):
     assert np.array_equal(host(sx).view(np.uint32), sx_ref.view(np.uint32))
     assert np.array_equal(host(acc), acc_ref)
     assert_y_close(host(Y), y_ref)
+
+
+def test_forward_act_copies_of_four_gigabytes():
+    """Appended and padding columns that are just below 2^32 lanes by themselves, and at it with the pass over X beside them."""
+    M, C, s, N = 640, 64, 3, (1 << 20) - 1
+    ldw, ldq, gen = C + 4096, B.ocs_padded_cols(C + s), torch.Generator(device="cuda").manual_seed(1)
+    X = torch.randn((M, C), device="cuda", generator=gen)
+    codes = torch.randint(-31, 32, (N, C), device="cuda", generator=gen, dtype=torch.int8)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    sw, ws, out = torch.tensor([1.5, 0.1], device="cuda"), B.alloc_workspace(M, C), []
+    for one in (True, False):
+        wd = torch.full((N, ldw), 55, dtype=torch.int8, device="cuda")
+        wd[:, :C] = codes
+        ss, cs, cd, mx, sx = torch.zeros(s, **i32), torch.zeros(C + s, **i32), torch.zeros(C + s, **i32), torch.zeros(1, device="cuda"), torch.zeros(2, device="cuda")
+        q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+        Y = torch.zeros((M, N), device="cuda")
+        if one:
+            B.ocs_forward_act(X, M, C, 1, C, s, 8, 1.0, ss, cs, cd, mx, q, ldq, sx, wd, ldw, N, 6, sw, None, 0, Y, N, ws)
+        else:
+            B.ocs_select_channels(X, M, C, 1, C, s, ss, cs, cd, mx, ws)
+            B.ocs_duplicate_weight_codes(wd, ldw, N, C, 1, s, cs)
+            B.ocs_split_act(X, M, C, 1, C, cs, cd, s, 8, mx, 1.0, q, ldq, sx, ws)
+            B.ocs_qgemm(q, ldq, wd, ldw, M, N, C + s, 8, 6, sx, sw, None, 0, Y, N)
+        out.append((ss, cs, cd, mx, q, sx, wd, Y))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
