@@ -303,8 +303,8 @@ int ocs_qgemm(const int8_t *Xq, int64_t ldx, const int8_t *Wq, int64_t ldw, int6
  * Xq [M, ldq] with its padding, scale_x_out {T, T / qmax}, Y and, if given, acc_out, bit for bit.  Layers of few output tiles, and
  * layers of many long rows with up to 256 outputs, run as one launch (plus the max|X| pass where it has to be one; fewer of the
  * first in a stream that is being captured, where a launch costs the host nothing); where Y,
- * acc_out, Xq or scale_x_out share memory with X, the threshold, chan_src or (for the batch's own maximum) the workspace, and on
- * every other shape, the two launches run.
+ * acc_out, Xq or scale_x_out share memory with X, the threshold, chan_src, Wq, scale_w or (for the batch's own maximum) the
+ * workspace, and on every other shape, the two launches run.
  */
 int ocs_forward(const float *X, int64_t M, int C, int g, int64_t ldx, const int32_t *chan_src,
                 int num_splits, int bits_x, const float *threshold, float clip_ratio, int8_t *Xq,

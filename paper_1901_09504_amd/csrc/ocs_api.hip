@@ -583,6 +583,8 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
     hipStream_t st = static_cast<hipStream_t>(stream);
     // One launch reads X while outputs are being written: an output that shares memory with X, the threshold, the sources or the
     // maxima (a layer applied to its own output) keeps the two, the first of which has read them all before the second begins.
+    // So do codes or a scale of X that are the weights' own (products of the rows of X with each other): the second launch reads
+    // what the first has written.
     const int64_t xb = 4 * ((M - 1) * ldx + K), yb = 4 * ((M - 1) * ldy + N), ab = 4 * ((M - 1) * ldacc + N), qb = M * ldq;
     auto clear_of_outputs = [&](const void* in, int64_t bytes) {
         return !overlap(in, bytes, Y, yb) && !overlap(in, bytes, acc_out, ab) && !overlap(in, bytes, Xq, qb) &&
@@ -590,7 +592,8 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
     };
     const bool apart = clear_of_outputs(X, xb) && clear_of_outputs(threshold, 4) &&
                        clear_of_outputs(num_splits > 0 ? chan_src : nullptr, 4 * (int64_t)(C + num_splits)) &&
-                       clear_of_outputs(threshold == nullptr ? workspace : nullptr, (int64_t)ws_bytes);
+                       clear_of_outputs(threshold == nullptr ? workspace : nullptr, (int64_t)ws_bytes) &&
+                       clear_of_outputs(Wq, N * ldw) && clear_of_outputs(scale_w, 8);
     ForwardRoute route = ForwardRoute::two;
     if (apart) {
         route = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, false);

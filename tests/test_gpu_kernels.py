@@ -1565,6 +1565,26 @@ def test_forward_over_its_own_input():
     assert_y_close(host(buf), y_ref)
 
 
+@pytest.mark.parametrize("own_scale", [False, True])
+def test_forward_on_its_own_codes_as_weights(own_scale):
+    """Wq is Xq (the products of the rows of X with each other), scale_w in one case scale_x_out: what the first step writes."""
+    M, C, s = 70, 256, 8
+    rng = np.random.default_rng(9)
+    X = _tensor(rng, M, C, "heavy")
+    cs = np.concatenate([np.arange(C), rng.integers(0, C, s)]).astype(np.int32)
+    ldq = B.ocs_padded_cols(C + s)
+    q = torch.full((M, ldq), 77, dtype=torch.int8, device="cuda")
+    sx, sw = torch.full((2,), -1.0, device="cuda"), torch.tensor([1.5, 0.1], device="cuda")
+    Y, acc = torch.empty((M, M), device="cuda"), torch.empty((M, M), dtype=torch.int32, device="cuda")
+    B.ocs_forward(dev(X), M, C, 1, C, dev(cs), s, 8, None, 1.0, q, ldq, sx, q, ldq, M, 8, sx if own_scale else sw, acc, M, Y, M,
+                  B.alloc_workspace(M, C))
+    q_ref, sx_ref, _ = ref.split_act(X, C, 1, cs, None, s, 8, threshold=None, clip_ratio=1.0, ldq=ldq)
+    acc_ref, y_ref = ref.qgemm(q_ref, q_ref, C + s, sx_ref[1], sx_ref[1] if own_scale else np.float32(0.1))
+    assert np.array_equal(host(q), q_ref) and np.array_equal(host(sx).view(np.uint32), sx_ref.view(np.uint32))
+    assert np.array_equal(host(acc), acc_ref)
+    assert_y_close(host(Y), y_ref)
+
+
 # ---- ocs_forward on many rows: quantizing and multiplying waves in one launch ------------------------
 
 def _panel(mode, fn):
