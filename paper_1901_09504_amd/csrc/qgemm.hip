@@ -1843,16 +1843,16 @@ struct PanelLayer {
 };
 
 constexpr int kPanelMaxTail = 256;     // appended columns s*g
+constexpr int kPanelStep = 128;        // columns of a step: whole lines of codes
 
-template <int BM, int BN, int BK, int NQ, int WAVES_M, int WAVES_N, int RA>
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_kernel(PanelLayer p) {
     constexpr int NM = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
-    constexpr int CPR = BK / 16, LG = BK == 64 ? 6 : 7;      // 16-byte pieces of a row of codes
+    constexpr int BK = kPanelStep, CPR = BK / 16, LG = 7;    // 16-byte pieces of a row of codes, BK = 1 << LG
     constexpr int LPR = BK / 4, RPL = 64 / LPR;              // X: lanes per row, rows per request
     constexpr int RPW = BM / NQ, LA = RPW / RPL;             // rows and requests of a step per quantizing wave
     constexpr int LB = BN * BK / 1024 / NM;                  // requests of a step of W per multiplying wave
-    static_assert(BK == 64 || BK == 128, "steps of half or whole lines of codes");
     static_assert(TM >= 1 && TN >= 1 && TM * 32 * WAVES_M == BM && TN * 32 * WAVES_N == BN && LA >= 1 && LB >= 1, "tile");
     static_assert(NQ + NM <= 16, "waves of a workgroup");
 
@@ -1895,12 +1895,12 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
 
     if (multiplier) {
         // W: request u of multiplying wave f fills block u * NM + f of the step (the swizzle is the same for every u)
-        static_assert(BK == 64 || NM % 2 == 0, "the blocks of a wave begin at rows of one parity");
+        static_assert(NM % 2 == 0, "the blocks of a wave begin at rows of one parity");
         unsigned wsrc[LB];
         const int w_end = (int)(p.ldw / 16);
         const int wpiece = swz<BK>((mw * 64 + lane) / CPR, lane % CPR);
 #pragma unroll
-        for (int u = 0; u < LB; ++u)                         // (N <= 512 rows of at most kFusedMaxK + kFusedMaxTail codes and their padding)
+        for (int u = 0; u < LB; ++u)                         // (at most 256 rows, ldw < 2^23)
             wsrc[u] = (unsigned)col_clamp(((u * NM + mw) * 64 + lane) / CPR, p.N) * (unsigned)p.ldw;
         const unsigned w0 = lds0 + (unsigned)(2 * BM * BK + mw * 1024);
         auto fetch_w = [&](int kt) {
@@ -1986,7 +1986,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
     int at[LA];                                              // this lane's four codes inside a step's buffer
     const char* xbase;
     char* qbase;
-    f32x4 av[RA][LA];
+    f32x4 av[LA];
     auto load_x = [&](int kt, int u) -> f32x4 {
         const bool main_step = kt < p.kmain, rest = kt == p.kmain && c4 < p.rem;
         // left-over columns: four floats that would cross the row's end start four before it (K >= 64) and are shifted into
@@ -2014,9 +2014,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
             at[u] = r * BK + swz<BK>(r, c4 >> 4) * 16 + (c4 & 15);
         }
 #pragma unroll
-        for (int k = 0; k < RA; ++k)
-#pragma unroll
-            for (int u = 0; u < LA; ++u) av[k][u] = load_x(k, u);
+        for (int u = 0; u < LA; ++u) av[u] = load_x(0, u);
     };
     auto code4 = [&](const f32x4& v) -> unsigned {
         return pack4(code_bits(v[0], inv, p.qmax), code_bits(v[1], inv, p.qmax), code_bits(v[2], inv, p.qmax), code_bits(v[3], inv, p.qmax));
@@ -2057,58 +2055,49 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                 if (r < own) *reinterpret_cast<i32x4*>(&tail[k * (BM * BK) + (wave * p.rpw + r) * BK + c * 16]) = z;
             }
         }
-        int it0 = 0;
-        if (live && p.kmain >= 2 * RA) {
-            // steps whose requests ahead are whole ones, without a condition; the first RA of them by themselves: the requests
-            // and writes under way are then the same number on every way into the loop, and its waits no stricter than they must be
-            auto steps = [&]() {
+        int it = 0;
+        if (live && p.kmain >= 2) {
+            // steps whose requests ahead are whole ones, without a condition; the first of them by itself: the requests and
+            // writes under way are then the same number on every way into the loop, and its waits no stricter than they must be
+            auto step = [&]() {
 #pragma unroll
-                for (int k = 0; k < RA; ++k) {
-#pragma unroll
-                    for (int u = 0; u < LA; ++u) {
-                        quantize(it0 + k, u, av[k][u]);
-                        av[k][u] = __builtin_nontemporal_load(
-                            reinterpret_cast<const f32x4u*>(xbase + (int64_t)step_of(it0 + k + RA) * (4 * BK) + xoff[u]));
-                        __builtin_amdgcn_sched_barrier(0);   // (or the arithmetic of later steps, and its waits, move ahead)
-                    }
-                    copies(it0 + k);
-                    step_barrier();
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int u = 0; u < LA; ++u) {
+                    quantize(it, u, av[u]);
+                    av[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(xbase + (int64_t)step_of(it + 1) * (4 * BK) + xoff[u]));
+                    __builtin_amdgcn_sched_barrier(0);       // (or the arithmetic of later requests, and its waits, move ahead)
                 }
-                it0 += RA;
-            };
-            steps();
-            while (it0 + 2 * RA <= p.kmain) steps();
-        }
-        for (; it0 < nx; it0 += RA) {
-#pragma unroll
-            for (int k = 0; k < RA; ++k) {
-                const int it = it0 + k;
-                if (it >= nx) break;
-                if (live && it < p.kmain) {
-#pragma unroll
-                    for (int u = 0; u < LA; ++u) {
-                        quantize(it, u, av[k][u]);
-                        av[k][u] = load_x(it + RA, u);
-                    }
-                    copies(it);
-                } else if (live) {
-#pragma unroll
-                    for (int u = 0; u < LA; ++u) {
-                        const unsigned q4 = code4(av[k][u]);
-                        if (c4 + 3 < p.rem) {
-                            *reinterpret_cast<unsigned*>(tail + at[u]) = q4;
-                        } else {
-                            const int d = c4 - (p.rem - 4);  // (fetched as columns rem - 4 .. rem - 1)
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (c4 + e < p.rem) tail[at[u] + e] = (int8_t)((q4 >> (8 * (e + d))) & 0xFFu);
-                        }
-                    }
-                    copies(it);
-                }
+                copies(it);
                 step_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                ++it;
+            };
+            step();
+            while (it + 2 <= p.kmain) step();
+        }
+        for (; it < nx; ++it) {
+            if (live && it < p.kmain) {
+#pragma unroll
+                for (int u = 0; u < LA; ++u) {
+                    quantize(it, u, av[u]);
+                    av[u] = load_x(it + 1, u);
+                }
+                copies(it);
+            } else if (live) {
+#pragma unroll
+                for (int u = 0; u < LA; ++u) {
+                    const unsigned q4 = code4(av[u]);
+                    if (c4 + 3 < p.rem) {
+                        *reinterpret_cast<unsigned*>(tail + at[u]) = q4;
+                    } else {
+                        const int d = c4 - (p.rem - 4);      // (fetched as columns rem - 4 .. rem - 1)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (c4 + e < p.rem) tail[at[u] + e] = (int8_t)((q4 >> (8 * (e + d))) & 0xFFu);
+                    }
+                }
+                copies(it);
             }
+            step_barrier();
         }
         // what follows the whole steps of a row: left-over columns, copies, and zeros up to the pitch (this wave's rows of the
         // tail are complete)
@@ -2123,12 +2112,13 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
             }
         }
         if (tile + (int)gridDim.x < p.tiles) begin(tile + (int)gridDim.x);
-        for (int it = nx; it < p.kall + 1; ++it) step_barrier();         // the tail's steps, and the last of the operands
+        for (; it < p.kall + 1; ++it) step_barrier();                    // the tail's steps, and the last of the operands
     }
 }
 
-template <int BM, int BN, int BK, int NQ, int WAVES_M>
+template <int BM, int BN, int NQ, int WAVES_M>
 static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
+    constexpr int BK = kPanelStep;
     const int64_t tail = 2 * (BM + BN) * BK, list = tail + tail_steps * BM * BK, stage = list + NQ * kPanelMaxTail * 4;
     if (p != nullptr) {
         p->tail_off = (int)tail;
@@ -2138,13 +2128,14 @@ static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
     return stage + WAVES_M * 8 * BN * 4;
 }
 
-template <int BM, int BN, int BK, int NQ, int WAVES_M, int WAVES_N, int RA>
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
 static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
+    constexpr int BK = kPanelStep;
     const int64_t K = (int64_t)p.C * p.g, Kexp = (int64_t)(p.C + p.s) * p.g;
     p.kmain = (int)(K / BK);
     p.kall = (int)ceil_div(Kexp, BK);
     p.rem = (int)(K - (int64_t)p.kmain * BK);
-    const int64_t o = panel_lds<BM, BN, BK, NQ, WAVES_M>(p.kall - p.kmain, &p);
+    const int64_t o = panel_lds<BM, BN, NQ, WAVES_M>(p.kall - p.kmain, &p);
     if (o > kWholeKMaxLds) return hipErrorInvalidValue;
     static std::atomic<bool> opted_in[kMaxDevices];
     int dev = 0;
@@ -2152,7 +2143,7 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     if (!opted_in[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, BK, NQ, WAVES_M, WAVES_N, RA>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
         if (e != hipSuccess) return e;
         opted_in[dev].store(true, std::memory_order_release);
@@ -2164,15 +2155,15 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     p.stride = (int)st;
     p.rpw = (int)ceil_div(st, NQ);
     p.tiles = (int)ceil_div(p.M, st);
-    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, BK, NQ, WAVES_M, WAVES_N, RA>,
+    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>,
                          dim3((unsigned)(p.tiles < slots ? p.tiles : slots)), dim3((NQ + WAVES_M * WAVES_N) * 64), (unsigned)o, stream, p);
 }
 
 static bool panel_fits(int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq, int64_t ldw, int64_t N) {
     const int64_t K = (int64_t)C * g, T = (int64_t)s * g, pitch = (int64_t)1 << 23;      // (offsets of 128 rows in 32 bits)
     if (K < 64 || T > kPanelMaxTail || N > 256 || M > 0x7FFFFFFF - 256 || ldx >= pitch || ldq >= pitch || ldw >= pitch) return false;
-    const int64_t tail_steps = ceil_div(K + T, 128) - K / 128;
-    return panel_lds<128, 256, 128, 8, 2>(tail_steps, nullptr) <= kWholeKMaxLds;         // (the widest)
+    const int64_t tail_steps = ceil_div(K + T, kPanelStep) - K / kPanelStep;
+    return panel_lds<128, 256, 8, 2>(tail_steps, nullptr) <= kWholeKMaxLds;              // (the widest: at most two steps of the tail)
 }
 
 hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
@@ -2184,9 +2175,9 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
-    if (N <= 64) return run_panel<128, 64, 128, 8, 4, 2, 1>(p, stream);
-    if (N <= 128) return run_panel<128, 128, 128, 8, 2, 4, 1>(p, stream);
-    return run_panel<128, 256, 128, 8, 2, 4, 1>(p, stream);
+    if (N <= 64) return run_panel<128, 64, 8, 4, 2>(p, stream);
+    if (N <= 128) return run_panel<128, 128, 8, 2, 4>(p, stream);
+    return run_panel<128, 256, 8, 2, 4>(p, stream);
 }
 
 // Where the one launch is ahead of the two (two launches / one; in a graph on inputs outside the caches, in a graph on the same input
