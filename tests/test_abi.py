@@ -277,3 +277,23 @@ def test_forward_reports_what_its_two_steps_report():
     assert fwd(bx=9) == -4 and fwd(bw=1) == -4 and fwd(s=-1) == -5
     assert fwd(C=7000, ldx=140000, g=20, s=0, ldq=140032, ldw=140032) == -6
     assert fwd(thr=None, w=None, wb=0) == -7 and fwd(thr=None, clip=0.0) == -10
+
+
+def test_forward_act_reports_what_its_steps_report():
+    L = B.lib()
+
+    def fwd(X=A, M=4, C=8, g=1, ldx=8, s=2, bx=8, clip=1.0, ss=A, cs=A, cd=A, mx=A + 4096, Xq=A, ldq=64, sx=A, Wq=A, ldw=64, N=4, bw=8,
+            sw=A, acc=None, ldacc=0, Y=A, ldy=4, w=A, wb=1 << 24):
+        return L.ocs_forward_act(X, M, C, g, ldx, s, bx, clip, ss, cs, cd, mx, Xq, ldq, sx, Wq, ldw, N, bw, sw, acc, ldacc, Y, ldy, w, wb,
+                                 None)
+
+    for name in ("X", "ss", "cs", "cd", "mx", "Xq", "sx", "Wq", "sw", "Y"):
+        assert fwd(**{name: None}) == -1, name
+    assert fwd(M=0) == -2 and fwd(ldx=7) == -2 and fwd(N=0) == -2 and fwd(ldq=0) == -2 and fwd(ldw=0) == -2 and fwd(ldy=3) == -2
+    assert fwd(acc=A, ldacc=3) == -2
+    assert fwd(Xq=A + 1) == -3 and fwd(ldq=24) == -3 and fwd(Wq=A + 4) == -3 and fwd(w=A + 16) == -3
+    assert fwd(bx=9) == -4 and fwd(bw=1) == -4 and fwd(s=-1) == -5
+    assert fwd(C=7000, ldx=140000, g=20, s=0, ldq=140032, ldw=140032) == -6
+    assert fwd(w=None, wb=0) == -7 and fwd(wb=16) == -7
+    assert fwd(clip=0.0) == -10 and fwd(clip=-1.0) == -10 and fwd(clip=float("inf")) == -10
+    assert fwd(mx=A) == -9 and fwd(mx=A + 4) == -9          # the maximum in scale_x_out: read by one workgroup, written by another

@@ -1463,8 +1463,9 @@ def test_activation_ocs_with_qa_members_end_to_end():
 
 # ---- ocs_forward: the layer as one call -------------------------------------------------------------
 
-def _forward_once(M, C, g, s, N, ld_extra, threshold, clip, mode, seed=0, bits_w=5, ldq_extra=0):
-    """One ocs_forward call with dirty outputs against the oracle's two steps, all outputs bit for bit."""
+def _forward_once(M, C, g, s, N, ld_extra, threshold, clip, mode, seed=0, bits_w=5, ldq_extra=0, route=None):
+    """One ocs_forward call with dirty outputs against the oracle's two steps, all outputs bit for bit.  route: the kernels it has
+    to take (by default the one launch of few tiles where mode asks for it)."""
     rng = np.random.default_rng(1000 * M + C + 7 * N + s + seed)
     K, Ke = C * g, (C + s) * g
     X, W = _tensor(rng, M, K, "heavy"), _tensor(rng, N, K, "normal")
@@ -1480,6 +1481,7 @@ def _forward_once(M, C, g, s, N, ld_extra, threshold, clip, mode, seed=0, bits_w
     th = None if threshold is None else torch.tensor([threshold], dtype=torch.float32, device="cuda")
     B.ocs_tune("slice_layer", mode)
     try:
+        assert B.ocs_forward_one_launch(M, C, g, Xd.stride(0), s, ldq, ldq, N, X=Xd) == (mode if route is None else route)
         B.ocs_forward(Xd, M, C, g, Xd.stride(0), dev(sp["chan_src"].astype(np.int32)), s, 8, th, clip, q, ldq, sx, dev(Wq),
                       ldq, N, bits_w, dev(sw), acc, N, Y, N, B.alloc_workspace(M, K))
     finally:
@@ -1587,6 +1589,44 @@ def test_forward_on_its_own_codes_as_weights(own_scale):
 
 # ---- ocs_forward on many rows: quantizing and multiplying waves in one launch ------------------------
 
+def _launched(fn):
+    """Families of kernels that fn launches, by the launch stamps they consume: a pair of events that lie 50 ms apart until then."""
+    families, found = (B.TIME_SPLIT_QUANTIZE, B.TIME_GEMM), []
+    ev = {}
+    for f in families:
+        ev[f] = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        ev[f][0].record()
+        torch.cuda._sleep(120_000_000)
+        ev[f][1].record()
+    torch.cuda.synchronize()
+    for f in families:
+        B.ocs_time_next(f, *ev[f])
+    fn()
+    torch.cuda.synchronize()
+    for f in families:
+        if ev[f][0].elapsed_time(ev[f][1]) < 10:
+            found.append(f)
+    # (pairs left over are used up)
+    X, q, sc = torch.zeros((64, 64), device="cuda"), torch.zeros((64, 64), dtype=torch.int8, device="cuda"), torch.ones(2, device="cuda")
+    B.ocs_quantize(X, 64, 64, 64, 8, sc, 1.0, q, 64, torch.zeros(2, device="cuda"), B.alloc_workspace(64, 64))
+    B.ocs_qgemm(q, 64, q, 64, 64, 64, 64, 8, 8, sc, sc, None, 0, X, 64)
+    torch.cuda.synchronize()
+    return found
+
+
+# The kernels that ocs_forward_one_launch names are those that run, static and per batch.
+@pytest.mark.parametrize("M,C,g,s,N,route", [(64, 256, 1, 13, 256, 1), (64, 1024, 1, 52, 64, 0), (25088, 512, 1, 26, 64, 2), (24576, 512, 1, 26, 64, 0)])
+@pytest.mark.parametrize("static", [True, False])
+def test_forward_takes_the_kernels_it_names(M, C, g, s, N, route, static):
+    from paper_1901_09504_amd.layer import ExpandedLayer
+    L = ExpandedLayer(N, C, g, s / C, 6, 8, max_rows=M)
+    L.prepare_weights(torch.randn((N, C * g), device="cuda"))
+    X, th = torch.randn((M, C * g), device="cuda"), torch.tensor([2.0], device="cuda") if static else None
+    assert L.s == s and B.ocs_forward_one_launch(M, C, g, C * g, s, L.ldq, L.ldq, N, X=X) == route
+    L.forward(X, th)
+    assert _launched(lambda: L.forward(X, th)) == ([B.TIME_GEMM] if route else [B.TIME_SPLIT_QUANTIZE, B.TIME_GEMM])
+
+
 def _panel(mode, fn):
     B.ocs_tune("panel_layer", mode)
     try:
@@ -1618,30 +1658,33 @@ def test_qgemm_route_of_one_round_of_192_rows(M, N, K):
 
 
 # Steps of 128 columns: none whole, one, two (the loop without conditions needs two), left-over columns of 1, 3, 4 and 127 that share
-# their step with copies, none left over; copies in one, two and three steps, none, the most (256); rows around the waves' sixteen,
+# their step with copies, none left over; copies in one step and in two, none, the most (256, with K = 132 in three steps, for which
+# there is no room in LDS: the two launches); rows around the waves' sixteen,
 # the tile's 128 and half of it; outputs around 32, 64, 128, 256; strided rows, padded code rows; rows of 4096 bytes (another
 # first step per workgroup); more tiles than compute units.
 @pytest.mark.parametrize("M,C,g,s,N,ld_extra,ldq_extra", [
     (1, 64, 1, 0, 1, 0, 0), (17, 65, 1, 3, 33, 1, 0), (63, 127, 1, 60, 64, 0, 0), (64, 128, 1, 0, 65, 0, 0), (65, 129, 1, 127, 100, 2, 16),
     (127, 131, 1, 10, 128, 0, 0), (128, 132, 1, 256, 129, 0, 128), (129, 255, 1, 1, 256, 0, 0), (130, 256, 1, 13, 200, 0, 0),
-    (200, 384, 1, 128, 31, 0, 0), (257, 57, 9, 28, 255, 3, 0), (300, 3, 49, 1, 64, 0, 0), (140, 1024, 1, 52, 256, 0, 0),
+    (90, 128, 1, 256, 129, 0, 128), (200, 384, 1, 128, 31, 0, 0), (257, 57, 9, 28, 255, 3, 0), (300, 3, 49, 1, 64, 0, 0), (140, 1024, 1, 52, 256, 0, 0),
     (300, 900, 1, 45, 70, 124, 0), (70, 2048, 4, 64, 20, 0, 0), (33001, 64, 1, 4, 64, 0, 0), (33001, 150, 1, 8, 130, 0, 0)])
 def test_forward_of_many_rows(M, C, g, s, N, ld_extra, ldq_extra):
-    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, ldq_extra=ldq_extra))
+    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, ldq_extra=ldq_extra, route=0 if C == 132 else 2))
 
 
 # Per-batch grids: one maximum, 256 of them, the thousands of a strided tensor
 @pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip", [
     (1, 64, 1, 1, 5, 0, 1.0), (700, 256, 1, 13, 256, 0, 0.9), (3000, 257, 1, 3, 64, 3, 0.8), (33000, 128, 1, 7, 33, 0, 1.0)])
 def test_forward_of_many_rows_per_batch(M, C, g, s, N, ld_extra, clip):
-    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0))
+    _panel(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0, route=2))
 
 
-# What the rule sends there, against the two launches, bit for bit: the fewest and the most rows of one round, rows just over it
-# (which stay with the two), more than a round; rows that begin inside a line stay too.
-@pytest.mark.parametrize("per,extra,C,g,N,ld", [
-    (96, 0, 384, 1, 72, 0), (128, 0, 1024, 1, 256, 0), (128, 5, 512, 1, 64, 0), (160, 3, 448, 1, 128, 0), (100, 1, 64, 9, 40, 32),
-    (100, 0, 400, 1, 64, 0)])
+# What the rule sends there, against the two launches, bit for bit: the fewest and the most rows of one round, rows just below and over it
+# (which stay with the two), more than a round; long rows with a gap, short ones (which stay); rows that begin inside a line stay too.
+MANY_ROWS = [(98, 0, 384, 1, 72, 0), (128, 0, 1024, 1, 256, 0), (192, 3, 448, 1, 128, 0), (100, 1, 1024, 1, 40, 32)]
+
+
+@pytest.mark.parametrize("per,extra,C,g,N,ld", MANY_ROWS + [
+    (96, 0, 384, 1, 72, 0), (128, 5, 512, 1, 64, 0), (160, 3, 448, 1, 128, 0), (100, 1, 64, 9, 40, 32), (100, 0, 400, 1, 64, 0)])
 @pytest.mark.parametrize("threshold", [3.0, None])
 def test_forward_route_of_many_rows(per, extra, C, g, N, ld, threshold):
     from paper_1901_09504_amd.layer import ExpandedLayer
@@ -1651,6 +1694,8 @@ def test_forward_route_of_many_rows(per, extra, C, g, N, ld, threshold):
     L = ExpandedLayer(N, C, g, s / C, 6, 8, max_rows=M)
     L.prepare_weights(torch.randn((N, K), device="cuda", generator=gen))
     th = None if threshold is None else torch.tensor([threshold], device="cuda")
+    route = B.ocs_forward_one_launch(M, C, g, K + ld, L.s, L.ldq, L.ldq, N, X=X)
+    assert route == (2 if (per, extra, C, g, N, ld) in MANY_ROWS else 0)
     out = []
     for mode in (0, -1, -1):          # (twice: nothing is left behind by a pass)
         acc = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
