@@ -17,7 +17,9 @@ its activation tensor (22.3 GB in all, resident in HBM before the timed region),
 reads of a tensor 22 GB stream through the chip and nothing is served by the 256 MB memory-side
 cache.  `value` is whole-pass throughput from the wall clock around the timed steps.  Kernel
 durations come from a second, untimed run of the same steps in which every split+quantize and
-GEMM launch stamps its own begin and end (HIP events on the launch stream).  Prints ONE JSON line.
+GEMM launch stamps its own begin and end (HIP events on the launch stream).  Prints ONE JSON line
+of the headline and the means behind it (under 2000 characters); `--details FILE` writes the whole
+record, with the per-layer table and every secondary measurement.
 """
 import argparse
 import hashlib
@@ -240,7 +242,7 @@ def config2_step(torch, B, wl, ExpandedLayer, steps=100, stamped=24, copies=6):
         "forward_per_batch_activation_ocs_qa_us": per_call(lambda i: L.forward_act_ocs(Wd, Xd[i % copies], qa=True)),
     }
     L.prepare_weights(Wd)
-    return {"workload": f"configs[1]: M={M} K={K} N={N} r={layer.r} (K'={L.Ke}, padded {L.ldq}), 8/8 bit, "
+    return {"workload": f"3x3 convolution 256 -> 256 at 14 x 14, batch 64: M={M} K={K} N={N} r={layer.r} (K'={L.Ke}, padded {L.ldq}), 8/8 bit, "
                         "weight path + per-batch grid + split+quantize + GEMM per step",
             "us_per_step": us, "tops_whole_step": ops / us / 1e6, "steps": steps,
             "absmax_kernel_us": x1_us, "gemm_kernel_us": g_us, "gemm_tops": ops / g_us / 1e6,
@@ -478,6 +480,27 @@ def cpu_baseline(wl, layers, clip, row_fraction=4):
             "seconds": t_total}
 
 
+def headline(out):
+    """The record without its tables: numbers to six digits, of the secondary passes their time."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.6g}")
+        return {k: short(x) for k, x in v.items()} if isinstance(v, dict) else v
+
+    keep = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline",
+            "dtype", "data", "config", "gemm_tops", "gemm_pct_mfma_peak", "split_quant_gbps", "split_quant_pct_hbm", "step_breakdown_ms")
+    line = {k: out[k] for k in keep}
+    line["config"] = {k: v for k, v in out["config"].items() if k not in ("activation_bytes_resident", "stamped_steps")}
+    drop = ("cache", "timing", "traffic_bytes_per_step", "launches_timed", "bytes_per_unit")
+    line["roofline"] = {k: v for k, v in out["roofline"].items() if k not in drop}
+    line["secondary_ms_per_step"] = {k: out[k]["ms_per_step"] for k in ("fused_split_gemm", "dynamic_grid", "single_stream",
+                                     "weights_prepared_off_line", "chained_unlowered") if "ms_per_step" in out.get(k, {})}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind", "seconds")}
+        line["cpu_baseline"]["sample"] = "the step on the first quarter of every layer's rows"
+    return short(line)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -496,6 +519,7 @@ def main():
                          "weight path by clip), chained, ceilings, config2, splitk")
     ap.add_argument("--only", choices=["chained", "ceilings", "config2", "splitk"], default=None,
                     help="run one secondary measurement alone and print it (no headline)")
+    ap.add_argument("--details", default="", help="file for the whole record (per-layer table, secondary measurements)")
     ap.add_argument("--no-extras", action="store_true",
                     help="skip the secondary measurements (dynamic grid, weight path, ceilings, config 2)")
     args = ap.parse_args()
@@ -569,7 +593,8 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "int8", "dtype_detail": "int8 codes x int8 codes -> int32 accumulators; fp32 in, fp32 out",
         "data": "synthetic",
-        "config": {"workload": "configs[4]: ResNet-50-shaped sweep, all 53 conv layers as im2col GEMMs at batch "
+        "config": {"model": "ResNet-50-shaped, 53 convolutions", "global_batch": 256,
+                   "workload": "ResNet-50-shaped sweep: all 53 conv layers as im2col GEMMs at batch "
                                f"256, r=0.05, 4-bit weights (clip {args.clip} x max|W'|), 8-bit activations on a "
                                "static grid; per layer: weight path, split+quantize, expanded GEMM; weight path "
                                + ("in order on the same stream" if side is None else "queued on a second stream"),
@@ -675,7 +700,10 @@ def main():
         out["gemm_split_k"] = split_k_compare(torch, B, wl, ExpandedLayer)
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(wl, layers, args.clip)
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(headline(out)))
 
 
 if __name__ == "__main__":
