@@ -2360,7 +2360,8 @@ static bool slice_layer_fits(int64_t M, int C, int g, int s, int64_t N, int64_t 
 // the other (the range over static grid and per batch, 10 to 4000 outputs, copies 5 % of the channels):
 //   values of X in a row of tiles  8192: 0.98-1.30, 1.07-1.25, 1.29-1.50; 12288: 1.02-1.20, 1.04-1.22, 1.36-1.49; 16384: 0.89-1.06,
 //                0.95-1.12, 1.18-1.49; 24576: 0.81-1.05, 0.93-1.11, 1.12-1.49; 32000: 0.62-0.97, 0.77-1.08, 0.74-1.39
-//   tiles of 128 columns           8192: 1.10, 1.11, 1.28; 12288: 0.98, 1.01, 1.24; 16384: 0.86, 0.94, 1.11; 24576: 0.80, 0.91, 0.99
+//   tiles of 128 columns           8192: 1.10-1.13, 1.11-1.18, 1.28-1.38; 12800: 0.99-1.22, 0.98-1.36, 1.11-1.49; 16384: 0.86-1.15,
+//                0.91-1.28, 1.04-1.40; 20480: 0.88-1.24, 0.94-1.37, 1.03-1.40; 22528: 0.87-1.17, 0.91-1.24, 0.99-1.37; 24576: 0.80, 0.91, 0.99
 //   a row of K = 4000: 0.97-1.15, 1.09-1.20, 1.29; 6000: 0.89-1.14, 1.01-1.19, 1.04; 8000: 0.84, 1.00, 1.01; 16000: 0.71, 0.83, 0.85
 //   copies, 8192 values: half of the channels 1.02, 1.04, 1.36, all of them 0.85, 0.86, 1.24 (tiles of 128 columns 0.96, 0.97, 1.25
 //                and 0.92, 0.92, 1.16); 12288: a quarter 0.90, 1.00, 1.22, half 0.88, 0.93, 1.12; four steps of them for a wave
@@ -2372,7 +2373,7 @@ bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx, bo
     if (tn.slice_layer == 0 || !slice_layer_fits(M, C, g, s, N, ldx)) return false;
     if (tn.slice_layer > 0) return true;
     const bool wide = slice_layer_tile(M, N) == 4;
-    const int64_t most = captured ? (wide ? 10240 : 13312) : (wide ? 13312 : 27648);
+    const int64_t most = captured ? (wide ? 10240 : 13312) : (wide ? 22528 : 27648);
     return rows * (K + 2 * (int64_t)s * g) <= most && K <= (captured ? 4096 : 6144) && round_up((int64_t)(C + s) * g, 64) - K / 64 * 64 <= 1024;
 }
 
