@@ -45,13 +45,13 @@ STATIC_T = 5.0               # the static activation grid's range (inputs are |N
 # reads for the plain copy kernel of known size that runs after the timed region
 # (profiles/bench_config5_headline.md).  Valid only for the kernel source it was measured on:
 # reported as null once that file changes.
-X2_TRAFFIC = {"quantize_hip_sha256": "e2b802a577991daaaba99bce1ce60e836e49dcd1ff20f46217196b803981f975",
-              "bytes_per_step": 28944930928}
+X2_TRAFFIC = {"quantize_hip_sha256": "c678164867694548cee33b4761aa163600baa1a13197af7fb916517cb487920b",
+              "bytes_per_step": 28946076060}
 
 
 # The same for the launches of the one-launch pass (`--extras fused`), keyed on the GEMM source.
-FUSED_TRAFFIC = {"qgemm_hip_sha256": "aef6f2f996ef5ec4626d7f3864cd3da6e3e339b3200163a584f359869642b092",
-                 "bytes_per_step": 22973685620}
+FUSED_TRAFFIC = {"qgemm_hip_sha256": "e07952ef07d0a4998eb7839abae26a69261e5194f80dfa478d420fcd72d4d450",
+                 "bytes_per_step": 22974429516}
 
 
 def fused_traffic():
