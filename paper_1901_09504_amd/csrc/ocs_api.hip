@@ -549,20 +549,26 @@ static bool overlap(const void* a, int64_t an, const void* b, int64_t bn) {
 
 // The kernels ocs_forward takes: the two of ocs_split_act and ocs_qgemm, or the one launch of few tiles or of many rows.
 enum class ForwardRoute { two = 0, few_tiles = 1, many_rows = 2 };
+// in_graph: the route in a stream that is being captured.
 static ForwardRoute forward_route(const float* X, int64_t M, int C, int g, int64_t ldx, int s, int64_t ldq, int64_t ldw, int64_t N,
-                                  bool captured) {
+                                  ForwardRoute* in_graph) {
+    *in_graph = ForwardRoute::two;
     const Tuning& tn = tuning();
     if (tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0)   // launch shapes of the two
         return ForwardRoute::two;
-    if (slice_layer_pays(M, C, g, s, N, ldx, captured)) return ForwardRoute::few_tiles;
-    if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) return ForwardRoute::many_rows;
-    return ForwardRoute::two;
+    const SliceLayerPays few = slice_layer_pays(M, C, g, s, N, ldx);
+    if (few.captured) *in_graph = ForwardRoute::few_tiles;
+    if (few.launched) return ForwardRoute::few_tiles;
+    if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) *in_graph = ForwardRoute::many_rows;
+    return *in_graph;
 }
 
 int ocs_forward_one_launch(const float* X, int64_t M, int C, int g, int64_t ldx, int num_splits, int64_t ldq, int64_t ldw,
                            int64_t N, int captured) {
     if (check_layer(M, C, g, ldx, num_splits) || N <= 0) return 0;
-    return (int)forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, captured != 0);
+    ForwardRoute in_graph;
+    const ForwardRoute route = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, &in_graph);
+    return (int)(captured ? in_graph : route);
 }
 
 int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int32_t* chan_src, int num_splits, int bits_x,
@@ -596,11 +602,11 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
                        clear_of_outputs(Wq, N * ldw) && clear_of_outputs(scale_w, 8);
     ForwardRoute route = ForwardRoute::two;
     if (apart) {
-        route = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, false);
-        if (route == ForwardRoute::few_tiles && st != nullptr) {       // (the null stream is never captured)
-            const ForwardRoute in_graph = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, true);
+        ForwardRoute in_graph;
+        route = forward_route(X, M, C, g, ldx, num_splits, ldq, ldw, N, &in_graph);
+        if (route != in_graph && st != nullptr) {            // (the null stream is never captured)
             hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-            const hipError_t e = in_graph == route ? hipSuccess : hipStreamIsCapturing(st, &status);
+            const hipError_t e = hipStreamIsCapturing(st, &status);
             if (e != hipSuccess) return hip_fail(e);
             if (status != hipStreamCaptureStatusNone) route = in_graph;
         }

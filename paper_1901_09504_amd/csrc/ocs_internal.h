@@ -195,9 +195,11 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
                               int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream);
 
 // The whole layer of few tiles as one launch, codes included (csrc/qgemm.hip: slice_layer_kernel).  thr: the threshold
-// (n_max == 0 and self == 0), or n_max maxima; self > 0: X is contiguous and looked through by every workgroup.  captured: the
-// launch goes into a graph, where it costs the host nothing.
-bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx, bool captured);
+// (n_max == 0 and self == 0), or n_max maxima; self > 0: X is contiguous and looked through by every workgroup.
+struct SliceLayerPays {
+    bool launched, captured;   // where the host launches; where the launch goes into a graph and costs the host nothing
+};
+SliceLayerPays slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx);
 hipError_t launch_slice_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
                               const float* thr, int n_max, int64_t self, float clip, float qmax, int8_t* Xq, int64_t ldq,
                               float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,

@@ -2342,10 +2342,10 @@ constexpr int kSliceLayerTail = 4096;      // columns of the table in LDS (16 KB
 
 // Whether an instance of launch_slice_layer takes the shape: a tile, 32-bit offsets, and the LDS of the tile's instance (the
 // wider two have room for 4088 columns of the table).
-static bool slice_layer_fits(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
+static bool slice_layer_fits(int tile, int C, int g, int s, int64_t ldx) {
     const int64_t K = (int64_t)C * g, tail = round_up((int64_t)(C + s) * g, 64) - K / 64 * 64, pitch = (int64_t)1 << 23;
     if (ldx >= pitch || K >= pitch || tail > kSliceLayerTail) return false;
-    switch (slice_layer_tile(M, N)) {
+    switch (tile) {
         case 1: return slice_layer_lds<1, 8, 3, true>(tail) <= kWholeKMaxLds;
         case 2: return slice_layer_lds<2, 8, 3, true>(tail) <= kWholeKMaxLds;
         case 4: return slice_layer_lds<4, 8, 2, false>(tail) <= kWholeKMaxLds;
@@ -2367,14 +2367,15 @@ static bool slice_layer_fits(int64_t M, int C, int g, int s, int64_t N, int64_t 
 //                and 0.92, 0.92, 1.16); 12288: a quarter 0.90, 1.00, 1.22, half 0.88, 0.93, 1.12; four steps of them for a wave
 //                (2000 to 2048 columns) 0.77, 0.78, 0.91, eight 0.64, 0.55, 0.58
 // So an appended column counts as two, and a wave has at most two steps of them.
-bool slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx, bool captured) {
-    const int64_t K = (int64_t)C * g, rows = M < 32 ? M : 32;
-    const Tuning& tn = tuning();
-    if (tn.slice_layer == 0 || !slice_layer_fits(M, C, g, s, N, ldx)) return false;
-    if (tn.slice_layer > 0) return true;
-    const bool wide = slice_layer_tile(M, N) == 4;
-    const int64_t most = captured ? (wide ? 10240 : 13312) : (wide ? 22528 : 27648);
-    return rows * (K + 2 * (int64_t)s * g) <= most && K <= (captured ? 4096 : 6144) && round_up((int64_t)(C + s) * g, 64) - K / 64 * 64 <= 1024;
+SliceLayerPays slice_layer_pays(int64_t M, int C, int g, int s, int64_t N, int64_t ldx) {
+    const int64_t K = (int64_t)C * g, rows = M < 32 ? M : 32, values = rows * (K + 2 * (int64_t)s * g);
+    const int mode = tuning().slice_layer;
+    if (mode == 0 || (mode < 0 && values > 27648)) return {false, false};
+    const int tile = slice_layer_tile(M, N);
+    if (!slice_layer_fits(tile, C, g, s, ldx)) return {false, false};
+    if (mode > 0) return {true, true};
+    if (round_up((int64_t)(C + s) * g, 64) - K / 64 * 64 > 1024) return {false, false};
+    return {values <= (tile == 4 ? 22528 : 27648) && K <= 6144, values <= (tile == 4 ? 10240 : 13312) && K <= 4096};
 }
 
 hipError_t launch_slice_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
