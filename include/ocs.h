@@ -301,7 +301,7 @@ int ocs_qgemm(const int8_t *Xq, int64_t ldx, const int8_t *Wq, int64_t ldw, int6
  * its codes, with the arguments those take.  threshold: device float, or NULL for the batch's own maximum times
  * clip_ratio (workspace as for ocs_split_act then; it may be NULL with a threshold).  Leaves what the two calls leave:
  * Xq [M, ldq] with its padding, scale_x_out {T, T / qmax}, Y and, if given, acc_out, bit for bit.  Layers of few output tiles, and
- * layers of many long rows with up to 256 outputs, run as one launch (plus the max|X| pass where it has to be one; fewer of the
+ * layers of many rows with up to 256 outputs, run as one launch (plus the max|X| pass where it has to be one; fewer of the
  * first in a stream that is being captured, where a launch costs the host nothing); where Y,
  * acc_out, Xq or scale_x_out share memory with X, the threshold, chan_src, Wq, scale_w or (for the batch's own maximum) the
  * workspace, and on every other shape, the two launches run.
@@ -314,7 +314,8 @@ int ocs_forward(const float *X, int64_t M, int C, int g, int64_t ldx, const int3
 
 /*
  * Which kernels ocs_forward takes for a layer whose outputs share no memory with its inputs: 0 the two of ocs_split_act and
- * ocs_qgemm, 1 the one launch of few output tiles, 2 the one launch of many rows.  captured: the call is recorded into a graph.
+ * ocs_qgemm, 1 the one launch of few output tiles, 2 the one launch of many long rows, 3 that of many short ones
+ * (code rows of up to OCS_SHORT_K bytes).  captured: the call is recorded into a graph.
  * X is looked at for its alignment only.  0 for shapes that ocs_forward refuses.  No device work.
  */
 int ocs_forward_one_launch(const float *X, int64_t M, int C, int g, int64_t ldx, int num_splits, int64_t ldq,

@@ -547,8 +547,9 @@ static bool overlap(const void* a, int64_t an, const void* b, int64_t bn) {
     return a != nullptr && b != nullptr && x < y + (uint64_t)bn && y < x + (uint64_t)an;
 }
 
-// The kernels ocs_forward takes: the two of ocs_split_act and ocs_qgemm, or the one launch of few tiles or of many rows.
-enum class ForwardRoute { two = 0, few_tiles = 1, many_rows = 2 };
+// The kernels ocs_forward takes: the two of ocs_split_act and ocs_qgemm, or the one launch of few tiles, of many long rows or of
+// many short ones.
+enum class ForwardRoute { two = 0, few_tiles = 1, many_rows = 2, short_rows = 3 };
 // in_graph: the route in a stream that is being captured.
 static ForwardRoute forward_route(const float* X, int64_t M, int C, int g, int64_t ldx, int s, int64_t ldq, int64_t ldw, int64_t N,
                                   ForwardRoute* in_graph) {
@@ -560,6 +561,7 @@ static ForwardRoute forward_route(const float* X, int64_t M, int C, int g, int64
     if (few.captured) *in_graph = ForwardRoute::few_tiles;
     if (few.launched) return ForwardRoute::few_tiles;
     if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) *in_graph = ForwardRoute::many_rows;
+    else if (rows_layer_pays(M, C, g, s, ldq, N)) *in_graph = ForwardRoute::short_rows;
     return *in_graph;
 }
 
@@ -631,7 +633,7 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
                                scale_x_out, Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
         return e == hipSuccess ? OCS_OK : hip_fail(e);
     }
-    if (route == ForwardRoute::many_rows) {
+    if (route == ForwardRoute::many_rows || route == ForwardRoute::short_rows) {
         const float* thr = threshold;
         int n = 0;
         hipError_t e = hipSuccess;
@@ -639,8 +641,12 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
             e = per_batch_maxima(X, M, K, ldx, workspace, st, &thr, &n);
             if (e != hipSuccess) return hip_fail(e);
         }
-        e = launch_panel_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, clip_ratio, qmax_of(bits_x), Xq, ldq, scale_x_out,
-                               Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
+        if (route == ForwardRoute::short_rows)
+            e = launch_rows_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, clip_ratio, qmax_of(bits_x), Xq, ldq, scale_x_out,
+                                  Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
+        else
+            e = launch_panel_layer(X, ldx, M, C, g, num_splits, chan_src, thr, n, clip_ratio, qmax_of(bits_x), Xq, ldq, scale_x_out,
+                                   Wq, ldw, N, scale_w, acc_out, ldacc, Y, ldy, st);
         return e == hipSuccess ? OCS_OK : hip_fail(e);
     }
     rc = ocs_split_act(X, M, C, g, ldx, chan_src, nullptr, num_splits, bits_x, threshold, clip_ratio, Xq, ldq, scale_x_out,
@@ -946,6 +952,7 @@ int ocs_tune(const char* key, int value) {
     else if (!strcmp(key, "fused_stride")) t.fused_stride = value;
     else if (!strcmp(key, "slice_layer")) t.slice_layer = value;
     else if (!strcmp(key, "panel_layer")) t.panel_layer = value;
+    else if (!strcmp(key, "rows_layer")) t.rows_layer = value;
     else if (!strcmp(key, "max_flat")) t.max_flat = value;
     else if (!strcmp(key, "max_grid")) t.max_grid = value;
     else if (!strcmp(key, "max_un")) t.max_un = value;

@@ -194,6 +194,13 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
                               float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
                               int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream);
 
+// The layer of short code rows as one launch, codes included (csrc/qgemm.hip: rows_layer_kernel).  thr as above.
+bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N);
+hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
+                             const float* thr, int n_max, float clip, float qmax, int8_t* Xq, int64_t ldq,
+                             float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
+                             int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream);
+
 // The whole layer of few tiles as one launch, codes included (csrc/qgemm.hip: slice_layer_kernel).  thr: the threshold
 // (n_max == 0 and self == 0), or n_max maxima; self > 0: X is contiguous and looked through by every workgroup.
 struct SliceLayerPays {
@@ -331,6 +338,7 @@ struct Tuning {
     int fused_variant = -1;  // workgroup shape / pipeline depth of the split+quantize+GEMM launch (default: by shape)
     int slice_layer = -1;    // ocs_forward: the one-launch layer of few tiles wherever it serves (1), never (0), by shape (-1)
     int panel_layer = -1;    // ocs_forward: the one launch of tall layers wherever it serves (1), never (0), by shape (-1)
+    int rows_layer = -1;     // ocs_forward: the one launch of short code rows wherever it serves (1), never (0), by shape (-1)
     int max_flat = -1;  // whole-tensor max|x| of a contiguous tensor as one flat stream (1), by columns (0), default (-1);
                         // 2: flat, and a per-batch grid's maxima always folded by a launch of their own
     int max_grid = -1;  // workgroups of the flat pass

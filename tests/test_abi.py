@@ -243,6 +243,25 @@ def test_forward_of_many_rows_by_rows_and_copies(C, g, s, N, extra, inside, outs
         assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=1 << 20) == 0, M
 
 
+# Rows (more than the layer of few tiles takes: sixteen per compute unit with 256 outputs, 32 with 64), code rows of up to 320 bytes
+# (192, and at most 160 columns of X, with more than 128 outputs),
+# outputs, more than 2^26 of them in more than 128 columns, padding past the last step; strides and alignment of X do not count.
+@pytest.mark.parametrize("C,g,s,N,inside,outside", [
+    (3, 49, 1, 64, (32 * 256 + 1, 401408, 3211264), (32 * 256,)), (304, 1, 16, 128, (8200, 802816), (32 * 256,)), (304, 1, 17, 128, (), (8200, 802816)),
+    (160, 1, 8, 129, (8200,), ()), (161, 1, 8, 129, (), (8200,)), (150, 1, 50, 129, (), (8200,)), (150, 1, 50, 128, (8200,), ()),
+    (64, 1, 4, 256, (16 * 256 + 1, 1 << 18), (16 * 256, (1 << 18) + 1, 802816)), (64, 1, 4, 257, (), (200000,)), (4, 1, 1, 1, (200000,), ()),
+    (3, 1, 1, 1, (), (200000,))])
+def test_forward_of_short_rows_by_rows_and_outputs(C, g, s, N, inside, outside):
+    ld = B.ocs_padded_cols((C + s) * g)
+    for M in inside:
+        for captured in (False, True):
+            assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, captured=captured) == 3, M
+            assert B.ocs_forward_one_launch(M, C, g, C * g + 5, s, ld, ld, N, captured=captured, X=(1 << 20) + 4) == 3, M
+        assert B.ocs_forward_one_launch(M, C, g, C * g, s, 384, ld, N) == 0, M
+    for M in outside:
+        assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N) != 3, M
+
+
 def test_forward_route_of_refused_shapes_and_forced_kernels():
     assert B.ocs_forward_one_launch(0, 64, 1, 64, 1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 63, 1, 128, 128, 64) == 0
     assert B.ocs_forward_one_launch(4, 64, 1, 64, -1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 0) == 0

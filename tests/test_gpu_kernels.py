@@ -1711,6 +1711,37 @@ def test_forward_of_many_rows_over_its_own_input():
     _panel(1, test_forward_over_its_own_input)
 
 
+# ---- ocs_forward on many short rows: one shot of 64 rows, codes and products in one launch -------------
+
+def _rows(mode, fn):
+    B.ocs_tune("rows_layer", mode)
+    B.ocs_tune("panel_layer", 0)
+    try:
+        fn()
+    finally:
+        B.ocs_tune("rows_layer", -1)
+        B.ocs_tune("panel_layer", -1)
+
+
+# Rows around a workgroup's 64; left-over columns of 0, 1 and 3, none, a single group of four; every count of 16-byte requests a lane has an
+# instance for (K = 64, 112, 160, 208, 256, 320, and one value more); code rows of one to five steps, that end on a step, inside
+# one, in as little padding as a pitch can have; outputs around 32, 64, 128, 256; strided rows; no copies, nearly only copies.
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra", [
+    (1, 4, 1, 0, 1, 0), (63, 5, 1, 3, 33, 1), (64, 64, 1, 0, 64, 0), (65, 64, 1, 4, 256, 0), (200, 65, 1, 7, 65, 3), (130, 3, 49, 1, 64, 0),
+    (129, 112, 1, 6, 128, 0), (70, 113, 1, 40, 129, 0), (64, 160, 1, 8, 255, 5), (100, 161, 1, 31, 100, 0), (3, 208, 1, 16, 31, 0),
+    (257, 209, 1, 10, 64, 0), (128, 256, 1, 64, 127, 0), (90, 257, 1, 13, 64, 2), (66, 33, 9, 2, 16, 0), (50, 320, 1, 0, 60, 0),
+    (67, 8, 1, 300, 40, 0), (300, 13, 9, 5, 200, 0)])
+def test_forward_of_short_rows(M, C, g, s, N, ld_extra):
+    _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, route=3))
+
+
+# Per-batch grids: a single maximum, 256 of them, the thousands of a strided tensor
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip", [
+    (1, 64, 1, 1, 5, 0, 1.0), (3000, 147, 1, 8, 64, 0, 0.9), (9000, 100, 1, 5, 70, 3, 0.8)])
+def test_forward_of_short_rows_per_batch(M, C, g, s, N, ld_extra, clip):
+    _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0, route=3))
+
+
 # ---- channel maxima in row blocks that the selector folds itself ------------------------------------
 
 # Rows and columns around the blocks' edges: a row's last group of four overlaps the one before (5, 7, 33, 130 columns, 8, 16 and
