@@ -442,6 +442,20 @@ int ocs_qconv_requant(const int8_t *Aq, int64_t ldc, int B, int H, int W, int C_
                       int32_t *acc_out, int64_t ldacc, void *stream);
 
 /*
+ * The first layer of a chain as one call: ocs_split_act of the un-lowered activations A fp32 [B*H*W, C] (contiguous, copies
+ * un-scaled, C + num_splits expanded channels) into Aq, and ocs_qconv_requant on those codes, with the arguments those take.
+ * Leaves what the two calls leave, bit for bit.  1x1 layers of stride 1 on many pixels with short code rows (up to OCS_SHORT_K bytes,
+ * up to 128 outputs) run as one launch where outputs share no memory with inputs; everything else as the two calls.
+ */
+int ocs_conv_forward_requant(const float *A, int B, int H, int W, int C, const int32_t *chan_src, int num_splits,
+                             int bits_x, const float *threshold, float clip_ratio, int8_t *Aq, int64_t ldc,
+                             float *scale_x_out, int kh, int kw, int stride, int pad, const int8_t *Wt, int64_t N,
+                             int bits_w, const float *scale_w, int relu, const float *next_threshold, int next_bits,
+                             const int32_t *next_chan_src, int next_splits, int8_t *Yq, int64_t ldyq,
+                             float *next_scale_out, int32_t *acc_out, int64_t ldacc, void *workspace, size_t ws_bytes,
+                             void *stream);
+
+/*
  * Weight side of Eq. 4 on codes, for a channel choice that changes with every batch (Sec. 5.3).
  * The copies of a duplicated weight channel are not scaled, so max|W'| = max|W|, the codes of
  * the first C*g columns are those of the un-expanded weights whatever the choice, and an appended

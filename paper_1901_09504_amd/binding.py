@@ -75,6 +75,10 @@ def lib():
     L.ocs_qconv_requant.restype = _i32
     L.ocs_qconv_requant.argtypes = [_vp, _i64, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _vp, _i64, _i32,
                                     _i32, _vp, _vp, _i32, _vp, _i32, _vp, _i32, _vp, _i64, _vp, _vp, _i64, _vp]
+    L.ocs_conv_forward_requant.restype = _i32
+    L.ocs_conv_forward_requant.argtypes = [_vp, _i32, _i32, _i32, _i32, _vp, _i32, _i32, _vp, _f32, _vp, _i64, _vp, _i32, _i32,
+                                           _i32, _i32, _vp, _i64, _i32, _vp, _i32, _vp, _i32, _vp, _i32, _vp, _i64, _vp, _vp,
+                                           _i64, _vp, _sz, _vp]
     L.ocs_fold_weights.restype = _i32
     L.ocs_fold_weights.argtypes = [_vp, _i64, _i64, _i32, _i32, _i32, _vp, _vp, _i64, _vp, _vp]
     L.ocs_split_act_qa.restype = _i32
@@ -297,6 +301,17 @@ def ocs_qconv_requant(Aq, ldc, Bn, H, W, C_exp, kh, kw, stride, pad, Wt, N, bits
                                    _stream(stream)), "ocs_qconv_requant")
 
 
+def ocs_conv_forward_requant(A, Bn, H, W, Cn, chan_src, num_splits, bits_x, threshold, clip_ratio, Aq, ldc, scale_x_out, kh, kw,
+                             stride, pad, Wt, N, bits_w, scale_w, relu, next_threshold, next_bits, next_chan_src, next_splits,
+                             Yq, ldyq, next_scale_out, acc_out=None, ldacc=0, workspace=None, stream=None):
+    w, wb = _ws(workspace)
+    _check(lib().ocs_conv_forward_requant(_ptr(A), Bn, H, W, Cn, _ptr(chan_src), num_splits, bits_x, _ptr(threshold), clip_ratio,
+                                          _ptr(Aq), ldc, _ptr(scale_x_out), kh, kw, stride, pad, _ptr(Wt), N, bits_w,
+                                          _ptr(scale_w), int(bool(relu)), _ptr(next_threshold), next_bits, _ptr(next_chan_src),
+                                          next_splits, _ptr(Yq), ldyq, _ptr(next_scale_out), _ptr(acc_out), ldacc,
+                                          w, wb, _stream(stream)), "ocs_conv_forward_requant")
+
+
 def ocs_duplicate_weight_codes(Wq, ldq, N, Cn, g, num_splits, chan_src, stream=None):
     _check(lib().ocs_duplicate_weight_codes(_ptr(Wq), ldq, N, Cn, g, num_splits, _ptr(chan_src),
                                             _stream(stream)), "ocs_duplicate_weight_codes")
@@ -364,7 +379,7 @@ def ocs_forward(X, M, Cn, g, ldx, chan_src, num_splits, bits_x, threshold, clip_
 
 
 def ocs_forward_one_launch(M, Cn, g, ldx, num_splits, ldq, ldw, N, captured=False, X=None):
-    """0: two kernels; 1: the one launch of few tiles; 2: that of many rows (X: tensor or address, for its alignment)."""
+    """0: two kernels; 1: the one launch of few tiles; 2: that of many long rows, 3: of many short ones (X: tensor or address, for its alignment)."""
     return int(lib().ocs_forward_one_launch(X if isinstance(X, int) else _ptr(X), M, Cn, g, ldx, num_splits, ldq, ldw, N, captured))
 
 

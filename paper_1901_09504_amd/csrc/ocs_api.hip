@@ -850,6 +850,64 @@ int ocs_qconv_requant(const int8_t* Aq, int64_t ldc, int B, int H, int W, int C_
     return OCS_OK;
 }
 
+int ocs_conv_forward_requant(const float* A, int B, int H, int W, int C, const int32_t* chan_src, int num_splits,
+                             int bits_x, const float* threshold, float clip_ratio, int8_t* Aq, int64_t ldc, float* scale_x_out,
+                             int kh, int kw, int stride, int pad, const int8_t* Wt, int64_t N, int bits_w,
+                             const float* scale_w, int relu, const float* next_threshold, int next_bits,
+                             const int32_t* next_chan_src, int next_splits, int8_t* Yq, int64_t ldyq, float* next_scale_out,
+                             int32_t* acc_out, int64_t ldacc, void* workspace, size_t ws_bytes, void* stream) {
+    if (!Wt || !scale_w) return OCS_E_NULL;
+    if (B <= 0 || H <= 0 || W <= 0) return OCS_E_SHAPE;
+    const int64_t M = (int64_t)B * H * W;
+    int rc = check_split_act(A, M, C, 1, C, chan_src, num_splits, bits_x, threshold, clip_ratio, Aq, ldc, scale_x_out);
+    if (rc) return rc;
+    const int E = C + num_splits;
+    rc = check_conv_operands(Aq, ldc, B, H, W, E, kh, kw, stride, pad, Wt, N, bits_x, bits_w, acc_out, ldacc);
+    if (rc) return rc;
+    rc = check_requant((int)N, next_threshold, next_bits, next_chan_src, next_splits, Yq, ldyq, next_scale_out);
+    if (rc) return rc;
+    const int64_t ldw = round_up((int64_t)kh * kw * ldc, OCS_KALIGN);
+    if (threshold == nullptr) {
+        rc = check_workspace(workspace, ws_bytes, M, C);
+        if (rc) return rc;
+    }
+    const Requant rq = make_requant(relu, next_threshold, next_bits, next_chan_src, next_splits, Yq, ldyq, next_scale_out);
+    const Tuning& tn = tuning();
+    const bool forced = tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0;
+    if (!forced && kh == 1 && kw == 1 && stride == 1 && pad == 0 && rows_layer_pays(M, C, 1, num_splits, ldc, N, rq)) {
+        // one launch: no output may share memory with an input (see ocs_forward), or with another output that the two calls
+        // write one after the other
+        struct Range { const void* at; int64_t bytes; };
+        const Range out[] = {{Aq, M * ldc}, {scale_x_out, 8}, {Yq, M * ldyq}, {next_scale_out, 8}, {acc_out, 4 * ((M - 1) * ldacc + N)}};
+        const Range in[] = {{A, 4 * M * C}, {threshold, 4}, {num_splits > 0 ? chan_src : nullptr, 4 * (int64_t)E}, {Wt, (N + 1) * ldw},
+                            {scale_w, 8}, {next_threshold, 4}, {next_splits > 0 ? next_chan_src : nullptr, 4 * (N + next_splits)},
+                            {threshold == nullptr ? workspace : nullptr, (int64_t)ws_bytes}};
+        bool apart = true;
+        for (int i = 0; i < 5; ++i) {
+            for (const Range& r : in) apart = apart && !overlap(out[i].at, out[i].bytes, r.at, r.bytes);
+            for (int j = i + 1; j < 5; ++j) apart = apart && !overlap(out[i].at, out[i].bytes, out[j].at, out[j].bytes);
+        }
+        if (apart) {
+            hipStream_t st = static_cast<hipStream_t>(stream);
+            const float* thr = threshold;
+            int n = 0;
+            hipError_t e = hipSuccess;
+            if (threshold == nullptr) {
+                e = per_batch_maxima(A, M, C, C, workspace, st, &thr, &n);
+                if (e != hipSuccess) return hip_fail(e);
+            }
+            e = launch_rows_layer(A, C, M, C, 1, num_splits, chan_src, thr, n, clip_ratio, qmax_of(bits_x), Aq, ldc, scale_x_out, Wt,
+                                  ldw, N, scale_w, acc_out, ldacc, nullptr, N, st, rq);
+            return e == hipSuccess ? OCS_OK : hip_fail(e);
+        }
+    }
+    rc = ocs_split_act(A, M, C, 1, C, chan_src, nullptr, num_splits, bits_x, threshold, clip_ratio, Aq, ldc, scale_x_out, workspace,
+                       ws_bytes, stream);
+    if (rc) return rc;
+    return ocs_qconv_requant(Aq, ldc, B, H, W, E, kh, kw, stride, pad, Wt, N, bits_x, bits_w, scale_x_out, scale_w, relu,
+                             next_threshold, next_bits, next_chan_src, next_splits, Yq, ldyq, next_scale_out, acc_out, ldacc, stream);
+}
+
 int ocs_duplicate_weight_codes(int8_t* Wq, int64_t ldq, int64_t N, int C, int g, int num_splits,
                                const int32_t* chan_src, void* stream) {
     if (!Wq || (num_splits > 0 && !chan_src)) return OCS_E_NULL;

@@ -194,12 +194,14 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
                               float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
                               int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream);
 
-// The layer of short code rows as one launch, codes included (csrc/qgemm.hip: rows_layer_kernel).  thr as above.
-bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N);
+// The layer of short code rows as one launch, codes included (csrc/qgemm.hip: rows_layer_kernel), its output as fp32 or as the next
+// layer's codes.  thr as above.
+bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, const Requant& rq = Requant{});
 hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
                              const float* thr, int n_max, float clip, float qmax, int8_t* Xq, int64_t ldq,
                              float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,
-                             int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream);
+                             int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy, hipStream_t stream,
+                             const Requant& rq = Requant{});
 
 // The whole layer of few tiles as one launch, codes included (csrc/qgemm.hip: slice_layer_kernel).  thr: the threshold
 // (n_max == 0 and self == 0), or n_max maxima; self > 0: X is contiguous and looked through by every workgroup.

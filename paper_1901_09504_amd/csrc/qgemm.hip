@@ -2212,10 +2212,13 @@ bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int 
 // a lane; nothing waits before the last is on its way) with all weight codes straight into LDS ahead of them, quantizes into the
 // operand image in LDS, assembles the rows' tails there (left-over columns, copies, padding; the streaming pass's table), writes the
 // image out as one block of whole 16-byte pieces, multiplies, and ends: no loop over tiles, so that the dispatcher keeps the chip inside one window
-// that slides over X.  The image's 64-byte steps lie a row of banks apart, so that the dwords a wave writes along a row of X
-// fall in different banks.
-// Bounded by HBM: X, codes and outputs at 6.1 TB/s where they are the traffic (401408 x 147 -> 64 88.5 -> 68.6 us for the layer,
-// 802816 x 64 -> 64 86.8 -> 70.4), 5.0 where the launch is short (100352 x 256 -> 64 36.6 -> 30.9).  X is read past the caches'
+// that slides over X.  The image lies in LDS by steps of 32 bytes of K (one matrix instruction's), a step's rows one after the other with
+// their two pieces exchanged every eight rows, the steps 32 bytes further apart: the reads of sixteen rows and the dwords a wave
+// writes along a row of X fall in different banks.  The weights lie in the whole-K kernel's 64-byte steps: requested by 32 bytes of a row
+// they cost the L1 twice the look-ups (401408 x 147 -> 64 71.5 us, 100352 x 256 -> 64 33.9).
+// Bounded by HBM: X, codes and outputs at 6.1 TB/s where they are the traffic (401408 x 147 -> 64 88.5 -> 67.8 us for the layer,
+// 802816 x 64 -> 64 86.8 -> 69.5), 5.0 where the launch is short (100352 x 256 -> 64 36.6 -> 30.8; with the next layer's codes as its
+// output 38.8 -> 31.7).  X is read past the caches'
 // replacement (with plain loads 74.6 and 80.8 us of the first two).  128 rows on eight waves: 74.9 and 72.1, 100352 x 256 -> 64 39.0;
 // fewer workgroups on a compute unit (three, two): 71 and 84, 80 and 95.
 // ---------------------------------------------------------------------------------------------
@@ -2238,9 +2241,9 @@ struct RowsLayer {
     int64_t ldacc;
     float* Y;
     int64_t ldy;
-    int ksteps;                                     // 64-byte steps of a row
+    int steps;                                      // 32-byte steps of a row
     unsigned magic_qc, magic_td, magic_pc;          // floor(2^32 / n): X's dwords, a tail's dwords, a code row's pieces
-    int w_off, tab_off;
+    int w_off, tab_off, dup_off;
 };
 
 
@@ -2254,14 +2257,18 @@ __device__ __forceinline__ int div_magic(int item, int n, unsigned magic, int& r
 }
 
 constexpr int kRowsBM = 64, kRowsNT = 256;             // rows and lanes of a workgroup: WAVES 2 x 2
-constexpr int kRowsStep = kRowsBM * 64 + 64;            // a step of the image, a row of banks further on than the one before
+constexpr int kRowsStep = kRowsBM * 32 + 32;            // a step of the image
+// where byte 16 * piece of row r begins inside its 32 bytes
+__device__ __forceinline__ int rows_swz(int r, int piece) { return ((piece ^ (r >> 3)) & 1) << 4; }
 
-template <int BN, int U>
-__global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
+template <int BN, int U, bool RQ>
+__global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p, Requant rq) {
     constexpr int BM = kRowsBM, NT = kRowsNT, NW = NT / 64, WN = BN / 2, TN = WN / 32, STEP = kRowsStep;
     extern __shared__ __align__(1024) int8_t rlds[];
     __shared__ float red[NW];
     int* tab = reinterpret_cast<int*>(rlds + p.tab_off);
+    int* dup_list = reinterpret_cast<int*>(rlds + p.dup_off);     // only with copies to write
+    int* dup_count = dup_list + kDupCap;
 #if defined(__HIP_DEVICE_COMPILE__)
     typedef __attribute__((address_space(3))) int8_t* lptr_t;
     const unsigned lds0 = (unsigned)(uintptr_t)(lptr_t)&rlds[0];
@@ -2273,16 +2280,16 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
     const int row0 = (int)blockIdx.x * BM;
     const int rows = p.M - row0 < BM ? p.M - row0 : BM;
     const int K = p.C * p.g, Ke = (p.C + p.s) * p.g, Q = K / 4, rem = K - 4 * Q, Qc = Q + (rem > 0 ? 1 : 0);
-    const int TD = p.ksteps * 16 - Q;                             // dwords of a row's tail
+    const int TD = p.steps * 8 - Q;                             // dwords of a row's tail
 
-    // weights: piece b of a step = rows 16b .. 16b+15, as in the whole-K kernel
+    // weights: piece b of a 64-byte step = rows 16b .. 16b+15, as in the whole-K kernel
     {
         const int w_pieces = (int)(p.ldw / 16);
         for (int b = wave; b < BN / 16; b += NW) {
             const int r = b * 16 + (lane >> 2);
             const int8_t* rowp = p.Wq + (int64_t)(r < p.N ? r : p.N - 1) * p.ldw;
             int piece = swz<64>(r, lane & 3);
-            for (int kt = 0; kt < p.ksteps; ++kt, piece += 4)
+            for (int kt = 0; 2 * kt < p.steps; ++kt, piece += 4)
                 lds_dma16(piece < w_pieces ? rowp + piece * 16 : zero_chunk, lds0 + (unsigned)(p.w_off + (kt * BN + b * 16) * 64));
         }
     }
@@ -2305,14 +2312,14 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
         const float* src = p.X + (int64_t)(row0 + (ok ? r : 0)) * p.ldx + (ok ? (d < Q ? 4 * d : K - 4) : 0);
         v[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(src));
     }
-    // a tail's sources as places in the image (step and byte inside it; the row's swizzle turns bits 4 and 5), -1: a zero code
+    // a tail's sources as places in the image (step and byte inside it; the row's exchange turns bit 4), -1: a zero code
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int e = tid + i * NT, k = 4 * Q + e;
         if (e < 4 * TD) {
             int col = k < K ? k : -1;
             if (k >= K && k < Ke) col = col_clamp(tsrc[i], p.C) * p.g + k % p.g;
-            tab[e] = col < 0 ? -1 : (col >> 6) * STEP + (col & 63);
+            tab[e] = col < 0 ? -1 : (col >> 5) * STEP + (col & 31);
         }
     }
     float T = first;
@@ -2332,7 +2339,6 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
         p.scale_x[0] = T;
         p.scale_x[1] = step_x;
     }
-    auto turn = [](int r) { return swz<64>(r, 0) << 4; };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         int d;
@@ -2341,22 +2347,25 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
         unsigned q4 = pack4(code_bits(v[u][0], inv, p.qmax), code_bits(v[u][1], inv, p.qmax),
                             code_bits(v[u][2], inv, p.qmax), code_bits(v[u][3], inv, p.qmax));
         if (d >= Q) q4 >>= 8 * (4 - rem);
-        *reinterpret_cast<unsigned*>(rlds + (d >> 4) * STEP + r * 64 + (((d & 15) * 4) ^ turn(r))) = q4;
+        *reinterpret_cast<unsigned*>(rlds + (d >> 3) * STEP + r * 32 + (((d & 7) * 4) ^ rows_swz(r, 0))) = q4;
     }
     __syncthreads();
     for (int it = tid; it < BM * TD; it += NT) {
         int td;
         const int r = div_magic(it, TD, p.magic_td, td);
         const i32x4 at = *reinterpret_cast<const i32x4*>(&tab[4 * td]);
-        const int8_t* irow = rlds + r * 64;
+        const int8_t* irow = rlds + r * 32;
         unsigned q4 = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const unsigned byte = (unsigned)(unsigned char)irow[at[e] < 0 ? 0 : at[e] ^ turn(r)];
+            const unsigned byte = (unsigned)(unsigned char)irow[at[e] < 0 ? 0 : at[e] ^ rows_swz(r, 0)];
             q4 |= (at[e] < 0 ? 0u : byte) << (8 * e);
         }
         const int d = Q + td;
-        *reinterpret_cast<unsigned*>(rlds + (d >> 4) * STEP + r * 64 + (((d & 15) * 4) ^ turn(r))) = q4;
+        *reinterpret_cast<unsigned*>(rlds + (d >> 3) * STEP + r * 32 + (((d & 7) * 4) ^ rows_swz(r, 0))) = q4;
+    }
+    if constexpr (RQ) {
+        if (p.dup_off > 0) build_dup_list<NT>(rq, p.N, 0, BN, dup_list, dup_count);
     }
     wait_vmcnt<0>();                                              // the weights (requested ahead of X: long there)
     __syncthreads();
@@ -2367,7 +2376,8 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
         for (int it = tid; it < rows * pc; it += NT) {
             int c;
             const int r = div_magic(it, pc, p.magic_pc, c);
-            const i32x4 q = *reinterpret_cast<const i32x4*>(rlds + (c >> 2) * STEP + r * 64 + swz<64>(r, c & 3) * 16);
+            i32x4 q = {0, 0, 0, 0};                               // (a pitch longer than the image)
+            if (c < 2 * p.steps) q = *reinterpret_cast<const i32x4*>(rlds + (c >> 1) * STEP + r * 32 + rows_swz(r, c));
             __builtin_nontemporal_store(q, reinterpret_cast<i32x4*>(out + (int64_t)it * 16));
         }
     }
@@ -2377,67 +2387,79 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[0][j][e] = 0;
-    for (int kt = 0; kt < p.ksteps; ++kt) {
-        const int8_t* am = rlds + kt * STEP;
-        const int8_t* wb = rlds + p.w_off + kt * (BN * 64);
+    const int ra = wm * 32 + frag_row, piece = rows_swz(frag_row, frag_half);     // (the exchange repeats every 16 rows)
+    for (int st = 0; st < p.steps; ++st) {
+        const i32x4 a = *reinterpret_cast<const i32x4*>(rlds + st * STEP + ra * 32 + piece);
+        const int8_t* wb = rlds + p.w_off + ((st >> 1) * BN + wn * WN + frag_row) * 64 + swz<64>(frag_row, (st & 1) * 2 + frag_half) * 16;
+        i32x4 b[TN];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int ra = wm * 32 + frag_row;
-            const i32x4 a = *reinterpret_cast<const i32x4*>(&am[ra * 64 + swz<64>(ra, ks * 2 + frag_half) * 16]);
-            i32x4 b[TN];
+        for (int j = 0; j < TN; ++j) b[j] = *reinterpret_cast<const i32x4*>(wb + j * 2048);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int r = wn * WN + j * 32 + frag_row;
-                b[j] = *reinterpret_cast<const i32x4*>(&wb[r * 64 + swz<64>(r, ks * 2 + frag_half) * 16]);
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[0][j] = mfma_tile<false>(a, b[j], acc[0][j]);
-        }
+        for (int j = 0; j < TN; ++j) acc[0][j] = mfma_tile<RQ>(a, b[j], acc[0][j]);
     }
     __syncthreads();                                              // image and weights have been read: their LDS is the stage
-    int32_t* stage = reinterpret_cast<int32_t*>(&rlds[wave * stage_bytes<false, WN, 8>()]);
-    emit_tile<false, 1, TN, 8>(acc, stage, lane, row0 + wm * 32, wn * WN, wn * WN, p.M, p.N, step_x * step_w, p.Y, p.ldy, p.acc_out,
-                               p.ldacc, Requant{}, 0.0f, nullptr, 0, false, row0 + BM <= p.M && BN <= p.N);
+    int32_t* stage = reinterpret_cast<int32_t*>(&rlds[wave * stage_bytes<RQ, WN, 8>()]);
+    const float inv_next = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
+    const int dup_n = RQ && p.dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
+    emit_tile<RQ, 1, TN, 8>(acc, stage, lane, row0 + wm * 32, wn * WN, wn * WN, p.M, p.N, step_x * step_w, p.Y, p.ldy, p.acc_out,
+                            p.ldacc, rq, inv_next, dup_list, dup_n, RQ && wn == 0, row0 + BM <= p.M && BN <= p.N);
 }
 
-template <int BN, int U>
-static hipError_t run_rows(RowsLayer p, hipStream_t stream) {
-    const int64_t K = (int64_t)p.C * p.g, TD = (int64_t)p.ksteps * 16 - K / 4;
+// Dynamic LDS of a launch: the image and the weights (or the epilogue's stage), the table of the tail's sources, the list of the next
+// layer's copies.  p (may be null) receives the offsets.
+template <int BN, bool RQ>
+static int64_t rows_layer_lds(int64_t K, int64_t steps, int s_next, RowsLayer* p) {
+    const int64_t w = round_up(steps * kRowsStep, 1024), operands = w + (steps + 1) / 2 * BN * 64;
+    const int64_t staging = (kRowsNT / 64) * stage_bytes<RQ, BN / 2, 8>();
+    const int64_t tab = round_up(operands > staging ? operands : staging, 16), dup = tab + 16 * (steps * 8 - K / 4);
+    const bool list = RQ && s_next > 0;
+    if (p != nullptr) {
+        p->w_off = (int)w;
+        p->tab_off = (int)tab;
+        p->dup_off = list ? (int)dup : 0;
+    }
+    return dup + (list ? (kDupCap + 1) * 4 : 0);
+}
+constexpr int64_t kRowsMaxLds = 65536 - 64;                       // (what no kernel has to opt into, less what is not dynamic)
+
+template <int BN, int U, bool RQ>
+static hipError_t run_rows(RowsLayer p, const Requant& rq, hipStream_t stream) {
+    const int64_t K = (int64_t)p.C * p.g;
     auto magic_of = [](int64_t n) {          // floor(2^32 / n), or 2^32 - 1 for n = 1
         const uint64_t m = (((uint64_t)1) << 32) / (uint64_t)(n > 0 ? n : 1);
         return (unsigned)(m > 0xFFFFFFFFull ? 0xFFFFFFFFull : m);
     };
     p.magic_qc = magic_of(ceil_div(K, 4));
-    p.magic_td = magic_of(TD);
+    p.magic_td = magic_of(p.steps * 8 - K / 4);
     p.magic_pc = magic_of(p.ldq / 16);
-    p.w_off = (int)round_up((int64_t)p.ksteps * kRowsStep, 1024);
-    const int64_t operands = p.w_off + (int64_t)p.ksteps * BN * 64, staging = (kRowsNT / 64) * stage_bytes<false, BN / 2, 8>();
-    const int64_t tab = round_up(operands > staging ? operands : staging, 16);
-    const int64_t lds = tab + 16 * TD;
-    p.tab_off = (int)tab;
-    if (lds > 64 * 1024) return hipErrorInvalidValue;             // (what no kernel has to opt into)
-    return launch_kernel(kTimeGemm, rows_layer_kernel<BN, U>, dim3((unsigned)ceil_div(p.M, kRowsBM)), dim3(kRowsNT), (unsigned)lds,
-                         stream, p);
+    const int64_t lds = rows_layer_lds<BN, RQ>(K, p.steps, rq.s_next, &p);
+    if (lds > kRowsMaxLds) return hipErrorInvalidValue;
+    return launch_kernel(kTimeGemm, rows_layer_kernel<BN, U, RQ>, dim3((unsigned)ceil_div(p.M, kRowsBM)), dim3(kRowsNT), (unsigned)lds,
+                         stream, p, rq);
 }
-template <int BN>
-static hipError_t run_rows_loads(const RowsLayer& p, hipStream_t stream) {
+template <int BN, bool RQ>
+static hipError_t run_rows_loads(const RowsLayer& p, const Requant& rq, hipStream_t stream) {
     const int64_t need = ceil_div(ceil_div((int64_t)p.C * p.g, 4), 4);   // 16-byte loads a lane
-    if (need <= 4) return run_rows<BN, 4>(p, stream);
-    if (need <= 7) return run_rows<BN, 7>(p, stream);
-    if (need <= 10) return run_rows<BN, 10>(p, stream);
+    if (need <= 4) return run_rows<BN, 4, RQ>(p, rq, stream);
+    if (need <= 7) return run_rows<BN, 7, RQ>(p, rq, stream);
+    if (need <= 10) return run_rows<BN, 10, RQ>(p, rq, stream);
     if constexpr (BN <= 128) {
-        if (need <= 13) return run_rows<BN, 13>(p, stream);
-        if (need <= 16) return run_rows<BN, 16>(p, stream);
-        if (need <= 20) return run_rows<BN, 20>(p, stream);
+        if (need <= 13) return run_rows<BN, 13, RQ>(p, rq, stream);
+        if (need <= 16) return run_rows<BN, 16, RQ>(p, rq, stream);
+        if (need <= 20) return run_rows<BN, 20, RQ>(p, rq, stream);
     }
     return hipErrorInvalidValue;
 }
 
 // Shapes it serves: what the table, the loads of a lane and 64 KB of LDS hold.
-static bool rows_layer_fits(int64_t M, int C, int g, int s, int64_t ldq, int64_t N) {
-    const int64_t K = (int64_t)C * g, Kpad = round_up(K + (int64_t)s * g, 64);
-    if (K < 4 || Kpad > 320 || ldq > Kpad || N > 256 || M > 0x7FFFFFFF - kRowsBM) return false;
-    return N <= 128 || (K <= 160 && Kpad <= 192);
+static bool rows_layer_fits(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, const Requant& rq) {
+    const int64_t K = (int64_t)C * g, steps = ceil_div(K + (int64_t)s * g, 32);
+    if (K < 4 || steps > 10 || ldq > round_up(32 * steps, 64) || N > 256 || M > 0x7FFFFFFF - kRowsBM) return false;
+    if (rq.Yq != nullptr)
+        return N <= 64 ? rows_layer_lds<64, true>(K, steps, rq.s_next, nullptr) <= kRowsMaxLds
+                       : N <= 128 && rows_layer_lds<128, true>(K, steps, rq.s_next, nullptr) <= kRowsMaxLds;
+    if (N <= 128) return rows_layer_lds<128, false>(K, steps, 0, nullptr) <= kRowsMaxLds;
+    return K <= 160 && rows_layer_lds<256, false>(K, steps, 0, nullptr) <= kRowsMaxLds;
 }
 // Where the one launch is ahead of the two (us, two / one; passes queued back to back, inputs rotating, static grid, copies 5 %):
 //   rows      from sixteen per compute unit on, where the layer of few tiles ends: 4100 x 100 -> 256 10.4 / 7.2 (in a graph 6.4 / 6.3),
@@ -2448,26 +2470,31 @@ static bool rows_layer_fits(int64_t M, int C, int g, int s, int64_t ldq, int64_t
 //   outputs   more than 128 of them on many rows are a stream of writes, which a launch of its own keeps up best: 50000 x 64 -> 256
 //             18.0 / 16.7, 200000 51.4 / 48.7, 400000 94.8 / 95.7, 802816 179 / 188; 400000 x 48 -> 256 88.4 / 92.0; 800000 x 64 -> 160
 //             136 / 145.  The line: 2^26 values.
-bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N) {
+bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, const Requant& rq) {
     const int mode = tuning().rows_layer;
-    if (mode == 0 || !rows_layer_fits(M, C, g, s, ldq, N)) return false;
+    if (mode == 0 || !rows_layer_fits(M, C, g, s, ldq, N, rq)) return false;
     if (mode > 0) return true;
-    return M >= 16 * (int64_t)compute_units() && (N <= 128 || M * N <= (int64_t)1 << 26);
+    const int64_t cus = compute_units();
+    // (codes out: 12544 x 256 -> 64 11.1 / 8.6, 50176 x 256 -> 128 28.1 / 25.6, 802816 x 64 -> 64 88.8 / 69.7, 4160 x 64 -> 128 7.1 / 6.8; half of
+    // the compute units without a workgroup, 8192 x 256 -> 128, 10.0 / 10.3)
+    if (rq.Yq != nullptr) return M >= ((int64_t)C * g <= 128 ? 16 : 48) * cus;
+    return M >= 16 * cus && (N <= 128 || M * N <= (int64_t)1 << 26);
 }
 
 hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src, const float* thr,
                              int n_max, float clip, float qmax, int8_t* Xq, int64_t ldq, float* scale_x, const int8_t* Wq, int64_t ldw,
                              int64_t N, const float* scale_w, int32_t* acc_out, int64_t ldacc, float* Y, int64_t ldy,
-                             hipStream_t stream) {
+                             hipStream_t stream, const Requant& rq) {
     RowsLayer p;
     p.X = X; p.ldx = ldx; p.M = (int)M; p.C = C; p.g = g; p.s = s;
     p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
-    p.ksteps = (int)ceil_div((int64_t)(C + s) * g, 64);
-    if (N <= 64) return run_rows_loads<64>(p, stream);
-    if (N <= 128) return run_rows_loads<128>(p, stream);
-    return run_rows_loads<256>(p, stream);
+    p.steps = (int)ceil_div((int64_t)(C + s) * g, 32);
+    if (rq.Yq != nullptr) return N <= 64 ? run_rows_loads<64, true>(p, rq, stream) : run_rows_loads<128, true>(p, rq, stream);
+    if (N <= 64) return run_rows_loads<64, false>(p, rq, stream);
+    if (N <= 128) return run_rows_loads<128, false>(p, rq, stream);
+    return run_rows_loads<256, false>(p, rq, stream);
 }
 
 // Dynamic LDS of a whole-K launch: operands (or the epilogue's staging area, if larger) and,

@@ -246,6 +246,20 @@ class ExpandedConv:
                             acc_out, 0 if acc_out is None else acc_out.stride(0), stream)
         return Ho, Wo
 
+    def forward_to_codes(self, A, nxt, threshold, next_threshold, relu=True, acc_out=None, stream=None):
+        """split_act(A, threshold) and conv_to_codes(..., nxt, next_threshold) as one call."""
+        Bn, H, W, C = A.shape
+        assert C == self.C and A.is_contiguous() and nxt.C == self.N
+        Ho, Wo = self.out_size(H, W)
+        self.ensure_input(Bn * H * W)
+        nxt.ensure_input(Bn * Ho * Wo)
+        B.ocs_conv_forward_requant(A, Bn, H, W, C, self.w.chan_src, self.s, self.w.bits_x, threshold, 1.0, self.Aq, self.ldc,
+                                   self.scale_x, self.kh, self.kw, self.stride, self.pad, self.Wt, self.N, self.w.bits_w,
+                                   self.w.scale_w, relu, next_threshold, nxt.w.bits_x, nxt.w.chan_src, nxt.s, nxt.Aq,
+                                   nxt.ldc, nxt.scale_x, acc_out, 0 if acc_out is None else acc_out.stride(0), self.ws_a,
+                                   stream)
+        return Ho, Wo
+
     def forward(self, A, threshold=None, acc_out=None, stream=None):
         """A fp32 [B, H, W, C] contiguous -> Y fp32 [B*Ho*Wo, N]."""
         Bn, H, W, _ = A.shape
@@ -276,7 +290,10 @@ class ConvChain:
         """A fp32 [B, H, W, C]; thresholds: one device float per layer (its input grid's range).
         Returns Y fp32 [B*Ho*Wo, N_last]; acc_out (optional) receives the last layer's accumulators."""
         Bn, H, W, _ = A.shape
-        self.layers[0].split_act(A, thresholds[0], stream)
-        for i, L in enumerate(self.layers[:-1]):
+        if len(self.layers) == 1:
+            self.layers[0].split_act(A, thresholds[0], stream)
+        else:
+            H, W = self.layers[0].forward_to_codes(A, self.layers[1], thresholds[0], thresholds[1], True, None, stream)
+        for i, L in enumerate(self.layers[1:-1], 1):
             H, W = L.conv_to_codes(Bn, H, W, self.layers[i + 1], thresholds[i + 1], True, None, stream)
         return self.layers[-1].conv(Bn, H, W, acc_out, stream)

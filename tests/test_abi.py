@@ -298,6 +298,23 @@ def test_forward_reports_what_its_two_steps_report():
     assert fwd(thr=None, w=None, wb=0) == -7 and fwd(thr=None, clip=0.0) == -10
 
 
+def test_first_layer_of_a_chain_reports_what_its_steps_report():
+    L = B.lib()
+
+    def fwd(X=A, Bn=1, H=4, W=4, C=8, src=A, s=2, bx=8, thr=A, clip=1.0, Aq=A, ldc=16, sx=A, k=1, stride=1, pad=0, Wt=A, N=4, bw=8, sw=A,
+            nt=A, nb=8, ns=A, nn=1, Yq=A, ldyq=16, nso=A + 64, acc=None, ldacc=0, w=A, wb=1 << 24):
+        return L.ocs_conv_forward_requant(X, Bn, H, W, C, src, s, bx, thr, clip, Aq, ldc, sx, k, k, stride, pad, Wt, N, bw, sw, 1, nt, nb,
+                                          ns, nn, Yq, ldyq, nso, acc, ldacc, w, wb, None)
+
+    for name in ("X", "src", "Aq", "sx", "Wt", "sw", "nt", "ns", "Yq"):
+        assert fwd(**{name: None}) == -1, name
+    assert fwd(Bn=0) == -2 and fwd(H=0) == -2 and fwd(N=0) == -2 and fwd(ldc=0) == -2 and fwd(k=7) == -2 and fwd(pad=-1) == -2
+    assert fwd(stride=0) == -2 and fwd(ldyq=0) == -2 and fwd(acc=A, ldacc=3) == -2
+    assert fwd(Aq=A + 1) == -3 and fwd(Wt=A + 4) == -3 and fwd(Yq=A + 4) == -3 and fwd(ldyq=24) == -3 and fwd(thr=None, w=A + 16) == -3
+    assert fwd(bx=9) == -4 and fwd(bw=1) == -4 and fwd(nb=9) == -4 and fwd(s=-1) == -5 and fwd(nn=513, ldyq=528) == -5
+    assert fwd(thr=None, w=None, wb=0) == -7 and fwd(thr=None, clip=0.0) == -10 and fwd(nso=A) == -9
+
+
 def test_forward_act_reports_what_its_steps_report():
     L = B.lib()
 

@@ -1742,6 +1742,48 @@ def test_forward_of_short_rows_per_batch(M, C, g, s, N, ld_extra, clip):
     _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0, route=3))
 
 
+# The first layer of a chain as one call against its two calls, all outputs bit for bit: the one launch (pixels around a workgroup's 64,
+# code rows of one to five steps, outputs around 32, 64 and 128, copies for the next layer: none, a few, more than outputs; padding of
+# the next layer's codes) and what stays with the two (3x3, stride 2, an output wider than 128, outputs on top of an input).
+@pytest.mark.parametrize("Bn,H,W,C,s,k,stride,N,s_next,bits_next,threshold", [
+    (1, 1, 1, 4, 0, 1, 1, 1, 0, 8, 2.5), (1, 7, 9, 5, 3, 1, 1, 33, 2, 8, 2.5), (1, 8, 8, 64, 4, 1, 1, 64, 4, 4, 2.5), (3, 13, 5, 256, 13, 1, 1, 64, 4, 8, 2.5),
+    (2, 9, 9, 256, 13, 1, 1, 64, 4, 8, None), (1, 20, 7, 100, 5, 1, 1, 100, 30, 8, 2.5), (2, 8, 8, 250, 12, 1, 1, 128, 7, 6, 2.5), (1, 16, 9, 30, 200, 1, 1, 65, 400, 8, 2.5),
+    (1, 10, 10, 64, 4, 1, 1, 129, 5, 8, 2.5), (2, 8, 8, 64, 4, 1, 2, 64, 4, 8, 2.5), (1, 12, 12, 32, 2, 3, 1, 64, 4, 8, None)])
+def test_first_layer_of_a_chain_as_one_call(Bn, H, W, C, s, k, stride, N, s_next, bits_next, threshold):
+    gen = torch.Generator(device="cuda").manual_seed(C + N)
+    pad, E, M = k // 2, C + s, Bn * H * W
+    Ho, Wo = (H + 2 * pad - k) // stride + 1, (W + 2 * pad - k) // stride + 1
+    Mo, ldc, ldyq = Bn * Ho * Wo, B.ocs_padded_channels(E), B.ocs_padded_channels(N + s_next) + 16
+    ldt = B.ocs_conv_weight_cols(k * k, ldc)
+    A = torch.randn((Bn, H, W, C), device="cuda", generator=gen)
+    Wt = torch.zeros((N + 1, ldt), dtype=torch.int8, device="cuda")
+    for t in range(k * k):
+        Wt[:N, t * ldc:t * ldc + E] = torch.randint(-15, 16, (N, E), device="cuda", generator=gen, dtype=torch.int8)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    cs = torch.cat([torch.arange(C, **i32), torch.randint(0, C, (s,), generator=gen, **i32)])
+    ns = torch.cat([torch.arange(N, **i32), torch.randint(0, N, (s_next,), generator=gen, **i32)])
+    sw, tn = torch.tensor([1.5, 0.01], device="cuda"), torch.tensor([3.0], device="cuda")
+    th = None if threshold is None else torch.tensor([threshold], device="cuda")
+    ws = B.alloc_workspace(M, C)
+
+    def call(two):
+        Aq, Yq = torch.full((M, ldc), 77, dtype=torch.int8, device="cuda"), torch.full((Mo, ldyq), 55, dtype=torch.int8, device="cuda")
+        sx, sn, acc = torch.full((2,), -1.0, device="cuda"), torch.full((2,), -1.0, device="cuda"), torch.full((Mo, N), 9, **i32)
+        if two:
+            B.ocs_split_act(A, M, C, 1, C, cs, None, s, 8, th, 0.9, Aq, ldc, sx, ws)
+            B.ocs_qconv_requant(Aq, ldc, Bn, H, W, E, k, k, stride, pad, Wt, N, 8, 5, sx, sw, True, tn, bits_next, ns, s_next, Yq, ldyq, sn, acc, N)
+        else:
+            B.ocs_conv_forward_requant(A, Bn, H, W, C, cs, s, 8, th, 0.9, Aq, ldc, sx, k, k, stride, pad, Wt, N, 5, sw, True, tn,
+                                       bits_next, ns, s_next, Yq, ldyq, sn, acc, N, ws)
+        return Aq, sx, Yq, sn, acc
+
+    want, got = call(True), []
+    _rows(1, lambda: got.extend(call(False)))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    _rows(1, lambda: got.extend(_launched(lambda: call(False))))
+    assert (B.TIME_SPLIT_QUANTIZE not in got[5:]) == (k == 1 and stride == 1 and N <= 128)
+
+
 # ---- channel maxima in row blocks that the selector folds itself ------------------------------------
 
 # Rows and columns around the blocks' edges: a row's last group of four overlaps the one before (5, 7, 33, 130 columns, 8, 16 and
