@@ -1810,8 +1810,11 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 // NQ waves only quantize: they hold no accumulators, so a step of 128 columns of X is on its way in their registers, each
 // register requested again as soon as it is read (with two steps they spill: 57 us).  Floats through LDS instead cost it as much
 // again as the fragments do (25088 x 1024 -> 256 39.8 us).  The other waves multiply, and request the weight codes straight
-// into LDS a step ahead: neither kind waits for the other's memory, and a step costs one barrier.  A workgroup of 128 rows on
-// every compute unit; the next tile's first steps are requested before the last one's outputs are written.
+// into LDS two steps ahead: neither kind waits for the other's memory, and a step costs one barrier.  A workgroup of 64 rows on
+// every compute unit; the next tile's first steps are requested before the last one's outputs are written.  Two steps of the weights, not
+// one, are what 64 rows need, whose steps are half as long as their way from the L2 (12544 x 2304 -> 256, static grid: two launches
+// 37.1 us, one step ahead 38.0, two 35.1, three 34.7; per batch 54.2, 52, 45.4); two steps of X, or half as many waves that
+// quantize, are level or behind.  128 rows with the weights two steps ahead stay where they are one round and K is short.
 // The copies of the split channels are moved byte by byte, by the wave that quantizes their rows, into the steps that follow X's
 // whole ones (`tail`), next to the columns left over after those; the tail is multiplied last.
 // Bounded by what the compute units draw from memory: X, codes and outputs at 4.5 TB/s (25088 x 1024 -> 256 40.5 -> 34.7 us for
@@ -1845,7 +1848,8 @@ struct PanelLayer {
 constexpr int kPanelMaxTail = 256;     // appended columns s*g
 constexpr int kPanelStep = 128;        // columns of a step: whole lines of codes
 
-template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
+// WBUF: steps of weight codes in LDS.
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N, int WBUF>
 __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_kernel(PanelLayer p) {
     constexpr int NM = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
@@ -1906,11 +1910,16 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
         auto fetch_w = [&](int kt) {
             const int q = step_of(kt) * CPR + wpiece;
             const int8_t* base = p.Wq + (int64_t)q * 16;
-            const unsigned slot = w0 + (unsigned)((kt & 1) * (BN * BK));
+            const unsigned slot = w0 + (unsigned)((WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK));
 #pragma unroll
             for (int u = 0; u < LB; ++u) lds_dma16(q < w_end ? base + wsrc[u] : zero_chunk, slot + u * (NM * 1024));
         };
-        fetch_w(0);
+        auto first_weights = [&]() {
+#pragma unroll
+            for (int k = 0; k < WBUF - 1; ++k)
+                if (k < p.kall) fetch_w(k);
+        };
+        first_weights();
         const int wm = mw / WAVES_N, wn = mw % WAVES_N;
         const int frag_row = lane & 31, frag_half = lane >> 5;
         int32_t* stage = reinterpret_cast<int32_t*>(plds + p.stage_off) + mw * (8 * WN);
@@ -1924,10 +1933,12 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
 #pragma unroll
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
             for (int kt = 0; kt < p.kall; ++kt) {
-                wait_vmcnt<0>();                                 // this wave's part of the step's weight codes
+                // this wave's part of the step's weight codes (behind them only those of later steps)
+                if (WBUF > 2 && kt + WBUF - 2 < p.kall) wait_vmcnt<(WBUF - 2) * LB>();
+                else wait_vmcnt<0>();
                 step_barrier();
                 const int8_t* am = kt < p.kmain ? codes + (kt & 1) * (BM * BK) : tail + (kt - p.kmain) * (BM * BK);
-                const int8_t* wb = wring + (kt & 1) * (BN * BK);
+                const int8_t* wb = wring + (WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK);
                 auto read_slice = [&](int ks) {
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
@@ -1942,7 +1953,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                 };
                 read_slice(0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (kt + 1 < p.kall) fetch_w(kt + 1);            // into the slot multiplied before this barrier
+                if (kt + WBUF - 1 < p.kall) fetch_w(kt + WBUF - 1);      // into the slot multiplied before this barrier
 #pragma unroll
                 for (int ks = 0; ks < BK / 32; ++ks) {
                     if (ks + 1 < BK / 32) read_slice(ks + 1);
@@ -1955,7 +1966,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                 }
             }
             step_barrier();                                      // the tile's operands have been read: the next one's may come
-            if (tile + (int)gridDim.x < p.tiles) fetch_w(0);
+            if (tile + (int)gridDim.x < p.tiles) first_weights();
             const int row0 = tile * p.stride, row_end = row0 + p.stride < p.M ? row0 + p.stride : p.M;
             const float scale = (threshold() / p.qmax) * p.scale_w[1];
             emit_tile<false, TM, TN, 8>(acc, stage, lane, row0 + wm * WM, wn * WN, wn * WN, row_end, p.N, scale, p.Y, p.ldy,
@@ -2116,26 +2127,30 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
     }
 }
 
-template <int BM, int BN, int NQ, int WAVES_M>
+template <int BM, int BN, int NQ, int WAVES_M, int WBUF>
 static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
     constexpr int BK = kPanelStep;
-    const int64_t tail = 2 * (BM + BN) * BK, list = tail + tail_steps * BM * BK, stage = list + NQ * kPanelMaxTail * 4;
+    const int64_t tail = (2 * BM + WBUF * BN) * BK, list = tail + tail_steps * BM * BK, end = list + NQ * kPanelMaxTail * 4;
+    // With three steps of weights or more the epilogue's stage is the last of their slots: the next tile's first steps go to the others,
+    // and that one is requested only behind a barrier that every wave reaches after its epilogue.
+    constexpr int STAGE = WAVES_M * 8 * BN * 4;
+    static_assert(WBUF == 2 || STAGE <= BN * BK, "the stage fits a step of weights");
     if (p != nullptr) {
         p->tail_off = (int)tail;
         p->list_off = (int)list;
-        p->stage_off = (int)stage;
+        p->stage_off = (int)(WBUF > 2 ? tail - BN * BK : end);
     }
-    return stage + WAVES_M * 8 * BN * 4;
+    return WBUF > 2 ? end : end + STAGE;
 }
 
-template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N, int WBUF>
 static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     constexpr int BK = kPanelStep;
     const int64_t K = (int64_t)p.C * p.g, Kexp = (int64_t)(p.C + p.s) * p.g;
     p.kmain = (int)(K / BK);
     p.kall = (int)ceil_div(Kexp, BK);
     p.rem = (int)(K - (int64_t)p.kmain * BK);
-    const int64_t o = panel_lds<BM, BN, NQ, WAVES_M>(p.kall - p.kmain, &p);
+    const int64_t o = panel_lds<BM, BN, NQ, WAVES_M, WBUF>(p.kall - p.kmain, &p);
     if (o > kWholeKMaxLds) return hipErrorInvalidValue;
     static std::atomic<bool> opted_in[kMaxDevices];
     int dev = 0;
@@ -2143,7 +2158,7 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     if (!opted_in[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N, WBUF>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
         if (e != hipSuccess) return e;
         opted_in[dev].store(true, std::memory_order_release);
@@ -2155,7 +2170,7 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     p.stride = (int)st;
     p.rpw = (int)ceil_div(st, NQ);
     p.tiles = (int)ceil_div(p.M, st);
-    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>,
+    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N, WBUF>,
                          dim3((unsigned)(p.tiles < slots ? p.tiles : slots)), dim3((NQ + WAVES_M * WAVES_N) * 64), (unsigned)o, stream, p);
 }
 
@@ -2163,7 +2178,7 @@ static bool panel_fits(int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq,
     const int64_t K = (int64_t)C * g, T = (int64_t)s * g, pitch = (int64_t)1 << 23;      // (offsets of 128 rows in 32 bits)
     if (K < 64 || T > kPanelMaxTail || N > 256 || M > 0x7FFFFFFF - 256 || ldx >= pitch || ldq >= pitch || ldw >= pitch) return false;
     const int64_t tail_steps = ceil_div(K + T, kPanelStep) - K / kPanelStep;
-    return panel_lds<128, 256, 8, 2>(tail_steps, nullptr) <= kWholeKMaxLds;              // (the widest: at most two steps of the tail)
+    return tail_steps <= 2;                              // (what the widest instance has LDS for, but for the one of 128 rows: one)
 }
 
 hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
@@ -2175,9 +2190,14 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
-    if (N <= 64) return run_panel<128, 64, 8, 4, 2>(p, stream);
-    if (N <= 128) return run_panel<128, 128, 8, 2, 4>(p, stream);
-    return run_panel<128, 256, 8, 2, 4>(p, stream);
+    if (N <= 64) return run_panel<64, 64, 8, 2, 2, 3>(p, stream);
+    if (N <= 128) return run_panel<64, 128, 8, 2, 4, 3>(p, stream);
+    // (a round of 128 rows, not two of 64, where K is short: us, 128 / 64 rows a tile: 25088 x 384 -> 256 19.2 / 19.0, x 512 21.9 / 22.7, x 1024
+    // 33.9 / 35.6, 30000 x 512 24.4 / 25.6, x 1024 37.9 / 39.8; x 2048 61.1 / 61.2, 30000 x 2048 76.1 / 69.0)
+    const int64_t K = (int64_t)C * g, cus = compute_units();
+    if (M > 64 * cus && M <= 128 * cus && K <= 1024 && ceil_div(K + (int64_t)s * g, kPanelStep) - K / kPanelStep <= 1)
+        return run_panel<128, 256, 8, 2, 4, 3>(p, stream);
+    return run_panel<64, 256, 8, 2, 4, 3>(p, stream);
 }
 
 // Where the one launch is ahead of the two (two launches / one; in a graph on inputs outside the caches, in a graph on the same input
@@ -2200,9 +2220,16 @@ bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int 
     if (mode == 0 || !panel_fits(ldx, M, C, g, s, ldq, ldw, N)) return false;
     if (mode > 0) return true;
     const int64_t K = (int64_t)C * g, cus = compute_units();
+    // One round of 64-row tiles.  Two launches / one (passes one after the other, a graph, a graph on the same input again, per batch in
+    // a graph): K = 512, N = 64 to 256: 36 rows per compute unit 1.26-1.41, 1.22-1.36, 1.14-1.26, 1.12-1.20; 44 to 64 1.24-1.44, 1.17-1.41,
+    // 1.19-1.49, 1.07-1.27.  K = 1152: 36 1.02-1.14, 0.98-1.10, 0.94-1.09, 1.09-1.15; 44 1.10-1.23, 1.06-1.20, 0.99-1.14, 1.15-1.21; 48 to 64
+    // 1.16-1.37, 1.09-1.28, 1.05-1.22, 1.17-1.28.  K = 2304: 32 0.91-0.98 in a graph; 36 1.01-1.07, 1.00-1.06, 0.89-0.98, 1.07-1.13; 44 to
+    // 64 1.05-1.23, 1.03-1.13, 0.94-1.11, 1.10-1.24.  K = 4608: 44 1.01-1.07, 0.99-1.05, 0.90-0.96, 1.19-1.24; 52 to 64 1.04-1.20, 1.02-1.19,
+    // 0.99-1.22, 1.16-1.25.  In two rounds of 39 rows 0.90-1.17.
+    const bool one_round = M <= 64 * cus && M >= (K <= 640 ? 36 : 44) * cus;
     if (K < 384 || K % 64 != 0 || ldx % 32 != 0 || reinterpret_cast<uintptr_t>(X) % 128 != 0) return false;
     if (5 * (int64_t)s * g > K || (ldx != K && K < 1024)) return false;
-    return (M >= 98 * cus && M <= 128 * cus) || M >= 192 * cus;
+    return one_round || (M >= 98 * cus && M <= 128 * cus) || M >= 192 * cus;
 }
 
 // ---------------------------------------------------------------------------------------------

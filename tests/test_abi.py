@@ -243,6 +243,21 @@ def test_forward_of_many_rows_by_rows_and_copies(C, g, s, N, extra, inside, outs
         assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=1 << 20) == 0, M
 
 
+# One round of 64-row tiles: 44 to 64 rows per compute unit, from 36 on up to 640 columns; whole lines, few copies.
+@pytest.mark.parametrize("C,g,s,N,inside,outside", [
+    (640, 1, 32, 64, (36 * 256, 64 * 256), (36 * 256 - 1, 64 * 256 + 1)), (704, 1, 35, 256, (44 * 256, 64 * 256), (44 * 256 - 1, 64 * 256 + 1)),
+    (256, 9, 6, 256, (12544,), ()), (512, 9, 26, 100, (12544,), ()), (512, 9, 26, 257, (), (12544,)), (400, 1, 20, 64, (), (12544,)),
+    (320, 1, 16, 64, (), (12544,)), (512, 1, 103, 64, (), (12544,))])
+def test_forward_of_one_round_of_64_rows(C, g, s, N, inside, outside):
+    ld = B.ocs_padded_cols((C + s) * g)
+    for M in inside:
+        for captured in (False, True):
+            assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, captured=captured, X=1 << 20) == 2, M
+        assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, X=(1 << 20) + 64) == 0, M
+    for M in outside:
+        assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N, X=1 << 20) == 0, M
+
+
 # Rows (more than the layer of few tiles takes: sixteen per compute unit with 256 outputs, 32 with 64), code rows of up to 320 bytes
 # (192, and at most 160 columns of X, with more than 128 outputs),
 # outputs, more than 2^26 of them in more than 128 columns, padding past the last step; strides and alignment of X do not count.

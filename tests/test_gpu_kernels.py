@@ -1707,6 +1707,30 @@ def test_forward_route_of_many_rows(per, extra, C, g, N, ld, threshold):
         assert all(torch.equal(a, b) for a, b in zip(out[0], o))
 
 
+# One round of 64-row tiles and one of 128 (short K, more than 128 outputs), the weights' ring around its three slots (three to six
+# steps), two steps of the tail with either; against the two launches, bit for bit.
+@pytest.mark.parametrize("per,extra,C,g,N", [
+    (36, 0, 384, 1, 256), (64, 0, 512, 1, 130), (44, 1, 704, 1, 64), (49, 0, 64, 9, 128), (127, 3, 384, 1, 256), (100, 0, 448, 1, 200), (98, 5, 1088, 1, 256)])
+@pytest.mark.parametrize("threshold", [3.0, None])
+def test_forward_of_many_rows_by_64_and_128(per, extra, C, g, N, threshold):
+    from paper_1901_09504_amd.layer import ExpandedLayer
+    M, K = per * 256 + extra, C * g
+    gen = torch.Generator(device="cuda").manual_seed(per + C)
+    X = torch.randn((M, K), device="cuda", generator=gen)
+    L = ExpandedLayer(N, C, g, 0.17, 6, 8, max_rows=M)
+    L.prepare_weights(torch.randn((N, K), device="cuda", generator=gen))
+    th = None if threshold is None else torch.tensor([threshold], device="cuda")
+    assert B.ocs_forward_one_launch(M, C, g, K, L.s, L.ldq, L.ldq, N, X=X) == 2
+    out = []
+    for mode in (0, -1, -1):
+        acc = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+        L.Xq.fill_(77)
+        _panel(mode, lambda: L.forward(X, th, acc_out=acc))
+        out.append((L.Xq.clone(), L.scale_x.clone(), acc, L.Y.clone()))
+    for o in out[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+
+
 def test_forward_of_many_rows_over_its_own_input():
     _panel(1, test_forward_over_its_own_input)
 
