@@ -2077,8 +2077,11 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                     av[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4u*>(xbase + (int64_t)step_of(it + 1) * (4 * BK) + xoff[u]));
                     __builtin_amdgcn_sched_barrier(0);       // (or the arithmetic of later requests, and its waits, move ahead)
                 }
-                copies(it);
+                // (the tail is read behind a later barrier: with 128 rows the copies are made while the others multiply, 25088 x 1024 -> 256
+                // 33.9 -> 33.1 us; with 64 the next step waits for them, 12544 x 2304 -> 256 per batch 45.2 -> 46.7)
+                if (BM < 128) copies(it);
                 step_barrier();
+                if (BM >= 128) copies(it);
                 __builtin_amdgcn_sched_barrier(0);
                 ++it;
             };
