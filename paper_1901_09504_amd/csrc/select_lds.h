@@ -180,6 +180,7 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                                               int32_t* split_src) {
     static_assert(NT % 64 == 0 && NT / 64 <= 16 && NT >= kGreedyBins, "waves of the workgroup");
     const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (what depends on it alone stays in scalar registers)
     const unsigned* vbits = reinterpret_cast<const unsigned*>(vals);
     if (s <= 0) return;
     unsigned m = 0;
@@ -214,30 +215,43 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
         auto key_of = [&](int j) {
             return ((unsigned long long)(mbits - vbits[j]) << 13) | (unsigned long long)j;
         };
-        // the round's entries, in no order yet (whole waves walk the list: one LDS atomic per wave).
-        // `count` is cleared ahead of the barrier that precedes this pass.
-        auto gather = [&](unsigned long long cut) {
-            for (int j0 = tid - lane; j0 < cur; j0 += NT) {
-                const int j = j0 + lane;
-                const bool in = j < cur && vbits[j] > hbits && key_of(j) <= cut;
-                const unsigned long long mask = __ballot(in);
-                if (mask == 0) continue;
-                unsigned base = 0;
-                if (lane == 0) base = atomicAdd(&sc.count, (unsigned)__popcll(mask));
-                base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-                const int pos = (int)base + __popcll(mask & ((1ull << lane) - 1ull));
-                if (in) cand[pos] = key_of(j);
-            }
-        };
+        // The round's entries, in no order yet.  Sixteen waves on four SIMDs: what a walk over the list costs is its instructions, so
+        // each wave counts its own first (a look-up and a comparison per entry), and keys are made of those only that take
+        // part: of all where the round is not cut, behind the waves' counts, else of the ones up to the bound found first (one
+        // LDS atomic per wave; `count` is cleared ahead of a barrier that precedes them).
+        unsigned own = 0;
+        for (int j0 = 64 * wave; j0 < cur; j0 += NT) {
+            const int j = j0 + lane;
+            own += (unsigned)__popcll(__ballot(vbits[j < cur ? j : cur - 1] > hbits && j < cur));
+        }
+        if (lane == 0) sc.red[wave] = own;
         if (tid == 0) sc.count = 0;
         __syncthreads();
-        gather(~0ull);
-        __syncthreads();
-        int in_round = (int)sc.count;
+        int in_round = 0, base0 = 0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) {
+            const int n = (int)sc.red[w];
+            base0 += w < wave ? n : 0;
+            in_round += n;
+        }
+        in_round = __builtin_amdgcn_readfirstlane(in_round);
+        auto before = [&](unsigned long long mask) {
+            return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
+        };
         // (counting costs in_round^2 / NT look-ups per lane, a digit three barriers: level at about 32
         // look-ups)
         auto countable = [&](int n) { return n * n <= 32 * NT; };
-        if (in_round > rem && !countable(in_round)) {
+        if (in_round <= rem || countable(in_round)) {
+            int base = __builtin_amdgcn_readfirstlane(base0);
+            for (int j0 = 64 * wave; j0 < cur && own != 0; j0 += NT) {
+                const int j = j0 + lane, jc = j < cur ? j : cur - 1;
+                const unsigned v = vbits[jc];
+                const unsigned long long mask = __ballot(v > hbits && j < cur);
+                if (v > hbits && j < cur) cand[base + before(mask)] = ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j;
+                base += __popcll(mask);
+            }
+            __syncthreads();
+        } else {
             // the rem smallest keys: find the largest of them
             unsigned long long prefix = 0;       // digits fixed so far
             int need = rem;
@@ -284,9 +298,18 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 }
                 shift = shift >= 12 ? shift - 8 : 0;
             }
-            if (tid == 0) sc.count = 0;
-            __syncthreads();
-            gather(cut);
+            for (int j0 = 64 * wave; j0 < cur && own != 0; j0 += NT) {
+                const int j = j0 + lane, jc = j < cur ? j : cur - 1;
+                const unsigned v = vbits[jc];
+                const unsigned long long k = ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j;
+                const bool in = v > hbits && j < cur && k <= cut;
+                const unsigned long long mask = __ballot(in);
+                if (mask == 0) continue;
+                unsigned base = 0;
+                if (lane == 0) base = atomicAdd(&sc.count, (unsigned)__popcll(mask));
+                base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
+                if (in) cand[(int)base + before(mask)] = k;
+            }
             __syncthreads();
         }
         const int take = in_round < rem ? in_round : rem;
