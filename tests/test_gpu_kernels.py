@@ -1766,6 +1766,42 @@ def test_forward_of_short_rows_per_batch(M, C, g, s, N, ld_extra, clip):
     _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0, route=3))
 
 
+# Code rows with more padding than asked for (pieces past the image are zeros), a base of X that is aligned to nothing but a float, and
+# replays from a graph with the input changing between them.
+@pytest.mark.parametrize("M,C,g,s,N,ldq_extra", [(65, 64, 1, 4, 64, 48), (130, 3, 49, 1, 64, 48), (40, 100, 1, 5, 70, 16), (70, 8, 1, 1, 20, 48)])
+def test_forward_of_short_rows_with_longer_pitches(M, C, g, s, N, ldq_extra):
+    _rows(1, lambda: _forward_once(M, C, g, s, N, 0, 2.5, 1.0, 0, ldq_extra=ldq_extra, route=3))
+
+
+@pytest.mark.parametrize("static", [True, False])
+def test_forward_of_short_rows_replays_from_a_graph(static):
+    from paper_1901_09504_amd.layer import ExpandedLayer
+    M, K, N = 20011, 100, 60
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    L = ExpandedLayer(N, K, 1, 0.05, 6, 8, max_rows=M)
+    L.prepare_weights(torch.randn((N, K), device="cuda", generator=gen))
+    X = torch.randn(M * K + 1, device="cuda", generator=gen)[1:].view(M, K)
+    th = torch.tensor([2.0], device="cuda") if static else None
+    acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    assert B.ocs_forward_one_launch(M, K, 1, K, L.s, L.ldq, L.ldq, N, captured=True, X=X) == 3
+    L.forward(X, th, acc_out=acc)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        L.forward(X, th, acc_out=acc)
+    for rep in range(4):
+        X.normal_(generator=gen)
+        X[rep, 3 * rep] = -9.0 - rep
+        L.Xq.fill_(77)
+        acc.fill_(-1)
+        graph.replay()
+        got = [t.clone() for t in (L.Y[:M], L.Xq[:M], L.scale_x, acc)]
+        _rows(0, lambda: L.forward(X, th, acc_out=acc))          # the two launches
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, (L.Y[:M], L.Xq[:M], L.scale_x, acc)))
+        assert static or float(got[2][0]) == 9.0 + rep
+
+
 # The first layer of a chain as one call against its two calls, all outputs bit for bit: the one launch (pixels around a workgroup's 64,
 # code rows of one to five steps, outputs around 32, 64 and 128, copies for the next layer: none, a few, more than outputs; padding of
 # the next layer's codes) and what stays with the two (3x3, stride 2, an output wider than 128, outputs on top of an input).
