@@ -1817,9 +1817,10 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 // quantize, are level or behind.  128 rows with the weights two steps ahead stay where they are one round and K is short.
 // The copies of the split channels are moved byte by byte, by the wave that quantizes their rows, into the steps that follow X's
 // whole ones (`tail`), next to the columns left over after those; the tail is multiplied last.
-// Bounded by what the compute units draw from memory: X, codes and outputs at 4.5 TB/s (25088 x 1024 -> 256 40.5 -> 34.7 us for
-// the layer), 4.9 (50176 x 2304 -> 256 150 -> 135), 5.5 behind a max|X| pass that left X in the last-level cache (50176 x 1024 ->
-// 256 99 -> 88 with that pass); with X's requests switched off 25 us of the first remain, with the weights' 36.
+// Bounded by what the compute units draw from memory: X, codes and outputs at 4.7 TB/s (25088 x 1024 -> 256 40.5 us as two launches,
+// 34.3 with the weights one step ahead, 33.1), 4.6 (12544 x 2304 -> 256 37.1 -> 34), 5.8 behind a max|X| pass that left X in the last-level
+// cache (the same per batch 57.5 -> 45.0 with that pass).  12544 x 2304 -> 256, 34.0 us in a graph: 32.5 without the products, 30.1
+// without the weights' requests, 28.2 without the stores of the codes, 23.2 without X's requests.
 // ---------------------------------------------------------------------------------------------
 struct PanelLayer {
     const float* X;
