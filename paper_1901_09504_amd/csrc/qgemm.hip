@@ -2274,7 +2274,7 @@ struct RowsLayer {
     int64_t ldy;
     int steps;                                      // 32-byte steps of a row
     unsigned magic_qc, magic_td, magic_pc;          // floor(2^32 / n): X's dwords, a tail's dwords, a code row's pieces
-    int w_off, tab_off, dup_off;
+    int w_off, tab_off, dup_off, red_off;
 };
 
 
@@ -2295,8 +2295,9 @@ __device__ __forceinline__ int rows_swz(int r, int piece) { return ((piece ^ (r 
 template <int BN, int U, bool RQ>
 __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p, Requant rq) {
     constexpr int BM = kRowsBM, NT = kRowsNT, NW = NT / 64, WN = BN / 2, TN = WN / 32, STEP = kRowsStep;
+    // (no static LDS: beside a block aligned to 1024 bytes it takes as many)
     extern __shared__ __align__(1024) int8_t rlds[];
-    __shared__ float red[NW];
+    float* red = reinterpret_cast<float*>(rlds + p.red_off);
     int* tab = reinterpret_cast<int*>(rlds + p.tab_off);
     int* dup_list = reinterpret_cast<int*>(rlds + p.dup_off);     // only with copies to write
     int* dup_count = dup_list + kDupCap;
@@ -2436,22 +2437,24 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p, Requan
                             p.ldacc, rq, inv_next, dup_list, dup_n, RQ && wn == 0, row0 + BM <= p.M && BN <= p.N);
 }
 
-// Dynamic LDS of a launch: the image and the weights (or the epilogue's stage), the table of the tail's sources, the list of the next
-// layer's copies.  p (may be null) receives the offsets.
+// LDS of a launch: the image and the weights (or the epilogue's stage), the table of the tail's sources, the list of the next
+// layer's copies, a word per wave for the maxima.  p (may be null) receives the offsets.
 template <int BN, bool RQ>
 static int64_t rows_layer_lds(int64_t K, int64_t steps, int s_next, RowsLayer* p) {
     const int64_t w = round_up(steps * kRowsStep, 1024), operands = w + (steps + 1) / 2 * BN * 64;
     const int64_t staging = (kRowsNT / 64) * stage_bytes<RQ, BN / 2, 8>();
     const int64_t tab = round_up(operands > staging ? operands : staging, 16), dup = tab + 16 * (steps * 8 - K / 4);
     const bool list = RQ && s_next > 0;
+    const int64_t red = dup + (list ? (kDupCap + 1) * 4 : 0);
     if (p != nullptr) {
         p->w_off = (int)w;
         p->tab_off = (int)tab;
         p->dup_off = list ? (int)dup : 0;
+        p->red_off = (int)red;
     }
-    return dup + (list ? (kDupCap + 1) * 4 : 0);
+    return red + (kRowsNT / 64) * 4;
 }
-constexpr int64_t kRowsMaxLds = 65536 - 64;                       // (what no kernel has to opt into, less what is not dynamic)
+constexpr int64_t kRowsMaxLds = 65536;                            // (what no kernel has to opt into)
 
 template <int BN, int U, bool RQ>
 static hipError_t run_rows(RowsLayer p, const Requant& rq, hipStream_t stream) {

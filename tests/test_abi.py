@@ -3,12 +3,15 @@ include/ocs.h declares, and rejects bad arguments before any device work."""
 import ctypes as C
 import os
 import re
+import struct
 
+import msgpack
 import numpy as np
 import pytest
 
 from oracle import ref
 from paper_1901_09504_amd import binding as B
+from paper_1901_09504_amd.build import LIB
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -27,6 +30,24 @@ def test_every_declared_symbol_is_exported():
     for n in names:
         assert hasattr(L, n), n
         assert hasattr(B, n) or n in ("ocs_strerror", "ocs_last_hip_error"), f"binding lacks {n}"
+
+
+def _kernels():
+    """What the compiler noted about every kernel of the built library: the AMDGPU metadata notes of its code objects."""
+    data, at, kernels = open(LIB, "rb").read(), 0, []
+    while (at := data.find(b"AMDGPU\0\0", at)) >= 0:
+        name, size, kind = struct.unpack_from("<III", data, at - 12)
+        if (name, kind) == (7, 32):
+            kernels += msgpack.unpackb(data[at + 8:at + 8 + size])["amdhsa.kernels"]
+        at += 8
+    return kernels
+
+
+# Kernels whose launches are sized to the last byte of 64 KB, or of a share of a compute unit's 160: all their LDS is the launch's.
+@pytest.mark.parametrize("family", ["rows_layer_kernel", "panel_layer_kernel", "qgemm_wholek_kernel"])
+def test_kernels_sized_by_the_launch_have_no_lds_of_their_own(family):
+    sizes = [k[".group_segment_fixed_size"] for k in _kernels() if family in k[".name"]]
+    assert sizes and set(sizes) == {0}
 
 
 def test_num_splits_matches_oracle_everywhere():

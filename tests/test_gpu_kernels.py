@@ -1803,12 +1803,13 @@ def test_forward_of_short_rows_replays_from_a_graph(static):
 
 
 # The first layer of a chain as one call against its two calls, all outputs bit for bit: the one launch (pixels around a workgroup's 64,
-# code rows of one to five steps, outputs around 32, 64 and 128, copies for the next layer: none, a few, more than outputs; padding of
+# code rows of one to five steps of 64, the longest with as much beside them as 64 KB of LDS hold; outputs around 32, 64 and 128, copies
+# for the next layer: none, a few, more than outputs; padding of
 # the next layer's codes) and what stays with the two (3x3, stride 2, an output wider than 128, outputs on top of an input).
 @pytest.mark.parametrize("Bn,H,W,C,s,k,stride,N,s_next,bits_next,threshold", [
     (1, 1, 1, 4, 0, 1, 1, 1, 0, 8, 2.5), (1, 7, 9, 5, 3, 1, 1, 33, 2, 8, 2.5), (1, 8, 8, 64, 4, 1, 1, 64, 4, 4, 2.5), (3, 13, 5, 256, 13, 1, 1, 64, 4, 8, 2.5),
     (2, 9, 9, 256, 13, 1, 1, 64, 4, 8, None), (1, 20, 7, 100, 5, 1, 1, 100, 30, 8, 2.5), (2, 8, 8, 250, 12, 1, 1, 128, 7, 6, 2.5), (1, 16, 9, 30, 200, 1, 1, 65, 400, 8, 2.5),
-    (1, 10, 10, 64, 4, 1, 1, 129, 5, 8, 2.5), (2, 8, 8, 64, 4, 1, 2, 64, 4, 8, 2.5), (1, 12, 12, 32, 2, 3, 1, 64, 4, 8, None)])
+    (2, 10, 7, 300, 15, 1, 1, 128, 7, 8, 2.5), (1, 9, 9, 100, 200, 1, 1, 100, 5, 8, None), (1, 10, 10, 64, 4, 1, 1, 129, 5, 8, 2.5), (2, 8, 8, 64, 4, 1, 2, 64, 4, 8, 2.5), (1, 12, 12, 32, 2, 3, 1, 64, 4, 8, None)])
 def test_first_layer_of_a_chain_as_one_call(Bn, H, W, C, s, k, stride, N, s_next, bits_next, threshold):
     gen = torch.Generator(device="cuda").manual_seed(C + N)
     pad, E, M = k // 2, C + s, Bn * H * W
