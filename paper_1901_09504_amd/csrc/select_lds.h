@@ -179,11 +179,13 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                                               unsigned long long* cand, GreedyScratch& sc, int C, int s,
                                               int32_t* split_src) {
     static_assert(NT % 64 == 0 && NT / 64 <= 16 && NT >= kGreedyBins, "waves of the workgroup");
+    static_assert(kMaxExpanded <= 32 * NT, "pieces of the list");
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (what depends on it alone stays in scalar registers)
     const unsigned* vbits = reinterpret_cast<const unsigned*>(vals);
     if (s <= 0) return;
     unsigned m = 0;
+    if (tid == 0) sc.count = 0;
     for (int j = tid; j < C; j += NT) m = vbits[j] > m ? vbits[j] : m;
     unsigned mbits = group_umax<NT>(m, sc.red);
     int cur = C, rem = s;
@@ -212,29 +214,25 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
             __syncthreads();
             return;
         }
-        auto key_of = [&](int j) {
-            return ((unsigned long long)(mbits - vbits[j]) << 13) | (unsigned long long)j;
-        };
+        auto key_of = [&](unsigned v, int j) { return ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j; };
         // The round's entries, in no order yet.  Sixteen waves on four SIMDs: what a walk over the list costs is its instructions, so
         // each wave counts its own first (a look-up and a comparison per entry), and keys are made of those only that take
-        // part: of all where the round is not cut, behind the waves' counts, else of the ones up to the bound found first (one
-        // LDS atomic per wave; `count` is cleared ahead of a barrier that precedes them).
-        unsigned own = 0;
-        for (int j0 = 64 * wave; j0 < cur; j0 += NT) {
+        // part: of all where the round is not cut, from the place on that the wave's count has in `count`, else of the ones up to the
+        // bound found first.  `some`: the pieces of the list (kMaxExpanded entries are at most 32 of NT) in which this wave has an
+        // entry; most rounds of a list with outliers have a few entries, and the second walk is as long as those (1024 channels, 103
+        // splits, the preparation in a graph 13.4 -> 13.15 us against a whole second walk; one walk that makes keys on its way: 13.1, but
+        // 3000 channels 15.3 -> 15.95).  `count` is cleared ahead of a barrier that precedes its use.
+        unsigned own = 0, some = 0, bit = 1;
+        for (int j0 = 64 * wave; j0 < cur; j0 += NT, bit <<= 1) {
             const int j = j0 + lane;
-            own += (unsigned)__popcll(__ballot(vbits[j < cur ? j : cur - 1] > hbits && j < cur));
+            const unsigned long long mask = __ballot(vbits[j < cur ? j : cur - 1] > hbits && j < cur);
+            own += (unsigned)__popcll(mask);
+            some |= mask != 0 ? bit : 0;
         }
-        if (lane == 0) sc.red[wave] = own;
-        if (tid == 0) sc.count = 0;
+        unsigned base0 = 0;
+        if (own != 0 && lane == 0) base0 = atomicAdd(&sc.count, own);
         __syncthreads();
-        int in_round = 0, base0 = 0;
-#pragma unroll
-        for (int w = 0; w < NT / 64; ++w) {
-            const int n = (int)sc.red[w];
-            base0 += w < wave ? n : 0;
-            in_round += n;
-        }
-        in_round = __builtin_amdgcn_readfirstlane(in_round);
+        int in_round = __builtin_amdgcn_readfirstlane((int)sc.count);
         auto before = [&](unsigned long long mask) {
             return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
         };
@@ -242,12 +240,12 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
         // look-ups)
         auto countable = [&](int n) { return n * n <= 32 * NT; };
         if (in_round <= rem || countable(in_round)) {
-            int base = __builtin_amdgcn_readfirstlane(base0);
-            for (int j0 = 64 * wave; j0 < cur && own != 0; j0 += NT) {
-                const int j = j0 + lane, jc = j < cur ? j : cur - 1;
+            int base = __builtin_amdgcn_readfirstlane((int)base0);
+            for (; some != 0; some &= some - 1) {
+                const int j = (__ffs((int)some) - 1) * NT + 64 * wave + lane, jc = j < cur ? j : cur - 1;
                 const unsigned v = vbits[jc];
                 const unsigned long long mask = __ballot(v > hbits && j < cur);
-                if (v > hbits && j < cur) cand[base + before(mask)] = ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j;
+                if (v > hbits && j < cur) cand[base + before(mask)] = key_of(v, j);
                 base += __popcll(mask);
             }
             __syncthreads();
@@ -262,11 +260,13 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 if (tid < kGreedyBins) sc.hist[tid] = 0;
                 __syncthreads();
                 for (int j = tid; j < cur; j += NT) {
-                    if (vbits[j] <= hbits) continue;
-                    const unsigned long long k = key_of(j);
+                    const unsigned v = vbits[j];
+                    if (v <= hbits) continue;
+                    const unsigned long long k = key_of(v, j);
                     if ((k >> (shift + width)) == prefix) atomicAdd(&sc.hist[(unsigned)(k >> shift) & ((1u << width) - 1u)], 1u);
                 }
                 __syncthreads();
+                if (tid == 0) sc.count = 0;
                 if (tid < 64) {                  // first bin at which the running count reaches `need`
                     unsigned h4[4], sum = 0;
 #pragma unroll
@@ -298,10 +298,10 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 }
                 shift = shift >= 12 ? shift - 8 : 0;
             }
-            for (int j0 = 64 * wave; j0 < cur && own != 0; j0 += NT) {
-                const int j = j0 + lane, jc = j < cur ? j : cur - 1;
+            for (; some != 0; some &= some - 1) {
+                const int j = (__ffs((int)some) - 1) * NT + 64 * wave + lane, jc = j < cur ? j : cur - 1;
                 const unsigned v = vbits[jc];
-                const unsigned long long k = ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j;
+                const unsigned long long k = key_of(v, j);
                 const bool in = v > hbits && j < cur && k <= cut;
                 const unsigned long long mask = __ballot(in);
                 if (mask == 0) continue;
@@ -312,6 +312,7 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
             }
             __syncthreads();
         }
+        if (tid == 0) sc.count = 0;
         const int take = in_round < rem ? in_round : rem;
         // rank of every entry of the round = how many keys are smaller; G lanes share one entry's count
         int log2_G = 0;

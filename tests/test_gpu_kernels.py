@@ -164,6 +164,12 @@ def _maxima(kind, C, rng):
         m = np.exp(rng.uniform(-3, 3, C)).astype(np.float32)
         m[[C // 3, C - 1]] = np.inf
         return m
+    if kind == "outliers":                    # short rounds of a few entries anywhere in the list, then long ones
+        m = rng.uniform(0.6, 1.0, C).astype(np.float32)
+        at = rng.permutation(C)[:max(1, C // 100)]
+        m[at] *= np.exp2(rng.integers(0, 9, len(at))).astype(np.float32)
+        m[C - 1] = 700.0
+        return m
     if kind == "denormal":                    # halving rounds, then reaches zero
         return (rng.integers(0, 9, C) * 1.4e-45).astype(np.float32)
     return np.exp(rng.uniform(-12, 12, C)).astype(np.float32)
@@ -171,7 +177,7 @@ def _maxima(kind, C, rng):
 
 @pytest.mark.parametrize("C,s", [(1, 1), (1, 40), (7, 6), (256, 1), (256, 255), (256, 256), (300, 301), (1100, 37),
                                  (4000, 4000), (7000, 600), (7999, 1)])
-@pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread", "infinite"])
+@pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread", "infinite", "outliers"])
 def test_select_rounds(C, s, kind):
     """Rounds cut at every digit of the sort key, rounds that end in zeros or never leave an infinite channel, the largest list."""
     m = _maxima(kind, C, np.random.default_rng(C + s))
