@@ -560,9 +560,9 @@ static ForwardRoute forward_route(const float* X, int64_t M, int C, int g, int64
     const SliceLayerPays few = slice_layer_pays(M, C, g, s, N, ldx);
     if (few.captured) *in_graph = ForwardRoute::few_tiles;
     if (few.launched) return ForwardRoute::few_tiles;
-    if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) *in_graph = ForwardRoute::many_rows;
-    else if (rows_layer_pays(M, C, g, s, ldq, N)) *in_graph = ForwardRoute::short_rows;
-    return *in_graph;
+    if (panel_layer_pays(X, ldx, M, C, g, s, ldq, ldw, N)) return *in_graph = ForwardRoute::many_rows;
+    if (rows_layer_pays(M, C, g, s, ldq, N, true)) *in_graph = ForwardRoute::short_rows;
+    return rows_layer_pays(M, C, g, s, ldq, N, false) ? ForwardRoute::short_rows : *in_graph;
 }
 
 int ocs_forward_one_launch(const float* X, int64_t M, int C, int g, int64_t ldx, int num_splits, int64_t ldq, int64_t ldw,
@@ -874,7 +874,7 @@ int ocs_conv_forward_requant(const float* A, int B, int H, int W, int C, const i
     const Requant rq = make_requant(relu, next_threshold, next_bits, next_chan_src, next_splits, Yq, ldyq, next_scale_out);
     const Tuning& tn = tuning();
     const bool forced = tn.gemm_tile >= 0 || tn.act_np >= 0 || tn.act_tile >= 0 || tn.act_map >= 0 || tn.act_grid > 0;
-    if (!forced && kh == 1 && kw == 1 && stride == 1 && pad == 0 && rows_layer_pays(M, C, 1, num_splits, ldc, N, rq)) {
+    if (!forced && kh == 1 && kw == 1 && stride == 1 && pad == 0 && rows_layer_pays(M, C, 1, num_splits, ldc, N, false, rq)) {
         // one launch: no output may share memory with an input (see ocs_forward), or with another output that the two calls
         // write one after the other
         struct Range { const void* at; int64_t bytes; };

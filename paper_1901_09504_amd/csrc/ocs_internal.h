@@ -196,7 +196,8 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
 
 // The layer of short code rows as one launch, codes included (csrc/qgemm.hip: rows_layer_kernel), its output as fp32 or as the next
 // layer's codes.  thr as above.
-bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, const Requant& rq = Requant{});
+// captured: in a stream that is being captured, where the launches cost the host nothing (with codes out the same either way).
+bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, bool captured, const Requant& rq = Requant{});
 hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
                              const float* thr, int n_max, float clip, float qmax, int8_t* Xq, int64_t ldq,
                              float* scale_x, const int8_t* Wq, int64_t ldw, int64_t N, const float* scale_w,

@@ -2495,24 +2495,49 @@ static bool rows_layer_fits(int64_t M, int C, int g, int s, int64_t ldq, int64_t
     if (N <= 128) return rows_layer_lds<128, false>(K, steps, 0, nullptr) <= kRowsMaxLds;
     return K <= 160 && rows_layer_lds<256, false>(K, steps, 0, nullptr) <= kRowsMaxLds;
 }
-// Where the one launch is ahead of the two (us, two / one; passes queued back to back, inputs rotating, static grid, copies 5 %):
-//   rows      from sixteen per compute unit on, where the layer of few tiles ends: 4100 x 100 -> 256 10.4 / 7.2 (in a graph 6.4 / 6.3),
-//             8200 x 300 -> 128 10.0 / 9.0 (9.9 / 8.8), 10000 x 64 -> 64 10.0 / 7.1 (6.6 / 4.8), 12544 x 147 -> 64 11.9 / 7.0 (12.0 / 6.8),
-//             25088 x 256 -> 64 13.1 / 11.1, 50176 x 300 -> 128 25.1 / 25.2, 50176 x 256 -> 128 22.7 / 23.3 (23.3 / 23.1; per batch
-//             30.9 / 30.5), 75000 33.5 / 29.7, 400000 161 / 131; 200000 x 300 -> 64 75.6 / 69.3; 400000 x 32 -> 16 26.0 / 21.2;
-//             50000 x 100 -> 100 15.2 / 11.4; 800000 x 64 -> 128 117.2 / 118.5
-//   outputs   more than 128 of them on many rows are a stream of writes, which a launch of its own keeps up best: 50000 x 64 -> 256
-//             18.0 / 16.7, 200000 51.4 / 48.7, 400000 94.8 / 95.7, 802816 179 / 188; 400000 x 48 -> 256 88.4 / 92.0; 800000 x 64 -> 160
-//             136 / 145.  The line: 2^26 values.
-bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, const Requant& rq) {
+// Where the one launch is ahead of the two: ranges of two / one in time at so many rows per compute unit, over passes queued back to back, the
+// same in a graph, and a graph on one input again, all with a static grid; in brackets passes queued with a per-batch grid.  Copies 5 % (1 and
+// 25 % alike).
+//   rows      from sixteen on, where the layer of few tiles ends.  Up to 128 outputs, 64 to 256 columns of X: 32 to 130 1.01-1.9 (1.01-1.34), 130 to
+//             400 0.97-1.75 (0.96-1.44), 784 to 10000 0.97-1.56 (1.01-1.42).
+//   columns   few columns at many rows: codes and outputs are all there is, and a workgroup's 64 rows are a few requests.  K = 4 to 20: 784
+//             1.02-1.48 (0.97-1.23), 1568 0.95-1.21 (0.93-1.12), 3136 0.85-1.24 (0.86-1.12), 6000 0.84-1.17 (0.79-1.12).  K = 24 to 56: 2200
+//             0.97-1.36 (1.04-1.26), 3136 0.95-1.33 (0.93-1.25), 4400 0.91-1.32 (0.81-1.30).  Codes of the next layer out: K = 4 to 20 784
+//             1.09-1.40 (1.01-1.29), 2200 0.93-1.20, 6000 0.84-1.15; 24 and more 0.98-1.48 (1.04-1.45).
+//   rounds    more than 256 columns leave a compute unit two workgroups, 128 rows a round.  Up to 64 outputs 125 1.21-1.56, 130 0.93-1.06
+//             (0.92-0.95), 140 0.96-1.15 (0.95-1.04), 150 0.98-1.12, 160 1.03-1.13.  Where the two launches' tiles come out even: 185
+//             1.09-1.22, 196 0.94-1.07 (0.94-1.03), 210 0.97-1.10 (0.98-1.03), 230 1.02-1.14; codes out and more than 64 outputs 196 1.04-1.10.
+//   outputs   more than 128: rows of outputs that begin anywhere cost the two launches more than the one.  N % 4 != 0: 16 0.81-1.34, 24
+//             0.99-1.29, 49 and more 1.02-1.60 (1.01-1.53).  N % 4 == 0, passes queued: 16 to 49 1.04-1.48 (1.02-1.35); in a graph up to 128 code
+//             bytes 16 0.89-1.22 (up to 48 columns, or 64 and more than 192 outputs, 0.95-1.22), 24 0.96-1.16, 32 0.98-1.21; longer 16 0.81-0.97, 32
+//             0.92-1.08, 49 0.99-1.18.  From there on up to 128 code bytes 0.95-1.55 (1.00-1.52); longer and N % 16 == 0, whole lines that a
+//             launch of its own keeps up best, up to 240 outputs 64 to 128 1.05-1.34, 129 to 250 0.89-1.11 (0.89-1.07), more
+//             0.80-1.12; other N % 4 == 0 140 0.95-1.18 (0.92-1.09), 196 and more 1.03-1.40.  256 outputs 0.95-1.13 (1.00-1.12).
+//             More than 2^26 output values, us two / one: 802816 x 64 -> 256 179 / 188, 400000 x 48 -> 256 88.4 / 92.0, 800000 x 64 -> 160 136 / 145.
+//   codes     of the next layer out: up to 64 columns 16 1.02-1.45; 96 and 128 16 0.89-1.34, with more than 64 outputs 20 0.95-1.34, 32 1.00-1.30;
+//             more 32 0.93-1.61, 40 1.06-1.69 (1.01-1.30).
+bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, bool captured, const Requant& rq) {
     const int mode = tuning().rows_layer;
     if (mode == 0 || !rows_layer_fits(M, C, g, s, ldq, N, rq)) return false;
     if (mode > 0) return true;
-    const int64_t cus = compute_units();
-    // (codes out: 12544 x 256 -> 64 11.1 / 8.6, 50176 x 256 -> 128 28.1 / 25.6, 802816 x 64 -> 64 88.8 / 69.7, 4160 x 64 -> 128 7.1 / 6.8; half of
-    // the compute units without a workgroup, 8192 x 256 -> 128, 10.0 / 10.3)
-    if (rq.Yq != nullptr) return M >= ((int64_t)C * g <= 128 ? 16 : 48) * cus;
-    return M >= 16 * cus && (N <= 128 || M * N <= (int64_t)1 << 26);
+    const int64_t cus = compute_units(), K = (int64_t)C * g, Kexp = K + (int64_t)s * g;
+    const bool codes = rq.Yq != nullptr;
+    auto between = [&](int64_t lo, int64_t hi) { return M > lo * cus && M <= hi * cus; };
+    if (M > 784 * cus && K < 24) return false;
+    if (M > 2200 * cus && K < 64 && !codes) return false;
+    if (K > 256 && N <= 64 && between(128, 150)) return false;
+    if (K > 256 && (N <= 64 || !codes) && between(190, 215)) return false;
+    if (codes) return M >= (K > 128 ? 48 : (K > 64 && N > 64 ? 32 : 16)) * cus;
+    if (N <= 128) return M >= 16 * cus;
+    if (M * N > (int64_t)1 << 26) return false;
+    if (Kexp > 128 && N <= 240 && N % 4 == 0 && (between(128, 160) || (N % 16 == 0 && M > 128 * cus))) return false;
+    int64_t least = Kexp > 128 && N % 4 != 0 ? 24 : 16;
+    if (captured) {
+        if (N % 4 != 0) least = 24;
+        else if (Kexp > 128) least = 48;
+        else least = K <= 48 || (K <= 64 && N > 192) ? 16 : 32;
+    }
+    return M >= least * cus;
 }
 
 hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src, const float* thr,

@@ -298,6 +298,24 @@ def test_forward_of_short_rows_by_rows_and_outputs(C, g, s, N, inside, outside):
         assert B.ocs_forward_one_launch(M, C, g, C * g, s, ld, ld, N) != 3, M
 
 
+# Where the two launches are ahead among them: few columns at many rows; the start of a second round and an even number of the
+# other kernel's tiles with more than 256 columns; more than 128 outputs in whole lines or groups of four with more than 128 code bytes, and in
+# a graph with few rows.
+@pytest.mark.parametrize("C,s,N,rows,eager,captured", [
+    (23, 2, 64, 784 * 256, 3, 3), (23, 2, 64, 784 * 256 + 1, 0, 0), (24, 2, 64, 784 * 256 + 1, 3, 3), (24, 2, 64, 2200 * 256, 3, 3), (63, 4, 64, 2200 * 256 + 1, 0, 0),
+    (64, 4, 64, 2200 * 256 + 1, 3, 3), (257, 13, 64, 128 * 256, 3, 3), (257, 13, 64, 128 * 256 + 1, 0, 0), (257, 13, 64, 150 * 256 + 1, 3, 3),
+    (257, 13, 65, 140 * 256, 3, 3), (256, 13, 64, 140 * 256, 3, 3), (300, 15, 128, 190 * 256, 3, 3), (300, 15, 128, 190 * 256 + 1, 0, 0),
+    (300, 15, 128, 215 * 256 + 1, 3, 3), (256, 13, 128, 200 * 256, 3, 3), (128, 7, 160, 128 * 256, 3, 3), (128, 7, 160, 128 * 256 + 1, 0, 0), (128, 7, 160, 500 * 256, 0, 0),
+    (128, 7, 164, 128 * 256 + 1, 0, 0), (128, 7, 164, 160 * 256 + 1, 3, 3), (128, 7, 162, 140 * 256, 3, 3), (128, 7, 256, 500 * 256, 3, 3), (120, 6, 160, 500 * 256, 3, 3),
+    (128, 7, 160, 48 * 256, 3, 3), (128, 7, 160, 48 * 256 - 1, 3, 0), (120, 6, 160, 32 * 256, 3, 3), (120, 6, 160, 32 * 256 - 1, 3, 0), (48, 3, 160, 17 * 256, 3, 3),
+    (64, 4, 160, 17 * 256, 3, 0), (64, 4, 196, 17 * 256, 3, 3), (65, 4, 196, 17 * 256, 3, 0), (64, 4, 201, 23 * 256, 3, 0), (64, 4, 201, 24 * 256, 3, 3),
+    (128, 7, 201, 23 * 256, 0, 0), (128, 7, 201, 24 * 256, 3, 3)])
+def test_forward_of_short_rows_where_two_launches_are_ahead(C, s, N, rows, eager, captured):
+    ld = B.ocs_padded_cols(C + s)
+    assert B.ocs_forward_one_launch(rows, C, 1, C, s, ld, ld, N, captured=False) == eager
+    assert B.ocs_forward_one_launch(rows, C, 1, C, s, ld, ld, N, captured=True) == captured
+
+
 def test_forward_route_of_refused_shapes_and_forced_kernels():
     assert B.ocs_forward_one_launch(0, 64, 1, 64, 1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 63, 1, 128, 128, 64) == 0
     assert B.ocs_forward_one_launch(4, 64, 1, 64, -1, 128, 128, 64) == 0 and B.ocs_forward_one_launch(4, 64, 1, 64, 1, 128, 128, 0) == 0
