@@ -2204,33 +2204,33 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     return run_panel<64, 256, 8, 2, 4, 3>(p, stream);
 }
 
-// Where the one launch is ahead of the two (two launches / one; in a graph on inputs outside the caches, in a graph on the same input
-// again, passes one after the other with the inputs rotating; 16 to 256 outputs, copies 5 % of the channels unless stated):
-//   rows per compute unit, static grid, K = 512: 64 1.01 in passes; 80 1.16; 98 to 128 1.21-1.44, 1.05-1.26, 1.10-1.27; 130 1.06; 160 and 176
-//                1.15-1.26, 0.96-1.04, 1.02-1.11; 192 to 400 1.16-1.41, 0.94-1.08, 1.04-1.15.  K = 1024: 64 0.91; 98 to 128 1.20-1.33,
-//                0.97-1.07, 1.04-1.15; 160 and 176 1.11-1.28, 0.88-0.98, 0.95-1.09; 192 to 400 1.21-1.38, 0.91-1.17, 1.01-1.17.  K = 2304:
-//                64 0.80; 96 1.26-1.34, 0.93-1.00, 0.97-1.03; 98 to 128 1.25-1.35, 0.99-1.11, 1.00-1.09; 130 0.96; 192 to 400 1.18-1.29,
-//                1.04-1.17, 1.06-1.18.  K = 4608: 98 to 400 1.21-1.27, 1.10-1.20, 1.10-1.20; 9216: 1.20-1.27, 1.15-1.23, 1.15-1.23.  Per batch 1.04-1.26, 0.99-1.27, 1.02-1.26 from
-//                98 rows on.  A workgroup per compute unit and 128 rows of tile: with fewer than 98 rows, or in two rounds of less than
-//                three quarters of a tile, the weights are read again for too little.
-//   columns      N = 64: K = 192 1.09 in passes, 0.97 per batch at 98 rows and 0.87, 0.94 at 196; 256 1.10, 1.04 and 0.95, 0.98.  16 to 64
-//                outputs 1.01-1.41, 0.93-1.31, 1.00-1.26; 100 to 128 0.99-1.47, 0.91-1.35, 1.00-1.34; 192 and 256 0.99-1.42, 0.93-1.25, 1.00-1.26.
-//   copies       moved byte by byte: more than a fifth of the columns 0.96-1.17 in passes, a third to two thirds 0.80-1.09.
-//   whole lines  rows that begin inside one share it with their neighbour's last step, which reads it again: K = 400, N = 64 1.00, 0.94 at
-//                165 rows, K = 1000 0.96, 0.99.
-//   pitch        rows that do not follow each other: K = 384 and 512 0.85-1.29 in passes, K = 1024 1.00-1.16.
+// Where the one launch is ahead of the two: ranges of two / one in time over 64, 128 and 256 outputs, copies 5 % (2 % in 3x3 layers), static grid, passes
+// queued back to back with the inputs rotating and the same in a graph; "again": a graph on one input again; in brackets passes queued with a
+// per-batch grid.
+//   rows per compute unit, K = 384 to 640: 28 and 32 0.99-1.29, again 1.04-1.14 (0.99-1.11); 36 to 64 1.15-1.60, again 1.10-1.64
+//                (1.06-1.30); 66 and 80, a second round of a few rows, 0.96-1.07; 98 to 128 1.07-1.41, again 1.11-1.28 (1.04-1.22); 130 and 144
+//                1.06-1.19, again 0.98-1.10; 160 to 191 1.11-1.25, again 1.02-1.13; 192 to 400 1.11-1.33, again 1.00-1.20 (1.05-1.24).
+//                K = 768 to 1152: 36 1.00-1.25; 44 to 64 1.10-1.72, again 1.07-1.55 (1.09-1.49); 66 and 80 0.86-1.13, again 0.82-1.03; 96 0.96-1.18;
+//                98 to 128 1.02-1.43, again 0.98-1.18 (1.12-1.21); 130 and 144 0.97-1.16, again 0.91-1.05; 160 to 191 1.04-1.22, again
+//                0.98-1.12; 192 to 400 1.09-1.29, again 1.01-1.29 (1.06-1.29).
+//                K = 2304: 28 and 32 0.92-1.04; 36 1.00-1.14, again 0.96-1.10; 44 to 64 1.05-1.31, again 1.00-1.16 (1.11-1.28); 66 and 80
+//                0.86-1.03; 98 to 128 1.03-1.14, again 1.01-1.14 (1.15-1.25); 130 to 191 1.08-1.24; 192 to 400 1.17-1.24 (1.14-1.25).
+//                K = 3456 and 4608: 44 and 48 1.00-1.21, again up to 128 outputs 1.01-1.09, 256 0.93-0.99 (1.14-1.25); 52 to 64 1.06-1.29, again
+//                0.99-1.29; 98 to 300 1.15-1.28 (1.16-1.30).  K = 6912 and 9216: 40 to 200 1.15-1.35 (1.13-1.36).  (129 to 191 rows would
+//                gain with long K and lose with short: left to the two.)
+//   columns      K = 192: 48 and 64 1.20-1.44, 98 to 300 0.80-1.16 (0.90-1.09); 256 1.17-1.49, 0.89-1.19; 320 1.25-1.58, 0.95-1.23.
+//   copies       moved byte by byte: a quarter of the columns 1.02-1.50, again 0.93-1.50 (0.99-1.24); half 0.96-1.36, again 0.88-1.36
+//                (0.94-1.15).
+//   whole lines  rows that begin inside one share it with their neighbour's last step, which reads it again: K = 400, 98 rows and more 1.01-1.11
+//                (0.98-1.04), K = 1000 1.05-1.15, again 1.00-1.13.
+//   pitch        rows that do not follow each other (32 values between them): K = 384 and 512 1.07-1.58 (0.98-1.15), K = 1024 1.07-1.27
+//                (1.06-1.26).
 bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq, int64_t ldw, int64_t N) {
     const int mode = tuning().panel_layer;
     if (mode == 0 || !panel_fits(ldx, M, C, g, s, ldq, ldw, N)) return false;
     if (mode > 0) return true;
     const int64_t K = (int64_t)C * g, cus = compute_units();
-    // One round of 64-row tiles.  Two launches / one (passes one after the other, a graph, a graph on the same input again, per batch in
-    // a graph): K = 512, N = 64 to 256: 36 rows per compute unit 1.26-1.41, 1.22-1.36, 1.14-1.26, 1.12-1.20; 44 to 64 1.24-1.44, 1.17-1.41,
-    // 1.19-1.49, 1.07-1.27.  K = 1152: 36 1.02-1.14, 0.98-1.10, 0.94-1.09, 1.09-1.15; 44 1.10-1.23, 1.06-1.20, 0.99-1.14, 1.15-1.21; 48 to 64
-    // 1.16-1.37, 1.09-1.28, 1.05-1.22, 1.17-1.28.  K = 2304: 32 0.91-0.98 in a graph; 36 1.01-1.07, 1.00-1.06, 0.89-0.98, 1.07-1.13; 44 to
-    // 64 1.05-1.23, 1.03-1.13, 0.94-1.11, 1.10-1.24.  K = 4608: 44 1.01-1.07, 0.99-1.05, 0.90-0.96, 1.19-1.24; 52 to 64 1.04-1.20, 1.02-1.19,
-    // 0.99-1.22, 1.16-1.25.  In two rounds of 39 rows 0.90-1.17.
-    const bool one_round = M <= 64 * cus && M >= (K <= 640 ? 36 : 44) * cus;
+    const bool one_round = M <= 64 * cus && M >= (K <= 640 ? 36 : (K > 2304 && N > 128 ? 52 : 44)) * cus;      // (of 64-row tiles)
     if (K < 384 || K % 64 != 0 || ldx % 32 != 0 || reinterpret_cast<uintptr_t>(X) % 128 != 0) return false;
     if (5 * (int64_t)s * g > K || (ldx != K && K < 1024)) return false;
     return one_round || (M >= 98 * cus && M <= 128 * cus) || M >= 192 * cus;

@@ -264,10 +264,11 @@ def test_forward_of_many_rows_by_rows_and_copies(C, g, s, N, extra, inside, outs
         assert B.ocs_forward_one_launch(M, C, g, C * g + extra, s, ld, ld, N, X=1 << 20) == 0, M
 
 
-# One round of 64-row tiles: 44 to 64 rows per compute unit, from 36 on up to 640 columns; whole lines, few copies.
+# One round of 64-row tiles: 44 to 64 rows per compute unit, from 36 on up to 640 columns, from 52 on beyond 2304 with more than 128 outputs;
+# whole lines, few copies.
 @pytest.mark.parametrize("C,g,s,N,inside,outside", [
     (640, 1, 32, 64, (36 * 256, 64 * 256), (36 * 256 - 1, 64 * 256 + 1)), (704, 1, 35, 256, (44 * 256, 64 * 256), (44 * 256 - 1, 64 * 256 + 1)),
-    (256, 9, 6, 256, (12544,), ()), (512, 9, 26, 100, (12544,), ()), (512, 9, 26, 257, (), (12544,)), (400, 1, 20, 64, (), (12544,)),
+    (256, 9, 6, 256, (12544,), ()), (512, 9, 26, 100, (12544,), ()), (512, 9, 26, 129, (52 * 256, 64 * 256), (52 * 256 - 1, 12544)), (512, 9, 26, 128, (44 * 256,), ()), (512, 9, 26, 257, (), (12544,)), (400, 1, 20, 64, (), (12544,)),
     (320, 1, 16, 64, (), (12544,)), (512, 1, 103, 64, (), (12544,))])
 def test_forward_of_one_round_of_64_rows(C, g, s, N, inside, outside):
     ld = B.ocs_padded_cols((C + s) * g)
