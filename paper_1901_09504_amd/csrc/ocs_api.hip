@@ -417,7 +417,7 @@ static int check_split_act(const float* X, int64_t M, int C, int g, int64_t ldx,
 
 // The maxima a per-batch grid is folded from: *out[0 .. *n).
 static hipError_t per_batch_maxima(const float* X, int64_t M, int64_t K, int64_t ldx, void* workspace, hipStream_t st,
-                                   const float** out, int* n) {
+                                   const float** out, int* n, bool short_rows = false) {
     Workspace w = plan_workspace(M, K);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
     hipError_t e = launch_absmax_partials(X, M, K, ldx, partial, n, st);
@@ -428,7 +428,12 @@ static hipError_t per_batch_maxima(const float* X, int64_t M, int64_t K, int64_t
     // faster pass gains), and for the narrowest rows (5 million x 12 120 -> 114 us).  Other contiguous
     // tensors leave 256 that cost their workgroups less than a launch.
     const int64_t cap = (int64_t)(w.total - w.partial_off) / 4;
-    const bool fold = (*n > 256 || K < 24) && M * K >= ((int64_t)40 << 20);
+    // The one launch of short rows has a workgroup per 64 of them, each of which folds what it is given, and gains from 32 MB on, where
+    // it would be behind the two launches otherwise (rows at a pitch of 5 values more, the layer as two launches / as one with every
+    // workgroup folding / with the launch: 200704 x 140 -> 256 94.0 / 98.7 / 88.4 us, 100352 x 300 -> 64 67.8 / 71.1 / 64.4, 35840 x 256 -> 128
+    // 28.4 / 29.8 / 27.4; but 128000 x 64 -> 64 27.9 / 23.8 / 25.2).
+    const int64_t values = M * K, from = (int64_t)(short_rows ? 8 : 40) << 20;
+    const bool fold = (*n > 256 && values >= from) || (K < 24 && values >= ((int64_t)40 << 20));
     if (*n > 1 && *n < cap && (fold || tuning().max_flat == 2)) {   // (max_flat 2: always, for tests)
         e = launch_fold_max(partial, *n, partial + *n, st);
         if (e != hipSuccess) return e;
@@ -638,7 +643,7 @@ int ocs_forward(const float* X, int64_t M, int C, int g, int64_t ldx, const int3
         int n = 0;
         hipError_t e = hipSuccess;
         if (threshold == nullptr) {
-            e = per_batch_maxima(X, M, K, ldx, workspace, st, &thr, &n);
+            e = per_batch_maxima(X, M, K, ldx, workspace, st, &thr, &n, route == ForwardRoute::short_rows);
             if (e != hipSuccess) return hip_fail(e);
         }
         if (route == ForwardRoute::short_rows)

@@ -1765,9 +1765,9 @@ def test_forward_of_short_rows(M, C, g, s, N, ld_extra):
     _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, route=3))
 
 
-# Per-batch grids: a single maximum, 256 of them, the thousands of a strided tensor
+# Per-batch grids: a single maximum, 256 of them, the thousands of a strided tensor, those folded by a launch of their own (from 2^23 values on)
 @pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip", [
-    (1, 64, 1, 1, 5, 0, 1.0), (3000, 147, 1, 8, 64, 0, 0.9), (9000, 100, 1, 5, 70, 3, 0.8)])
+    (1, 64, 1, 1, 5, 0, 1.0), (3000, 147, 1, 8, 64, 0, 0.9), (9000, 100, 1, 5, 70, 3, 0.8), (83887, 100, 1, 5, 70, 3, 0.8)])
 def test_forward_of_short_rows_per_batch(M, C, g, s, N, ld_extra, clip):
     _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, None, clip, 0, route=3))
 
