@@ -1848,9 +1848,9 @@ struct PanelLayer {
 
 constexpr int kPanelMaxTail = 256;     // appended columns s*g
 constexpr int kPanelStep = 128;        // columns of a step: whole lines of codes
+constexpr int kPanelW = 3;             // steps of weight codes in LDS
 
-// WBUF: steps of weight codes in LDS.
-template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N, int WBUF>
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_kernel(PanelLayer p) {
     constexpr int NM = WAVES_M * WAVES_N;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
@@ -1911,13 +1911,13 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
         auto fetch_w = [&](int kt) {
             const int q = step_of(kt) * CPR + wpiece;
             const int8_t* base = p.Wq + (int64_t)q * 16;
-            const unsigned slot = w0 + (unsigned)((WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK));
+            const unsigned slot = w0 + (unsigned)(kt % kPanelW * (BN * BK));
 #pragma unroll
             for (int u = 0; u < LB; ++u) lds_dma16(q < w_end ? base + wsrc[u] : zero_chunk, slot + u * (NM * 1024));
         };
         auto first_weights = [&]() {
 #pragma unroll
-            for (int k = 0; k < WBUF - 1; ++k)
+            for (int k = 0; k < kPanelW - 1; ++k)
                 if (k < p.kall) fetch_w(k);
         };
         first_weights();
@@ -1935,11 +1935,11 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
             for (int kt = 0; kt < p.kall; ++kt) {
                 // this wave's part of the step's weight codes (behind them only those of later steps)
-                if (WBUF > 2 && kt + WBUF - 2 < p.kall) wait_vmcnt<(WBUF - 2) * LB>();
+                if (kt + kPanelW - 2 < p.kall) wait_vmcnt<(kPanelW - 2) * LB>();
                 else wait_vmcnt<0>();
                 step_barrier();
                 const int8_t* am = kt < p.kmain ? codes + (kt & 1) * (BM * BK) : tail + (kt - p.kmain) * (BM * BK);
-                const int8_t* wb = wring + (WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK);
+                const int8_t* wb = wring + kt % kPanelW * (BN * BK);
                 auto read_slice = [&](int ks) {
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
@@ -1954,7 +1954,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                 };
                 read_slice(0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (kt + WBUF - 1 < p.kall) fetch_w(kt + WBUF - 1);      // into the slot multiplied before this barrier
+                if (kt + kPanelW - 1 < p.kall) fetch_w(kt + kPanelW - 1);      // into the slot multiplied before this barrier
 #pragma unroll
                 for (int ks = 0; ks < BK / 32; ++ks) {
                     if (ks + 1 < BK / 32) read_slice(ks + 1);
@@ -2131,30 +2131,29 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
     }
 }
 
-template <int BM, int BN, int NQ, int WAVES_M, int WBUF>
+template <int BM, int BN, int NQ, int WAVES_M>
 static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
     constexpr int BK = kPanelStep;
-    const int64_t tail = (2 * BM + WBUF * BN) * BK, list = tail + tail_steps * BM * BK, end = list + NQ * kPanelMaxTail * 4;
-    // With three steps of weights or more the epilogue's stage is the last of their slots: the next tile's first steps go to the others,
-    // and that one is requested only behind a barrier that every wave reaches after its epilogue.
-    constexpr int STAGE = WAVES_M * 8 * BN * 4;
-    static_assert(WBUF == 2 || STAGE <= BN * BK, "the stage fits a step of weights");
+    const int64_t tail = (2 * BM + kPanelW * BN) * BK, list = tail + tail_steps * BM * BK, end = list + NQ * kPanelMaxTail * 4;
+    // The epilogue's stage is the last of the weights' slots: the next tile's first steps go to the others, and that one is requested
+    // only behind a barrier that every wave reaches after its epilogue.
+    static_assert(kPanelW >= 3 && WAVES_M * 8 * BN * 4 <= BN * BK, "the stage fits a slot that no first step goes to");
     if (p != nullptr) {
         p->tail_off = (int)tail;
         p->list_off = (int)list;
-        p->stage_off = (int)(WBUF > 2 ? tail - BN * BK : end);
+        p->stage_off = (int)(tail - BN * BK);
     }
-    return WBUF > 2 ? end : end + STAGE;
+    return end;
 }
 
-template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N, int WBUF>
+template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
 static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     constexpr int BK = kPanelStep;
     const int64_t K = (int64_t)p.C * p.g, Kexp = (int64_t)(p.C + p.s) * p.g;
     p.kmain = (int)(K / BK);
     p.kall = (int)ceil_div(Kexp, BK);
     p.rem = (int)(K - (int64_t)p.kmain * BK);
-    const int64_t o = panel_lds<BM, BN, NQ, WAVES_M, WBUF>(p.kall - p.kmain, &p);
+    const int64_t o = panel_lds<BM, BN, NQ, WAVES_M>(p.kall - p.kmain, &p);
     if (o > kWholeKMaxLds) return hipErrorInvalidValue;
     static std::atomic<bool> opted_in[kMaxDevices];
     int dev = 0;
@@ -2162,7 +2161,7 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
     if (!opted_in[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N, WBUF>),
+        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kWholeKMaxLds);
         if (e != hipSuccess) return e;
         opted_in[dev].store(true, std::memory_order_release);
@@ -2174,7 +2173,7 @@ static hipError_t run_panel(PanelLayer p, hipStream_t stream) {
     p.stride = (int)st;
     p.rpw = (int)ceil_div(st, NQ);
     p.tiles = (int)ceil_div(p.M, st);
-    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N, WBUF>,
+    return launch_kernel(kTimeGemm, panel_layer_kernel<BM, BN, NQ, WAVES_M, WAVES_N>,
                          dim3((unsigned)(p.tiles < slots ? p.tiles : slots)), dim3((NQ + WAVES_M * WAVES_N) * 64), (unsigned)o, stream, p);
 }
 
@@ -2194,14 +2193,14 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
-    if (N <= 64) return run_panel<64, 64, 8, 2, 2, 3>(p, stream);
-    if (N <= 128) return run_panel<64, 128, 8, 2, 4, 3>(p, stream);
+    if (N <= 64) return run_panel<64, 64, 8, 2, 2>(p, stream);
+    if (N <= 128) return run_panel<64, 128, 8, 2, 4>(p, stream);
     // (a round of 128 rows, not two of 64, where K is short: us, 128 / 64 rows a tile: 25088 x 384 -> 256 19.2 / 19.0, x 512 21.9 / 22.7, x 1024
     // 33.9 / 35.6, 30000 x 512 24.4 / 25.6, x 1024 37.9 / 39.8; x 2048 61.1 / 61.2, 30000 x 2048 76.1 / 69.0)
     const int64_t K = (int64_t)C * g, cus = compute_units();
     if (M > 64 * cus && M <= 128 * cus && K <= 1024 && ceil_div(K + (int64_t)s * g, kPanelStep) - K / kPanelStep <= 1)
-        return run_panel<128, 256, 8, 2, 4, 3>(p, stream);
-    return run_panel<64, 256, 8, 2, 4, 3>(p, stream);
+        return run_panel<128, 256, 8, 2, 4>(p, stream);
+    return run_panel<64, 256, 8, 2, 4>(p, stream);
 }
 
 // Where the one launch is ahead of the two: ranges of two / one in time over 64, 128 and 256 outputs, copies 5 % (2 % in 3x3 layers), static grid, passes
