@@ -1713,8 +1713,9 @@ def test_forward_route_of_many_rows(per, extra, C, g, N, ld, threshold):
         assert all(torch.equal(a, b) for a, b in zip(out[0], o))
 
 
-# One round of 64-row tiles and one of 128 (short K, more than 128 outputs), the weights' ring around its three slots (three to six
-# steps), two steps of the tail with either; against the two launches, bit for bit.
+# One round of 64-row tiles (with a step of the tail and with two) and one of 128 (the fifth: short K, more than 128 outputs, one step of
+# the tail, which begins where X's whole steps end), the weights' ring around its three slots (three to six steps); against the two
+# launches, bit for bit.
 @pytest.mark.parametrize("per,extra,C,g,N", [
     (36, 0, 384, 1, 256), (64, 0, 512, 1, 130), (44, 1, 704, 1, 64), (49, 0, 64, 9, 128), (127, 3, 384, 1, 256), (100, 0, 448, 1, 200), (98, 5, 1088, 1, 256)])
 @pytest.mark.parametrize("threshold", [3.0, None])
@@ -1735,6 +1736,41 @@ def test_forward_of_many_rows_by_64_and_128(per, extra, C, g, N, threshold):
         out.append((L.Xq.clone(), L.scale_x.clone(), acc, L.Y.clone()))
     for o in out[1:]:
         assert all(torch.equal(a, b) for a, b in zip(out[0], o))
+
+
+# The instance of 128-row tiles (64 to 128 rows per compute unit, up to 1024 columns, more than 128 outputs, one step of the tail), which
+# makes the copies behind the step's barrier: left-over columns of 1, 2, 63, 64 and 125 that share their step with the copies, no whole
+# step at all, a full last step, strided rows; the first two as the rule sends them there, the others forced.
+@pytest.mark.parametrize("M,C,g,s,N,ld_extra,mode", [
+    (98 * 256, 448, 1, 22, 200, 0, -1), (128 * 256, 960, 1, 48, 256, 0, -1), (98 * 256 + 5, 447, 1, 22, 129, 0, 1), (64 * 256 + 1, 65, 1, 63, 130, 0, 1),
+    (20000, 130, 1, 6, 255, 3, 1), (128 * 256, 1021, 1, 3, 256, 0, 1), (17001, 43, 9, 4, 192, 1, 1), (25088, 897, 1, 44, 256, 0, 1)])
+@pytest.mark.parametrize("threshold", [3.0, None])
+def test_forward_of_many_rows_by_128_with_left_over_columns(M, C, g, s, N, ld_extra, mode, threshold):
+    from paper_1901_09504_amd.layer import ExpandedLayer
+    K = C * g
+    gen = torch.Generator(device="cuda").manual_seed(M + C)
+    X = torch.randn((M, K + ld_extra), device="cuda", generator=gen)
+    L = ExpandedLayer(N, C, g, s / C, 6, 8, max_rows=M)
+    assert L.s == s and (K + s * g + 127) // 128 - K // 128 <= 1
+    L.prepare_weights(torch.randn((N, K), device="cuda", generator=gen))
+    th = None if threshold is None else torch.tensor([threshold], device="cuda")
+    out = []
+    for m in (0, mode):
+        acc = torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+        L.Xq.fill_(77)
+        L.scale_x.fill_(-1)
+
+        def forward():
+            assert B.ocs_forward_one_launch(M, C, g, K + ld_extra, L.s, L.ldq, L.ldq, N, X=X) == (2 if m else 0)
+            L.forward(X[:, :K], th, acc_out=acc)
+
+        B.ocs_tune("rows_layer", 0)
+        try:
+            _panel(m, forward)
+        finally:
+            B.ocs_tune("rows_layer", -1)
+        out.append((L.Xq.clone(), L.scale_x.clone(), acc, L.Y.clone()))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
 def test_forward_of_many_rows_over_its_own_input():
@@ -1808,10 +1844,80 @@ def test_forward_of_short_rows_replays_from_a_graph(static):
         assert static or float(got[2][0]) == 9.0 + rep
 
 
+def _bits(t):
+    return t.view(torch.int32) if t.dtype == torch.float32 else t
+
+
+# Infinities and NaN among X's whole groups, its left-over columns and the copied channels: what the two launches leave, bit for bit, and
+# the infinities of a static grid as its outermost codes.
+@pytest.mark.parametrize("values", [(float("inf"), float("-inf")), (float("nan"), float("inf"))])
+@pytest.mark.parametrize("threshold", [2.5, None])
+def test_forward_of_short_rows_of_infinities_and_nan(threshold, values):
+    M, C, s, N = 300, 99, 5, 60
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    X = torch.randn((M, C), device="cuda", generator=gen)
+    for i, (r, c) in enumerate([(0, 0), (1, 98), (63, 40), (64, 97), (200, 12), (299, 96), (299, 98)]):
+        X[r, c] = values[i % 2]
+    ld = B.ocs_padded_cols(C + s)
+    Wq = torch.randint(-15, 16, (N, ld), device="cuda", generator=gen, dtype=torch.int8)
+    Wq[:, C + s:] = 0
+    cs = torch.cat([torch.arange(C, dtype=torch.int32), torch.tensor([0, 98, 40, 98, 7], dtype=torch.int32)]).cuda()
+    th, sw = None if threshold is None else torch.tensor([threshold], device="cuda"), torch.tensor([1.5, 0.1], device="cuda")
+    out = []
+
+    def forward(route):
+        q, sx = torch.full((M, ld), 77, dtype=torch.int8, device="cuda"), torch.full((2,), -1.0, device="cuda")
+        Y, acc = torch.full((M, N), -1.0, device="cuda"), torch.full((M, N), 9, dtype=torch.int32, device="cuda")
+        B.ocs_tune("slice_layer", 0)
+        try:
+            assert B.ocs_forward_one_launch(M, C, 1, C, s, ld, ld, N, X=X) == route
+            B.ocs_forward(X, M, C, 1, C, cs, s, 8, th, 0.9, q, ld, sx, Wq, ld, N, 5, sw, acc, N, Y, N, B.alloc_workspace(M, C))
+        finally:
+            B.ocs_tune("slice_layer", -1)
+        out.append((q, sx, acc, Y))
+
+    _rows(0, lambda: forward(0))
+    _rows(1, lambda: forward(3))
+    assert all(torch.equal(_bits(a), _bits(b)) for a, b in zip(*out))
+    if threshold is not None:
+        at = X.isinf()
+        assert torch.equal(out[1][0][:, :C][at].float(), 127 * X[at].sign())
+
+
+@pytest.mark.parametrize("threshold", [2.5, None])
+def test_forward_of_short_rows_over_its_own_input(threshold):
+    """Y on top of X: the rule of outputs apart from inputs keeps the two launches, which have read X before any output is written."""
+    M, C, s, N = 300, 128, 6, 128
+    rng = np.random.default_rng(4)
+    X, W = _tensor(rng, M, C, "heavy"), _tensor(rng, N, C, "normal")
+    sp = ref.split_weights(W, C, 1, s)
+    ld = B.ocs_padded_cols(C + s)
+    Wq, sw = ref.quantize(sp["T_out"], 6, ldq=ld)
+    buf, Wd, cs, swd = dev(X), dev(Wq), dev(sp["chan_src"].astype(np.int32)), dev(sw)
+    q, sx = torch.full((M, ld), 77, dtype=torch.int8, device="cuda"), torch.empty(2, device="cuda")
+    th, ws = None if threshold is None else torch.tensor([threshold], device="cuda"), B.alloc_workspace(M, C)
+    ran = []
+
+    def forward():
+        B.ocs_forward(buf, M, C, 1, C, cs, s, 8, th, 1.0, q, ld, sx, Wd, ld, N, 6, swd, None, 0, buf, N, ws)
+
+    B.ocs_tune("slice_layer", 0)
+    try:
+        assert B.ocs_forward_one_launch(M, C, 1, C, s, ld, ld, N, X=buf) == 0
+        _rows(1, lambda: ran.extend(_launched(forward)))
+    finally:
+        B.ocs_tune("slice_layer", -1)
+    assert ran == [B.TIME_SPLIT_QUANTIZE, B.TIME_GEMM]
+    q_ref, sx_ref, _ = ref.split_act(X, C, 1, sp["chan_src"], None, s, 8, threshold=threshold, ldq=ld)
+    _, y_ref = ref.qgemm(q_ref, Wq, C + s, sx_ref[1], sw[1])
+    assert np.array_equal(host(q), q_ref)
+    assert_y_close(host(buf), y_ref)
+
+
 # The first layer of a chain as one call against its two calls, all outputs bit for bit: the one launch (pixels around a workgroup's 64,
 # code rows of one to five steps of 64, the longest with as much beside them as 64 KB of LDS hold; outputs around 32, 64 and 128, copies
 # for the next layer: none, a few, more than outputs; padding of
-# the next layer's codes) and what stays with the two (3x3, stride 2, an output wider than 128, outputs on top of an input).
+# the next layer's codes) and what stays with the two (3x3, stride 2, an output wider than 128).
 @pytest.mark.parametrize("Bn,H,W,C,s,k,stride,N,s_next,bits_next,threshold", [
     (1, 1, 1, 4, 0, 1, 1, 1, 0, 8, 2.5), (1, 7, 9, 5, 3, 1, 1, 33, 2, 8, 2.5), (1, 8, 8, 64, 4, 1, 1, 64, 4, 4, 2.5), (3, 13, 5, 256, 13, 1, 1, 64, 4, 8, 2.5),
     (2, 9, 9, 256, 13, 1, 1, 64, 4, 8, None), (1, 20, 7, 100, 5, 1, 1, 100, 30, 8, 2.5), (2, 8, 8, 250, 12, 1, 1, 128, 7, 6, 2.5), (1, 16, 9, 30, 200, 1, 1, 65, 400, 8, 2.5),
@@ -1849,6 +1955,76 @@ def test_first_layer_of_a_chain_as_one_call(Bn, H, W, C, s, k, stride, N, s_next
     assert all(torch.equal(a, b) for a, b in zip(want, got))
     _rows(1, lambda: got.extend(_launched(lambda: call(False))))
     assert (B.TIME_SPLIT_QUANTIZE not in got[5:]) == (k == 1 and stride == 1 and N <= 128)
+
+
+# Outputs on top of inputs, and a pair of scales that is an input of the second call (the first call's own output there, where the one
+# launch reads it as it comes): the two calls' kernels run and leave what they leave.  Every pair here is one that the two calls, one
+# after the other, leave a single result for.
+@pytest.mark.parametrize("over", ["Yq on A", "acc on A", "Yq on the workspace", "next scale on the threshold", "scale on the next threshold",
+                                  "scale on the weights' scale", "nothing"])
+def test_first_layer_of_a_chain_with_outputs_on_inputs(over):
+    Bn, H, W, C, s, N, s_next = 2, 9, 9, 64, 4, 64, 4
+    M, E = Bn * H * W, C + s
+    gen = torch.Generator(device="cuda").manual_seed(21)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    ldc, ldyq = B.ocs_padded_channels(E), B.ocs_padded_channels(N + s_next)
+    values = torch.randn((M, C), device="cuda", generator=gen)
+    Wt = torch.zeros((N + 1, B.ocs_conv_weight_cols(1, ldc)), dtype=torch.int8, device="cuda")
+    Wt[:N, :E] = torch.randint(-15, 16, (N, E), device="cuda", generator=gen, dtype=torch.int8)
+    cs = torch.cat([torch.arange(C, **i32), torch.randint(0, C, (s,), generator=gen, **i32)])
+    ns = torch.cat([torch.arange(N, **i32), torch.randint(0, N, (s_next,), generator=gen, **i32)])
+    per_batch = over == "Yq on the workspace"
+
+    def call(two):
+        A, ws = values.clone(), torch.zeros(max(B.alloc_workspace(M, C).numel(), M * ldyq), dtype=torch.uint8, device="cuda")
+        Aq, Yq = torch.full((M, ldc), 77, dtype=torch.int8, device="cuda"), torch.full((M, ldyq), 55, dtype=torch.int8, device="cuda")
+        acc, th = torch.full((M, N), 9, **i32), torch.tensor([2.5, 7.0], device="cuda")
+        sx, sn = torch.full((2,), -1.0, device="cuda"), torch.full((2,), -1.0, device="cuda")
+        sw, tn = torch.tensor([1.5, 0.01], device="cuda"), torch.tensor([3.0, 5.0], device="cuda")
+        if over == "Yq on A":
+            Yq = A.view(-1).view(torch.int8)[:M * ldyq].view(M, ldyq)
+        elif over == "acc on A":
+            acc = A.view(torch.int32)
+        elif per_batch:
+            Yq = ws.view(torch.int8)[:M * ldyq].view(M, ldyq)
+        elif over == "next scale on the threshold":
+            sn = th
+        elif over == "scale on the next threshold":
+            sx = tn
+        elif over == "scale on the weights' scale":
+            sx = sw
+        t = None if per_batch else th
+        if two:
+            B.ocs_split_act(A, M, C, 1, C, cs, None, s, 8, t, 1.0, Aq, ldc, sx, ws)
+            B.ocs_qconv_requant(Aq, ldc, Bn, H, W, E, 1, 1, 1, 0, Wt, N, 8, 5, sx, sw, True, tn, 8, ns, s_next, Yq, ldyq, sn, acc, N)
+        else:
+            B.ocs_conv_forward_requant(A, Bn, H, W, C, cs, s, 8, t, 1.0, Aq, ldc, sx, 1, 1, 1, 0, Wt, N, 5, sw, True, tn, 8, ns, s_next,
+                                       Yq, ldyq, sn, acc, N, ws)
+        return [x.clone() for x in (Aq, sx, Yq, sn, acc)]
+
+    want, got, ran = call(True), [], []
+    _rows(1, lambda: got.extend(call(False)))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    _rows(1, lambda: ran.extend(_launched(lambda: call(False))))
+    assert ran == ([] if over == "nothing" else [B.TIME_SPLIT_QUANTIZE]) + [B.TIME_GEMM]
+
+
+# Which of the two runs by itself, on both sides of each line: 16 rows per compute unit up to 64 columns, or 128 with up to 64 outputs; 32 up to 128
+# columns; 48 beyond; the start of a second round and an even number of the other kernel's tiles beyond 256; few columns at many rows.
+@pytest.mark.parametrize("C,N,inside,outside", [
+    (64, 128, (16 * 256,), (16 * 256 - 1,)), (128, 64, (16 * 256,), (16 * 256 - 1,)), (65, 65, (32 * 256,), (32 * 256 - 1,)),
+    (129, 64, (48 * 256,), (48 * 256 - 1,)), (257, 64, (128 * 256, 150 * 256 + 1), (128 * 256 + 1, 190 * 256 + 1)),
+    (23, 16, (784 * 256,), (784 * 256 + 1,)), (64, 129, (), (16 * 256,))])
+def test_first_layer_of_a_chain_by_rows(C, N, inside, outside):
+    from paper_1901_09504_amd.layer import ExpandedConv
+    gen = torch.Generator(device="cuda").manual_seed(C + N)
+    L, nxt = ExpandedConv(N, C, 1, 1, 1, 0, 0.05, 6, 8), ExpandedConv(8, N, 1, 1, 1, 0, 0.05, 6, 8)
+    L.prepare_weights(torch.randn((N, C), device="cuda", generator=gen))
+    nxt.prepare_weights(torch.randn((8, N), device="cuda", generator=gen))
+    th, tn = torch.tensor([2.5], device="cuda"), torch.tensor([3.0], device="cuda")
+    for M in inside + outside:
+        A = torch.randn((1, M, 1, C), device="cuda", generator=gen)
+        assert _launched(lambda: L.forward_to_codes(A, nxt, th, tn)) == ([] if M in inside else [B.TIME_SPLIT_QUANTIZE]) + [B.TIME_GEMM], M
 
 
 # ---- channel maxima in row blocks that the selector folds itself ------------------------------------
