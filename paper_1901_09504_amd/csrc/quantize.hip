@@ -1128,6 +1128,8 @@ hipError_t launch_expand_quantize(const float* X, int64_t ldx, int64_t M, int C,
     return err;
 }
 
+constexpr int kInlineHeld = 3;              // pieces of the longest list that is not taken step by step
+
 // The weight pass with the greedy selection of Sec. 3.4 in its prologue: W2 and W3 as one launch.
 // The selection needs only the column maxima (a few KB, already in memory) and a handful of
 // rounds on them, so every workgroup repeats it for itself in LDS, behind its first 16-byte fetch
@@ -1176,7 +1178,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
     fetch(o, cur, row, d);
 
     channel_maxima_to_lds<kThreads, BLOCKS>(colmax, blocks, C, g, vals, src, dep);
-    greedy_select<kThreads, FEW>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
+    greedy_select<kThreads, FEW, kInlineHeld>(vals, src, dep, cand, sc, C, s, first ? split_src : nullptr);
     unsigned m = 0;   // bit pattern of the largest entry (all entries are non-negative)
     for (int j = tid; j < E; j += kThreads) {
         if (first) {
@@ -1240,6 +1242,7 @@ __global__ __launch_bounds__(kThreads) void select_expand_quantize_kernel(
 // 15.7 against 16.1; 2048 x 1000 with 10 splits 22 against 19) or taken step by step, 32-bit item indices.
 bool select_expand_quantize_fits(int C, int s, int64_t N, int64_t ldq) {
     const int limit = tuning().sel_inline < 0 ? 64 : tuning().sel_inline;
+    static_assert(640 <= kInlineHeld * kThreads, "what its lanes hold");
     if ((C + s > 640 && !few_steps(C, s)) || s > limit || limit == 0) return false;
     return N * (ldq / 4) + 2 * 2048 * (int64_t)kThreads < ((int64_t)1 << 32);
 }

@@ -16,7 +16,7 @@ namespace ocs {
 // 3000 channels, 150 splits: 78 -> 11 us with the column maxima in the caches, 14 without, against one split per
 // step (0.2 us a step on one wave, 0.5 us on four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
 // taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
-template <int NT, bool FEW, bool BLOCKS>
+template <int NT, bool FEW, bool BLOCKS, int HELD>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ colmax, int C, int g, int s, int mode,
     const int32_t* split_in, int32_t* split_src,
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
     channel_maxima_to_lds<NT, BLOCKS>(colmax, blocks, C, g, vals, src, dep);
 
     if (mode == 0) {
-        greedy_select<NT, FEW>(vals, src, dep, cand, sc, C, s, split_src);
+        greedy_select<NT, FEW, HELD>(vals, src, dep, cand, sc, C, s, split_src);
     } else {
         if (tid == 0) {
             for (int i = 0; i < s; ++i) {
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(NT) void select_kernel(
 
 constexpr unsigned kSelectMaxLds = 128 * 1024;   // holds the list of kMaxExpanded channels
 
-template <int NT, bool FEW, bool BLOCKS>
+template <int NT, bool FEW, bool BLOCKS, int HELD>
 static hipError_t run_select(const float* colmax, int blocks, int C, int g, int s, int mode, const int32_t* split_in,
                              int32_t* split_src, int32_t* chan_src, int32_t* chan_depth, float* max_out,
                              float clip_ratio, float qmax, float* scale_out, hipStream_t stream) {
@@ -86,13 +86,13 @@ static hipError_t run_select(const float* colmax, int blocks, int C, int g, int 
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!opted_in[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT, FEW, BLOCKS>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<NT, FEW, BLOCKS, HELD>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectMaxLds);
             if (e != hipSuccess) return e;
             opted_in[dev].store(true, std::memory_order_release);
         }
     }
-    select_kernel<NT, FEW, BLOCKS><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
+    select_kernel<NT, FEW, BLOCKS, HELD><<<1, NT, lds, stream>>>(colmax, C, g, s, mode, split_in, split_src, chan_src, chan_depth,
                                               max_out, clip_ratio, qmax, scale_out, blocks);
     return hipGetLastError();
 }
@@ -104,10 +104,15 @@ hipError_t launch_select(const float* colmax, int blocks, int C, int g, int s, i
     // E = C + s <= kMaxExpanded is checked by the caller
     const bool few = mode == 0 && few_steps(C, s);
     const bool narrow = C + s <= 512 && (int64_t)C * g <= 1024 && (int64_t)blocks * C * g <= 8192;
-    const auto run = blocks > 1 ? (narrow ? (few ? run_select<256, true, true> : run_select<256, false, true>)
-                                          : (few ? run_select<1024, true, true> : run_select<1024, false, true>))
-                                : (narrow ? (few ? run_select<256, true, false> : run_select<256, false, false>)
-                                          : (few ? run_select<1024, true, false> : run_select<1024, false, false>));
+    static_assert(kMaxExpanded <= 8 * 1024, "pieces of the longest list");
+    auto instance = [&](auto blk) {
+        constexpr bool BLOCKS = decltype(blk)::value;
+        if (narrow) return few ? run_select<256, true, BLOCKS, 2> : run_select<256, false, BLOCKS, 2>;
+        if (few) return run_select<1024, true, BLOCKS, 2>;
+        if (C + s <= 2048) return run_select<1024, false, BLOCKS, 2>;
+        return C + s <= 4096 ? run_select<1024, false, BLOCKS, 4> : run_select<1024, false, BLOCKS, 8>;
+    };
+    const auto run = blocks > 1 ? instance(std::true_type()) : instance(std::false_type());
     return run(colmax, blocks, C, g, s, mode, split_in, split_src, chan_src, chan_depth, max_out, clip_ratio, qmax, scale_out,
                stream);
 }

@@ -85,7 +85,7 @@ constexpr int kGreedyBins = 256;
 struct GreedyScratch {
     unsigned hist[kGreedyBins];
     unsigned red[16];
-    unsigned count, bin, before, size;
+    unsigned count[2], bin, before, size;
 };
 // LDS of the list: the keys of a round's entries, the values, sources and depths (in this order).
 __host__ __device__ inline unsigned greedy_list_bytes(int E) { return (unsigned)E * 16u; }
@@ -174,21 +174,20 @@ __host__ __device__ inline bool few_steps(int C, int s) {
 //   round holds more entries than splits are left and too many to count over, a bound on the largest
 //   key that still takes part is found first, digit by digit (8 bits at a time, a histogram in LDS per
 //   digit) until few enough entries lie below it.
-template <int NT>
+//   HELD: the list is at most HELD pieces of NT entries.
+template <int NT, int HELD>
 __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, unsigned short* dep,
                                               unsigned long long* cand, GreedyScratch& sc, int C, int s,
                                               int32_t* split_src) {
     static_assert(NT % 64 == 0 && NT / 64 <= 16 && NT >= kGreedyBins, "waves of the workgroup");
-    static_assert(kMaxExpanded <= 32 * NT, "pieces of the list");
     const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (what depends on it alone stays in scalar registers)
     const unsigned* vbits = reinterpret_cast<const unsigned*>(vals);
     if (s <= 0) return;
     unsigned m = 0;
-    if (tid == 0) sc.count = 0;
+    if (tid == 0) sc.count[0] = 0;
     for (int j = tid; j < C; j += NT) m = vbits[j] > m ? vbits[j] : m;
     unsigned mbits = group_umax<NT>(m, sc.red);
-    int cur = C, rem = s;
+    int cur = C, rem = s, turn = 0;
     while (rem > 0) {
         const unsigned hbits = __float_as_uint(__uint_as_float(mbits) * 0.5f);
         if (!(mbits > hbits)) {
@@ -215,41 +214,47 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
             return;
         }
         auto key_of = [&](unsigned v, int j) { return ((unsigned long long)(mbits - v) << 13) | (unsigned long long)j; };
-        // The round's entries, in no order yet.  Sixteen waves on four SIMDs: what a walk over the list costs is its instructions, so
-        // each wave counts its own first (a look-up and a comparison per entry), and keys are made of those only that take
-        // part: of all where the round is not cut, from the place on that the wave's count has in `count`, else of the ones up to the
-        // bound found first.  `some`: the pieces of the list (kMaxExpanded entries are at most 32 of NT) in which this wave has an
-        // entry; most rounds of a list with outliers have a few entries, and the second walk is as long as those (1024 channels, 103
-        // splits, the preparation in a graph 13.4 -> 13.15 us against a whole second walk; one walk that makes keys on its way: 13.1, but
-        // 3000 channels 15.3 -> 15.95).  `count` is cleared ahead of a barrier that precedes its use.
-        unsigned own = 0, some = 0, bit = 1;
-        for (int j0 = 64 * wave; j0 < cur; j0 += NT, bit <<= 1) {
-            const int j = j0 + lane;
-            const unsigned long long mask = __ballot(vbits[j < cur ? j : cur - 1] > hbits && j < cur);
-            own += (unsigned)__popcll(mask);
-            some |= mask != 0 ? bit : 0;
-        }
-        unsigned base0 = 0;
-        if (own != 0 && lane == 0) base0 = atomicAdd(&sc.count, own);
-        __syncthreads();
-        int in_round = __builtin_amdgcn_readfirstlane((int)sc.count);
         auto before = [&](unsigned long long mask) {
             return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0));
         };
         // (counting costs in_round^2 / NT look-ups per lane, a digit three barriers: level at about 32
         // look-ups)
         auto countable = [&](int n) { return n * n <= 32 * NT; };
-        if (in_round <= rem || countable(in_round)) {
-            int base = __builtin_amdgcn_readfirstlane((int)base0);
-            for (; some != 0; some &= some - 1) {
-                const int j = (__ffs((int)some) - 1) * NT + 64 * wave + lane, jc = j < cur ? j : cur - 1;
-                const unsigned v = vbits[jc];
-                const unsigned long long mask = __ballot(v > hbits && j < cur);
-                if (v > hbits && j < cur) cand[base + before(mask)] = key_of(v, j);
-                base += __popcll(mask);
-            }
-            __syncthreads();
-        } else {
+        // The round's entries, in no order yet.  Sixteen waves on four SIMDs, once through code that no cache holds: what a round costs is its
+        // instructions, their fetches, and the trips to LDS that wait for each other.  A wave reads its part of the list once, a
+        // value a lane and piece, all on their way together, and keeps it for the round; it takes the places of all its entries
+        // with one LDS atomic, and makes their keys at once unless its own are too many for a round that is not cut.  Kernel alone in
+        // a graph, us, keys made piece by piece with an atomic each / counted first and read again / so: 2000 channels, 40 splits,
+        // heavy tails 12.1 / 12.6 / 11.3, 3700 x 185 16.2 / 15.5 / 14.6, 7000 x 350 27.2 / 26.7 / 24.5; 300 x 512 whole
+        // preparation, 26 splits, 12.5 / 11.8 / 11.5.  Instances for two, four and eight pieces: eight for all 8.7 -> 9.7 at 1024.
+        unsigned v[HELD], own = 0, first = 0;
+        unsigned long long mask[HELD];
+#pragma unroll
+        for (int q = 0; q < HELD; ++q) v[q] = vbits[q * NT + tid < cur ? q * NT + tid : cur - 1];
+#pragma unroll
+        for (int q = 0; q < HELD; ++q) {
+            mask[q] = __ballot(v[q] > hbits && q * NT + tid < cur);
+            own += (unsigned)__popcll(mask[q]);
+        }
+        // f(value, entries of this wave's piece, index) for every piece that has any
+        auto each = [&](auto&& f) {
+#pragma unroll
+            for (int q = 0; q < HELD; ++q)
+                if (mask[q] != 0) f(v[q], mask[q], q * NT + tid);
+        };
+        if (own != 0 && lane == 0) first = atomicAdd(&sc.count[turn], own);
+        if ((int)own <= rem || countable((int)own)) {
+            int base = __builtin_amdgcn_readfirstlane((int)first);
+            each([&](unsigned u, unsigned long long m, int j) {
+                if ((m >> lane) & 1) cand[base + before(m)] = key_of(u, j);
+                base += __popcll(m);
+            });
+        }
+        __syncthreads();
+        int in_round = __builtin_amdgcn_readfirstlane((int)sc.count[turn]);
+        turn ^= 1;
+        if (tid == 0) sc.count[turn] = 0;                        // (last read before the barrier that ended the round before)
+        if (in_round > rem && !countable(in_round)) {
             // the rem smallest keys: find the largest of them
             unsigned long long prefix = 0;       // digits fixed so far
             int need = rem;
@@ -259,14 +264,12 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 const int width = shift == 0 ? 4 : 8;
                 if (tid < kGreedyBins) sc.hist[tid] = 0;
                 __syncthreads();
-                for (int j = tid; j < cur; j += NT) {
-                    const unsigned v = vbits[j];
-                    if (v <= hbits) continue;
-                    const unsigned long long k = key_of(v, j);
-                    if ((k >> (shift + width)) == prefix) atomicAdd(&sc.hist[(unsigned)(k >> shift) & ((1u << width) - 1u)], 1u);
-                }
+                each([&](unsigned u, unsigned long long m, int j) {
+                    const unsigned long long k = key_of(u, j);
+                    if (((m >> lane) & 1) && (k >> (shift + width)) == prefix)
+                        atomicAdd(&sc.hist[(unsigned)(k >> shift) & ((1u << width) - 1u)], 1u);
+                });
                 __syncthreads();
-                if (tid == 0) sc.count = 0;
                 if (tid < 64) {                  // first bin at which the running count reaches `need`
                     unsigned h4[4], sum = 0;
 #pragma unroll
@@ -298,21 +301,15 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
                 }
                 shift = shift >= 12 ? shift - 8 : 0;
             }
-            for (; some != 0; some &= some - 1) {
-                const int j = (__ffs((int)some) - 1) * NT + 64 * wave + lane, jc = j < cur ? j : cur - 1;
-                const unsigned v = vbits[jc];
-                const unsigned long long k = key_of(v, j);
-                const bool in = v > hbits && j < cur && k <= cut;
-                const unsigned long long mask = __ballot(in);
-                if (mask == 0) continue;
+            each([&](unsigned u, unsigned long long m, int j) {
+                const unsigned long long k = key_of(u, j), in = __ballot(((m >> lane) & 1) && k <= cut);
                 unsigned base = 0;
-                if (lane == 0) base = atomicAdd(&sc.count, (unsigned)__popcll(mask));
+                if (lane == 0) base = atomicAdd(&sc.count[turn], (unsigned)__popcll(in));
                 base = (unsigned)__builtin_amdgcn_readfirstlane((int)base);
-                if (in) cand[(int)base + before(mask)] = k;
-            }
+                if ((in >> lane) & 1) cand[(int)base + before(in)] = k;
+            });
             __syncthreads();
         }
-        if (tid == 0) sc.count = 0;
         const int take = in_round < rem ? in_round : rem;
         // rank of every entry of the round = how many keys are smaller; G lanes share one entry's count
         int log2_G = 0;
@@ -352,7 +349,7 @@ __device__ __forceinline__ void greedy_rounds(float* vals, unsigned short* src, 
 
 // One or the other, as the launch says (FEW: few_steps holds), in instances of their own: the rounds' kernels stay what
 // they are without the steps' code.
-template <int NT, bool FEW>
+template <int NT, bool FEW, int HELD>
 __device__ __forceinline__ void greedy_select(float* vals, unsigned short* src, unsigned short* dep, unsigned long long* cand,
                                               GreedyScratch& sc, int C, int s, int32_t* split_src) {
     if constexpr (FEW) {
@@ -362,7 +359,7 @@ __device__ __forceinline__ void greedy_select(float* vals, unsigned short* src, 
         else if (C <= 640) greedy_few<10>(vals, src, dep, C, s, split_src);
         else greedy_few<16>(vals, src, dep, C, s, split_src);
     } else {
-        greedy_rounds<NT>(vals, src, dep, cand, sc, C, s, split_src);
+        greedy_rounds<NT, HELD>(vals, src, dep, cand, sc, C, s, split_src);
     }
 }
 

@@ -176,7 +176,7 @@ def _maxima(kind, C, rng):
 
 
 @pytest.mark.parametrize("C,s", [(1, 1), (1, 40), (7, 6), (256, 1), (256, 255), (256, 256), (300, 301), (1100, 37),
-                                 (4000, 4000), (7000, 600), (7999, 1)])
+                                 (4000, 4000), (7000, 600), (7999, 1), (500, 12), (500, 13), (2000, 48), (2000, 49), (4000, 96), (4000, 97)])
 @pytest.mark.parametrize("kind", ["equal", "last_digits", "octaves", "just_above_half", "denormal", "spread", "infinite", "outliers"])
 def test_select_rounds(C, s, kind):
     """Rounds cut at every digit of the sort key, rounds that end in zeros or never leave an infinite channel, the largest list."""
