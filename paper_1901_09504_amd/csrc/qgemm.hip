@@ -1810,15 +1810,15 @@ hipError_t launch_split_act_qgemm(const float* X, int64_t ldx, int64_t M, int C,
 // NQ waves only quantize: they hold no accumulators, so a step of 128 columns of X is on its way in their registers, each
 // register requested again as soon as it is read (with two steps they spill: 57 us).  Floats through LDS instead cost it as much
 // again as the fragments do (25088 x 1024 -> 256 39.8 us).  The other waves multiply, and request the weight codes straight
-// into LDS two steps ahead: neither kind waits for the other's memory, and a step costs one barrier.  A workgroup of 64 rows on
+// into LDS ahead of their step: neither kind waits for the other's memory, and a step costs one barrier.  A workgroup of 64 rows on
 // every compute unit; the next tile's first steps are requested before the last one's outputs are written.  Two steps of the weights, not
 // one, are what 64 rows need, whose steps are half as long as their way from the L2 (12544 x 2304 -> 256, static grid: two launches
 // 37.1 us, one step ahead 38.0, two 35.1, three 34.7; per batch 54.2, 52, 45.4); two steps of X, or half as many waves that
-// quantize, are level or behind.  128 rows with the weights two steps ahead stay where they are one round and K is short.
+// quantize, are level or behind.  Where K is short it is 128 rows and one step (launch_panel_layer).
 // The copies of the split channels are moved byte by byte, by the wave that quantizes their rows, into the steps that follow X's
 // whole ones (`tail`), next to the columns left over after those; the tail is multiplied last.
 // Bounded by what the compute units draw from memory: X, codes and outputs at 4.7 TB/s (25088 x 1024 -> 256 40.5 us as two launches,
-// 34.3 with the weights one step ahead, 33.1), 4.6 (12544 x 2304 -> 256 37.1 -> 34), 5.8 behind a max|X| pass that left X in the last-level
+// 32.7), 4.6 (12544 x 2304 -> 256 37.1 -> 34), 5.8 behind a max|X| pass that left X in the last-level
 // cache (the same per batch 57.5 -> 45.0 with that pass).  12544 x 2304 -> 256, 34.0 us in a graph: 32.5 without the products, 30.1
 // without the weights' requests, 28.2 without the stores of the codes, 23.2 without X's requests.
 // ---------------------------------------------------------------------------------------------
@@ -1848,11 +1848,12 @@ struct PanelLayer {
 
 constexpr int kPanelMaxTail = 256;     // appended columns s*g
 constexpr int kPanelStep = 128;        // columns of a step: whole lines of codes
-constexpr int kPanelW = 3;             // steps of weight codes in LDS
+// Steps of weight codes in LDS: 128 rows multiply for as long as a step is on its way (with three, 256 outputs 2-6 % behind, fewer level).
+constexpr int panel_wbuf(int BM) { return BM >= 128 ? 2 : 3; }
 
 template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_kernel(PanelLayer p) {
-    constexpr int NM = WAVES_M * WAVES_N;
+    constexpr int NM = WAVES_M * WAVES_N, WBUF = panel_wbuf(BM);
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
     constexpr int BK = kPanelStep, CPR = BK / 16, LG = 7;    // 16-byte pieces of a row of codes, BK = 1 << LG
     constexpr int LPR = BK / 4, RPL = 64 / LPR;              // X: lanes per row, rows per request
@@ -1911,13 +1912,13 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
         auto fetch_w = [&](int kt) {
             const int q = step_of(kt) * CPR + wpiece;
             const int8_t* base = p.Wq + (int64_t)q * 16;
-            const unsigned slot = w0 + (unsigned)(kt % kPanelW * (BN * BK));
+            const unsigned slot = w0 + (unsigned)((WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK));
 #pragma unroll
             for (int u = 0; u < LB; ++u) lds_dma16(q < w_end ? base + wsrc[u] : zero_chunk, slot + u * (NM * 1024));
         };
         auto first_weights = [&]() {
 #pragma unroll
-            for (int k = 0; k < kPanelW - 1; ++k)
+            for (int k = 0; k < WBUF - 1; ++k)
                 if (k < p.kall) fetch_w(k);
         };
         first_weights();
@@ -1935,11 +1936,11 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
             for (int kt = 0; kt < p.kall; ++kt) {
                 // this wave's part of the step's weight codes (behind them only those of later steps)
-                if (kt + kPanelW - 2 < p.kall) wait_vmcnt<(kPanelW - 2) * LB>();
+                if (WBUF > 2 && kt + WBUF - 2 < p.kall) wait_vmcnt<(WBUF - 2) * LB>();
                 else wait_vmcnt<0>();
                 step_barrier();
                 const int8_t* am = kt < p.kmain ? codes + (kt & 1) * (BM * BK) : tail + (kt - p.kmain) * (BM * BK);
-                const int8_t* wb = wring + kt % kPanelW * (BN * BK);
+                const int8_t* wb = wring + (WBUF == 2 ? kt & 1 : kt % WBUF) * (BN * BK);
                 auto read_slice = [&](int ks) {
 #pragma unroll
                     for (int i = 0; i < TM; ++i) {
@@ -1954,7 +1955,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                 };
                 read_slice(0);
                 __builtin_amdgcn_sched_barrier(0);
-                if (kt + kPanelW - 1 < p.kall) fetch_w(kt + kPanelW - 1);      // into the slot multiplied before this barrier
+                if (kt + WBUF - 1 < p.kall) fetch_w(kt + WBUF - 1);      // into the slot multiplied before this barrier
 #pragma unroll
                 for (int ks = 0; ks < BK / 32; ++ks) {
                     if (ks + 1 < BK / 32) read_slice(ks + 1);
@@ -2079,7 +2080,7 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
                     __builtin_amdgcn_sched_barrier(0);       // (or the arithmetic of later requests, and its waits, move ahead)
                 }
                 // (the tail is read behind a later barrier: with 128 rows the copies are made while the others multiply, 25088 x 1024 -> 256
-                // 33.9 -> 33.1 us; with 64 the next step waits for them, 12544 x 2304 -> 256 per batch 45.2 -> 46.7)
+                // 34.2 -> 32.7 us; with 64 the next step waits for them, 12544 x 2304 -> 256 per batch 45.2 -> 46.7)
                 if (BM < 128) copies(it);
                 step_barrier();
                 if (BM >= 128) copies(it);
@@ -2133,17 +2134,18 @@ __global__ __launch_bounds__((NQ + WAVES_M * WAVES_N) * 64) void panel_layer_ker
 
 template <int BM, int BN, int NQ, int WAVES_M>
 static int64_t panel_lds(int64_t tail_steps, PanelLayer* p) {
-    constexpr int BK = kPanelStep;
-    const int64_t tail = (2 * BM + kPanelW * BN) * BK, list = tail + tail_steps * BM * BK, end = list + NQ * kPanelMaxTail * 4;
-    // The epilogue's stage is the last of the weights' slots: the next tile's first steps go to the others, and that one is requested
-    // only behind a barrier that every wave reaches after its epilogue.
-    static_assert(kPanelW >= 3 && WAVES_M * 8 * BN * 4 <= BN * BK, "the stage fits a slot that no first step goes to");
+    constexpr int BK = kPanelStep, WBUF = panel_wbuf(BM);
+    const int64_t tail = (2 * BM + WBUF * BN) * BK, list = tail + tail_steps * BM * BK, end = list + NQ * kPanelMaxTail * 4;
+    // With three steps of weights the epilogue's stage is the last of their slots: the next tile's first steps go to the others,
+    // and that one is requested only behind a barrier that every wave reaches after its epilogue.
+    constexpr int STAGE = WAVES_M * 8 * BN * 4;
+    static_assert(WBUF == 2 || STAGE <= BN * BK, "the stage fits a step of weights");
     if (p != nullptr) {
         p->tail_off = (int)tail;
         p->list_off = (int)list;
-        p->stage_off = (int)(tail - BN * BK);
+        p->stage_off = (int)(WBUF > 2 ? tail - BN * BK : end);
     }
-    return end;
+    return WBUF > 2 ? end : end + STAGE;
 }
 
 template <int BM, int BN, int NQ, int WAVES_M, int WAVES_N>
@@ -2181,7 +2183,7 @@ static bool panel_fits(int64_t ldx, int64_t M, int C, int g, int s, int64_t ldq,
     const int64_t K = (int64_t)C * g, T = (int64_t)s * g, pitch = (int64_t)1 << 23;      // (offsets of 128 rows in 32 bits)
     if (K < 64 || T > kPanelMaxTail || N > 256 || M > 0x7FFFFFFF - 256 || ldx >= pitch || ldq >= pitch || ldw >= pitch) return false;
     const int64_t tail_steps = ceil_div(K + T, kPanelStep) - K / kPanelStep;
-    return tail_steps <= 2;                              // (what the widest instance has LDS for, but for the one of 128 rows: one)
+    return tail_steps <= 2;                              // (what the widest instance has LDS for)
 }
 
 hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int g, int s, const int32_t* chan_src,
@@ -2193,14 +2195,25 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     p.chan_src = chan_src; p.thr = thr; p.n_max = n_max; p.clip = clip; p.qmax = qmax;
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
-    if (N <= 64) return run_panel<64, 64, 8, 2, 2>(p, stream);
-    if (N <= 128) return run_panel<64, 128, 8, 2, 4>(p, stream);
-    // (a round of 128 rows, not two of 64, where K is short: us, 128 / 64 rows a tile: 25088 x 384 -> 256 19.2 / 19.0, x 512 21.9 / 22.7, x 1024
-    // 33.9 / 35.6, 30000 x 512 24.4 / 25.6, x 1024 37.9 / 39.8; x 2048 61.1 / 61.2, 30000 x 2048 76.1 / 69.0)
-    const int64_t K = (int64_t)C * g, cus = compute_units();
-    if (M > 64 * cus && M <= 128 * cus && K <= 1024 && ceil_div(K + (int64_t)s * g, kPanelStep) - K / kPanelStep <= 1)
-        return run_panel<128, 256, 8, 2, 4>(p, stream);
-    return run_panel<64, 256, 8, 2, 4>(p, stream);
+    // Tiles of 128 rows where K is short: half of the steps, each twice as long.  Time with 64 rows / with 128 where the rule takes these (layers in a graph,
+    // inputs rotating, K = 384 to 1280, 50 to 256 outputs, 100 to 2500 rows per compute unit; rounds: of 64-row tiles):
+    //   up to 64 outputs     static, more than 20 rounds 1.00-1.04; per batch 0.97-1.05
+    //   65 to 128            static, 2 rounds 0.95-1.09, 6 and more 0.98-1.08; per batch 0.98-1.08
+    //   more                 2 rounds 0.97-1.15 static (1024 columns 0.94-1.06), 0.96-1.06 per batch; 4 and more 0.97-1.10, 0.99-1.08
+    // An odd count leaves the last round of 128 rows half empty (5 rounds 0.89-0.99).  Outputs that share lines between rows lose by taller tiles (100
+    // outputs, 6 rounds and more 0.95-1.00; 110, 2 rounds 0.93-0.99).  More columns: 896 0.95-1.02, 128 outputs of 768 0.92-1.01, 1536 to 4608 in 2
+    // rounds 0.89-1.05.  With 64 rows throughout 512 -> 128 takes 19.7 / 161 / 362 us at 25563 / 281563 / 639963 rows, 18.8 / 154 / 334 so.
+    const int64_t K = (int64_t)C * g, rounds = ceil_div(M, 64 * compute_units());
+    const bool even = rounds % 2 == 0, lines = N % 32 == 0;
+    bool tall;
+    if (N <= 128 && n_max > 0) tall = K <= 704;
+    else if (N <= 64) tall = K <= 576 && rounds > 20 && lines;
+    else if (N <= 128) tall = K <= 704 && ((rounds == 2 && N % 4 == 0) || (lines && ((rounds > 5 && even) || rounds > 12)));
+    else tall = K <= (rounds == 2 ? 1280 : 768) && (even || rounds > 16);
+    tall = tall && rounds > 1;
+    if (N <= 64) return tall ? run_panel<128, 64, 8, 4, 2>(p, stream) : run_panel<64, 64, 8, 2, 2>(p, stream);
+    if (N <= 128) return tall ? run_panel<128, 128, 8, 2, 4>(p, stream) : run_panel<64, 128, 8, 2, 4>(p, stream);
+    return tall ? run_panel<128, 256, 8, 2, 4>(p, stream) : run_panel<64, 256, 8, 2, 4>(p, stream);
 }
 
 // Where the one launch is ahead of the two: ranges of two / one in time over 64, 128 and 256 outputs, copies 5 % (2 % in 3x3 layers), static grid, passes
