@@ -2249,7 +2249,7 @@ bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int 
 }
 
 // ---------------------------------------------------------------------------------------------
-// The layer of short code rows (up to OCS_SHORT_K bytes) as one launch, codes included (ocs_forward, ocs_forward_requant): the
+// The layer of short code rows (up to OCS_SHORT_K bytes) as one launch, codes included (ocs_forward, ocs_conv_forward_requant): the
 // streaming pass's one shot with the whole-K GEMM behind it.  The two launches write every code and read it back, and at this
 // length of K neither has much else to do.  A workgroup of four waves takes 64 rows of X, requests all of them at once (U 16-byte loads
 // a lane; nothing waits before the last is on its way) with all weight codes straight into LDS ahead of them, quantizes into the
@@ -2287,6 +2287,7 @@ struct RowsLayer {
     int steps;                                      // 32-byte steps of a row
     unsigned magic_qc, magic_td, magic_pc;          // floor(2^32 / n): X's dwords, a tail's dwords, a code row's pieces
     int w_off, tab_off, dup_off, red_off;
+    int flat;                                       // outputs leave as one block of a workgroup's rows
 };
 
 
@@ -2442,6 +2443,27 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p, Requan
         for (int j = 0; j < TN; ++j) acc[0][j] = mfma_tile<RQ>(a, b[j], acc[0][j]);
     }
     __syncthreads();                                              // image and weights have been read: their LDS is the stage
+    if constexpr (!RQ && BN <= 128) {
+        if (p.flat) {
+            float* out = reinterpret_cast<float*>(rlds);
+            const float scale = step_x * step_w;
+            const int col = wn * WN + (lane & 31);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (col + j * 32 >= p.N) continue;
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    out[(wm * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3)) * p.N + col + j * 32] = (float)acc[0][j][e] * scale;
+            }
+            __syncthreads();
+            float* y = p.Y + (int64_t)row0 * p.N;                 // (64 rows: whole pieces of 16 bytes; fewer end the tensor)
+            const int n = rows * p.N;
+            for (int it = 4 * tid; it + 3 < n; it += 4 * NT)
+                __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(out + it), reinterpret_cast<f32x4*>(y + it));
+            if (tid < (n & 3)) y[(n & ~3) + tid] = out[(n & ~3) + tid];
+            return;
+        }
+    }
     int32_t* stage = reinterpret_cast<int32_t*>(&rlds[wave * stage_bytes<RQ, WN, 8>()]);
     const float inv_next = RQ ? requant_inv(rq, blockIdx.x == 0 && tid == 0) : 0.0f;
     const int dup_n = RQ && p.dup_off > 0 ? (*dup_count < kDupCap ? *dup_count : kDupCap) : 0;
@@ -2454,7 +2476,7 @@ __global__ __launch_bounds__(kRowsNT) void rows_layer_kernel(RowsLayer p, Requan
 template <int BN, bool RQ>
 static int64_t rows_layer_lds(int64_t K, int64_t steps, int s_next, RowsLayer* p) {
     const int64_t w = round_up(steps * kRowsStep, 1024), operands = w + (steps + 1) / 2 * BN * 64;
-    const int64_t staging = (kRowsNT / 64) * stage_bytes<RQ, BN / 2, 8>();
+    const int64_t staging = p != nullptr && p->flat ? (int64_t)kRowsBM * 4 * p->N : (kRowsNT / 64) * stage_bytes<RQ, BN / 2, 8>();
     const int64_t tab = round_up(operands > staging ? operands : staging, 16), dup = tab + 16 * (steps * 8 - K / 4);
     const bool list = RQ && s_next > 0;
     const int64_t red = dup + (list ? (kDupCap + 1) * 4 : 0);
@@ -2562,6 +2584,12 @@ hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int 
     p.Xq = Xq; p.ldq = ldq; p.scale_x = scale_x; p.Wq = Wq; p.ldw = ldw; p.N = (int)N; p.scale_w = scale_w;
     p.acc_out = acc_out; p.ldacc = ldacc; p.Y = Y; p.ldy = ldy;
     p.steps = (int)ceil_div((int64_t)(C + s) * g, 32);
+    // Rows of outputs that share lines leave through LDS as the one block that a workgroup's 64 rows are: stored row by row a line's parts come from several
+    // instructions and waves, apart in time (us, row by row / as a block; past the caches' replacement row by row is 1.4 to 3 times as long): 332763 x
+    // 64 -> 63 static 58.0 / 34.3, 511963 x 44 -> 94 105 / 53.4, x 64 -> 100 90 / 75, x 64 -> 5 40.8 / 38.8; N % 4 != 0 1.03-2.06 in time, from 48 on 1.00-1.30,
+    // 40 and 44 0.96-1.10, whole lines are stored as they are.
+    p.flat = rq.Yq == nullptr && acc_out == nullptr && N % 32 != 0 && (N % 4 != 0 || N >= 48) && N <= 128 && ldy == N &&
+             reinterpret_cast<uintptr_t>(Y) % 16 == 0;
     if (rq.Yq != nullptr) return N <= 64 ? run_rows_loads<64, true>(p, rq, stream) : run_rows_loads<128, true>(p, rq, stream);
     if (N <= 64) return run_rows_loads<64, false>(p, rq, stream);
     if (N <= 128) return run_rows_loads<128, false>(p, rq, stream);

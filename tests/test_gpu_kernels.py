@@ -1802,6 +1802,36 @@ def test_forward_of_short_rows(M, C, g, s, N, ld_extra):
     _rows(1, lambda: _forward_once(M, C, g, s, N, ld_extra, 2.5, 1.0, 0, route=3))
 
 
+# Outputs as one block of a workgroup's rows (no accumulators asked for, rows that are not whole lines): against the two launches bit for bit,
+# nothing written past the end; outputs around 32, 64 and 128, one row to several workgroups, a last block of 1 to 3 values over; and what is stored row by
+# row: a longer pitch, a base off 16 bytes.
+@pytest.mark.parametrize("M,N", [(1, 1), (1, 3), (63, 31), (65, 33), (64, 5), (127, 50), (130, 63), (66, 65), (193, 100), (70, 127), (129, 48), (131, 60)])
+@pytest.mark.parametrize("C,ldy_extra,off", [(64, 0, 0), (300, 0, 0), (64, 1, 0), (64, 0, 1)])
+def test_forward_of_short_rows_as_a_block(M, N, C, ldy_extra, off):
+    s, gen = 5, torch.Generator(device="cuda").manual_seed(M + N)
+    X = torch.randn((M, C), device="cuda", generator=gen)
+    ld, ldy = B.ocs_padded_cols(C + s), N + ldy_extra
+    Wq = torch.randint(-15, 16, (N, ld), device="cuda", generator=gen, dtype=torch.int8)
+    cs = torch.cat([torch.arange(C, dtype=torch.int32), torch.randint(0, C, (s,), dtype=torch.int32)]).cuda()
+    q, sx = torch.empty((M, ld), dtype=torch.int8, device="cuda"), torch.empty(2, device="cuda")
+    th, sw = torch.tensor([2.5], device="cuda"), torch.tensor([1.5, 0.1], device="cuda")
+    out = []
+    B.ocs_tune("slice_layer", 0)
+    try:
+        for route in (0, 3):
+            Y = torch.full((M * ldy + 70,), -3.0, device="cuda")
+
+            def forward():
+                assert B.ocs_forward_one_launch(M, C, 1, C, s, ld, ld, N, X=X) == route
+                B.ocs_forward(X, M, C, 1, C, cs, s, 8, th, 1.0, q, ld, sx, Wq, ld, N, 5, sw, None, 0, Y[off:], ldy, None)
+
+            _rows(1 if route else 0, forward)
+            out.append(Y)
+    finally:
+        B.ocs_tune("slice_layer", -1)
+    assert torch.equal(out[0], out[1]) and bool((out[1][off + (M - 1) * ldy + N:] == -3.0).all())
+
+
 # Per-batch grids: a single maximum, 256 of them, the thousands of a strided tensor, those folded by a launch of their own (from 2^23 values on)
 @pytest.mark.parametrize("M,C,g,s,N,ld_extra,clip", [
     (1, 64, 1, 1, 5, 0, 1.0), (3000, 147, 1, 8, 64, 0, 0.9), (9000, 100, 1, 5, 70, 3, 0.8), (83887, 100, 1, 5, 70, 3, 0.8)])
