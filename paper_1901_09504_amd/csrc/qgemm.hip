@@ -2541,6 +2541,9 @@ static bool rows_layer_fits(int64_t M, int C, int g, int s, int64_t ldq, int64_t
 //   rounds    more than 256 columns leave a compute unit two workgroups, 128 rows a round.  Up to 64 outputs 125 1.21-1.56, 130 0.93-1.06
 //             (0.92-0.95), 140 0.96-1.15 (0.95-1.04), 150 0.98-1.12, 160 1.03-1.13.  Where the two launches' tiles come out even: 185
 //             1.09-1.22, 196 0.94-1.07 (0.94-1.03), 210 0.97-1.10 (0.98-1.03), 230 1.02-1.14; codes out and more than 64 outputs 196 1.04-1.10.
+//             Outputs in whole lines, which the two launches store best: 64 of them 217 0.91-0.96, 232 0.93-0.99 (0.94-0.98), 250 0.97-1.04, 262 0.97-1.02,
+//             280 0.99-1.07; 128 129 0.95-1.01, 140 1.00-1.04, 217 0.95-1.02, 225 0.97-1.04, 232 1.00-1.07. 241 to 256 columns and 128 outputs 193 0.91-0.94 (0.99),
+//             201 to 204 0.96-0.99 (0.99-1.02), 210 (1.03).
 //   outputs   more than 128: rows of outputs that begin anywhere cost the two launches more than the one.  N % 4 != 0: 16 0.81-1.34, 24
 //             0.99-1.29, 49 and more 1.02-1.60 (1.01-1.53).  N % 4 == 0, passes queued: 16 to 49 1.04-1.48 (1.02-1.35); in a graph up to 128 code
 //             bytes 16 0.89-1.22 (up to 48 columns, or 64 and more than 192 outputs, 0.95-1.22), 24 0.96-1.16, 32 0.98-1.21; longer 16 0.81-0.97, 32
@@ -2561,6 +2564,8 @@ bool rows_layer_pays(int64_t M, int C, int g, int s, int64_t ldq, int64_t N, boo
     if (M > 2200 * cus && K < 64 && !codes) return false;
     if (K > 256 && N <= 64 && between(128, 150)) return false;
     if (K > 256 && (N <= 64 || !codes) && between(190, 215)) return false;
+    if (K > 256 && (N == 64 || N == 128) && !codes && (between(215, N == 64 ? 270 : 225) || (N == 128 && between(128, 134)))) return false;
+    if (K > 240 && N == 128 && !codes && between(190, 206)) return false;
     if (codes) return M >= (K > 128 ? 48 : (K > 64 && N > 64 ? 32 : 16)) * cus;
     if (N <= 128) return M >= 16 * cus;
     if (M * N > (int64_t)1 << 26) return false;
@@ -2586,7 +2591,7 @@ hipError_t launch_rows_layer(const float* X, int64_t ldx, int64_t M, int C, int 
     p.steps = (int)ceil_div((int64_t)(C + s) * g, 32);
     // Rows of outputs that share lines leave through LDS as the one block that a workgroup's 64 rows are: stored row by row a line's parts come from several
     // instructions and waves, apart in time (us, row by row / as a block; past the caches' replacement row by row is 1.4 to 3 times as long): 332763 x
-    // 64 -> 63 static 58.0 / 34.3, 511963 x 44 -> 94 105 / 53.4, x 64 -> 100 90 / 75, x 64 -> 5 40.8 / 38.8; N % 4 != 0 1.03-2.06 in time, from 48 on 1.00-1.30,
+    // 64 -> 63 static 58.0 / 34.3, 511963 x 44 -> 94 105 / 53.4, x 64 -> 100 77 / 65; N % 4 != 0 1.03-2.06 in time, from 48 on 1.00-1.30,
     // 40 and 44 0.96-1.10, whole lines are stored as they are.
     p.flat = rq.Yq == nullptr && acc_out == nullptr && N % 32 != 0 && (N % 4 != 0 || N >= 48) && N <= 128 && ldy == N &&
              reinterpret_cast<uintptr_t>(Y) % 16 == 0;

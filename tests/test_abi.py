@@ -305,8 +305,10 @@ def test_forward_of_short_rows_by_rows_and_outputs(C, g, s, N, inside, outside):
 @pytest.mark.parametrize("C,s,N,rows,eager,captured", [
     (23, 2, 64, 784 * 256, 3, 3), (23, 2, 64, 784 * 256 + 1, 0, 0), (24, 2, 64, 784 * 256 + 1, 3, 3), (24, 2, 64, 2200 * 256, 3, 3), (63, 4, 64, 2200 * 256 + 1, 0, 0),
     (64, 4, 64, 2200 * 256 + 1, 3, 3), (257, 13, 64, 128 * 256, 3, 3), (257, 13, 64, 128 * 256 + 1, 0, 0), (257, 13, 64, 150 * 256 + 1, 3, 3),
-    (257, 13, 65, 140 * 256, 3, 3), (256, 13, 64, 140 * 256, 3, 3), (300, 15, 128, 190 * 256, 3, 3), (300, 15, 128, 190 * 256 + 1, 0, 0),
-    (300, 15, 128, 215 * 256 + 1, 3, 3), (256, 13, 128, 200 * 256, 3, 3), (128, 7, 160, 128 * 256, 3, 3), (128, 7, 160, 128 * 256 + 1, 0, 0), (128, 7, 160, 500 * 256, 0, 0),
+    (257, 13, 65, 140 * 256, 3, 3), (256, 13, 64, 140 * 256, 3, 3), (300, 15, 128, 128 * 256 + 1, 0, 0), (300, 15, 128, 134 * 256 + 1, 3, 3), (300, 15, 128, 190 * 256, 3, 3),
+    (300, 15, 128, 190 * 256 + 1, 0, 0), (300, 15, 100, 215 * 256 + 1, 3, 3), (300, 15, 128, 225 * 256, 0, 0), (300, 15, 128, 225 * 256 + 1, 3, 3), (300, 15, 64, 270 * 256, 0, 0),
+    (300, 15, 64, 270 * 256 + 1, 3, 3), (300, 15, 50, 215 * 256 + 1, 3, 3),
+    (256, 13, 128, 206 * 256, 0, 0), (256, 13, 128, 206 * 256 + 1, 3, 3), (240, 12, 128, 200 * 256, 3, 3), (128, 7, 160, 128 * 256, 3, 3), (128, 7, 160, 128 * 256 + 1, 0, 0), (128, 7, 160, 500 * 256, 0, 0),
     (128, 7, 164, 128 * 256 + 1, 0, 0), (128, 7, 164, 160 * 256 + 1, 3, 3), (128, 7, 162, 140 * 256, 3, 3), (128, 7, 256, 500 * 256, 3, 3), (120, 6, 160, 500 * 256, 3, 3),
     (128, 7, 160, 48 * 256, 3, 3), (128, 7, 160, 48 * 256 - 1, 3, 0), (120, 6, 160, 32 * 256, 3, 3), (120, 6, 160, 32 * 256 - 1, 3, 0), (48, 3, 160, 17 * 256, 3, 3),
     (64, 4, 160, 17 * 256, 3, 0), (64, 4, 196, 17 * 256, 3, 3), (65, 4, 196, 17 * 256, 3, 0), (64, 4, 201, 23 * 256, 3, 0), (64, 4, 201, 24 * 256, 3, 3),
