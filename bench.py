@@ -45,13 +45,13 @@ STATIC_T = 5.0               # the static activation grid's range (inputs are |N
 # reads for the plain copy kernel of known size that runs after the timed region
 # (profiles/bench_config5_headline.md).  Valid only for the kernel source it was measured on:
 # reported as null once that file changes.
-X2_TRAFFIC = {"quantize_hip_sha256": "c678164867694548cee33b4761aa163600baa1a13197af7fb916517cb487920b",
-              "bytes_per_step": 28944416643}
+X2_TRAFFIC = {"quantize_hip_sha256": "c969a59ea904503635583852d98030eb51d5de673b4467cf1583e673e45a92e8",
+              "bytes_per_step": 28944528989}
 
 
 # The same for the launches of the one-launch pass (`--extras fused`), keyed on the GEMM source.
-FUSED_TRAFFIC = {"qgemm_hip_sha256": "ebf72ca90b0e8fd7fd6406330737231791fad8454e6e68ddbfdc561252a06be3",
-                 "bytes_per_step": 22973279990}
+FUSED_TRAFFIC = {"qgemm_hip_sha256": "036ed361fafce78c3349d816d37b3d8f4650ea20a76efed16665ba20fb38b5e4",
+                 "bytes_per_step": 22972976995}
 
 
 def fused_traffic():

@@ -2259,9 +2259,10 @@ bool panel_layer_pays(const float* X, int64_t ldx, int64_t M, int C, int g, int 
 // their two pieces exchanged every eight rows, the steps 32 bytes further apart: the reads of sixteen rows and the dwords a wave
 // writes along a row of X fall in different banks.  The weights lie in the whole-K kernel's 64-byte steps: requested by 32 bytes of a row
 // they cost the L1 twice the look-ups (401408 x 147 -> 64 71.5 us, 100352 x 256 -> 64 33.9).
-// Bounded by HBM: X, codes and outputs at 6.1 TB/s where they are the traffic (401408 x 147 -> 64 88.5 -> 67.8 us for the layer,
-// 802816 x 64 -> 64 86.8 -> 69.5), 5.0 where the launch is short (100352 x 256 -> 64 36.6 -> 30.8; with the next layer's codes as its
-// output 38.8 -> 31.7).  X is read past the caches'
+// Bounded by HBM and the issue of vector instructions: X, codes and outputs at 6.1 TB/s where they are the traffic (401408 x 147 -> 64 88.5 ->
+// 67.8 us for the layer, 802816 x 64 -> 64 86.8 -> 69.5), 5.0 where the launch is short (100352 x 256 -> 64 36.6 -> 30.8; with the next
+// layer's codes as its output 38.8 -> 31.7).  By counters behind a max|X| pass the first reads 242 MB and writes 186 in 65 us (6.6 TB/s with what the
+// last-level cache holds), 82 % of the vector issue in use, 9 % of the busy cycles bank conflicts of its tails; the last 55 % and 2 %.  X is read past the caches'
 // replacement (with plain loads 74.6 and 80.8 us of the first two).  128 rows on eight waves: 74.9 and 72.1, 100352 x 256 -> 64 39.0;
 // fewer workgroups on a compute unit (three, two): 71 and 84, 80 and 95.
 // ---------------------------------------------------------------------------------------------

@@ -13,9 +13,10 @@
 namespace ocs {
 
 // What bounds it: the latency of one workgroup's passes over LDS, its barriers and one trip to memory.
-// 3000 channels, 150 splits: 78 -> 11 us with the column maxima in the caches, 14 without, against one split per
-// step (0.2 us a step on one wave, 0.5 us on four); 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
-// taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.
+// 3000 channels, 150 splits, the column maxima outside the caches: 78 us with one split per step (0.2 us a step on one wave, 0.5 us
+// on four), 14 in rounds, 11.7 with a round's list in registers; 1075 channels, 52 splits: the whole weight path 33 -> 14 us; a few splits of up to 1024 channels are
+// taken step by step (select_lds.h).  NT: sixteen waves where the list or its column maxima give every lane something to do.  HELD: pieces of NT
+// entries that the list is at most, as few as hold it: every one more is code to fetch.
 template <int NT, bool FEW, bool BLOCKS, int HELD>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ colmax, int C, int g, int s, int mode,
