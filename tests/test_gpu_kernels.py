@@ -252,6 +252,7 @@ def test_split_weights_halve(N, C, g, s, bits, clip):
     (20, 251, 1, 6, "ties"), (9, 500, 2, 12, "heavy"), (9, 501, 1, 12, "heavy"), (5, 1010, 1, 14, "normal"),
     (5, 1010, 1, 15, "normal"), (12, 16, 3, 40, "heavy"), (300, 8, 1, 9, "zero"),
     (20, 620, 1, 20, "heavy"), (20, 621, 1, 20, "heavy"),               # lists of 640 and 641
+    (20, 230, 1, 26, "heavy"), (20, 230, 1, 27, "heavy"), (20, 500, 1, 12, "heavy"), (20, 500, 1, 13, "heavy"),   # lists of 256 and 512, and one more
     (5, 1010, 1, 4, "heavy"), (5, 1010, 1, 5, "heavy"),                 # ... longer ones only for a few steps
     (30, 100, 3, 64, "heavy"), (30, 100, 3, 65, "heavy"), (6, 540, 2, 100, "heavy"),
     (9, 576, 1, 64, "last_digits"), (9, 500, 1, 140, "last_digits"), (9, 300, 1, 60, "equal")])   # cut rounds of hundreds of entries
