@@ -2201,12 +2201,13 @@ hipError_t launch_panel_layer(const float* X, int64_t ldx, int64_t M, int C, int
     //   65 to 128            static, 2 rounds 0.95-1.09, 6 and more 0.98-1.08; per batch 0.98-1.08
     //   more                 2 rounds 0.97-1.15 static (1024 columns 0.94-1.06), 0.96-1.06 per batch; 4 and more 0.97-1.10, 0.99-1.08
     // An odd count leaves the last round of 128 rows half empty (5 rounds 0.89-0.99).  Outputs that share lines between rows lose by taller tiles (100
-    // outputs, 6 rounds and more 0.95-1.00; 110, 2 rounds 0.93-0.99).  More columns: 896 0.95-1.02, 128 outputs of 768 0.92-1.01, 1536 to 4608 in 2
-    // rounds 0.89-1.05.  With 64 rows throughout 512 -> 128 takes 19.7 / 161 / 362 us at 25563 / 281563 / 639963 rows, 18.8 / 154 / 334 so.
+    // outputs, 6 rounds and more 0.95-1.00; 110, 2 rounds 0.93-0.99).  More columns: 896 0.95-1.02, 128 outputs of 768 static 0.92-1.01, 1536 to 4608 in 2
+    // rounds 0.89-1.05; per batch up to 128 outputs 1024 to 3456 0.92-1.03, 4608 0.96-1.06, 9216 in 2 rounds 1.00-1.06.  With 64 rows throughout
+    // 512 -> 128 takes 19.7 / 161 / 362 us at 25563 / 281563 / 639963 rows, 18.8 / 154 / 334 so.
     const int64_t K = (int64_t)C * g, rounds = ceil_div(M, 64 * compute_units());
     const bool even = rounds % 2 == 0, lines = N % 32 == 0;
     bool tall;
-    if (N <= 128 && n_max > 0) tall = K <= 704;
+    if (N <= 128 && n_max > 0) tall = K <= (N > 64 ? 768 : 704) || (K > 4608 && rounds == 2);
     else if (N <= 64) tall = K <= 576 && rounds > 20 && lines;
     else if (N <= 128) tall = K <= 704 && ((rounds == 2 && N % 4 == 0) || (lines && ((rounds > 5 && even) || rounds > 12)));
     else tall = K <= (rounds == 2 ? 1280 : 768) && (even || rounds > 16);
