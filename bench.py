@@ -45,13 +45,13 @@ STATIC_T = 5.0               # the static activation grid's range (inputs are |N
 # reads for the plain copy kernel of known size that runs after the timed region
 # (profiles/bench_config5_headline.md).  Valid only for the kernel source it was measured on:
 # reported as null once that file changes.
-X2_TRAFFIC = {"quantize_hip_sha256": "c969a59ea904503635583852d98030eb51d5de673b4467cf1583e673e45a92e8",
-              "bytes_per_step": 28944528989}
+X2_TRAFFIC = {"quantize_hip_sha256": "9013a5808f324a5f5aa17bf6b5079fdc5527ece866a19f027c532f31e8c916a6",
+              "bytes_per_step": 28944028202}
 
 
 # The same for the launches of the one-launch pass (`--extras fused`), keyed on the GEMM source.
-FUSED_TRAFFIC = {"qgemm_hip_sha256": "036ed361fafce78c3349d816d37b3d8f4650ea20a76efed16665ba20fb38b5e4",
-                 "bytes_per_step": 22972976995}
+FUSED_TRAFFIC = {"qgemm_hip_sha256": "275fc3e9be022cf8f6ca48663dd322fd314653a0c77a26545d6df95d3993dcae",
+                 "bytes_per_step": 22973095031}
 
 
 def fused_traffic():
